@@ -147,13 +147,52 @@ __device__ inline void store_out(const IgemmP &p, long row, int col, float v)
     }
 }
 
+// ---- fp32 products on the bf16 matrix instruction ---------------------------------------------------------------------
+// An fp32 number is the exact sum of three bfloat16 numbers (8 significant bits each): hi = bf16(x), mid = bf16(x - hi),
+// lo = x - hi - mid.  Of the nine partial products of two such sums the six of weight 2^-18 and more are formed
+// (hi*hi; hi*mid, mid*hi; hi*lo, mid*mid, lo*hi); the three left out are below 2^-26 of the product.  bf16 products are exact in fp32, so the
+// error is that of the sums: hi*hi and the five small products keep accumulators of their own, which rounds the large sum once
+// per 16 products (the fp32 instruction rounds it at every product).  Measured against 64 bits (relative 2-norm, normal
+// operands, reduction of 64 / 576 / 4608): 4.9e-8 / 1.4e-7 / 4.2e-7, with v_mfma_f32_32x32x2_f32 1.4e-7 / 4.3e-7 / 1.2e-6.
+// Rate: six v_mfma_f32_32x32x16_bf16 (32 cycles each) do the work of eight v_mfma_f32_32x32x2_f32 (64 cycles each): 192
+// against 512 cycles, 407 against 149 TFLOP/s at the clocks a loop of nothing else sustains.
+// An infinite operand (or one that rounds to infinity) has no finite remainder: the sums it enters become NaN, and the kernels
+// form a wavefront's outputs again with the fp32 instruction when one of them is not finite.
+struct Split8 { uint4 hi, mid, lo; };  // eight numbers, two to a word
+__device__ inline uint32_t split_pair(float &x, float &y)  // rounds a pair to bf16 and leaves the exact remainders
+{
+    const uint32_t h = bf16_pack2(x, y);
+    x -= bf16_lo(h);
+    y -= bf16_hi(h);
+    return h;
+}
+__device__ inline Split8 split8(float4 a, float4 b)
+{
+    Split8 s;
+    s.hi = make_uint4(split_pair(a.x, a.y), split_pair(a.z, a.w), split_pair(b.x, b.y), split_pair(b.z, b.w));
+    s.mid = make_uint4(split_pair(a.x, a.y), split_pair(a.z, a.w), split_pair(b.x, b.y), split_pair(b.z, b.w));
+    s.lo = make_uint4(bf16_pack2(a.x, a.y), bf16_pack2(a.z, a.w), bf16_pack2(b.x, b.y), bf16_pack2(b.z, b.w));
+    return s;
+}
+__device__ inline float4 bn_relu4(float4 v, const float4 &sc, const float4 &sh)
+{
+    return make_float4(fmaxf(fmaf(v.x, sc.x, sh.x), 0.f), fmaxf(fmaf(v.y, sc.y, sh.y), 0.f), fmaxf(fmaf(v.z, sc.z, sh.z), 0.f),
+                       fmaxf(fmaf(v.w, sc.w, sh.w), 0.f));
+}
+// LDS image of a split operand tile: a row of 32 reduction elements is three planes of four 16-byte chunks, 192 bytes, no padding;
+// chunk c of a plane sits at c ^ (row/4 % 4), so that the 16 rows a quarter of a fragment read touches, and the four rows
+// a quarter of a store touches, fall into different banks.  Chunk c holds elements 4c .. 4c+3 and 16+4c .. 16+4c+3 (the order in
+// which a thread loads them; the sum does not depend on the order as long as both operands share it).
+constexpr int kSplitRow = 48;  // words of a row
+__device__ inline int split_chunk(int row, int plane, int c) { return row * (kSplitRow / 4) + plane * 4 + (c ^ ((row >> 2) & 3)); }
+
 // Workgroups of the implicit-GEMM kernel that one CU holds at once (= wavefronts per SIMD, since a workgroup puts
 // one wavefront on each SIMD).  The launch bounds make the compiler keep the register count within this, and the
 // host sizes the persistent grid with the same number.
 constexpr int igemm_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) ? 2 : (bm == 64 && bn == 64) ? 4 : 3; }
 
 // MODE 0: Cin % 32 == 0, sd == 1.  MODE 1: Cin % 32 == 0, sd > 1.  MODE 2: any Cin and sd (scalar gather).
-// BF = false: fp32 operands, v_mfma_f32_32x32x2_f32 (the paper's single precision).
+// BF = false: fp32 operands (the paper's single precision), each split into three bf16 terms on its way into LDS (see split8).
 // BF = true : operands are rounded to bfloat16 (RNE) on their way into LDS and multiplied with
 //             v_mfma_f32_32x32x16_bf16; accumulation and outputs stay fp32.
 // INAFF (MODE 0 only): per-channel scale, shift and ReLU applied to the gathered operand (see IgemmP::in_scale).
@@ -173,13 +212,18 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
     static_assert(ACT == 0 || BF, "bf16 activations are multiplied on the bf16 MFMA");
     constexpr bool A16 = ACT == 1, O16 = ACT != 0;
     constexpr bool AV16 = A16 && MODE <= 1;    // vector gather of bf16: 8 elements per load, 4 loads per row of a stage
+    constexpr bool SPLIT = !BF;
     constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
-    constexpr int ATPR = AV16 ? BK / 8 : TPR;  // threads per gathered row (eight bf16 or four fp32 elements per load)
+    // threads per row of each operand tile: eight bf16 or four fp32 elements per load; a split operand takes two loads of four
+    constexpr int BTPR = SPLIT ? 4 : TPR, BROWS = kConvThreads / BTPR;
+    constexpr int ATPR = SPLIT ? 4 : AV16 ? BK / 8 : TPR;
     constexpr int AROWS = kConvThreads / ATPR;  // rows of the gathered tile one pass of the workgroup's loads covers
-    constexpr int RA = BM / AROWS, RB = BN / ROWS;  // rows per thread of each operand tile
-    static_assert(BM % AROWS == 0 && BN % ROWS == 0, "whole passes");
-    __shared__ __attribute__((aligned(16))) float As[BM * kLDK];
-    __shared__ __attribute__((aligned(16))) float Bs[BN * kLDK];
+    constexpr int RA = BM / AROWS, RB = BN / BROWS;  // rows per thread of each operand tile
+    constexpr int NL = SPLIT ? 2 : 1;                // 16-byte loads per row and thread, 16 elements apart
+    static_assert(BM % AROWS == 0 && BN % BROWS == 0, "whole passes");
+    constexpr int LROW = SPLIT ? kSplitRow : kLDK;   // words of a row in LDS
+    __shared__ __attribute__((aligned(16))) float As[BM * LROW];
+    __shared__ __attribute__((aligned(16))) float Bs[BN * LROW];
     __shared__ float s_stat[2][STATS ? BN : 1];  // column statistics of a tile's second row half, on their way to the first half's wavefronts
 
     // The kernels of the step's main chain (forward pass, data gradients, BN backward) raise the issue priority of their
@@ -188,15 +232,11 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
     main_chain_priority();
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const int kq = tid % TPR, row_in = tid / TPR;
+    const int kq = tid % BTPR, row_in = tid / BTPR;
     const int akq = tid % ATPR, arow = tid / ATPR;  // this thread's piece of a gathered row, and its row
     const bf16_t *a16 = reinterpret_cast<const bf16_t *>(p.a);
     const int G = gridDim.x;
     const int n_items = p.full_items + p.tail_tiles * p.tail_split;
-    // MFMA operand for lane l: row l%32 of the block, reduction element l/32 of the current pair.  A lane
-    // reads four consecutive reduction elements at once; pairing element e of lanes 0-31 with element e
-    // of lanes 32-63 is a permutation of the reduction order, applied identically to both operands.
-    const int frag_off = (lane & 31) * kLDK + (lane >> 5) * 4;
 
     for (int item = blockIdx.x; item < n_items; item += G) {
         int tile, kc_begin, kc_end;
@@ -245,10 +285,10 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
             }
         }
 
-        float4 ra[RA], rb[RB];
+        float4 ra[RA][NL], rb[RB][NL];
         uint4 ra16[RA];                                                 // AV16: eight bf16 elements per register
         float4 in_sc = make_float4(0.f, 0.f, 0.f, 0.f), in_sh = in_sc;  // INAFF: scale and shift of this thread's four channels
-        float4 in_sc2 = in_sc, in_sh2 = in_sc;                          // INAFF with AV16: of the next four
+        float4 in_sc2 = in_sc, in_sh2 = in_sc;                          // INAFF with AV16 or SPLIT: of this thread's other four
         unsigned in_ok = 0;                                             // INAFF: bit i set when ra[i] was loaded (not padding)
         auto load_chunk = [&](int kc) {
             const int k0 = kc * BK;
@@ -259,9 +299,9 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                 if (INAFF) {
                     in_sc = ldg4(p.in_scale + c0);
                     in_sh = ldg4(p.in_shift + c0);
-                    if (AV16) {
-                        in_sc2 = ldg4(p.in_scale + c0 + 4);
-                        in_sh2 = ldg4(p.in_shift + c0 + 4);
+                    if (AV16 || SPLIT) {
+                        in_sc2 = ldg4(p.in_scale + c0 + (SPLIT ? 16 : 4));
+                        in_sh2 = ldg4(p.in_shift + c0 + (SPLIT ? 16 : 4));
                     }
                     in_ok = 0;
                 }
@@ -283,19 +323,24 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                     ok = ok && ih < p.IH && iw < p.IW;
                     const unsigned aoff = (unsigned)(abase[i] + (int)__umul24(__umul24(ih, p.IW) + iw, p.Cin) + c0);
                     if (AV16) ra16[i] = ok ? *reinterpret_cast<const uint4 *>(a16 + aoff) : make_uint4(0u, 0u, 0u, 0u);
-                    else ra[i] = ok ? ldg4(p.a + aoff) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    else {
+#pragma unroll
+                        for (int q = 0; q < NL; ++q) ra[i][q] = ok ? ldg4(p.a + (aoff + 16 * q)) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
                     if (INAFF && ok) in_ok |= 1u << i;
                 }
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
-                    const int j = n0 + row_in + ROWS * i;
-                    rb[i] = j < p.Nout ? ldg4(p.b + (long)j * p.Kdim + k0 + kq * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const int j = n0 + row_in + BROWS * i;
+                    const float *bp = p.b + (long)j * p.Kdim + k0 + kq * 4;
+#pragma unroll
+                    for (int q = 0; q < NL; ++q) rb[i][q] = j < p.Nout ? ldg4(bp + 16 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
                 }
             } else {
-                float va[RA][4], vb[RB][4];
+                float va[RA][4 * NL], vb[RB][4 * NL];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int k = k0 + kq * 4 + e;
+                for (int e = 0; e < 4 * NL; ++e) {
+                    const int k = k0 + kq * 4 + (e & 3) + 16 * (e >> 2);
                     const bool kin = k < p.Kdim;
                     const int tap = (int)fdiv(k, p.div_cin), c = k - tap * p.Cin;
                     const int r = (int)fdiv(tap, p.div_s), s = tap - r * p.S;
@@ -315,14 +360,17 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                     }
 #pragma unroll
                     for (int i = 0; i < RB; ++i) {
-                        const int j = n0 + row_in + ROWS * i;
+                        const int j = n0 + row_in + BROWS * i;
                         vb[i][e] = (kin && j < p.Nout) ? p.b[(long)j * p.Kdim + k] : 0.f;
                     }
                 }
 #pragma unroll
-                for (int i = 0; i < RA; ++i) ra[i] = make_float4(va[i][0], va[i][1], va[i][2], va[i][3]);
+                for (int q = 0; q < NL; ++q) {
 #pragma unroll
-                for (int i = 0; i < RB; ++i) rb[i] = make_float4(vb[i][0], vb[i][1], vb[i][2], vb[i][3]);
+                    for (int i = 0; i < RA; ++i) ra[i][q] = make_float4(va[i][4 * q], va[i][4 * q + 1], va[i][4 * q + 2], va[i][4 * q + 3]);
+#pragma unroll
+                    for (int i = 0; i < RB; ++i) rb[i][q] = make_float4(vb[i][4 * q], vb[i][4 * q + 1], vb[i][4 * q + 2], vb[i][4 * q + 3]);
+                }
             }
         };
         auto store_chunk = [&]() {
@@ -342,45 +390,60 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                 }
 #pragma unroll
                 for (int i = 0; i < RB; ++i)
-                    *reinterpret_cast<uint2 *>(&bh[(row_in + ROWS * i) * LDH + kq * 4]) =
-                        make_uint2(bf16_pack2(rb[i].x, rb[i].y), bf16_pack2(rb[i].z, rb[i].w));
+                    *reinterpret_cast<uint2 *>(&bh[(row_in + BROWS * i) * LDH + kq * 4]) =
+                        make_uint2(bf16_pack2(rb[i][0].x, rb[i][0].y), bf16_pack2(rb[i][0].z, rb[i][0].w));
                 return;
             }
             if (INAFF) {
 #pragma unroll
                 for (int i = 0; i < RA; ++i)
                     if (in_ok & (1u << i)) {
-                        ra[i].x = fmaxf(fmaf(ra[i].x, in_sc.x, in_sh.x), 0.f);
-                        ra[i].y = fmaxf(fmaf(ra[i].y, in_sc.y, in_sh.y), 0.f);
-                        ra[i].z = fmaxf(fmaf(ra[i].z, in_sc.z, in_sh.z), 0.f);
-                        ra[i].w = fmaxf(fmaf(ra[i].w, in_sc.w, in_sh.w), 0.f);
+                        ra[i][0] = bn_relu4(ra[i][0], in_sc, in_sh);
+                        if (SPLIT) ra[i][NL - 1] = bn_relu4(ra[i][NL - 1], in_sc2, in_sh2);
                     }
             }
-            if (BF) {
+            if constexpr (SPLIT) {
+                uint4 *aq = reinterpret_cast<uint4 *>(As), *bq = reinterpret_cast<uint4 *>(Bs);
+#pragma unroll
+                for (int i = 0; i < RA; ++i) {
+                    const Split8 v = split8(ra[i][0], ra[i][1]);
+                    const int at = split_chunk(arow + AROWS * i, 0, akq);
+                    aq[at] = v.hi;
+                    aq[at + 4] = v.mid;
+                    aq[at + 8] = v.lo;
+                }
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    const Split8 v = split8(rb[i][0], rb[i][1]);
+                    const int at = split_chunk(row_in + BROWS * i, 0, kq);
+                    bq[at] = v.hi;
+                    bq[at + 4] = v.mid;
+                    bq[at + 8] = v.lo;
+                }
+            } else {
                 uint16_t *ah = reinterpret_cast<uint16_t *>(As), *bh = reinterpret_cast<uint16_t *>(Bs);
 #pragma unroll
                 for (int i = 0; i < RA; ++i)
-                    *reinterpret_cast<uint2 *>(&ah[(row_in + ROWS * i) * LDH + kq * 4]) =
-                        make_uint2(bf16_pack2(ra[i].x, ra[i].y), bf16_pack2(ra[i].z, ra[i].w));
+                    *reinterpret_cast<uint2 *>(&ah[(arow + AROWS * i) * LDH + akq * 4]) =
+                        make_uint2(bf16_pack2(ra[i][0].x, ra[i][0].y), bf16_pack2(ra[i][0].z, ra[i][0].w));
 #pragma unroll
                 for (int i = 0; i < RB; ++i)
-                    *reinterpret_cast<uint2 *>(&bh[(row_in + ROWS * i) * LDH + kq * 4]) =
-                        make_uint2(bf16_pack2(rb[i].x, rb[i].y), bf16_pack2(rb[i].z, rb[i].w));
-                return;
+                    *reinterpret_cast<uint2 *>(&bh[(row_in + BROWS * i) * LDH + kq * 4]) =
+                        make_uint2(bf16_pack2(rb[i][0].x, rb[i][0].y), bf16_pack2(rb[i][0].z, rb[i][0].w));
             }
-#pragma unroll
-            for (int i = 0; i < RA; ++i) *reinterpret_cast<float4 *>(&As[(row_in + ROWS * i) * kLDK + kq * 4]) = ra[i];
-#pragma unroll
-            for (int i = 0; i < RB; ++i) *reinterpret_cast<float4 *>(&Bs[(row_in + ROWS * i) * kLDK + kq * 4]) = rb[i];
         };
 
         floatx16 acc[MI][NI];
+        floatx16 accl[SPLIT ? MI : 1][SPLIT ? NI : 1];  // SPLIT: the five small products
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                for (int e = 0; e < 16; ++e) {
+                    acc[i][j][e] = 0.f;
+                    if constexpr (SPLIT) accl[i][j][e] = 0.f;
+                }
 
         // Row order 2, tile inside one parity class (ph, pw): tap (r, s) reaches a row only when ph + off + r and
         // pw + off + s are multiples of the dilation (2): the other chunks are skipped.  Uniform over the workgroup.
@@ -429,58 +492,33 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                         for (int j = 0; j < NI; ++j)
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah8[i], bh8[j], acc[i][j], 0, 0, 0);
                 }
-            } else if constexpr (BM == 128 && BN == 64) {
-                // no registers to spare for a second fragment set here (it spills)
-#pragma unroll
-                for (int kg = 0; kg < kBK / 8; ++kg) {
-                    float4 af[MI], bf[NI];
-#pragma unroll
-                    for (int i = 0; i < MI; ++i) af[i] = *reinterpret_cast<const float4 *>(&As[(wm * WTM + i * 32) * kLDK + frag_off + kg * 8]);
-#pragma unroll
-                    for (int j = 0; j < NI; ++j) bf[j] = *reinterpret_cast<const float4 *>(&Bs[(wn * WTN + j * 32) * kLDK + frag_off + kg * 8]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-#pragma unroll
-                            for (int j = 0; j < NI; ++j) {
-                                const float av = e == 0 ? af[i].x : e == 1 ? af[i].y : e == 2 ? af[i].z : af[i].w;
-                                const float bv = e == 0 ? bf[j].x : e == 1 ? bf[j].y : e == 2 ? bf[j].z : bf[j].w;
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
-                            }
-                }
             } else {
-                // The fragments of group kg+1 are read from LDS while the MFMAs of group kg run (two register sets); the
-                // scheduling hints keep that order: read, then multiply, group by group.  Read and used back to back, every
-                // group would start with the latency of its LDS reads.
-                float4 af[2][MI], bf[2][NI];
-                auto load_frag = [&](int set, int kg) {
+                // lane l: row l%32 of the block, chunk l/32 of the two that one MFMA takes
+                const uint4 *aq = reinterpret_cast<const uint4 *>(As), *bq = reinterpret_cast<const uint4 *>(Bs);
 #pragma unroll
-                    for (int i = 0; i < MI; ++i) af[set][i] = *reinterpret_cast<const float4 *>(&As[(wm * WTM + i * 32) * kLDK + frag_off + kg * 8]);
+                for (int ks = 0; ks < 2; ++ks) {
+                    const int c = ks * 2 + (lane >> 5);
+                    uint4 af[MI][3], bf[NI][3];
 #pragma unroll
-                    for (int j = 0; j < NI; ++j) bf[set][j] = *reinterpret_cast<const float4 *>(&Bs[(wn * WTN + j * 32) * kLDK + frag_off + kg * 8]);
-                };
-                load_frag(0, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+                    for (int t = 0; t < 3; ++t) {
 #pragma unroll
-                for (int kg = 0; kg < kBK / 8; ++kg) {
-                    if (kg + 1 < kBK / 8) {
-                        load_frag((kg + 1) & 1, kg + 1);
-                        __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+                        for (int i = 0; i < MI; ++i) af[i][t] = aq[split_chunk(wm * WTM + i * 32 + (lane & 31), t, c)];
+#pragma unroll
+                        for (int j = 0; j < NI; ++j) bf[j][t] = bq[split_chunk(wn * WTN + j * 32 + (lane & 31), t, c)];
                     }
-                    // consecutive MFMAs go to different accumulators
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                    for (int pr = 0; pr < 6; ++pr) {
+                        // (hi,hi) (hi,mid) (mid,hi) (mid,mid) (hi,lo) (lo,hi); consecutive MFMAs go to different accumulators
+                        constexpr int ta[6] = {0, 0, 1, 1, 0, 2}, tb[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll
                         for (int i = 0; i < MI; ++i)
 #pragma unroll
                             for (int j = 0; j < NI; ++j) {
-                                const float4 a4 = af[kg & 1][i], b4 = bf[kg & 1][j];
-                                const float av = e == 0 ? a4.x : e == 1 ? a4.y : e == 2 ? a4.z : a4.w;
-                                const float bv = e == 0 ? b4.x : e == 1 ? b4.y : e == 2 ? b4.z : b4.w;
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                                floatx16 &d = pr == 0 ? acc[i][j] : accl[i][j];
+                                d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i][ta[pr]]),
+                                                                            __builtin_bit_cast(bf16x8, bf[j][tb[pr]]), d, 0, 0, 0);
                             }
-                    __builtin_amdgcn_sched_group_barrier(0x008, 4 * MI * NI, 0);
+                    }
                 }
             }
             __syncthreads();
@@ -490,6 +528,69 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                 __syncthreads();
             }
             kc = kc_next;
+        }
+
+        if constexpr (SPLIT) {
+            float probe = 0.f;  // NaN when a sum is not finite
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        acc[i][j][e] += accl[i][j][e];
+                        probe = fmaf(acc[i][j][e], 0.f, probe);
+                    }
+            if (__any(probe != probe)) {
+                // an operand or a sum that is not finite: this wavefront's block again on the fp32 instruction, straight from
+                // memory (slow, and only where the answer holds infinities or NaNs)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                int ih0[MI], iw0[MI], base[MI];
+#pragma unroll
+                for (int i = 0; i < MI; ++i) {
+                    const int m = m0 + wm * WTM + i * 32 + (lane & 31);
+                    int cls, n, oh, ow;
+                    decode_row(p, min(m, p.M - 1), cls, n, oh, ow);
+                    if (p.scatter2 == 2) {
+                        oh = 2 * oh + (cls >> 1);
+                        ow = 2 * ow + (cls & 1);
+                    }
+                    ih0[i] = m < p.M ? oh * p.so + p.off : -(1 << 28);
+                    iw0[i] = ow * p.so + p.off;
+                    base[i] = n * (p.IH * p.IW * p.Cin);
+                }
+                for (int kr = next_chunk(kc_begin); kr < kc_end; kr = next_chunk(kr + 1))
+                    for (int k2 = 0; k2 < BK; k2 += 2) {
+                        const int k = kr * BK + k2 + (lane >> 5);
+                        const bool kin = k < p.Kdim;
+                        const int tap = (int)fdiv(k, p.div_cin), c = k - tap * p.Cin;
+                        const int r = (int)fdiv(tap, p.div_s), sx = tap - r * p.S;
+                        float va[MI], vb[NI];
+#pragma unroll
+                        for (int i = 0; i < MI; ++i) {
+                            int ih = ih0[i] + r, iw = iw0[i] + sx;
+                            const bool ok = kin && ih >= 0 && iw >= 0 && ih % p.sd == 0 && iw % p.sd == 0 && ih / p.sd < p.IH && iw / p.sd < p.IW;
+                            ih /= p.sd;
+                            iw /= p.sd;
+                            va[i] = ok ? p.a[(unsigned)(base[i] + (ih * p.IW + iw) * p.Cin + c)] : 0.f;
+                            if (INAFF && ok) va[i] = fmaxf(fmaf(va[i], p.in_scale[c], p.in_shift[c]), 0.f);
+                        }
+#pragma unroll
+                        for (int j = 0; j < NI; ++j) {
+                            const int col = n0 + wn * WTN + j * 32 + (lane & 31);
+                            vb[j] = kin && col < p.Nout ? p.b[(long)col * p.Kdim + k] : 0.f;
+                        }
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+#pragma unroll
+                            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], acc[i][j], 0, 0, 0);
+                    }
+            }
         }
 
         // Column statistics of the tile (whole tiles only: the pieces of a split tile are added up by another kernel, which

@@ -1,0 +1,110 @@
+"""fp32 convolutions on the bf16 matrix instruction: every operand is the exact sum of three bf16 terms.  What that could break
+and a plain comparison at the usual bar would not show: precision below the bar, operands that have no finite split, magnitudes
+whose small terms leave the bf16 range.  References: float64 on the CPU from the same fp32 operands."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1711_04325_amd import binding as rn
+from tests.gpu_util import empty, ws_bytes
+
+pytestmark = pytest.mark.gpu
+
+# (n, c, h, k, r, stride, pad): vector and scalar gathers, ragged row and column tiles, strided data gradients of both kinds
+CASES = [(2, 64, 14, 64, 3, 1, 1), (1, 32, 9, 68, 1, 1, 0), (3, 96, 13, 160, 3, 2, 1), (2, 20, 11, 24, 3, 1, 1), (2, 128, 8, 64, 1, 2, 0),
+         (4, 256, 7, 256, 3, 1, 1), (2, 64, 16, 128, 3, 2, 1)]
+
+
+def _conv64(x, w, stride, pad):
+    return torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), w.double().permute(0, 3, 1, 2), stride=stride, padding=pad).permute(0, 2, 3, 1)
+
+
+def _dx64(dy, w, stride, pad, h):
+    return torch.nn.grad.conv2d_input((dy.shape[0], w.shape[3], h, h), w.double().permute(0, 3, 1, 2), dy.double().permute(0, 3, 1, 2), stride,
+                                      pad).permute(0, 2, 3, 1)
+
+
+def _dw64(x, dy, r, stride, pad):
+    return torch.nn.grad.conv2d_weight(x.double().permute(0, 3, 1, 2), (dy.shape[3], x.shape[3], r, r), dy.double().permute(0, 3, 1, 2), stride,
+                                       pad).permute(0, 2, 3, 1)
+
+
+def _operands(case, seed, scale=1.0):
+    n, c, h, k, r, stride, pad = case
+    g = torch.Generator().manual_seed(seed)
+    p = (h + 2 * pad - r) // stride + 1
+    x, dy = torch.randn(n, h, h, c, generator=g) * scale, torch.randn(n, p, p, k, generator=g) * scale
+    return x, torch.randn(k, r, r, c, generator=g) * (2.0 / (c * r * r)) ** 0.5, dy
+
+
+def _device(case, x, w, dy):
+    """Forward output, data gradient, filter gradient."""
+    n, c, h, k, r, stride, pad = case
+    d = rn.conv_desc(n, c, h, h, k, r, r, stride, pad)
+    dx_, dw_, ddy = x.cuda(), w.cuda(), dy.cuda()
+    y, dx, dw = torch.full_like(ddy, 7.0), torch.full_like(dx_, 7.0), torch.full_like(dw_, 7.0)
+    rn.conv2d_fwd(d, dx_, dw_, y, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD)))
+    rn.conv2d_bwd_data(d, ddy, dw_, dx, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA)))
+    rn.conv2d_bwd_weight(d, dx_, ddy, dw, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_WEIGHT)))
+    torch.cuda.synchronize()
+    return y.cpu(), dx.cpu(), dw.cpu()
+
+
+# 1e-30: the smallest terms of a split are 2^-24 of it, 6e-38, still normal; sums of products stay above 1e-38 as w is of order 0.1
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 1e25])
+@pytest.mark.parametrize("case", CASES)
+def test_precision_is_that_of_fp32_sums(case, scale):
+    """One rounding of a sum of up to 16 products at a time: rms error of L/16 roundings of 2^-25 of the growing sum, below
+    2^-25 * sqrt(L/16) * 2; the longest reduction here (2304) gives 7e-7.  The bar is 8e-7 for all (fp32 sums product by product
+    would need 2e-6)."""
+    n, c, h, k, r, stride, pad = case
+    x, w, dy = _operands(case, 11 + sum(case), scale)
+    got = _device(case, x, w, dy)
+    if scale != 1.0:
+        got = got[:2]   # the filter gradient multiplies two scaled tensors: out of range by design
+    refs = (_conv64(x, w, stride, pad), _dx64(dy, w, stride, pad, h), _dw64(x, dy, r, stride, pad))
+    for what, a, b in zip(("fwd", "bwd_data", "bwd_weight"), got, refs):
+        err = ((a.double() - b).norm() / b.norm()).item()
+        assert err <= 8e-7, "%s %s scale %g: %.2e" % (what, case, scale, err)
+
+
+@pytest.mark.parametrize("plan", [None, "128,128,1", "64,64,3"])
+@pytest.mark.parametrize("case", CASES)
+def test_values_without_a_finite_split(case, plan):
+    """Infinities, NaNs and numbers that round to infinity in bf16 (3.39e38 .. 3.4028e38) give what fp32 arithmetic gives:
+    infinities stay infinities of their sign, NaN only where infinities of both signs or a NaN meet, and every output
+    that the value does not touch is what it was."""
+    n, c, h, k, r, stride, pad = case
+    x, w, dy = _operands(case, 23 + sum(case))
+    x[0, 1, 2, 3], x[n - 1, h - 1, h - 1, c - 1], x[0, h - 1, 0, 5], x[0, 3, 3, 1] = np.inf, -np.inf, np.nan, 3.4e38
+    dy[0, 0, 0, 2], dy[n - 1, -1, -1, k - 1], dy[0, -1, 0, 7] = np.inf, -np.inf, np.nan
+    w[k - 1, 0, 0, 0] = np.inf
+    if plan:
+        rn.rn50_set_option("igemm_plan", plan)
+        rn.rn50_set_option("wgrad_plan", plan)
+    try:
+        y, dx, dw = _device(case, x, w, dy)
+    finally:
+        rn.rn50_set_option("igemm_plan", None)
+        rn.rn50_set_option("wgrad_plan", None)
+    # float64 sums of the same operands; beyond the fp32 range they are infinities in fp32.  Padding multiplies as a zero on both
+    # sides, so an infinite weight makes NaNs along the border.
+    for what, got, ref in (("fwd", y, _conv64(x, w, stride, pad)), ("bwd_weight", dw, _dw64(x, dy, r, stride, pad))):
+        ref32 = ref.float()
+        fine = torch.isfinite(ref32) & (ref.abs() < 1e38)
+        assert torch.equal(torch.isfinite(got)[fine], fine[fine]), what
+        ok = fine & (ref.abs() < 1e30)
+        err = ((got.double() - ref)[ok].norm() / ref[ok].norm()).item()
+        assert err <= 8e-7, "%s: %.2e" % (what, err)
+        both = torch.isinf(ref32) & torch.isinf(ref)
+        assert torch.equal(got[both], ref32[both]), what      # signed infinities
+        assert torch.isnan(got[torch.isnan(ref32)]).all(), what
+    # the data gradient: elements that no special value reaches (the infinite weight touches input channel 0 of the border too)
+    ref = _dx64(dy, w, stride, pad, h)
+    assert torch.isnan(dx[torch.isnan(ref)]).all()
+    fine = torch.isfinite(ref)
+    fine[..., 0] = False
+    assert torch.isfinite(dx[fine]).all() and ((dx.double() - ref)[fine].norm() / ref[fine].norm()).item() <= 8e-7
+    both = torch.isinf(ref)
+    both[..., 0] = False
+    assert torch.equal(dx.double()[both], ref[both])
