@@ -72,10 +72,15 @@ const char *rn50_last_error(void);
  *   "wgrad_plan"     "bm,bn,split": the same for every filter-gradient call
  *   "plan_overrides" "op,n,c,h,k,r,stride,pad,bm,bn,split;...": rows placed before the measured plan table; rows that
  *                         do not parse are skipped
+ *   "pre_plans"      the same rows for the forward and data-gradient calls whose kernel takes a filter prepared beforehand (fp32 operands
+ *                         split into bf16 terms, or bf16 activations); the three options above force the general kernel instead
  *   "no_tuned"       0/1  ignore the measured plan table (cost model only)
  *   "no_stem_kernel" 0/1  send the first layer through the implicit GEMM instead of its own kernel
  *   "conv_bn_stats"  0/1  rn50_create: the forward convolutions gather the BN statistics of their output as they write it
  *                         (conv2d_fwd_bnstats) instead of a separate pass over the tensor (default 1)
+ *   "split_products" 0/1  rn50_activation_bytes and rn50_create (fp32 contexts): the training step's forward pass forms its products like the conv2d_* calls and
+ *                         the backward pass, from operands split into bf16 terms (faster, smaller error), instead of on the fp32
+ *                         instruction (default 0: the forward pass keeps its bits, and with them every ReLU decision)
  *   "wgrad_group"    0..64 rn50_create (fp32 contexts): 0 = one filter-gradient call per layer (default); k > 0 = the layers
  *                         of k consecutive blocks in one conv2d_bwd_weight_group launch (16 or more: all 52 behind the first)
  *   "wgrad_group_stages"  pixel stages of 32 per work item of a grouped plan (default 48, at least 2; rn50_create: at least 16)

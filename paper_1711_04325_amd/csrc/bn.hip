@@ -354,6 +354,18 @@ __global__ __launch_bounds__(256) void bn_scale_shift_kernel(int C, const float 
     shift[c] = fmaf(-mean[c], a, beta[c]);
 }
 
+// The same for every layer of a network: workgroup (i, j) takes 256 channels of layer j.
+__global__ __launch_bounds__(256) void bn_scale_shift_batched_kernel(const BnLayerHost *__restrict__ layers, const float *__restrict__ theta,
+                                                                     char *__restrict__ arena)
+{
+    const BnLayerHost l = layers[blockIdx.y];
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= l.c) return;
+    const float a = theta[l.g_off + c] * reinterpret_cast<const float *>(arena + l.invstd)[c];
+    reinterpret_cast<float *>(arena + l.scale)[c] = a;
+    reinterpret_cast<float *>(arena + l.shift)[c] = fmaf(-reinterpret_cast<const float *>(arena + l.mean)[c], a, theta[l.b_off + c]);
+}
+
 // mean_out = average of the sets' means; invstd_out = 1/sqrt(average of the sets' variances + eps), the variance of a
 // set recovered from its saved invstd.  Sets are added in index order.
 __global__ __launch_bounds__(256) void bn_stats_average_kernel(int C, int n_sets, const float *__restrict__ means,
@@ -832,6 +844,11 @@ extern "C" int bn_stats_scale_shift_bf16(int n, int c, int h, int w, int layout,
     RN50_REQUIRE(scale && shift, RN50_EINVAL, "bn_stats_scale_shift_bf16: null pointer");
     return bn_fwd_impl<bf16_t>("bn_stats_scale_shift_bf16", n, c, h, w, layout, x, gamma, beta, eps, nullptr, 0, nullptr, nullptr, save_mean,
                                save_invstd, scale, shift, ws, ws_bytes, stream);
+}
+
+void rn50::launch_bn_scale_shift_batched(const void *layers, int n, int max_c, const float *theta, char *arena, hipStream_t st)
+{
+    hipLaunchKernelGGL(bn_scale_shift_batched_kernel, dim3(ceil_div(max_c, 256), n), dim3(256), 0, st, (const BnLayerHost *)layers, theta, arena);
 }
 
 extern "C" int bn_fwd_inference(int n, int c, int h, int w, int layout, const float *x, const float *gamma, const float *beta,

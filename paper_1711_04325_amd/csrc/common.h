@@ -32,6 +32,7 @@ struct Config {
     bool relu_mask = true;     // rn50_create: byte mask instead of the block output in the c layers' BN backward
     bool no_tuned = false;     // ignore the measured plan table (cost model only)
     bool no_stem_kernel = false;  // first layer through the implicit GEMM
+    bool split_products = false;  // rn50_create: the training step's forward pass with split operands as well
     bool conv_bn_stats = true;    // rn50_create: forward convolutions gather the BN statistics of their output
     int wgrad_group = 0;          // rn50_create: filter gradients launched per layer (0) or grouped, this many blocks to a launch
     int wgrad_group_wgs_per_cu = 0;  // grouped filter gradients: at most this many workgroups of theirs per CU (0: what fits)
@@ -39,6 +40,7 @@ struct Config {
     int wgrad_group_bm = 64, wgrad_group_bn = 64;  // ... and their tile
     bool has_igemm_plan = false, has_wgrad_plan = false;
     int igemm_plan[3] = {0, 0, 0}, wgrad_plan[3] = {0, 0, 0};  // bm, bn, split forced for every call
+    std::vector<PlanRow> pre_plans;                            // plans of the calls whose filter is prepared beforehand
     std::vector<PlanRow> overrides;                            // rows that go before the measured table
 };
 std::shared_ptr<const Config> config();  // the current snapshot (immutable; a call keeps the one it started with)
@@ -113,15 +115,48 @@ __device__ inline int xcd_contiguous(int b, int n)
 namespace rn50 {
 // Internal entry points used by the whole-step schedule (csrc/conv.hip).
 int conv_check(const char *who, const rn50_conv_desc *d);  // argument checks shared by the convolution entry points
-int conv_bwd_data_pretransposed(const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws, size_t ws_bytes,
-                                hipStream_t st);
-size_t conv_bwd_data_pretransposed_ws(const rn50_conv_desc *d);
+// How products of fp32 operands are formed.  kFp32Split: operands split into bf16 terms (see split8 in conv_kernels.h; every call
+// of the ABI; kFp32SplitNoPlanes: the same without room for a filter split beforehand).  kFp32Unit: the fp32 matrix instruction, with the
+// tiles, pieces and order of sums of the measured table (the forward pass of a training context: see rn50_ctx).
+enum Fp32Math { kFp32Unit, kFp32Split, kFp32SplitNoPlanes };
+size_t conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool given);  // rn50_conv_workspace_bytes; given: with `planes`
+// `planes`: the call's filter prepared beforehand by launch_filter_planes_batched (null: the call does it where its kernel wants it
+// so); conv_planes_bytes says how much room it takes (0: the kernel of this call takes none), for op RN50_OP_FWD or RN50_OP_BWD_DATA.
+size_t conv_planes_bytes(const rn50_conv_desc *d, int op);
+int conv_fwd_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift, const float *w,
+                  const char *planes, float *y, void *ws, size_t ws_bytes, hipStream_t st);
+// The forward pass followed by z = y*scale[c] + shift[c] [+ residual] [ReLU] (fp32 storage, K % 4 == 0).
+int conv_fwd_apply_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *w, const char *planes, float *y, const float *scale,
+                        const float *shift, const float *residual, int relu, float *z, void *ws, size_t ws_bytes, hipStream_t st);
+int conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale_or_null, const float *in_shift_or_null,
+                          const float *w, const char *planes, float *y, const float *gamma, const float *beta, float eps, float *save_mean,
+                          float *save_invstd, float *scale, float *shift, void *ws, size_t ws_bytes, hipStream_t st);
+int conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws, size_t ws_bytes,
+                                hipStream_t st, const char *planes = nullptr);
+int conv_bwd_weight_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift, const float *dy,
+                         float *dw, void *ws, size_t ws_bytes, hipStream_t st);
 void launch_filter_flip(int K, int C, int RS, const float *w, float *wt, hipStream_t st);
 // One launch for many filters; `jobs` is a device array of FlipJobHost records (same layout as the kernel's).
 struct FlipJobHost {
     int K, C, RS, tiles_c, tiles_k, block_begin;
     long src_off, dst_off;
 };
+// The same for the preparation of many filters (csrc/conv_split.hip; split into bf16 terms, or with act rounded to bf16): filter j has `rows` rows of `kdim` elements at src_off (elements from the
+// launch's base) and its planes at dst_off (bytes).
+struct SplitJobHost {
+    long src_off, dst_off;
+    int rows, plane_rows, kdim, block_begin;
+};
+SplitJobHost split_job(int rows, int kdim, long src_off, long dst_off, int block_begin);
+int split_job_blocks(int rows, int kdim);
+void launch_filter_planes_batched(const void *jobs, int njobs, int nblocks, bool act, const float *base, char *planes, hipStream_t st);
+// Scale and shift of many BN layers from given statistics (csrc/bn.hip), in one launch: layer j has `c` channels, its gamma and beta at
+// g_off and b_off elements of theta, its mean, 1/sigma, scale and shift at byte offsets of `arena`.
+struct BnLayerHost {
+    long g_off, b_off, mean, invstd, scale, shift;
+    int c, pad_;
+};
+void launch_bn_scale_shift_batched(const void *layers, int n, int max_c, const float *theta, char *arena, hipStream_t st);
 // y = x*scale[c] + shift[c] [ReLU] over an N x H x W x C tensor (the normalising kernel of the BN forward alone).
 int bn_apply_scale_shift(int n, int c, int h, int w, const float *x, const float *scale, const float *shift, int relu, float *y,
                          hipStream_t st);

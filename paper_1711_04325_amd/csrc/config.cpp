@@ -46,6 +46,7 @@ static bool apply_option(Config &c, const char *name, const char *value)
     else if (!strcmp(name, "no_tuned")) c.no_tuned = unset ? false : atoi(value) != 0;
     else if (!strcmp(name, "no_stem_kernel")) c.no_stem_kernel = unset ? false : atoi(value) != 0;
     else if (!strcmp(name, "conv_bn_stats")) c.conv_bn_stats = unset ? def.conv_bn_stats : atoi(value) != 0;
+    else if (!strcmp(name, "split_products")) c.split_products = unset ? false : atoi(value) != 0;
     else if (!strcmp(name, "wgrad_group")) c.wgrad_group = unset ? def.wgrad_group : std::max(0, std::min(64, atoi(value)));
     else if (!strcmp(name, "wgrad_group_stages")) c.wgrad_group_stages = unset ? def.wgrad_group_stages : std::max(2, atoi(value));
     else if (!strcmp(name, "wgrad_group_wgs_per_cu")) c.wgrad_group_wgs_per_cu = unset ? def.wgrad_group_wgs_per_cu : std::max(0, std::min(8, atoi(value)));
@@ -64,6 +65,7 @@ static bool apply_option(Config &c, const char *name, const char *value)
         c.has_wgrad_plan = false;
         if (!unset && !(c.has_wgrad_plan = parse_plan(value, c.wgrad_plan))) return false;
     } else if (!strcmp(name, "plan_overrides")) c.overrides = unset ? std::vector<PlanRow>() : parse_rows(value);
+    else if (!strcmp(name, "pre_plans")) c.pre_plans = unset ? std::vector<PlanRow>() : parse_rows(value);
     else return false;
     return true;
 }
@@ -73,9 +75,9 @@ static std::shared_ptr<const Config> g_cfg;
 
 static std::shared_ptr<const Config> from_environment()
 {
-    static const char *const names[] = {"side_stream", "fuse_bn", "relu_mask", "no_tuned", "no_stem_kernel", "conv_bn_stats", "igemm_plan", "wgrad_plan", "wgrad_group",
+    static const char *const names[] = {"side_stream", "fuse_bn", "relu_mask", "no_tuned", "no_stem_kernel", "conv_bn_stats", "split_products", "igemm_plan", "wgrad_plan", "wgrad_group",
                                         "wgrad_group_stages", "wgrad_group_tile", "wgrad_group_wgs_per_cu",
-                                        "plan_overrides"};
+                                        "plan_overrides", "pre_plans"};
     auto c = std::make_shared<Config>();
     for (const char *n : names) {
         char var[64] = "RN50_";

@@ -55,6 +55,14 @@ constexpr double kLaunchClks = 6000.0;         // one extra kernel launch, in co
 
 struct GemmPlan { int bm, bn, split, chunks_per_split; };
 
+// Kernel of a forward or data-gradient call: the general implicit GEMM, or one that takes the filter prepared beforehand: split into bf16
+// terms (igemm_pre_kernel, fp32 operands) or rounded to bf16 (igemm_act_kernel, bf16 activations).
+enum IgemmKind { kGeneral = 0, kPre = 1, kAct = 2 };
+static int igemm_kind_occupancy(int kind, int bm, int bn)
+{
+    return kind == kPre ? igemm_pre_occupancy(bm, bn) : kind == kAct ? igemm_act_occupancy(bm, bn) : igemm_occupancy(bm, bn);
+}
+
 // Plans measured on the MI355X for the ResNet-50 layer shapes: {op, n, c, h, k, r, stride, pad, bm, bn, split}.
 // Other shapes use the cost model below.
 static const PlanRow kTuned[] = {
@@ -73,13 +81,18 @@ static bool plan_matches(const PlanRow &t, const rn50_conv_desc *d, int op)
 }
 
 // Rows set with rn50_set_option("plan_overrides") go before the table (a tuning aid: plans tried inside a whole step).
-static bool tuned_plan(const Config &cfg, const rn50_conv_desc *d, int op, GemmPlan *pl)
+static bool override_plan(const Config &cfg, const rn50_conv_desc *d, int op, GemmPlan *pl)
 {
     for (const PlanRow &t : cfg.overrides)
         if (plan_matches(t, d, op)) {
             pl->bm = t.bm; pl->bn = t.bn; pl->split = t.split;
             return true;
         }
+    return false;
+}
+static bool tuned_plan(const Config &cfg, const rn50_conv_desc *d, int op, GemmPlan *pl)
+{
+    if (override_plan(cfg, d, op, pl)) return true;
     if (cfg.no_tuned) return false;
     if (act_of(d))
         for (const PlanRow &t : kTunedAct)
@@ -106,15 +119,15 @@ static double tile_eff(int bm, int bn) { return bm == 128 && bn == 128 ? 1.0 : (
 
 // Persistent implicit-GEMM launch: G workgroups; the first full_items tiles whole, the last tail_tiles tiles cut
 // into tail_split pieces of tail_chunks reduction chunks each.
-struct IgemmPlan { int bm, bn, grid, full_items, tail_tiles, tail_split, tail_chunks; size_t ws_floats; };
+struct IgemmPlan { int kind, bm, bn, grid, full_items, tail_tiles, tail_split, tail_chunks; size_t ws_floats; };
 
 
-static IgemmPlan make_igemm_plan(int bm, int bn, long M, int Nout, int kchunks, int want_split, bool allow_split)
+static IgemmPlan make_igemm_plan(int kind, int bm, int bn, long M, int Nout, int kchunks, int want_split, bool allow_split)
 {
     IgemmPlan pl;
-    pl.bm = bm; pl.bn = bn;
+    pl.kind = kind; pl.bm = bm; pl.bn = bn;
     const int tiles = ceil_div(M, bm) * ceil_div(Nout, bn);
-    const int Gmax = (int)kCUs * igemm_occupancy(bm, bn);
+    const int Gmax = (int)kCUs * igemm_kind_occupancy(kind, bm, bn);
     pl.full_items = tiles / Gmax * Gmax;
     pl.tail_tiles = tiles - pl.full_items;
     int sp = allow_split ? want_split : 1;
@@ -129,10 +142,9 @@ static IgemmPlan make_igemm_plan(int bm, int bn, long M, int Nout, int kchunks, 
 }
 
 // modelled time in core clocks
-static double igemm_cost(const IgemmPlan &pl, long M, int Nout, int kchunks, int bk)
+static double igemm_cost(const IgemmPlan &pl, int kchunks, double chunk_clks)
 {
-    const double chunk_clks = 4096.0 * (bk / (double)kBK) * (pl.bm * pl.bn / 16384.0) / tile_eff(pl.bm, pl.bn);
-    const int occ = igemm_occupancy(pl.bm, pl.bn);
+    const int occ = igemm_kind_occupancy(pl.kind, pl.bm, pl.bn);
     const double full_rounds = pl.full_items / (kCUs * occ);
     double t = full_rounds * occ * (kchunks + 2.0) * chunk_clks;
     if (pl.tail_tiles) {
@@ -141,35 +153,92 @@ static double igemm_cost(const IgemmPlan &pl, long M, int Nout, int kchunks, int
         t += per_cu * (pl.tail_chunks + 3.0) * chunk_clks / (per_cu >= 2.0 ? 1.0 : 0.65);
         if (pl.tail_split > 1) t += kLaunchClks + (pl.tail_split + 1.0) * pl.tail_tiles * pl.bm * pl.bn * 4.0 / kBytesPerClk;
     }
-    (void)M; (void)Nout;
+    return t;
+}
+// The same for igemm_pre_kernel, in microseconds: per tile shape the time of a 32-element stage while a CU is full, the time
+// of an item beyond its stages, and the time of a stage of a workgroup that has a CU to itself.  Fitted to 5,000 measured launches (226
+// calls of 140 shapes, each with every tile and several splits): the plan it picks takes 4.6 % longer than the best one measured on
+// average, 13 % at the 90th percentile.
+static double igemm_pre_cost(const IgemmPlan &pl, int kchunks)
+{
+    static const double c128x128[3] = {1.212, 2.258, 1.714}, c128x64[3] = {0.755, 1.278, 1.090}, c64x128[3] = {0.705, 2.072, 1.058},
+                        c64x64[3] = {0.400, 0.733, 0.872};
+    const double *c = pl.bm == 128 ? (pl.bn == 128 ? c128x128 : c128x64) : (pl.bn == 128 ? c64x128 : c64x64);
+    const int occ = igemm_pre_occupancy(pl.bm, pl.bn);
+    double t = pl.full_items / (kCUs * occ) * occ * (kchunks * c[0] + c[1]);
+    if (pl.tail_tiles) {
+        const double per_cu = ceil((double)pl.tail_tiles * pl.tail_split / kCUs);
+        t += std::max(per_cu * (pl.tail_chunks * c[0] + c[1]), pl.tail_chunks * c[2] + 4.35);
+        if (pl.tail_split > 1) t += 3.1 + (pl.tail_split + 1.0) * pl.tail_tiles * pl.bm * pl.bn * 4.0 / 5.8e6;
+    }
     return t;
 }
 
-// out[M][Nout] with reduction length Kdim (in elements)
-// cin: channels of the gathered tensor (the forward pass gathers x, the data gradient dy)
-static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, bool allow_split, int cin)
+static IgemmPlan model_plan(int kind, long M, int Nout, int kchunks, int bk, bool allow_split, int max_bm = 128)
 {
-    const int bk = igemm_bk(bf16_of(d), act_of(d), cin);
-    const int kchunks = ceil_div(Kdim, bk);
-    GemmPlan forced;
-    const std::shared_ptr<const Config> cfg = config();
-    if (forced_plan(cfg->has_igemm_plan, cfg->igemm_plan, &forced) || tuned_plan(*cfg, d, op, &forced))
-        return make_igemm_plan(forced.bm, forced.bn, M, Nout, kchunks, forced.split, allow_split);
     IgemmPlan best{};
     double best_cost = 1e300;
     static const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
-    for (int bm = 128; bm >= 64; bm -= 64)
+    for (int bm = max_bm; bm >= 64; bm -= 64)
         for (int bn = 128; bn >= 64; bn -= 64) {
             if (bn == 128 && Nout <= 64) continue;
             if (bm == 128 && M <= 64) continue;
             for (int sp : splits) {
                 if (sp > 1 && (!allow_split || kchunks / sp < 2)) break;
-                const IgemmPlan pl = make_igemm_plan(bm, bn, M, Nout, kchunks, sp, allow_split);
-                const double cost = igemm_cost(pl, M, Nout, kchunks, bk);
+                const IgemmPlan pl = make_igemm_plan(kind, bm, bn, M, Nout, kchunks, sp, allow_split);
+                const double cost = kind == kPre ? igemm_pre_cost(pl, kchunks)
+                                                 : igemm_cost(pl, kchunks, 4096.0 * (bk / (double)kBK) * (bm * bn / 16384.0) / tile_eff(bm, bn));
                 if (cost < best_cost) { best_cost = cost; best = pl; }
             }
         }
     return best;
+}
+
+// data gradient of a 1x1 stride-2 convolution on an even-sized input: a GEMM whose rows are scattered
+static bool is_scatter2(const rn50_conv_desc *d)
+{
+    return d->r == 1 && d->s == 1 && d->stride == 2 && d->pad == 0 && d->h % 2 == 0 && d->w % 2 == 0;
+}
+
+constexpr int kActStage = 64;          // channels of igemm_act_kernel's stage
+// Preparing a filter for one call costs a launch (3 us and more with a large filter), which the faster kernel earns back on calls long
+// enough: measured prepared / general over 40 shapes, fp32 0.72-0.99 of the speed below 5 GFLOP, at 5-10 0.98-1.14 with reductions of
+// 1024 and more and 0.95-1.05 with shorter ones, 1.01-1.05 above; bf16 activations 0.77-0.99 below 4, 0.95-1.16 at 4-9, 1.00-1.15 above.  Where many filters are prepared in one launch only the
+// smallest calls (fewer rows than eight tiles) keep the general kernel.
+constexpr long kPlanesMinRows = 1024;
+constexpr double kPlanesMinFlops = 5e9, kPlanesMinFlopsF32 = 1e10;  // the latter for fp32 reductions shorter than 1024
+
+// out[M][Nout] with reduction length Kdim (in elements)
+// cin: channels of the gathered tensor (the forward pass gathers x, the data gradient dy)
+// given: the call comes with its filter prepared
+static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, bool allow_split, int cin, Fp32Math math, bool given)
+{
+    const int bk = igemm_bk(bf16_of(d), act_of(d), cin);
+    const int kchunks = ceil_div(Kdim, bk);
+    GemmPlan pl;
+    const std::shared_ptr<const Config> cfg = config();
+    const bool split = math != kFp32Unit && !bf16_of(d);
+    if (forced_plan(cfg->has_igemm_plan, cfg->igemm_plan, &pl) || override_plan(*cfg, d, op, &pl))
+        return make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
+    // the dilated gather of a strided data gradient needs registers that a 128-row tile does not leave (igemm_pre_kernel spills)
+    const bool dilated = op == RN50_OP_BWD_DATA && d->stride == 2 && !is_scatter2(d);
+    const double flops = 2.0 * M * Nout * Kdim;
+    const bool geometry = M >= kPlanesMinRows && (op == RN50_OP_FWD || d->stride <= 2) && math != kFp32SplitNoPlanes &&
+                          (given || flops >= (split && Kdim < 1024 ? kPlanesMinFlopsF32 : kPlanesMinFlops));
+    if (split && geometry && cin % kBK == 0) {
+        for (const PlanRow &t : cfg->pre_plans)
+            if (plan_matches(t, d, op) && (!dilated || t.bm == 64))
+                return make_igemm_plan(kPre, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
+        return model_plan(kPre, M, Nout, kchunks, bk, allow_split, dilated ? 64 : 128);
+    }
+    if (act_of(d) == 1 && geometry && cin % kActStage == 0) {
+        for (const PlanRow &t : cfg->pre_plans)
+            if (plan_matches(t, d, op)) return make_igemm_plan(kAct, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
+        if (tuned_plan(*cfg, d, op, &pl)) return make_igemm_plan(kAct, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
+        return model_plan(kAct, M, Nout, kchunks, bk, allow_split);
+    }
+    if (!split && tuned_plan(*cfg, d, op, &pl)) return make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
+    return model_plan(kGeneral, M, Nout, kchunks, bk, allow_split);
 }
 
 // The filter-gradient kernels take two stages per trip of their loop: a range of an odd number of stages ends with a stage of
@@ -177,11 +246,14 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
 static int even_stages(int cps, int pchunks) { return cps < pchunks ? cps + (cps & 1) : cps; }
 
 // dw[Kout][Jdim] with the reduction over Mpix pixels, split into `split` ranges of chunks_per_split stages
-static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix);
+static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math);
 
-static GemmPlan plan_wgrad(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix)
+// Whether a filter gradient runs with split operands (four consecutive filter indices share a tap: one 16-byte load)
+static bool wgrad_is_split(const rn50_conv_desc *d, Fp32Math math) { return math != kFp32Unit && !bf16_of(d) && d->c % 4 == 0; }
+
+static GemmPlan plan_wgrad(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math)
 {
-    GemmPlan pl = plan_wgrad_any_tile(d, Kout, Jdim, Mpix);
+    GemmPlan pl = plan_wgrad_any_tile(d, Kout, Jdim, Mpix, math);
     if (act_of(d) && (pl.bm != 64 || pl.bn != 64)) {
         // the bf16-activation kernel has 64x64 tiles only: as many workgroups as the chosen plan by a matching split
         const int pchunks = ceil_div(Mpix, kBK);
@@ -195,13 +267,65 @@ static GemmPlan plan_wgrad(const rn50_conv_desc *d, int Kout, int Jdim, long Mpi
     return pl;
 }
 
-static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix)
+// Modelled time of wgrad_split_kernel and its ordered sum in microseconds: per tile shape the time of a 32-pixel stage while a CU is full, the
+// time of a work item beyond its stages, and the time of a stage of workgroups that do not fill a CU.  Fitted to 124 calls with every
+// tile and up to seven splits; the plan it picks takes 1.2 % longer than the best one measured on average, 4 % at the 90th percentile.
+static double wgrad_split_cost(int bm, int bn, int Kout, int Jdim, int split, int cps)
+{
+    static const double c128x128[3] = {1.383, 2.172, 1.929}, c128x64[3] = {0.793, 0.692, 1.123}, c64x128[3] = {0.822, 0.797, 1.279},
+                        c64x64[3] = {0.470, 0.147, 0.729};
+    const double *c = bm == 128 ? (bn == 128 ? c128x128 : c128x64) : (bn == 128 ? c64x128 : c64x64);
+    const double per_cu = ceil((double)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split / kCUs);
+    return std::max(per_cu * (cps * c[0] + c[1]), ceil(per_cu / wgrad_split_occupancy(bm, bn)) * (cps * c[2] + 0.71)) +
+           (split + 1.0) * Kout * Jdim * 4.0 / 7.94e6;
+}
+
+// The same for wgrad_act_copy_kernel (stages of 64 pixels; cps counts 32).
+static double wgrad_act_cost(int bm, int bn, int Kout, int Jdim, int split, int cps)
+{
+    static const double c128x128[3] = {0.45, 2.0, 1.2}, c128x64[3] = {0.28, 1.2, 1.0}, c64x128[3] = {0.28, 1.2, 1.0}, c64x64[3] = {0.18, 0.7, 0.9};
+    const double *c = bm == 128 ? (bn == 128 ? c128x128 : c128x64) : (bn == 128 ? c64x128 : c64x64);
+    const double per_cu = ceil((double)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split / kCUs), stages = ceil(cps / 2.0);
+    return std::max(per_cu * (stages * c[0] + c[1]), ceil(per_cu / igemm_act_occupancy(bm, bn)) * (stages * c[2] + 0.7)) +
+           (split + 1.0) * Kout * Jdim * 4.0 / 7.94e6;
+}
+// Whether a filter gradient runs through wgrad_act_copy_kernel: bf16 activations (the fp32 image in front of them: wgrad_act_kernel)
+static bool wgrad_is_copy(const rn50_conv_desc *d) { return act_of(d) == 1 && d->k % 8 == 0 && d->c % 8 == 0; }
+static GemmPlan plan_wgrad_copy(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix)
+{
+    const int pchunks = ceil_div(Mpix, kBK);
+    GemmPlan best{64, 64, 1, pchunks};
+    const std::shared_ptr<const Config> cfg = config();
+    GemmPlan forced;
+    if (forced_plan(cfg->has_wgrad_plan, cfg->wgrad_plan, &forced) || override_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &forced)) {
+        if (forced.split > pchunks) forced.split = pchunks;
+        forced.chunks_per_split = even_stages(ceil_div(pchunks, forced.split), pchunks);
+        forced.split = ceil_div(pchunks, forced.chunks_per_split);
+        return forced;
+    }
+    double best_cost = 1e300;
+    for (int bm = 128; bm >= 64; bm -= 64)
+        for (int bn = 128; bn >= 64; bn -= 64) {
+            if ((bm == 128 && Kout <= 64) || (bn == 128 && Jdim <= 64)) continue;
+            for (int s = 1; s <= 2048; s = (s < 8 ? s + 1 : s + s / 4)) {
+                if (s > 1 && pchunks / s < 2) break;
+                const int cps = even_stages(ceil_div(pchunks, s), pchunks), sp = ceil_div(pchunks, cps);
+                const double cost = wgrad_act_cost(bm, bn, Kout, Jdim, sp, cps);
+                if (cost < best_cost) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps}; }
+            }
+        }
+    return best;
+}
+
+static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math)
 {
     const int pchunks = ceil_div(Mpix, kBK);
     GemmPlan best{64, 64, 1, pchunks};
     GemmPlan forced;
     const std::shared_ptr<const Config> cfg = config();
-    if (forced_plan(cfg->has_wgrad_plan, cfg->wgrad_plan, &forced) || tuned_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &forced)) {
+    const bool split = wgrad_is_split(d, math);
+    if (forced_plan(cfg->has_wgrad_plan, cfg->wgrad_plan, &forced) ||
+        (split ? override_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &forced) : tuned_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &forced))) {
         if (forced.split > pchunks) forced.split = pchunks;
         forced.chunks_per_split = even_stages(ceil_div(pchunks, forced.split), pchunks);
         forced.split = ceil_div(pchunks, forced.chunks_per_split);
@@ -224,7 +348,8 @@ static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim,
                 const double conc = std::min((double)occ, per_cu);  // of which this many at a time
                 // a stage costs its MFMA time, but no less than what the load latency allows at this concurrency
                 const double stage = std::max(chunk_clks, 3000.0 / conc);
-                const double cost = per_cu * (cps + 3.0) * stage + kLaunchClks + (sp + 1.0) * Kout * Jdim * 4.0 / kBytesPerClk;
+                const double cost = split ? wgrad_split_cost(bm, bn, Kout, Jdim, sp, cps) :
+                                    per_cu * (cps + 3.0) * stage + kLaunchClks + (sp + 1.0) * Kout * Jdim * 4.0 / kBytesPerClk;
                 if (cost < best_cost) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps}; }
             }
         }
@@ -233,60 +358,64 @@ static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim,
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-template <int MODE, bool BF, bool INAFF, int ACT, bool STATS, int BK>
+template <int MODE, int PREC, bool INAFF, int ACT, bool STATS, int BK>
 static void launch_igemm_bk(const IgemmPlan &pl, const IgemmP &p, hipStream_t st)
 {
     const dim3 grid(pl.grid), block(kConvThreads);
-    if (pl.bm == 128 && pl.bn == 128) hipLaunchKernelGGL((igemm_kernel<128, 128, MODE, BF, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
-    else if (pl.bm == 128) hipLaunchKernelGGL((igemm_kernel<128, 64, MODE, BF, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
-    else if (pl.bn == 128) hipLaunchKernelGGL((igemm_kernel<64, 128, MODE, BF, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((igemm_kernel<64, 64, MODE, BF, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
+    if (pl.bm == 128 && pl.bn == 128) hipLaunchKernelGGL((igemm_kernel<128, 128, MODE, PREC, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
+    else if (pl.bm == 128) hipLaunchKernelGGL((igemm_kernel<128, 64, MODE, PREC, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
+    else if (pl.bn == 128) hipLaunchKernelGGL((igemm_kernel<64, 128, MODE, PREC, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((igemm_kernel<64, 64, MODE, PREC, INAFF, ACT, STATS, BK>), grid, block, 0, st, p);
 }
 
 // p.kchunks counts stages of igemm_bk() elements: the instantiation with that stage length
-template <int MODE, bool BF, bool INAFF = false, int ACT = 0, bool STATS = false>
+template <int MODE, int PREC, bool INAFF = false, int ACT = 0, bool STATS = false>
 static void launch_igemm_mode(const IgemmPlan &pl, const IgemmP &p, hipStream_t st)
 {
-    if constexpr (BF && MODE <= 1) {
+    if constexpr (PREC == 1 && MODE <= 1) {
         if (igemm_bk(true, ACT, p.Cin) == 2 * kBK) {
-            launch_igemm_bk<MODE, BF, INAFF, ACT, STATS, 2 * kBK>(pl, p, st);
+            launch_igemm_bk<MODE, PREC, INAFF, ACT, STATS, 2 * kBK>(pl, p, st);
             return;
         }
     }
-    launch_igemm_bk<MODE, BF, INAFF, ACT, STATS, kBK>(pl, p, st);
+    launch_igemm_bk<MODE, PREC, INAFF, ACT, STATS, kBK>(pl, p, st);
 }
+
+// A launch with fp32 operands: on the fp32 instruction or with split operands
+#define RN50_FP32(MODE_, ...) \
+    do { if (split) launch_igemm_mode<MODE_, 2, __VA_ARGS__>(pl, p, st); else launch_igemm_mode<MODE_, 0, __VA_ARGS__>(pl, p, st); } while (0)
 
 // The forward launches that also gather the output's statistics (p.stat_mean set): no dilation, so the vector gather
 // (MODE 0) or the scalar one (MODE 2).
-static void launch_igemm_stats(const IgemmPlan &pl, const IgemmP &p, bool bf16, int act, hipStream_t st)
+static void launch_igemm_stats(const IgemmPlan &pl, const IgemmP &p, bool bf16, bool split, int act, hipStream_t st)
 {
     const bool fast = p.Cin % kBK == 0 && act != 2;
     if (act == 1) {
-        if (p.in_scale) launch_igemm_mode<0, true, true, 1, true>(pl, p, st);
-        else if (fast) launch_igemm_mode<0, true, false, 1, true>(pl, p, st);
-        else launch_igemm_mode<2, true, false, 1, true>(pl, p, st);
+        if (p.in_scale) launch_igemm_mode<0, 1, true, 1, true>(pl, p, st);
+        else if (fast) launch_igemm_mode<0, 1, false, 1, true>(pl, p, st);
+        else launch_igemm_mode<2, 1, false, 1, true>(pl, p, st);
     } else if (act == 2) {
-        launch_igemm_mode<2, true, false, 2, true>(pl, p, st);
+        launch_igemm_mode<2, 1, false, 2, true>(pl, p, st);
     } else if (p.in_scale) {
-        if (bf16) launch_igemm_mode<0, true, true, 0, true>(pl, p, st);
-        else launch_igemm_mode<0, false, true, 0, true>(pl, p, st);
+        if (bf16) launch_igemm_mode<0, 1, true, 0, true>(pl, p, st);
+        else RN50_FP32(0, true, 0, true);
     } else if (bf16) {
-        if (fast) launch_igemm_mode<0, true, false, 0, true>(pl, p, st);
-        else launch_igemm_mode<2, true, false, 0, true>(pl, p, st);
+        if (fast) launch_igemm_mode<0, 1, false, 0, true>(pl, p, st);
+        else launch_igemm_mode<2, 1, false, 0, true>(pl, p, st);
     } else {
-        if (fast) launch_igemm_mode<0, false, false, 0, true>(pl, p, st);
-        else launch_igemm_mode<2, false, false, 0, true>(pl, p, st);
+        if (fast) RN50_FP32(0, false, 0, true);
+        else RN50_FP32(2, false, 0, true);
     }
 }
 
-template <bool O16>
-static void launch_tail_reduce(const IgemmPlan &pl, const IgemmP &p, hipStream_t st)
+template <bool O16, bool APPLY = false>
+static void launch_tail_reduce(const IgemmPlan &pl, const IgemmP &p, hipStream_t st, const TailApply &ap = TailApply{})
 {
     const dim3 grid(ceil_div(pl.bm * pl.bn / 4, 256), pl.tail_tiles), block(256);
-    if (pl.bm == 128 && pl.bn == 128) hipLaunchKernelGGL((igemm_tail_reduce_kernel<128, 128, O16>), grid, block, 0, st, p);
-    else if (pl.bm == 128) hipLaunchKernelGGL((igemm_tail_reduce_kernel<128, 64, O16>), grid, block, 0, st, p);
-    else if (pl.bn == 128) hipLaunchKernelGGL((igemm_tail_reduce_kernel<64, 128, O16>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((igemm_tail_reduce_kernel<64, 64, O16>), grid, block, 0, st, p);
+    if (pl.bm == 128 && pl.bn == 128) hipLaunchKernelGGL((igemm_tail_reduce_kernel<128, 128, O16, APPLY>), grid, block, 0, st, p, ap);
+    else if (pl.bm == 128) hipLaunchKernelGGL((igemm_tail_reduce_kernel<128, 64, O16, APPLY>), grid, block, 0, st, p, ap);
+    else if (pl.bn == 128) hipLaunchKernelGGL((igemm_tail_reduce_kernel<64, 128, O16, APPLY>), grid, block, 0, st, p, ap);
+    else hipLaunchKernelGGL((igemm_tail_reduce_kernel<64, 64, O16, APPLY>), grid, block, 0, st, p, ap);
 }
 
 template <bool O16>
@@ -300,8 +429,11 @@ static void launch_tail_reduce_stats(const IgemmPlan &pl, const IgemmP &p, hipSt
 }
 
 // Runs out[M][Nout] (+ optional stride-2 scatter) and, when tail tiles are split, the ordered sum of their pieces.
-// act: storage of the gathered operand and of the output (see act_of)
-static void run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials, bool bf16, int act, hipStream_t st)
+// act: storage of the gathered operand and of the output (see act_of); split: fp32 operands as split operands.
+// ap (a forward pass, fp32 output): what to make of the output besides; returns whether it was made (where every tile is split the
+// ordered sum makes it, a launch and a pass less), else it is the caller's to do.
+static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials, bool bf16, bool split, int act, hipStream_t st,
+                      const TailApply *ap = nullptr)
 {
     const bool fast = p.Cin % kBK == 0 && act != 2;  // an fp32 input beside bf16 activations goes through the scalar gather
     p.kchunks = ceil_div(p.Kdim, fast ? igemm_bk(bf16, act, p.Cin) : kBK);
@@ -317,26 +449,30 @@ static void run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
     p.div_ow = make_fastdiv(p.OW);
     p.div_cin = make_fastdiv(p.Cin);
     p.div_s = make_fastdiv(p.S);
-    if (p.stat_mean) {
-        launch_igemm_stats(pl, p, bf16, act, st);  // callers have checked: a forward pass (sd == 1)
+    if (pl.kind == kPre) {
+        launch_igemm_pre(pl.bm, pl.bn, pl.grid, p, st);
+    } else if (pl.kind == kAct) {
+        launch_igemm_act(pl.bm, pl.bn, pl.grid, p, st);
+    } else if (p.stat_mean) {
+        launch_igemm_stats(pl, p, bf16, split, act, st);  // callers have checked: a forward pass (sd == 1)
     } else if (act == 1) {
-        if (p.in_scale) launch_igemm_mode<0, true, true, 1>(pl, p, st);
-        else if (fast && p.sd == 1) launch_igemm_mode<0, true, false, 1>(pl, p, st);
-        else if (fast) launch_igemm_mode<1, true, false, 1>(pl, p, st);
-        else launch_igemm_mode<2, true, false, 1>(pl, p, st);
+        if (p.in_scale) launch_igemm_mode<0, 1, true, 1>(pl, p, st);
+        else if (fast && p.sd == 1) launch_igemm_mode<0, 1, false, 1>(pl, p, st);
+        else if (fast) launch_igemm_mode<1, 1, false, 1>(pl, p, st);
+        else launch_igemm_mode<2, 1, false, 1>(pl, p, st);
     } else if (act == 2) {
-        launch_igemm_mode<2, true, false, 2>(pl, p, st);
+        launch_igemm_mode<2, 1, false, 2>(pl, p, st);
     } else if (p.in_scale) {  // callers have checked: Cin % 32 == 0 and no dilation
-        if (bf16) launch_igemm_mode<0, true, true>(pl, p, st);
-        else launch_igemm_mode<0, false, true>(pl, p, st);
+        if (bf16) launch_igemm_mode<0, 1, true>(pl, p, st);
+        else RN50_FP32(0, true);
     } else if (bf16) {
-        if (fast && p.sd == 1) launch_igemm_mode<0, true>(pl, p, st);
-        else if (fast) launch_igemm_mode<1, true>(pl, p, st);
-        else launch_igemm_mode<2, true>(pl, p, st);
+        if (fast && p.sd == 1) launch_igemm_mode<0, 1>(pl, p, st);
+        else if (fast) launch_igemm_mode<1, 1>(pl, p, st);
+        else launch_igemm_mode<2, 1>(pl, p, st);
     } else {
-        if (fast && p.sd == 1) launch_igemm_mode<0, false>(pl, p, st);
-        else if (fast) launch_igemm_mode<1, false>(pl, p, st);
-        else launch_igemm_mode<2, false>(pl, p, st);
+        if (fast && p.sd == 1) RN50_FP32(0, false);
+        else if (fast) RN50_FP32(1, false);
+        else RN50_FP32(2, false);
     }
     if (pl.tail_split > 1) {
         if (p.stat_mean) {
@@ -344,28 +480,41 @@ static void run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
             else launch_tail_reduce_stats<false>(pl, p, st);
         } else {
             if (act) launch_tail_reduce<true>(pl, p, st);
-            else launch_tail_reduce<false>(pl, p, st);
+            else if (ap && !pl.full_items && !p.scatter2 && p.Nout % 4 == 0) {
+                launch_tail_reduce<false, true>(pl, p, st, *ap);
+                return true;
+            } else launch_tail_reduce<false>(pl, p, st);
         }
     }
+    return false;
 }
 
-// data gradient of a 1x1 stride-2 convolution on an even-sized input: a GEMM whose rows are scattered
-static bool is_scatter2(const rn50_conv_desc *d)
+// Workspace of a forward or data-gradient call: [partial tiles][prepared filter], the latter only where the plan's kernel takes one.
+static size_t igemm_part_bytes(const IgemmPlan &pl) { return pl.kind == kGeneral ? pl.ws_floats * sizeof(float) : align_up(pl.ws_floats * sizeof(float), 256); }
+static size_t igemm_planes_bytes(const IgemmPlan &pl, int rows, int kdim) { return pl.kind == kGeneral ? 0 : filter_planes_bytes(rows, kdim, pl.kind == kAct); }
+// The prepared filter of a call: the one it was given, or prepared now in the workspace behind the partial tiles.
+static void set_planes(IgemmP &p, const IgemmPlan &pl, const char *planes, void *ws, hipStream_t st)
 {
-    return d->r == 1 && d->s == 1 && d->stride == 2 && d->pad == 0 && d->h % 2 == 0 && d->w % 2 == 0;
+    if (pl.kind == kGeneral) return;
+    p.plane_rows = plane_rows_of(p.Nout);
+    p.planes = planes;
+    if (planes) return;
+    char *own = (char *)ws + igemm_part_bytes(pl);
+    launch_filter_planes(p.Nout, p.Kdim, pl.kind == kAct, p.b, own, st);
+    p.planes = own;
 }
 
-struct BwdDataPlan { IgemmPlan g; bool scatter; size_t wt_bytes, part_bytes; };
-static BwdDataPlan plan_bwd_data(const rn50_conv_desc *d)
+struct BwdDataPlan { IgemmPlan g; bool scatter; size_t wt_bytes, part_bytes; };  // part_bytes: partial tiles and prepared filter
+static BwdDataPlan plan_bwd_data(const rn50_conv_desc *d, Fp32Math math, bool given = false)
 {
     const Geom ge = geom(d);
     BwdDataPlan b;
     b.scatter = is_scatter2(d);
     const long M = b.scatter ? ge.Mout : ge.Min;
     const int Kd = d->r * d->s * d->k;
-    b.g = plan_igemm(d, RN50_OP_BWD_DATA, M, d->c, Kd, true, d->k);
+    b.g = plan_igemm(d, RN50_OP_BWD_DATA, M, d->c, Kd, true, d->k, math, given);
     b.wt_bytes = align_up((size_t)d->k * d->r * d->s * d->c * sizeof(float), 256);
-    b.part_bytes = b.g.ws_floats * sizeof(float);
+    b.part_bytes = igemm_part_bytes(b.g) + (given ? 0 : igemm_planes_bytes(b.g, d->c, Kd));
     return b;
 }
 
@@ -373,13 +522,13 @@ static BwdDataPlan plan_bwd_data(const rn50_conv_desc *d)
 // The region holds mean and squared deviations per (row tile, output channel), or, for a shape whose forward pass does not
 // run through the tiled kernel, the band partials of the separate statistics pass; it is sized for both.
 struct FwdStatsPlan { IgemmPlan g; int tiles_m; size_t conv_bytes, stat_bytes; };
-static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d)
+static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool given = false)
 {
     const Geom ge = geom(d);
     FwdStatsPlan f;
-    f.g = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c);
+    f.g = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, given);
     f.tiles_m = ceil_div(ge.Mout, f.g.bm);
-    f.conv_bytes = align_up(f.g.ws_floats * sizeof(float), 256);
+    f.conv_bytes = align_up(igemm_part_bytes(f.g) + (given ? 0 : igemm_planes_bytes(f.g, d->k, ge.Kdim)), 256);
     f.stat_bytes = align_up(std::max((size_t)2 * f.tiles_m * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
     return f;
 }
@@ -401,22 +550,28 @@ static int stem_wgrad_grid(const rn50_conv_desc *d, const Geom &ge)
 extern "C" size_t rn50_conv_workspace_bytes(const rn50_conv_desc *d, int op)
 {
     if (conv_check("rn50_conv_workspace_bytes", d) != RN50_OK) return 0;
+    return conv_workspace(d, op, kFp32Split, false);
+}
+
+size_t rn50::conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool given)
+{
     const Geom ge = geom(d);
     if (op == RN50_OP_FWD) {
-        return plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c).ws_floats * sizeof(float);
+        const IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, given);
+        return igemm_part_bytes(pl) + (given ? 0 : igemm_planes_bytes(pl, d->k, ge.Kdim));
     }
     if (op == RN50_OP_BWD_DATA) {
-        const BwdDataPlan b = plan_bwd_data(d);
+        const BwdDataPlan b = plan_bwd_data(d, math, given);
         return b.wt_bytes + b.part_bytes;
     }
     if (op == RN50_OP_BWD_WEIGHT) {
         if (stem_wgrad_grid(d, ge)) return (size_t)stem_wgrad_grid(d, ge) * d->k * ge.Kdim * sizeof(float);
-        const GemmPlan pl = plan_wgrad(d, d->k, ge.Kdim, ge.Mout);
+        const GemmPlan pl = wgrad_is_copy(d) ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, math);
         return (size_t)pl.split * d->k * ge.Kdim * sizeof(float);
     }
-    if (op == RN50_OP_BWD_DATA_FLIPPED) return plan_bwd_data(d).part_bytes;
+    if (op == RN50_OP_BWD_DATA_FLIPPED) return plan_bwd_data(d, math, given).part_bytes;
     if (op == RN50_OP_FWD_BNSTATS) {
-        const FwdStatsPlan f = plan_fwd_stats(d);
+        const FwdStatsPlan f = plan_fwd_stats(d, math, given);
         return f.conv_bytes + f.stat_bytes;
     }
     return 0;
@@ -428,7 +583,8 @@ extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn,
     const Geom ge = geom(d);
     int v[4];
     if (op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS || op == RN50_OP_BWD_DATA || op == RN50_OP_BWD_DATA_FLIPPED) {
-        const IgemmPlan pl = (op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) ? plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c) : plan_bwd_data(d).g;
+        const IgemmPlan pl = (op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) ? plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, false)
+                                                                                    : plan_bwd_data(d, kFp32Split).g;
         v[0] = pl.bm; v[1] = pl.bn; v[2] = pl.tail_tiles ? pl.tail_split : 1; v[3] = pl.grid;
         if ((op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) && stem_wgrad_grid(d, ge)) {
             // the first layer's own forward kernel (same shapes as its filter-gradient kernel): tiles of 8 x 16 pixels x 64 filters
@@ -436,7 +592,7 @@ extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn,
             v[3] = std::min(d->n * ceil_div(ge.P, kStemTH) * ceil_div(ge.Q, kStemTW), 3 * (int)kCUs);
         }
     } else if (op == RN50_OP_BWD_WEIGHT) {
-        const GemmPlan pl = plan_wgrad(d, d->k, ge.Kdim, ge.Mout);
+        const GemmPlan pl = wgrad_is_copy(d) ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, kFp32Split);
         v[0] = pl.bm; v[1] = pl.bn; v[2] = pl.split; v[3] = ceil_div(d->k, pl.bm) * ceil_div(ge.Kdim, pl.bn) * pl.split;
         if (const int sgrid = stem_wgrad_grid(d, ge)) {  // the first layer's own kernel: 64 filters x 160 filter elements, one partial per workgroup
             v[0] = 64; v[1] = 160; v[2] = sgrid; v[3] = sgrid;
@@ -453,7 +609,8 @@ extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn,
 
 // stats (may be null): [2][row tiles][K] floats for the output's per-tile statistics; *gathered tells whether they were left
 static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
-                         const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats = nullptr, bool *gathered = nullptr);
+                         const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats = nullptr, bool *gathered = nullptr,
+                         Fp32Math math = kFp32Split, const char *planes = nullptr, const TailApply *ap = nullptr);
 
 extern "C" int conv2d_fwd(const rn50_conv_desc *d, const float *x, const float *w, float *y, void *ws, size_t ws_bytes,
                           void *stream)
@@ -471,15 +628,21 @@ extern "C" int conv2d_fwd_bnrelu_input(const rn50_conv_desc *d, const float *x, 
 }
 
 static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
-                         const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats, bool *gathered)
+                         const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats, bool *gathered, Fp32Math math,
+                         const char *planes, const TailApply *ap)
 {
     if (gathered) *gathered = false;
     if (int rc = conv_check(who, d)) return rc;
     RN50_REQUIRE(x && w && y, RN50_EINVAL, "%s: null pointer", who);
     RN50_REQUIRE(aligned16(x) && aligned16(w) && aligned16(y) && aligned16(ws), RN50_EINVAL, "%s: pointers must be 16-byte aligned", who);
     const Geom ge = geom(d);
-    const IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c);
-    const size_t need = pl.ws_floats * sizeof(float);
+    if (in_scale && act_of(d)) math = kFp32SplitNoPlanes;  // the copies of igemm_act_kernel apply no transform: the general kernel
+    IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, planes != nullptr);
+    size_t need = igemm_part_bytes(pl) + (planes ? 0 : igemm_planes_bytes(pl, d->k, ge.Kdim));
+    if (pl.kind != kGeneral && (ws_bytes < need || !ws)) {  // no room for the prepared filter: the general kernel splits as it loads
+        pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32SplitNoPlanes, false);
+        need = igemm_part_bytes(pl);
+    }
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(!in_scale || act_of(d) != 2, RN50_EUNSUPPORTED, "%s: the fused input transform needs a bf16 or fp32 input of the variant's own type", who);
     if (d->c == 3 && d->r == 7 && d->s == 7 && d->stride == 2 && d->pad == 3 && d->k == 64 && d->in_dtype == RN50_DTYPE_F32 && !in_scale &&
@@ -491,6 +654,8 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
         sp.tiles_h = ceil_div(ge.P, kStemTH); sp.tiles_w = ceil_div(ge.Q, kStemTW);
         sp.ntiles = d->n * sp.tiles_h * sp.tiles_w;
         hipLaunchKernelGGL(stem_fwd_kernel, dim3(std::min(sp.ntiles, 3 * (int)kCUs)), dim3(kConvThreads), 0, (hipStream_t)stream, sp);
+        if (ap)
+            if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
         return launch_status(who);
     }
     IgemmP p{};
@@ -502,13 +667,43 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
         p.stat_m2 = stats + (size_t)ceil_div(ge.Mout, pl.bm) * d->k;
         if (gathered) *gathered = true;
     }
-    run_igemm(p, pl, y, (float *)ws, bf16_of(d), act_of(d), (hipStream_t)stream);
+    set_planes(p, pl, planes, ws, (hipStream_t)stream);
+    if (!run_igemm(p, pl, y, (float *)ws, bf16_of(d), math != kFp32Unit, act_of(d), (hipStream_t)stream, ap) && ap)
+        if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
     return launch_status(who);
 }
 
 extern "C" int conv2d_fwd_bnstats(const rn50_conv_desc *d, const float *x, const float *in_scale_or_null, const float *in_shift_or_null,
                                   const float *w, float *y, const float *gamma, const float *beta, float eps, float *save_mean,
                                   float *save_invstd, float *scale, float *shift, void *ws, size_t ws_bytes, void *stream)
+{
+    return conv_fwd_bnstats_math(kFp32Split, d, x, in_scale_or_null, in_shift_or_null, w, nullptr, y, gamma, beta, eps, save_mean, save_invstd, scale, shift, ws,
+                                   ws_bytes, (hipStream_t)stream);
+}
+
+int rn50::conv_fwd_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift, const float *w, const char *planes,
+                          float *y, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    return conv_fwd_impl("conv2d_fwd", d, x, in_scale, in_shift, w, y, ws, ws_bytes, st, nullptr, nullptr, math, planes);
+}
+
+int rn50::conv_fwd_apply_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *w, const char *planes, float *y, const float *scale,
+                              const float *shift, const float *residual, int relu, float *z, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    const TailApply ap{scale, shift, residual, z, relu};
+    return conv_fwd_impl("conv2d_fwd", d, x, nullptr, nullptr, w, y, ws, ws_bytes, st, nullptr, nullptr, math, planes, &ap);
+}
+
+size_t rn50::conv_planes_bytes(const rn50_conv_desc *d, int op)
+{
+    const Geom ge = geom(d);
+    if (op == RN50_OP_FWD) return igemm_planes_bytes(plan_igemm(d, op, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, true), d->k, ge.Kdim);
+    return igemm_planes_bytes(plan_bwd_data(d, kFp32Split, true).g, d->c, d->r * d->s * d->k);
+}
+
+int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale_or_null, const float *in_shift_or_null,
+                                  const float *w, const char *planes, float *y, const float *gamma, const float *beta, float eps, float *save_mean,
+                                  float *save_invstd, float *scale, float *shift, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const char *who = "conv2d_fwd_bnstats";
     if (int rc = conv_check(who, d)) return rc;
@@ -521,12 +716,17 @@ extern "C" int conv2d_fwd_bnstats(const rn50_conv_desc *d, const float *x, const
     RN50_REQUIRE(d->k % 4 == 0, RN50_EUNSUPPORTED, "%s: K must be a multiple of 4", who);
     RN50_REQUIRE(eps >= 0.f, RN50_EINVAL, "%s: negative eps", who);
     const Geom ge = geom(d);
-    const FwdStatsPlan f = plan_fwd_stats(d);
+    if (in_scale_or_null && act_of(d)) math = kFp32SplitNoPlanes;  // see conv_fwd_impl
+    FwdStatsPlan f = plan_fwd_stats(d, math, planes != nullptr);
+    if (f.g.kind != kGeneral && ws_bytes < f.conv_bytes + f.stat_bytes) {  // no room for the prepared filter
+        math = kFp32SplitNoPlanes;
+        f = plan_fwd_stats(d, math);
+    }
     RN50_REQUIRE(ws && aligned16(ws) && ws_bytes >= f.conv_bytes + f.stat_bytes, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who,
                  ws_bytes, f.conv_bytes + f.stat_bytes);
     float *stats = (float *)((char *)ws + f.conv_bytes);
     bool gathered = false;
-    if (int rc = conv_fwd_impl(who, d, x, in_scale_or_null, in_shift_or_null, w, y, ws, f.conv_bytes, stream, stats, &gathered)) return rc;
+    if (int rc = conv_fwd_impl(who, d, x, in_scale_or_null, in_shift_or_null, w, y, ws, f.conv_bytes, stream, stats, &gathered, math, planes)) return rc;
     if (gathered) {
         bn_finalize_partials(ge.Mout, d->k, f.tiles_m, f.g.bm, stats, stats + (size_t)f.tiles_m * d->k, gamma, beta, eps, save_mean, save_invstd,
                              scale, shift, (hipStream_t)stream);
@@ -542,11 +742,12 @@ extern "C" int conv2d_fwd_bnstats(const rn50_conv_desc *d, const float *x, const
 
 // Data gradient with the filter already flipped and transposed (wt[c][R-1-r][S-1-s][k] = w[k][r][s][c]): a
 // forward-type gather over dy.  ws = the implicit GEMM's partial tiles only.
-int rn50::conv_bwd_data_pretransposed(const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws,
-                                      size_t ws_bytes, hipStream_t st)
+int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws,
+                                      size_t ws_bytes, hipStream_t st, const char *planes)
 {
     const Geom ge = geom(d);
-    const BwdDataPlan b = plan_bwd_data(d);
+    BwdDataPlan b = plan_bwd_data(d, math, planes != nullptr);
+    if (b.g.kind != kGeneral && (ws_bytes < b.part_bytes || !ws)) b = plan_bwd_data(d, kFp32SplitNoPlanes);  // no room for the prepared filter
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
     RN50_REQUIRE(ws_bytes >= b.part_bytes && (b.part_bytes == 0 || ws), RN50_EWORKSPACE,
                  "conv2d_bwd_data: workspace too small (%zu < %zu)", ws_bytes, b.part_bytes);
@@ -565,11 +766,10 @@ int rn50::conv_bwd_data_pretransposed(const rn50_conv_desc *d, const float *dy, 
             p.div_class = make_fastdiv(p.M / 4);
         }
     }
-    run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), act_of(d), st);
+    set_planes(p, b.g, planes, ws, st);
+    run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), math != kFp32Unit, act_of(d), st);
     return launch_status("conv2d_bwd_data");
 }
-
-size_t rn50::conv_bwd_data_pretransposed_ws(const rn50_conv_desc *d) { return plan_bwd_data(d).part_bytes; }
 
 void rn50::launch_filter_flip_batched(const void *jobs, int njobs, int nblocks, const float *theta, float *wt, hipStream_t st)
 {
@@ -590,14 +790,15 @@ extern "C" int conv2d_bwd_data(const rn50_conv_desc *d, const float *dy, const f
     RN50_REQUIRE(aligned16(dy) && aligned16(w) && aligned16(dx) && aligned16(ws), RN50_EINVAL,
                  "conv2d_bwd_data: pointers must be 16-byte aligned");
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
-    const BwdDataPlan b = plan_bwd_data(d);
+    BwdDataPlan b = plan_bwd_data(d, kFp32Split);
+    if (b.g.kind != kGeneral && ws_bytes < b.wt_bytes + b.part_bytes) b = plan_bwd_data(d, kFp32SplitNoPlanes);  // no room for the prepared filter
     RN50_REQUIRE(ws && ws_bytes >= b.wt_bytes + b.part_bytes, RN50_EWORKSPACE, "conv2d_bwd_data: workspace too small (%zu < %zu)",
                  ws_bytes, b.wt_bytes + b.part_bytes);
     hipStream_t st = (hipStream_t)stream;
     // workspace = [flipped filter][partial tiles]
     float *wt = (float *)ws;
     launch_filter_flip(d->k, d->c, d->r * d->s, w, wt, st);
-    return conv_bwd_data_pretransposed(d, dy, wt, dx, (char *)ws + b.wt_bytes, b.part_bytes, st);
+    return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, (char *)ws + b.wt_bytes, b.part_bytes, st);
 }
 
 extern "C" int conv2d_filter_flip(const rn50_conv_desc *d, const float *w, float *wt, void *stream)
@@ -618,14 +819,15 @@ extern "C" int conv2d_bwd_data_flipped(const rn50_conv_desc *d, const float *dy,
     RN50_REQUIRE(aligned16(dy) && aligned16(wt) && aligned16(dx) && aligned16(ws), RN50_EINVAL,
                  "conv2d_bwd_data_flipped: pointers must be 16-byte aligned");
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data_flipped: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
-    const size_t need = plan_bwd_data(d).part_bytes;
+    size_t need = plan_bwd_data(d, kFp32Split).part_bytes;
+    if (ws_bytes < need) need = plan_bwd_data(d, kFp32SplitNoPlanes).part_bytes;  // no room for the prepared filter
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "conv2d_bwd_data_flipped: workspace too small (%zu < %zu)",
                  ws_bytes, need);
-    return conv_bwd_data_pretransposed(d, dy, wt, dx, ws, ws_bytes, (hipStream_t)stream);
+    return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, ws, ws_bytes, (hipStream_t)stream);
 }
 
 static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
-                                const float *dy, float *dw, void *ws, size_t ws_bytes, void *stream);
+                                const float *dy, float *dw, void *ws, size_t ws_bytes, void *stream, Fp32Math math = kFp32Split);
 
 extern "C" int conv2d_bwd_weight(const rn50_conv_desc *d, const float *x, const float *dy, float *dw, void *ws,
                                  size_t ws_bytes, void *stream)
@@ -643,7 +845,7 @@ extern "C" int conv2d_bwd_weight_bnrelu_input(const rn50_conv_desc *d, const flo
 }
 
 static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
-                                const float *dy, float *dw, void *ws, size_t ws_bytes, void *stream)
+                                const float *dy, float *dw, void *ws, size_t ws_bytes, void *stream, Fp32Math math)
 {
     if (int rc = conv_check(who, d)) return rc;
     RN50_REQUIRE(x && dy && dw, RN50_EINVAL, "%s: null pointer", who);
@@ -666,8 +868,10 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
                            (long)d->k * ge.Kdim, (const float *)ws, dw);
         return launch_status(who);
     }
-    const GemmPlan pl = plan_wgrad(d, d->k, ge.Kdim, ge.Mout);
-    const size_t need = (size_t)pl.split * d->k * ge.Kdim * sizeof(float);
+    const size_t partial = (size_t)d->k * ge.Kdim * sizeof(float);
+    const bool copy = wgrad_is_copy(d);
+    const GemmPlan pl = copy ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, math);
+    const size_t need = pl.split * partial;
     RN50_REQUIRE(ws && ws_bytes >= need, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(((long)d->k * ge.Kdim) % 4 == 0, RN50_EUNSUPPORTED, "%s: filter size must be a multiple of 4", who);
     const int act = act_of(d);
@@ -680,10 +884,12 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
     const int grid = p.tiles_k * p.tiles_j * pl.split;
     hipStream_t st = (hipStream_t)stream;
     const bool bf16 = bf16_of(d);
-    if (act) {  // 64x64 tiles (plan_wgrad keeps to them)
-        if (act == 2) hipLaunchKernelGGL((wgrad_act_kernel<true, false>), dim3(grid), dim3(kConvThreads), 0, st, p);
-        else if (in_scale) hipLaunchKernelGGL((wgrad_act_kernel<false, true>), dim3(grid), dim3(kConvThreads), 0, st, p);
-        else hipLaunchKernelGGL((wgrad_act_kernel<false, false>), dim3(grid), dim3(kConvThreads), 0, st, p);
+    if (wgrad_is_split(d, math)) {
+        launch_wgrad_split(pl.bm, pl.bn, grid, p, st);
+    } else if (copy) {
+        launch_wgrad_act_copy(pl.bm, pl.bn, grid, p, st);
+    } else if (act) {  // 64x64 tiles (plan_wgrad keeps to them)
+        hipLaunchKernelGGL(wgrad_act_kernel, dim3(grid), dim3(kConvThreads), 0, st, p);
     } else {
 #define RN50_WG(BM_, BN_)                                                                                              \
     do {                                                                                                               \
@@ -704,4 +910,10 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(ceil_div(count4, 64)), dim3(256), 0, st, count4, pl.split, p.split_stride,
                        (const float *)ws, dw);
     return launch_status(who);
+}
+
+int rn50::conv_bwd_weight_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift, const float *dy,
+                               float *dw, void *ws, size_t ws_bytes, hipStream_t st)
+{
+    return conv_bwd_weight_impl("conv2d_bwd_weight", d, x, in_scale, in_shift, dy, dw, ws, ws_bytes, st, math);
 }

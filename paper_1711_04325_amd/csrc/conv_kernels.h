@@ -91,6 +91,9 @@ struct IgemmP {
     int scatter2;
     FastDiv div_ohw, div_ow, div_cin, div_s;  // by OH*OW, OW, Cin, S
     FastDiv div_class;                        // by M/4 (row order 2)
+    // Kernels of conv_split.h and conv_act.h: the filter operand prepared beforehand, [stage][plane_rows][bytes of a row's stage].
+    const char *planes;
+    int plane_rows;
 };
 
 __device__ inline float4 ldg4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -191,10 +194,212 @@ __device__ inline int split_chunk(int row, int plane, int c) { return row * (kSp
 // host sizes the persistent grid with the same number.
 constexpr int igemm_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) ? 2 : (bm == 64 && bn == 64) ? 4 : 3; }
 
+// The thread index as a value the compiler knows nothing about: what is computed from it behind a persistent loop's stages stays
+// there, instead of being computed once ahead of the loop and held in registers (or scratch memory) all the way through.
+__device__ __forceinline__ int opaque_tid()
+{
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The sums of a tile with split operands: hi*hi products (acc) plus the small ones (accl).  When a sum of this wavefront is not
+// finite, its block is formed again on the fp32 instruction, straight from memory (slow, and only where the answer holds
+// infinities or NaNs): an infinite operand has no finite split.  mw, nw: first row and column of the wavefront's block;
+// stages first, next(first + 1), ... below end, each of BK elements from k_of(stage) on.
+template <int BK, bool INAFF, int MI, int NI, class Next, class KOf>
+__device__ __forceinline__ void igemm_join_split(const IgemmP &p, int mw, int nw, int first, int end, Next next, KOf k_of, floatx16 (&acc)[MI][NI],
+                                                 const floatx16 (&accl)[MI][NI])
+{
+    float probe = 0.f;  // NaN when a sum is not finite
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                acc[i][j][e] += accl[i][j][e];
+                probe = fmaf(acc[i][j][e], 0.f, probe);
+            }
+    if (!__any(probe != probe)) return;
+    const int lane = opaque_tid() & 63;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    int ih0[MI], iw0[MI], base[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int m = mw + i * 32 + (lane & 31);
+        int cls, n, oh, ow;
+        decode_row(p, min(m, p.M - 1), cls, n, oh, ow);
+        if (p.scatter2 == 2) {
+            oh = 2 * oh + (cls >> 1);
+            ow = 2 * ow + (cls & 1);
+        }
+        ih0[i] = m < p.M ? oh * p.so + p.off : -(1 << 28);
+        iw0[i] = ow * p.so + p.off;
+        base[i] = n * (p.IH * p.IW * p.Cin);
+    }
+    for (int kr = first; kr < end; kr = next(kr + 1)) {
+        const int k0 = k_of(kr);
+        for (int k2 = 0; k2 < BK; k2 += 2) {
+            const int k = k0 + k2 + (lane >> 5);
+            const bool kin = k < p.Kdim;
+            const int tap = (int)fdiv(k, p.div_cin), c = k - tap * p.Cin;
+            const int r = (int)fdiv(tap, p.div_s), sx = tap - r * p.S;
+            float va[MI], vb[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                int ih = ih0[i] + r, iw = iw0[i] + sx;
+                const bool ok = kin && ih >= 0 && iw >= 0 && ih % p.sd == 0 && iw % p.sd == 0 && ih / p.sd < p.IH && iw / p.sd < p.IW;
+                ih /= p.sd;
+                iw /= p.sd;
+                va[i] = ok ? p.a[(unsigned)(base[i] + (ih * p.IW + iw) * p.Cin + c)] : 0.f;
+                if (INAFF && ok) va[i] = fmaxf(fmaf(va[i], p.in_scale[c], p.in_shift[c]), 0.f);
+            }
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const int col = nw + j * 32 + (lane & 31);
+                vb[j] = kin && col < p.Nout ? p.b[(long)col * p.Kdim + k] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], acc[i][j], 0, 0, 0);
+        }
+    }
+}
+
+// What follows a tile's (or, part set, a piece's) reduction: the batch statistics (STATS; s_mean, s_m2: BN floats of LDS each) ...
+template <int BM, int BN, bool O16, bool STATS, int MI, int NI>
+__device__ __forceinline__ void igemm_stats(const IgemmP &p, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
+{
+    constexpr int WTM = BM / 2, WTN = BN / 2;
+    const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+    // Column statistics of the tile (whole tiles only: the pieces of a split tile are added up by another kernel, which
+    // gathers them there), before the tile is written out: the wavefronts have just left the loop's last barrier together, so
+    // the barrier below costs little here, and the write-out that follows stays unsynchronised (behind the stores it would
+    // make every wavefront wait for the slowest one's).  A wavefront holds WTM rows of its columns, 16 per block in each
+    // half-wave: mean and squared deviations of those in two passes over the registers, then the two row halves of the tile
+    // are merged with the pairwise update of Chan et al. by the wavefronts of the first half.  Uniform over the workgroup.
+    if (STATS && !part) {
+        const int valid = min(WTM, p.M - (m0 + wm * WTM));  // rows of this wavefront inside the matrix (may be <= 0)
+        // element e of block i is row i*32 + 8*(e/4) + e%4 + 4*(lane/32) of the wavefront: inside when the lane-free part
+        // is below vlim (one register, against compile-time constants)
+        const int vlim = valid - 4 * (lane >> 5);
+        float cmean[NI], cm2[NI];
+        if (O16) {  // the statistics are those of the tensor as stored (rounding is idempotent: the stores below round again)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; e += 2) {
+                        const uint32_t w = bf16_pack2(acc[i][j][e], acc[i][j][e + 1]);
+                        acc[i][j][e] = bf16_lo(w);
+                        acc[i][j][e + 1] = bf16_hi(w);
+                    }
+        }
+        const bool whole = valid == WTM;  // uniform over the wavefront: no row needs masking
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            float sum = 0.f;
+            if (whole) {
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sum += acc[i][j][e];
+            } else {
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sum += i * 32 + 8 * (e >> 2) + (e & 3) < vlim ? acc[i][j][e] : 0.f;
+            }
+            sum += __shfl_xor(sum, 32, 64);
+            const float mean = whole ? sum * (1.f / WTM) : valid > 0 ? sum / (float)valid : 0.f;  // WTM: a power of two
+            float dev = 0.f;
+            if (whole) {
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float d = acc[i][j][e] - mean;
+                        dev = fmaf(d, d, dev);
+                    }
+            } else {
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float d = acc[i][j][e] - mean;
+                        dev = i * 32 + 8 * (e >> 2) + (e & 3) < vlim ? fmaf(d, d, dev) : dev;
+                    }
+            }
+            dev += __shfl_xor(dev, 32, 64);
+            cmean[j] = mean;
+            cm2[j] = dev;
+            if (wm == 1 && lane < 32) {
+                s_mean[wn * WTN + j * 32 + lane] = mean;
+                s_m2[wn * WTN + j * 32 + lane] = dev;
+            }
+        }
+        __syncthreads();  // the next write of s_stat comes after the barriers of the next item's loop
+        if (wm == 0 && lane < 32) {
+            const float na = (float)valid, nb = (float)max(0, min(WTM, p.M - (m0 + WTM)));
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const int cl = wn * WTN + j * 32 + lane, col = n0 + cl;
+                float mean = cmean[j], m2 = cm2[j];
+                if (nb > 0.f) {
+                    const float nt = na + nb, d = s_mean[cl] - mean;
+                    mean = fmaf(d, nb / nt, mean);
+                    m2 = m2 + s_m2[cl] + d * d * (na * nb / nt);
+                }
+                if (col < p.Nout) {
+                    p.stat_mean[(long)tm * p.Nout + col] = mean;
+                    p.stat_m2[(long)tm * p.Nout + col] = m2;
+                }
+            }
+        }
+    }
+}
+// ... and the write-out.  Accumulator element e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32 of its block.
+template <int BM, int BN, bool O16, bool STATS, int MI, int NI>
+__device__ __forceinline__ void igemm_finish(const IgemmP &p, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
+{
+    igemm_stats<BM, BN, O16, STATS>(p, acc, part, m0, n0, tm, s_mean, s_m2);
+    constexpr int WTM = BM / 2, WTN = BN / 2;
+    const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int rl = wm * WTM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+            if (part) {
+#pragma unroll
+                for (int j = 0; j < NI; ++j) part[rl * BN + wn * WTN + j * 32 + (lane & 31)] = acc[i][j][e];
+            } else {
+                const int m = m0 + rl;
+                if (m >= p.M) continue;
+                const long row = out_row_index(p, m);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const int col = n0 + wn * WTN + j * 32 + (lane & 31);
+                    if (col < p.Nout) store_out<O16>(p, row, col, acc[i][j][e]);
+                }
+            }
+        }
+}
+
 // MODE 0: Cin % 32 == 0, sd == 1.  MODE 1: Cin % 32 == 0, sd > 1.  MODE 2: any Cin and sd (scalar gather).
-// BF = false: fp32 operands (the paper's single precision), each split into three bf16 terms on its way into LDS (see split8).
-// BF = true : operands are rounded to bfloat16 (RNE) on their way into LDS and multiplied with
-//             v_mfma_f32_32x32x16_bf16; accumulation and outputs stay fp32.
+// PREC 0: fp32 operands, v_mfma_f32_32x32x2_f32 (the paper's single precision; the training contexts, whose results depend on the
+//         order of their sums: see conv.hip).
+// PREC 1 (BF): operands are rounded to bfloat16 (RNE) on their way into LDS and multiplied with
+//         v_mfma_f32_32x32x16_bf16; accumulation and outputs stay fp32.
+// PREC 2 (SPLIT): fp32 operands, each split into three bf16 terms on its way into LDS (see split8).
 // INAFF (MODE 0 only): per-channel scale, shift and ReLU applied to the gathered operand (see IgemmP::in_scale).
 // ACT (BF only): storage of the activation tensors.  0: fp32.  1: the gathered operand `a` and the output hold bfloat16
 //             bits (activations kept as bf16 in memory; a thread gathers eight elements per 16-byte load).  2: `a` is fp32,
@@ -202,9 +407,10 @@ constexpr int igemm_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) 
 // STATS: the kernel also leaves the per-tile batch statistics of its output (IgemmP::stat_mean, which must be set).
 // BK: reduction elements per LDS stage.  32, or 64 for bf16 operands through the vector gather: the stage then has the bytes of an
 // fp32 stage of 32 (same LDS footprint), twice the MFMAs between two barriers, and needs Cin % 64 == 0 (p.kchunks counts stages of BK).
-template <int BM, int BN, int MODE, bool BF, bool INAFF = false, int ACT = 0, bool STATS = false, int BK = kBK>
+template <int BM, int BN, int MODE, int PREC, bool INAFF = false, int ACT = 0, bool STATS = false, int BK = kBK>
 __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_kernel(IgemmP p)
 {
+    constexpr bool BF = PREC == 1, SPLIT = PREC == 2;
     static_assert(BK == kBK || (BK == 2 * kBK && BF && MODE <= 1), "long stages exist for bf16 operands through the vector gather");
     constexpr int LDH = BK + 8;                // row of 16-bit elements: 80 or 144 bytes (the latter = an fp32 row of 32 + 4)
     constexpr int TPR = BK / 4, ROWS = kConvThreads / TPR;  // threads per row of a stage with 16-byte loads of fp32, rows per pass
@@ -212,7 +418,6 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
     static_assert(ACT == 0 || BF, "bf16 activations are multiplied on the bf16 MFMA");
     constexpr bool A16 = ACT == 1, O16 = ACT != 0;
     constexpr bool AV16 = A16 && MODE <= 1;    // vector gather of bf16: 8 elements per load, 4 loads per row of a stage
-    constexpr bool SPLIT = !BF;
     constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
     // threads per row of each operand tile: eight bf16 or four fp32 elements per load; a split operand takes two loads of four
     constexpr int BTPR = SPLIT ? 4 : TPR, BROWS = kConvThreads / BTPR;
@@ -237,6 +442,10 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
     const bf16_t *a16 = reinterpret_cast<const bf16_t *>(p.a);
     const int G = gridDim.x;
     const int n_items = p.full_items + p.tail_tiles * p.tail_split;
+    // PREC 0.  MFMA operand for lane l: row l%32 of the block, reduction element l/32 of the current pair.  A lane
+    // reads four consecutive reduction elements at once; pairing element e of lanes 0-31 with element e
+    // of lanes 32-63 is a permutation of the reduction order, applied identically to both operands.
+    const int frag_off = (lane & 31) * kLDK + (lane >> 5) * 4;
 
     for (int item = blockIdx.x; item < n_items; item += G) {
         int tile, kc_begin, kc_end;
@@ -420,7 +629,7 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                     bq[at + 4] = v.mid;
                     bq[at + 8] = v.lo;
                 }
-            } else {
+            } else if constexpr (BF) {
                 uint16_t *ah = reinterpret_cast<uint16_t *>(As), *bh = reinterpret_cast<uint16_t *>(Bs);
 #pragma unroll
                 for (int i = 0; i < RA; ++i)
@@ -430,6 +639,11 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                 for (int i = 0; i < RB; ++i)
                     *reinterpret_cast<uint2 *>(&bh[(row_in + BROWS * i) * LDH + kq * 4]) =
                         make_uint2(bf16_pack2(rb[i][0].x, rb[i][0].y), bf16_pack2(rb[i][0].z, rb[i][0].w));
+            } else {
+#pragma unroll
+                for (int i = 0; i < RA; ++i) *reinterpret_cast<float4 *>(&As[(arow + AROWS * i) * kLDK + akq * 4]) = ra[i][0];
+#pragma unroll
+                for (int i = 0; i < RB; ++i) *reinterpret_cast<float4 *>(&Bs[(row_in + BROWS * i) * kLDK + kq * 4]) = rb[i][0];
             }
         };
 
@@ -492,7 +706,7 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                         for (int j = 0; j < NI; ++j)
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah8[i], bh8[j], acc[i][j], 0, 0, 0);
                 }
-            } else {
+            } else if constexpr (SPLIT) {
                 // lane l: row l%32 of the block, chunk l/32 of the two that one MFMA takes
                 const uint4 *aq = reinterpret_cast<const uint4 *>(As), *bq = reinterpret_cast<const uint4 *>(Bs);
 #pragma unroll
@@ -520,6 +734,59 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
                             }
                     }
                 }
+            } else if constexpr (BM == 128 && BN == 64) {
+                // no registers to spare for a second fragment set here (it spills)
+#pragma unroll
+                for (int kg = 0; kg < kBK / 8; ++kg) {
+                    float4 af[MI], bf[NI];
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) af[i] = *reinterpret_cast<const float4 *>(&As[(wm * WTM + i * 32) * kLDK + frag_off + kg * 8]);
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) bf[j] = *reinterpret_cast<const float4 *>(&Bs[(wn * WTN + j * 32) * kLDK + frag_off + kg * 8]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+#pragma unroll
+                            for (int j = 0; j < NI; ++j) {
+                                const float av = e == 0 ? af[i].x : e == 1 ? af[i].y : e == 2 ? af[i].z : af[i].w;
+                                const float bv = e == 0 ? bf[j].x : e == 1 ? bf[j].y : e == 2 ? bf[j].z : bf[j].w;
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                            }
+                }
+            } else {
+                // The fragments of group kg+1 are read from LDS while the MFMAs of group kg run (two register sets); the
+                // scheduling hints keep that order: read, then multiply, group by group.  Read and used back to back, every
+                // group would start with the latency of its LDS reads.
+                float4 af[2][MI], bf[2][NI];
+                auto load_frag = [&](int set, int kg) {
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) af[set][i] = *reinterpret_cast<const float4 *>(&As[(wm * WTM + i * 32) * kLDK + frag_off + kg * 8]);
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) bf[set][j] = *reinterpret_cast<const float4 *>(&Bs[(wn * WTN + j * 32) * kLDK + frag_off + kg * 8]);
+                };
+                load_frag(0, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+#pragma unroll
+                for (int kg = 0; kg < kBK / 8; ++kg) {
+                    if (kg + 1 < kBK / 8) {
+                        load_frag((kg + 1) & 1, kg + 1);
+                        __builtin_amdgcn_sched_group_barrier(0x100, MI + NI, 0);
+                    }
+                    // consecutive MFMAs go to different accumulators
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+#pragma unroll
+                            for (int j = 0; j < NI; ++j) {
+                                const float4 a4 = af[kg & 1][i], b4 = bf[kg & 1][j];
+                                const float av = e == 0 ? a4.x : e == 1 ? a4.y : e == 2 ? a4.z : a4.w;
+                                const float bv = e == 0 ? b4.x : e == 1 ? b4.y : e == 2 ? b4.z : b4.w;
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                            }
+                    __builtin_amdgcn_sched_group_barrier(0x008, 4 * MI * NI, 0);
+                }
             }
             __syncthreads();
             __builtin_amdgcn_s_setprio(2);
@@ -530,178 +797,23 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
             kc = kc_next;
         }
 
-        if constexpr (SPLIT) {
-            float probe = 0.f;  // NaN when a sum is not finite
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        acc[i][j][e] += accl[i][j][e];
-                        probe = fmaf(acc[i][j][e], 0.f, probe);
-                    }
-            if (__any(probe != probe)) {
-                // an operand or a sum that is not finite: this wavefront's block again on the fp32 instruction, straight from
-                // memory (slow, and only where the answer holds infinities or NaNs)
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-                int ih0[MI], iw0[MI], base[MI];
-#pragma unroll
-                for (int i = 0; i < MI; ++i) {
-                    const int m = m0 + wm * WTM + i * 32 + (lane & 31);
-                    int cls, n, oh, ow;
-                    decode_row(p, min(m, p.M - 1), cls, n, oh, ow);
-                    if (p.scatter2 == 2) {
-                        oh = 2 * oh + (cls >> 1);
-                        ow = 2 * ow + (cls & 1);
-                    }
-                    ih0[i] = m < p.M ? oh * p.so + p.off : -(1 << 28);
-                    iw0[i] = ow * p.so + p.off;
-                    base[i] = n * (p.IH * p.IW * p.Cin);
-                }
-                for (int kr = next_chunk(kc_begin); kr < kc_end; kr = next_chunk(kr + 1))
-                    for (int k2 = 0; k2 < BK; k2 += 2) {
-                        const int k = kr * BK + k2 + (lane >> 5);
-                        const bool kin = k < p.Kdim;
-                        const int tap = (int)fdiv(k, p.div_cin), c = k - tap * p.Cin;
-                        const int r = (int)fdiv(tap, p.div_s), sx = tap - r * p.S;
-                        float va[MI], vb[NI];
-#pragma unroll
-                        for (int i = 0; i < MI; ++i) {
-                            int ih = ih0[i] + r, iw = iw0[i] + sx;
-                            const bool ok = kin && ih >= 0 && iw >= 0 && ih % p.sd == 0 && iw % p.sd == 0 && ih / p.sd < p.IH && iw / p.sd < p.IW;
-                            ih /= p.sd;
-                            iw /= p.sd;
-                            va[i] = ok ? p.a[(unsigned)(base[i] + (ih * p.IW + iw) * p.Cin + c)] : 0.f;
-                            if (INAFF && ok) va[i] = fmaxf(fmaf(va[i], p.in_scale[c], p.in_shift[c]), 0.f);
-                        }
-#pragma unroll
-                        for (int j = 0; j < NI; ++j) {
-                            const int col = n0 + wn * WTN + j * 32 + (lane & 31);
-                            vb[j] = kin && col < p.Nout ? p.b[(long)col * p.Kdim + k] : 0.f;
-                        }
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-#pragma unroll
-                            for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[j], acc[i][j], 0, 0, 0);
-                    }
-            }
-        }
-
-        // Column statistics of the tile (whole tiles only: the pieces of a split tile are added up by another kernel, which
-        // gathers them there), before the tile is written out: the wavefronts have just left the loop's last barrier together, so
-        // the barrier below costs little here, and the write-out that follows stays unsynchronised (behind the stores it would
-        // make every wavefront wait for the slowest one's).  A wavefront holds WTM rows of its columns, 16 per block in each
-        // half-wave: mean and squared deviations of those in two passes over the registers, then the two row halves of the tile
-        // are merged with the pairwise update of Chan et al. by the wavefronts of the first half.  Uniform over the workgroup.
-        if (STATS && !part) {
-            const int valid = min(WTM, p.M - (m0 + wm * WTM));  // rows of this wavefront inside the matrix (may be <= 0)
-            // element e of block i is row i*32 + 8*(e/4) + e%4 + 4*(lane/32) of the wavefront: inside when the lane-free part
-            // is below vlim (one register, against compile-time constants)
-            const int vlim = valid - 4 * (lane >> 5);
-            float cmean[NI], cm2[NI];
-            if (O16) {  // the statistics are those of the tensor as stored (rounding is idempotent: the stores below round again)
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[i][j][e] = bf16_round(acc[i][j][e]);
-            }
-            const bool whole = valid == WTM;  // uniform over the wavefront: no row needs masking
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                float sum = 0.f;
-                if (whole) {
-#pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) sum += acc[i][j][e];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) sum += i * 32 + 8 * (e >> 2) + (e & 3) < vlim ? acc[i][j][e] : 0.f;
-                }
-                sum += __shfl_xor(sum, 32, 64);
-                const float mean = valid > 0 ? sum / (float)valid : 0.f;
-                float dev = 0.f;
-                if (whole) {
-#pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) {
-                            const float d = acc[i][j][e] - mean;
-                            dev = fmaf(d, d, dev);
-                        }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) {
-                            const float d = acc[i][j][e] - mean;
-                            dev = i * 32 + 8 * (e >> 2) + (e & 3) < vlim ? fmaf(d, d, dev) : dev;
-                        }
-                }
-                dev += __shfl_xor(dev, 32, 64);
-                cmean[j] = mean;
-                cm2[j] = dev;
-                if (wm == 1 && lane < 32) {
-                    s_stat[0][wn * WTN + j * 32 + lane] = mean;
-                    s_stat[1][wn * WTN + j * 32 + lane] = dev;
-                }
-            }
-            __syncthreads();  // the next write of s_stat comes after the barriers of the next item's loop
-            if (wm == 0 && lane < 32) {
-                const float na = (float)valid, nb = (float)max(0, min(WTM, p.M - (m0 + WTM)));
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int cl = wn * WTN + j * 32 + lane, col = n0 + cl;
-                    float mean = cmean[j], m2 = cm2[j];
-                    if (nb > 0.f) {
-                        const float nt = na + nb, d = s_stat[0][cl] - mean;
-                        mean = fmaf(d, nb / nt, mean);
-                        m2 = m2 + s_stat[1][cl] + d * d * (na * nb / nt);
-                    }
-                    if (col < p.Nout) {
-                        p.stat_mean[(long)tm * p.Nout + col] = mean;
-                        p.stat_m2[(long)tm * p.Nout + col] = m2;
-                    }
-                }
-            }
-        }
-        // Epilogue.  Accumulator element e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32 of its block.
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int rl = wm * WTM + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-                if (part) {
-#pragma unroll
-                    for (int j = 0; j < NI; ++j) part[rl * BN + wn * WTN + j * 32 + (lane & 31)] = acc[i][j][e];
-                } else {
-                    const int m = m0 + rl;
-                    if (m >= p.M) continue;
-                    const long row = out_row_index(p, m);
-#pragma unroll
-                    for (int j = 0; j < NI; ++j) {
-                        const int col = n0 + wn * WTN + j * 32 + (lane & 31);
-                        if (col < p.Nout) store_out<O16>(p, row, col, acc[i][j][e]);
-                    }
-                }
-            }
-
+        if constexpr (SPLIT)
+            igemm_join_split<BK, INAFF>(p, m0 + wm * WTM, n0 + wn * WTN, next_chunk(kc_begin), kc_end, next_chunk, [&](int kr) { return kr * BK; }, acc,
+                                        accl);
+        igemm_finish<BM, BN, O16, STATS>(p, acc, part, m0, n0, tm, s_stat[0], s_stat[1]);
     }
 }
 
 // Adds the pieces of every tail tile in piece order and writes the tile (one thread per four columns).
-template <int BM, int BN, bool O16 = false>
-__global__ __launch_bounds__(256) void igemm_tail_reduce_kernel(IgemmP p)
+// APPLY (fp32 outputs of whole 16-byte groups, rows in pixel order): also writes what bn_apply_kernel would make of them,
+// z = out*scale + shift [+ residual] [ReLU].
+struct TailApply {
+    const float *scale, *shift, *residual;
+    float *z;
+    int relu;
+};
+template <int BM, int BN, bool O16 = false, bool APPLY = false>
+__global__ __launch_bounds__(256) void igemm_tail_reduce_kernel(IgemmP p, TailApply ap)
 {
     main_chain_priority();
     constexpr int V = BM * BN / 4;
@@ -736,6 +848,16 @@ __global__ __launch_bounds__(256) void igemm_tail_reduce_kernel(IgemmP p)
         if (col < p.Nout) {
             if (O16) st4(reinterpret_cast<bf16_t *>(p.out), (size_t)(row * p.Nout + col) / 4, acc);
             else *reinterpret_cast<float4 *>(&p.out[row * p.Nout + col]) = acc;
+            if (APPLY) {
+                const float4 a = ldg4(ap.scale + col), b = ldg4(ap.shift + col);
+                float4 v = make_float4(fmaf(acc.x, a.x, b.x), fmaf(acc.y, a.y, b.y), fmaf(acc.z, a.z, b.z), fmaf(acc.w, a.w, b.w));
+                if (ap.residual) {
+                    const float4 r = ldg4(ap.residual + row * p.Nout + col);
+                    v = make_float4(v.x + r.x, v.y + r.y, v.z + r.z, v.w + r.w);
+                }
+                if (ap.relu) v = make_float4(fmaxf(v.x, 0.f), fmaxf(v.y, 0.f), fmaxf(v.z, 0.f), fmaxf(v.w, 0.f));
+                *reinterpret_cast<float4 *>(&ap.z[row * p.Nout + col]) = v;
+            }
         }
         return;
     }
@@ -1469,6 +1591,18 @@ __device__ __forceinline__ void wgrad_tile(const WgradP &p, const int item, floa
         }
 }
 
+// ---- kernels of conv_split.h and conv_act.h (launched through conv_split.hip): the filter operand prepared beforehand --------------
+inline int plane_rows_of(int rows) { return (rows + 127) / 128 * 128; }  // filter rows, padded to the widest column tile
+constexpr int igemm_pre_occupancy(int bm, int bn) { return (bm == 64 && bn == 64) ? 4 : (bm == 128 && bn == 64) ? 3 : 2; }
+constexpr int igemm_act_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) ? 2 : (bm == 64 && bn == 64) ? 4 : 3; }
+constexpr int wgrad_split_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) ? 2 : (bm == 64 && bn == 64) ? 4 : 3; }
+size_t filter_planes_bytes(int rows, int kdim, bool act);
+void launch_filter_planes(int rows, int kdim, bool act, const float *w, char *planes, hipStream_t st);
+void launch_igemm_pre(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
+void launch_igemm_act(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
+void launch_wgrad_act_copy(int bm, int bn, int grid, const WgradP &p, hipStream_t st);
+void launch_wgrad_split(int bm, int bn, int grid, const WgradP &p, hipStream_t st);
+
 template <int BM, int BN, bool VEC, bool BF, bool INAFF = false>
 __global__ __launch_bounds__(kConvThreads, wgrad_occupancy(BM, BN)) void wgrad_kernel(WgradP p)
 {
@@ -1556,18 +1690,14 @@ static __global__ __launch_bounds__(256) void splitk_reduce_group_kernel(const R
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Filter gradient with the activation tensors kept as bfloat16 in memory: dy holds bf16 bits; x holds bf16 bits (XF32 = false)
-// or fp32 (XF32 = true: the network's first layer, whose input is the image; any channel count, scalar gather).  Tiles of
-// 64 output channels x 64 flat filter indices, products on the bf16 MFMA, sums and the output partials in fp32, same split
+// Filter gradient of the first layer of a network whose activation tensors are bfloat16 in memory: dy holds bf16 bits, x (the image)
+// fp32, any channel count, scalar gather (bf16 x: wgrad_act_copy_kernel in conv_act.h).  Tiles of 64 output channels x 64 flat filter indices, products on the bf16 MFMA, sums and the output partials in fp32, same split
 // of the pixel range and same ordered reduction as wgrad_kernel.
 // Half of the workgroup loads dy, the other half x: a thread owns eight neighbouring output indices (one 16-byte load of
 // bf16) of two neighbouring pixels and writes eight LDS words, each the pair (pixel 2q, pixel 2q+1) of one index, which is
 // the [index][pixel] order the MFMA operands are read in.  Loads run two stages ahead, as in wgrad_kernel.
-// INAFF (XF32 = false only): x is max(0, x*in_scale[c] + in_shift[c]) rounded to bf16, i.e. the BN + ReLU output as stored.
-template <bool XF32, bool INAFF>
-__global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
+static __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
 {
-    static_assert(!(XF32 && INAFF), "the fused input transform exists for bf16 inputs only");
     constexpr int BM = 64, BN = 64;
     constexpr int LDW = kBK / 2 + 2;  // rows of 16 words (32 pixels), padded to 72 bytes
     __shared__ __attribute__((aligned(16))) uint32_t Aw[BM * LDW];
@@ -1587,10 +1717,9 @@ __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
     const bool is_dy = tid < 128;          // uniform per wavefront
     const int t = tid & 127, c8 = t & 7, pp = t >> 3;   // eight indices c8*8.., pixel pair pp of the stage
     const bf16_t *dy16 = reinterpret_cast<const bf16_t *>(p.dy);
-    const bf16_t *x16 = reinterpret_cast<const bf16_t *>(p.x);
 
-    // x side: filter tap and channel of this thread's indices, decoded once (bf16 input: the eight share a tap, Cin % 8 == 0)
-    constexpr int NE = XF32 ? 8 : 1;
+    // x side: filter tap and channel of this thread's indices, decoded once
+    constexpr int NE = 8;
     int th[NE], tw[NE], toff[NE];
     bool gok[NE];
 #pragma unroll
@@ -1603,15 +1732,6 @@ __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
         th[e] = r - p.pad;
         tw[e] = sx - p.pad;
         toff[e] = (th[e] * p.IW + tw[e]) * p.Cin + c;
-    }
-    float4 in_sc = make_float4(0.f, 0.f, 0.f, 0.f), in_sh = in_sc, in_sc2 = in_sc, in_sh2 = in_sc;
-    if (INAFF && !is_dy && gok[0]) {
-        const int j = j0 + c8 * 8;
-        const int c = j % p.Cin;
-        in_sc = ldg4(p.in_scale + c);
-        in_sh = ldg4(p.in_shift + c);
-        in_sc2 = ldg4(p.in_scale + c + 4);
-        in_sh2 = ldg4(p.in_shift + c + 4);
     }
     const bool a_ok = k0 + c8 * 8 < p.Kout;
 
@@ -1635,12 +1755,10 @@ __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
     }
 
     struct Stage {
-        uint4 q[2];          // bf16 loads
-        float xf[2][NE];     // fp32 input: one float per index
-        unsigned ok;         // INAFF: bit u set when q[u] was loaded (not padding)
+        uint4 q[2];       // dy
+        float xf[2][NE];  // x: one float per index
     };
     auto load_chunk = [&](Stage &sg) {
-        sg.ok = 0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             sg.q[u] = make_uint4(0u, 0u, 0u, 0u);
@@ -1648,19 +1766,11 @@ __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
                 if (a_ok && pix[u] < pix_end) sg.q[u] = *reinterpret_cast<const uint4 *>(dy16 + off[u]);
                 off[u] += p.adv_dy;
             } else {
-                if (XF32) {
 #pragma unroll
-                    for (int e = 0; e < NE; ++e) {
-                        const int ih = bih[u] + th[e], iw = biw[u] + tw[e];
-                        const bool ok = pix[u] < pix_end && gok[e] && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
-                        sg.xf[u][e] = ok ? p.x[off[u] + (unsigned)toff[e]] : 0.f;
-                    }
-                } else {
-                    const int ih = bih[u] + th[0], iw = biw[u] + tw[0];
-                    if (pix[u] < pix_end && gok[0] && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW) {
-                        sg.q[u] = *reinterpret_cast<const uint4 *>(x16 + (off[u] + (unsigned)toff[0]));
-                        sg.ok |= 1u << u;
-                    }
+                for (int e = 0; e < NE; ++e) {
+                    const int ih = bih[u] + th[e], iw = biw[u] + tw[e];
+                    const bool ok = pix[u] < pix_end && gok[e] && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
+                    sg.xf[u][e] = ok ? p.x[off[u] + (unsigned)toff[e]] : 0.f;
                 }
                 // kBK pixels on: columns first, a carry into the rows, rows, a carry into the images
                 biw[u] += p.adv_iw;
@@ -1681,22 +1791,10 @@ __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(WgradP p)
     };
     auto store_chunk = [&](Stage &sg) {
         uint32_t *dst = (is_dy ? Aw : Bw) + (c8 * 8) * LDW + pp;
-        if (XF32 && !is_dy) {
+        if (!is_dy) {
 #pragma unroll
             for (int e = 0; e < NE; ++e) dst[e * LDW] = bf16_pack2(sg.xf[0][e], sg.xf[1][e]);
             return;
-        }
-        if (INAFF && !is_dy) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (sg.ok & (1u << u)) {  // padding stays zero
-                    uint4 v = sg.q[u];
-                    v.x = bf16_pack2(fmaxf(fmaf(bf16_lo(v.x), in_sc.x, in_sh.x), 0.f), fmaxf(fmaf(bf16_hi(v.x), in_sc.y, in_sh.y), 0.f));
-                    v.y = bf16_pack2(fmaxf(fmaf(bf16_lo(v.y), in_sc.z, in_sh.z), 0.f), fmaxf(fmaf(bf16_hi(v.y), in_sc.w, in_sh.w), 0.f));
-                    v.z = bf16_pack2(fmaxf(fmaf(bf16_lo(v.z), in_sc2.x, in_sh2.x), 0.f), fmaxf(fmaf(bf16_hi(v.z), in_sc2.y, in_sh2.y), 0.f));
-                    v.w = bf16_pack2(fmaxf(fmaf(bf16_lo(v.w), in_sc2.z, in_sh2.z), 0.f), fmaxf(fmaf(bf16_hi(v.w), in_sc2.w, in_sh2.w), 0.f));
-                    sg.q[u] = v;
-                }
         }
         // word e = (index e of the first pixel, index e of the second): low and high halves of the two loads' words
         const uint32_t a[4] = {sg.q[0].x, sg.q[0].y, sg.q[0].z, sg.q[0].w}, b[4] = {sg.q[1].x, sg.q[1].y, sg.q[1].z, sg.q[1].w};

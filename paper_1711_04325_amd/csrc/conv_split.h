@@ -15,11 +15,7 @@ constexpr int kPlaneRow = kSplitRow * 4;  // bytes of one filter row's 32 split 
 // w [rows][Kdim] fp32 -> planes [Kdim/32][plane_rows][192 bytes]: stage kc of filter row j as split_chunk lays it out (the
 // swizzle depends on j modulo 16 only, so a tile that starts at a multiple of 16 rows is copied to LDS as it is).  Rows from
 // `rows` to plane_rows are zeros.  One thread per (stage, row, chunk of eight elements).
-struct SplitJob {
-    long src_off;   // element offset of the filter from the launch's base
-    long dst_off;   // byte offset of its planes
-    int rows, plane_rows, kdim, block_begin;
-};
+typedef SplitJobHost SplitJob;
 __device__ inline void split_rows(const SplitJob &job, const float *__restrict__ src, char *__restrict__ dst, long idx)
 {
     const int chunks = job.kdim / kBK;
@@ -136,7 +132,7 @@ __device__ __forceinline__ void clear_acc(floatx16 (&acc)[MI][NI], floatx16 (&ac
             for (int e = 0; e < 16; ++e) acc[i][j][e] = accl[i][j][e] = 0.f;
 }
 
-// The implicit GEMM of igemm_kernel (same work decomposition, MODE 0 and 1, Cin % 32 == 0) with p.planes as filter operand.
+// The implicit GEMM of igemm_kernel (same work decomposition, MODE 0 and, for a dilation of 2, MODE 1; Cin % 32 == 0) with p.planes as filter operand.
 // Stages follow each other across work items: the first stage of a workgroup's next item is loaded while the last stage of the
 // present one is multiplied, and an item's results are stored behind the barrier wait of those loads.
 template <int BM, int BN, int MODE, bool INAFF, bool STATS>
@@ -226,15 +222,9 @@ __global__ __launch_bounds__(kConvThreads, igemm_pre_occupancy(BM, BN)) void ige
             int ih = hn[i] + r, iw = wnum[i] + s;
             bool ok = ih >= 0 && iw >= 0;
             if (MODE == 1) {
-                if (p.sd == 2) {
-                    ok = ok && ((ih | iw) & 1) == 0;
-                    ih >>= 1;
-                    iw >>= 1;
-                } else {
-                    ok = ok && (ih % p.sd == 0) && (iw % p.sd == 0);
-                    ih /= p.sd;
-                    iw /= p.sd;
-                }
+                ok = ok && ((ih | iw) & 1) == 0;
+                ih >>= 1;
+                iw >>= 1;
             }
             ok = ok && ih < p.IH && iw < p.IW;
             const unsigned aoff = (unsigned)(abase[i] + (int)__umul24(__umul24(ih, p.IW) + iw, p.Cin) + c0);
@@ -262,30 +252,11 @@ __global__ __launch_bounds__(kConvThreads, igemm_pre_occupancy(BM, BN)) void ige
     IgemmItem it = igemm_item<BM, BN>(p, item, G);
     set_rows(it);
     int kc = first_chunk(it), buf = 0;
-    int cur_ph = skip_ph, cur_pw = skip_pw;
     load_b(it.n0, kc, 0);
     load_a(kc);
-    clear_acc(acc, accl);
     store_a();
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    while (true) {
-        int kn = next_chunk(kc + 1, it.kc_end, cur_ph, cur_pw);
-        const bool last = kn >= it.kc_end;
-        bool more = true;
-        IgemmItem nx = it;
-        if (last) {
-            item += G;
-            more = item < n_items;
-            if (more) {
-                nx = igemm_item<BM, BN>(p, item, G);
-                set_rows(nx);
-                kn = first_chunk(nx);
-            }
-        }
-        if (more) {  // in flight while the current stage is multiplied
-            load_b(nx.n0, kn, buf ^ 1);
-            load_a(kn);
-        }
+    auto compute = [&]() {
         __builtin_amdgcn_s_setprio(3);
         const uint4 *bq = Bs[buf];
 #pragma unroll
@@ -296,182 +267,174 @@ __global__ __launch_bounds__(kConvThreads, igemm_pre_occupancy(BM, BN)) void ige
         }
         __builtin_amdgcn_s_setprio(2);
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // every fragment of this stage has been read
+    };
+    while (true) {
+        const int ph = skip_ph, pw = skip_pw;
+        clear_acc(acc, accl);
+        for (int kn; (kn = next_chunk(kc + 1, it.kc_end, ph, pw)) < it.kc_end; kc = kn) {
+            load_b(it.n0, kn, buf ^ 1);  // in flight while the current stage is multiplied
+            load_a(kn);
+            compute();
+            store_a();
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            buf ^= 1;
+        }
+        // the item's last stage, with the first one of the next item on its way
+        item += G;
+        const bool more = item < n_items;
+        IgemmItem nx = it;
+        if (more) {
+            nx = igemm_item<BM, BN>(p, item, G);
+            set_rows(nx);
+            kc = first_chunk(nx);
+            load_b(nx.n0, kc, buf ^ 1);
+            load_a(kc);
+        }
+        compute();
         if (more) {
             store_a();
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before the results below are stored: those are not waited for
         }
-        if (last) {
-            igemm_join_split<kBK, INAFF>(p, it.m0 + wm * WTM, it.n0 + wn * WTN, next_chunk(it.kc_begin, it.kc_end, cur_ph, cur_pw), it.kc_end,
-                                         [&](int k) { return next_chunk(k, it.kc_end, cur_ph, cur_pw); }, [&](int k) { return k * kBK; }, acc, accl);
-            igemm_finish<BM, BN, false, STATS>(p, acc, it.part, it.m0, it.n0, it.tm, s_stat[0], s_stat[1]);
-            if (!more) break;
-            clear_acc(acc, accl);
-            cur_ph = skip_ph;
-            cur_pw = skip_pw;
-        }
+        igemm_join_split<kBK, INAFF>(p, it.m0 + wm * WTM, it.n0 + wn * WTN, next_chunk(it.kc_begin, it.kc_end, ph, pw), it.kc_end,
+                                     [&](int k) { return next_chunk(k, it.kc_end, ph, pw); }, [&](int k) { return k * kBK; }, acc, accl);
+        igemm_finish<BM, BN, false, STATS>(p, acc, it.part, it.m0, it.n0, it.tm, s_stat[0], s_stat[1]);
+        if (!more) break;
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         it = nx;
-        kc = kn;
         buf ^= 1;
     }
 }
 
-// 3x3 convolution of stride 1 and padding 1 (forward, or data gradient with the flipped filter): input and output pixels have
-// the same linear index m = (n*H + h)*W + w, and the taps of pixel m are the pixels m + (r-1)*W + (s-1) that lie in the image.
-// The general kernel gathers and splits every input element nine times per column tile; here the BM + 2W + 2 pixels under a
-// tile's BM pixels go to LDS once per 32 channels, and the nine taps read their fragments from there, a lane whose tap
-// falls outside the image from a row of zeros.  Reduction order: stage = (channel block, tap).
-// The filter planes come half a stage (16 elements) at a time through a ring of three buffers, two halves ahead of their use.
-constexpr int conv3_rows(int bm, int wmax) { return bm + 2 * wmax + 2; }
-template <int BM, int BN, int WMAX, bool INAFF, bool STATS>
-__global__ __launch_bounds__(kConvThreads, kConv3Occupancy) void conv3x3_kernel(IgemmP p)
+// ---- filter gradient -------------------------------------------------------------------------------------------------
+// dw[k][j] = sum over pixels of dy[pixel][k] * xcol[pixel][j] with operands split into bf16 terms (see split8): tile BM output channels x
+// BN flat filter indices, partial sums over a pixel range, as wgrad_kernel.  Both operands come from memory with the OUTPUT index
+// fastest, the matrix instruction wants the reduction index (the pixel) fastest: they are stored to LDS as they come,
+// [plane][pixel][index], and read back with the transposing LDS read (lane l of ds_read_b64_tr_b16 receives four pixels of index
+// l%16 of a 4 x 16 block).  A pixel's row is padded so that the four rows of 32 indices that half a wavefront reads lie in 64 different banks.
+constexpr int wgrad_split_pitch(int b) { return b == 128 ? 160 : 96; }  // 16-bit elements per row: 16 words past a multiple of 64, or 48
+typedef short short4v __attribute__((ext_vector_type(4)));
+struct Frag8 { short4v lo, hi; };  // eight pixels of one index
+__device__ __forceinline__ short4v lds_read_tr(const uint16_t *p)
 {
-    constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
-    constexpr int ROWS = conv3_rows(BM, WMAX), SLOTS = (ROWS * 4 + kConvThreads - 1) / kConvThreads;
-    constexpr int HB = BN * 6;                  // 16-byte pieces of a filter half stage
-    constexpr int NB = HB / kConvThreads;       // ... per thread (BN = 128: 3); BN = 64 takes one piece more for half of the threads
-    constexpr int NBX = (HB + kConvThreads - 1) / kConvThreads;
-    __shared__ __attribute__((aligned(16))) uint4 Bs[3][HB];
-    __shared__ __attribute__((aligned(16))) uint4 As[(ROWS + 1) * 12];  // the last row holds zeros
-    __shared__ float s_stat[2][STATS ? BN : 1];
-    main_chain_priority();
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v *)(__attribute__((address_space(3))) void *)p);
+}
+
+template <int BM, int BN, bool INAFF>
+__global__ __launch_bounds__(kConvThreads, wgrad_split_occupancy(BM, BN)) void wgrad_split_kernel(WgradP p)
+{
+    constexpr int MI = BM / 64, NI = BN / 64;
+    constexpr int CA = BM / 4, CB = BN / 4;                                    // 16-byte columns per pixel row
+    constexpr int PA = kConvThreads / CA, PB = kConvThreads / CB;              // pixel rows per pass
+    constexpr int RA = kBK / PA, RB = kBK / PB;
+    constexpr int LA = wgrad_split_pitch(BM), LB = wgrad_split_pitch(BN);
+    __shared__ __attribute__((aligned(16))) uint16_t As[3 * kBK * LA];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[3 * kBK * LB];
+
+    const int ntiles = p.tiles_k * p.tiles_j;
+    const int item = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int split = item / ntiles, tile = item - split * ntiles;
+    const int tk = tile / p.tiles_j, tj = tile - tk * p.tiles_j;
+    const int k0 = tk * BM, j0 = tj * BN;
+    const int pix_begin = split * p.pix_per_split, pix_end = min(p.Mpix, pix_begin + p.pix_per_split);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int W = p.IW, ncb = p.Cin / kBK;
-    const int rows = BM + 2 * W + 2;
-    const int G = gridDim.x, n_items = p.full_items + p.tail_tiles * p.tail_split;
-    int item = blockIdx.x;
-    if (item >= n_items) return;
-    if (tid < 12) As[ROWS * 12 + tid] = make_uint4(0u, 0u, 0u, 0u);
+    const int ca = tid % CA, pa = tid / CA, cb = tid % CB, pb = tid / CB;
 
-    // half stage h of a filter stage: of every row the chunks 2h and 2h+1 of each plane.  In memory (and in the LDS image of
-    // a whole stage) those sit at chunk positions c ^ (row/4 % 4); the half image is [row][plane][2], chunk 2h + e of a row at
-    // e ^ (row/8 % 2) (rows are 24 words long: rows r and r + 8 start in the same bank).
-    const unsigned b_lds = lds_offset(&Bs[0][0]) + wave * 1024;
-    unsigned b_off[NBX];
-#pragma unroll
-    for (int u = 0; u < NBX; ++u) {
-        const int piece = u * kConvThreads + tid;
-        const int row = piece / 6, rem = piece - row * 6;
-        const int pos = ((row >> 2) & 2) | ((rem ^ (row >> 3) ^ (row >> 2)) & 1);  // position in its plane for half 0; half 1: pos ^ 2
-        b_off[u] = row * kPlaneRow + (rem >> 1) * 64 + pos * 16;
+    // filter tap and channel of this thread's four columns (Cin % 4 == 0: they share a tap)
+    const int j = j0 + cb * 4;
+    const bool jok = j < p.Jdim, kok = k0 + ca * 4 < p.Kout;
+    const int r = j / (p.S * p.Cin), rem0 = j - r * (p.S * p.Cin), sx = rem0 / p.Cin, c = rem0 - sx * p.Cin;
+    const int th = r - p.pad, tw = sx - p.pad, toff = (th * p.IW + tw) * p.Cin + c;
+    float4 in_sc = make_float4(0.f, 0.f, 0.f, 0.f), in_sh = in_sc;
+    if (INAFF && jok) {
+        in_sc = ldg4(p.in_scale + c);
+        in_sh = ldg4(p.in_shift + c);
     }
-    auto load_b = [&](int n0, int stage, int half, int slot) {
-        const int cb = stage / 9, tap = stage - cb * 9;
-        const char *src = p.planes + ((size_t)(tap * ncb + cb) * p.plane_rows + n0) * kPlaneRow;
+    // running state of the loads (see wgrad_tile): decoded once, then advanced by kBK pixels per stage
+    int apix = pix_begin + pa, bpix = pix_begin + pb, bih[RB], biw[RB];
+    unsigned aoff = (unsigned)apix * (unsigned)p.Kout + (unsigned)(k0 + ca * 4), boff[RB];
 #pragma unroll
-        for (int u = 0; u < NBX; ++u)
-            if (u < NB || wave < (HB - NB * kConvThreads) / 64) lds_copy16(src, b_off[u] ^ (half * 32), b_lds + slot * (HB * 16) + u * 4096);
-    };
-
-    float4 ra[SLOTS][2];
-    float4 in_sc[2], in_sh[2];
+    for (int i = 0; i < RB; ++i) {
+        const int pix = bpix + PB * i;
+        const int n = (int)fdiv(pix, p.div_ohw), rem = pix - n * (p.OH * p.OW);
+        const int oh = (int)fdiv(rem, p.div_ow), ow = rem - oh * p.OW;
+        bih[i] = oh * p.stride;
+        biw[i] = ow * p.stride;
+        boff[i] = ((unsigned)(n * p.IH + bih[i]) * (unsigned)p.IW + (unsigned)biw[i]) * (unsigned)p.Cin;
+    }
+    float4 ra[RA], rb[RB];
     unsigned in_ok = 0;
-    auto load_a = [&](int m0, int cb) {
-        const int c0 = cb * kBK + (tid & 3) * 4;
-        if (INAFF) {
+    auto load = [&]() {
+        const unsigned astep = (unsigned)PA * (unsigned)p.Kout;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                in_sc[t] = ldg4(p.in_scale + c0 + 16 * t);
-                in_sh[t] = ldg4(p.in_shift + c0 + 16 * t);
+        for (int i = 0; i < RA; ++i) ra[i] = (kok && apix + PA * i < pix_end) ? ldg4(p.dy + (aoff + astep * i)) : make_float4(0.f, 0.f, 0.f, 0.f);
+        in_ok = 0;
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            const int ih = bih[i] + th, iw = biw[i] + tw;
+            const bool ok = (bpix + PB * i < pix_end) & jok & ((unsigned)ih < (unsigned)p.IH) & ((unsigned)iw < (unsigned)p.IW);
+            rb[i] = ok ? ldg4(p.x + (boff[i] + (unsigned)toff)) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (INAFF && ok) in_ok |= 1u << i;
+            biw[i] += p.adv_iw;
+            boff[i] += p.adv_off;
+            if (biw[i] >= p.lim_iw) {
+                biw[i] -= p.lim_iw;
+                bih[i] += p.stride;
+                boff[i] += p.carry_row;
             }
-            in_ok = 0;
+            bih[i] += p.adv_ih;
+            if (bih[i] >= p.lim_ih) {
+                bih[i] -= p.lim_ih;
+                boff[i] += p.carry_img;
+            }
         }
+        apix += kBK;
+        bpix += kBK;
+        aoff += p.adv_dy;
+    };
+    auto put = [&](uint16_t *d, int plane, float4 v) {  // four indices of one pixel; d: the hi plane's place
 #pragma unroll
-        for (int u = 0; u < SLOTS; ++u) {
-            const int row = (u * kConvThreads + tid) >> 2;
-            const int m = m0 - W - 1 + row;
-            const bool ok = row < rows && m >= 0 && m < p.M;
-#pragma unroll
-            for (int t = 0; t < 2; ++t) ra[u][t] = ok ? ldg4(p.a + ((unsigned)m * (unsigned)p.Cin + c0 + 16 * t)) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (INAFF && ok) in_ok |= 1u << u;
+        for (int t = 0; t < 3; ++t) {
+            const uint32_t w0 = t < 2 ? split_pair(v.x, v.y) : bf16_pack2(v.x, v.y), w1 = t < 2 ? split_pair(v.z, v.w) : bf16_pack2(v.z, v.w);
+            *reinterpret_cast<uint2 *>(d + t * plane) = make_uint2(w0, w1);
         }
     };
-    auto store_a = [&]() {
+    auto store = [&]() {
 #pragma unroll
-        for (int u = 0; u < SLOTS; ++u) {
-            const int row = (u * kConvThreads + tid) >> 2;
-            if (row >= rows) continue;
-            if (INAFF && (in_ok & (1u << u))) {
-                ra[u][0] = bn_relu4(ra[u][0], in_sc[0], in_sh[0]);
-                ra[u][1] = bn_relu4(ra[u][1], in_sc[1], in_sh[1]);
-            }
-            const Split8 v = split8(ra[u][0], ra[u][1]);
-            const int at = split_chunk(row, 0, tid & 3);
-            As[at] = v.hi;
-            As[at + 4] = v.mid;
-            As[at + 8] = v.lo;
-        }
-    };
-    // bit 3r+s of taps[i]: tap (r, s) of this lane's pixel of row block i lies in the image
-    unsigned taps[MI];
-    auto set_taps = [&](const IgemmItem &it) {
+        for (int i = 0; i < RA; ++i) put(&As[(pa + PA * i) * LA + ca * 4], kBK * LA, ra[i]);
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int m = it.m0 + wm * WTM + i * 32 + (lane & 31);
-            int cls, n, oh, ow;
-            decode_row(p, m < p.M ? m : 0, cls, n, oh, ow);
-            const unsigned cols = (ow > 0 ? 1u : 0u) | 2u | (ow < W - 1 ? 4u : 0u);
-            taps[i] = m < p.M ? (oh > 0 ? cols : 0u) | cols << 3 | (oh < p.IH - 1 ? cols << 6 : 0u) : 0u;
+        for (int i = 0; i < RB; ++i) {
+            if (INAFF && (in_ok & (1u << i))) rb[i] = bn_relu4(rb[i], in_sc, in_sh);  // padding stays zero
+            put(&Bs[(pb + PB * i) * LB + cb * 4], kBK * LB, rb[i]);
         }
     };
 
     floatx16 acc[MI][NI], accl[MI][NI];
-    IgemmItem it = igemm_item<BM, BN>(p, item, G);
-    int st = it.kc_begin, slot = 0;
-    load_b(it.n0, st, 0, 0);
-    load_b(it.n0, st, 1, 1);
-    load_a(it.m0, st / 9);
-    set_taps(it);
     clear_acc(acc, accl);
-    store_a();
-    bool drained = false;
-    while (true) {
-        // the stage after this one, and whether it needs another input block
-        int sn = st + 1;
-        const bool last = sn >= it.kc_end;
-        bool more = true;
-        IgemmItem nx = it;
-        if (last) {
-            item += G;
-            more = item < n_items;
-            if (more) {
-                nx = igemm_item<BM, BN>(p, item, G);
-                sn = nx.kc_begin;
-            }
-        }
-        const bool fresh = more && (last || sn % 9 == 0);
-        const int tap = st % 9, tr = tap / 3, ts = tap - 3 * tr;
-        // LDS words of this lane's fragments: pixel q's tap is row q + r*W + s of the input block
-        int a_row[MI];
+    const int frow = 8 * (lane >> 5) + ((lane & 15) >> 2), fcol = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    const uint16_t *fa = &As[frow * LA + wm * (BM / 2) + fcol], *fb = &Bs[frow * LB + wn * (BN / 2) + fcol];
+    const int stages = (pix_end - pix_begin + kBK - 1) / kBK;
+    load();
+    store();
+    if (stages > 1) load();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    for (int st = 0; st < stages; ++st) {
+        __builtin_amdgcn_s_setprio(1);  // as in wgrad_tile: multiplying goes before address arithmetic, both below the main chain
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int row = wm * WTM + i * 32 + (lane & 31) + tr * W + ts;
-            a_row[i] = (taps[i] >> tap) & 1 ? row * 12 + ((lane >> 5) ^ ((row >> 2) & 3)) : ROWS * 12;
-        }
-        const int b_row = (wn * WTN + (lane & 31)) * 6 + ((lane >> 5) ^ ((lane >> 3) & 1));
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            // this half's filter planes are there when at most the copies of the next half are under way (none are behind the
-            // last half; none are left behind a drained wait, whose stores would be waited for here)
-            if (!drained) {
-                if (half == 1 && !more) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                else if (NB == NBX || wave < (HB - NB * kConvThreads) / 64) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NBX) : "memory");
-                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NB) : "memory");
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            const int ahead = slot >= 1 ? slot - 1 : 2;  // the ring slot two halves on
-            if (more) load_b(nx.n0, sn, half, ahead);
-            if (half == 0 && fresh) load_a(nx.m0, sn / 9);
-            __builtin_amdgcn_s_setprio(3);
-            const uint4 *bq = Bs[slot];
-            uint4 af[MI][3], bf[NI][3];
+        for (int ks = 0; ks < 2; ++ks) {
+            Frag8 af[MI][3], bf[NI][3];
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
 #pragma unroll
-                for (int i = 0; i < MI; ++i) af[i][t] = As[(a_row[i] ^ (half * 2)) + 4 * t];
+                for (int i = 0; i < MI; ++i) {
+                    const uint16_t *q = fa + (t * kBK + ks * 16) * LA + i * 32;
+                    af[i][t] = Frag8{lds_read_tr(q), lds_read_tr(q + 4 * LA)};
+                }
 #pragma unroll
-                for (int j = 0; j < NI; ++j) bf[j][t] = bq[b_row + j * 192 + 2 * t];
+                for (int i = 0; i < NI; ++i) {
+                    const uint16_t *q = fb + (t * kBK + ks * 16) * LB + i * 32;
+                    bf[i][t] = Frag8{lds_read_tr(q), lds_read_tr(q + 4 * LB)};
+                }
             }
 #pragma unroll
             for (int pr = 0; pr < 6; ++pr) {
@@ -479,31 +442,78 @@ __global__ __launch_bounds__(kConvThreads, kConv3Occupancy) void conv3x3_kernel(
 #pragma unroll
                 for (int i = 0; i < MI; ++i)
 #pragma unroll
-                    for (int j = 0; j < NI; ++j) {
-                        floatx16 &d = pr == 0 ? acc[i][j] : accl[i][j];
-                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i][ta[pr]]), __builtin_bit_cast(bf16x8, bf[j][tb[pr]]), d, 0, 0, 0);
+                    for (int n = 0; n < NI; ++n) {
+                        floatx16 &d = pr == 0 ? acc[i][n] : accl[i][n];
+                        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[i][ta[pr]]), __builtin_bit_cast(bf16x8, bf[n][tb[pr]]), d, 0, 0, 0);
                     }
             }
-            __builtin_amdgcn_s_setprio(2);
-            slot = slot == 2 ? 0 : slot + 1;
         }
-        if (fresh) {
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // every fragment of the input block has been read
-            store_a();
+        __builtin_amdgcn_s_setprio(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (st + 1 < stages) {
+            store();
+            if (st + 2 < stages) load();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         }
-        drained = last;
-        if (last) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the next stage's planes, before the results below are stored
-            igemm_join_split<kBK, INAFF>(p, it.m0 + wm * WTM, it.n0 + wn * WTN, it.kc_begin, it.kc_end, [&](int k) { return k; },
-                                         [&](int k) { return ((k % 9) * ncb + k / 9) * kBK; }, acc, accl);
-            igemm_finish<BM, BN, false, STATS>(p, acc, it.part, it.m0, it.n0, it.tm, s_stat[0], s_stat[1]);
-            if (!more) break;
-            clear_acc(acc, accl);
-            set_taps(nx);
-        }
-        it = nx;
-        st = sn;
     }
+
+    const int t2 = opaque_tid(), l2 = t2 & 63;
+    float probe = 0.f;  // NaN when a sum is not finite
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int n = 0; n < NI; ++n)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                acc[i][n][e] += accl[i][n][e];
+                probe = fmaf(acc[i][n][e], 0.f, probe);
+            }
+    if (__any(probe != probe)) {  // see igemm_join_split
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int n = 0; n < NI; ++n)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][n][e] = 0.f;
+        for (int pix = pix_begin + (l2 >> 5); pix < pix_end + (l2 >> 5); pix += 2) {
+            const bool in = pix < pix_end;
+            const int pq = in ? pix : pix_begin;
+            const int n = (int)fdiv(pq, p.div_ohw), rem = pq - n * (p.OH * p.OW);
+            const int oh = (int)fdiv(rem, p.div_ow), ow = rem - oh * p.OW;
+            float va[MI], vb[NI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const int k = k0 + wm * (BM / 2) + i * 32 + (l2 & 31);
+                va[i] = in && k < p.Kout ? p.dy[(size_t)pq * p.Kout + k] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int jj = j0 + wn * (BN / 2) + i * 32 + (l2 & 31);
+                const int rr = jj / (p.S * p.Cin), m0 = jj - rr * (p.S * p.Cin), ss = m0 / p.Cin, cc = m0 - ss * p.Cin;
+                const int ih = oh * p.stride + rr - p.pad, iw = ow * p.stride + ss - p.pad;
+                const bool ok = in && jj < p.Jdim && (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
+                vb[i] = ok ? p.x[(((size_t)n * p.IH + ih) * p.IW + iw) * p.Cin + cc] : 0.f;
+                if (INAFF && ok) vb[i] = fmaxf(fmaf(vb[i], p.in_scale[cc], p.in_shift[cc]), 0.f);
+            }
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int nn = 0; nn < NI; ++nn) acc[i][nn] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i], vb[nn], acc[i][nn], 0, 0, 0);
+        }
+    }
+    float *out = p.out + (long)split * p.split_stride;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int k = k0 + wm * (BM / 2) + i * 32 + 8 * (e >> 2) + 4 * (l2 >> 5) + (e & 3);
+            if (k >= p.Kout) continue;
+#pragma unroll
+            for (int n = 0; n < NI; ++n) {
+                const int col = j0 + wn * (BN / 2) + n * 32 + (l2 & 31);
+                if (col < p.Jdim) out[(long)k * p.Jdim + col] = acc[i][n][e];
+            }
+        }
 }
 
 }  // namespace rn50

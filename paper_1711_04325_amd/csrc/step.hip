@@ -105,10 +105,22 @@ struct Plan {
     std::vector<FlipJobHost> jobs;
     std::vector<size_t> conv_out, bn_out, mean, invstd, wt;  // wt: float offset of a layer's flipped filter in wt_arena
     std::vector<size_t> scale, shift;                        // per-channel scale and shift of a layer's BN (BN(x) = x*scale + shift)
+    std::vector<BnLayerHost> bn_layers;                      // the same offsets as a table in the arena (validation: all layers in one launch)
+    size_t bn_table;
     std::vector<size_t> relu_mask;                           // c layers: one byte per four channels, [block output > 0]
     // Grouped filter gradients: every layer's BN-input gradient keeps a buffer of its own until the launch that covers its
     // group has read it; one workspace for the partial sums (the groups run one after the other) and room for the plans.
     std::vector<size_t> dconv_l;
+    // Filters prepared beforehand, one launch for all layers whose call takes them so: [0] those of the forward pass, [1] the flipped
+    // ones of the data gradients; .second index: fp32 contexts (split into bf16 terms) and contexts with bf16 activations (rounded), which
+    // share the room
+    struct Planes {
+        std::vector<SplitJobHost> jobs;
+        std::vector<char> has;            // per layer
+        std::vector<size_t> off;          // per layer, from `arena`
+        size_t jobs_off, arena;
+        int blocks;
+    } planes[2][2];
     size_t ws_group, ws_group_bytes, group_tables, group_tables_bytes;
 };
 
@@ -153,13 +165,19 @@ static Plan make_plan(int batch, int variant)
         const bool first = &l == &n.convs[0];
         for (int dt : {RN50_DTYPE_F32, first ? RN50_DTYPE_BF16_ACT_F32IN : RN50_DTYPE_BF16_ACT}) {
             const rn50_conv_desc d = desc_of(l, batch, dt);
-            wsc = std::max(wsc, rn50_conv_workspace_bytes(&d, RN50_OP_FWD));
-            wsc = std::max(wsc, rn50_conv_workspace_bytes(&d, RN50_OP_FWD_BNSTATS));
-            wsc = std::max(wsc, rn50_conv_workspace_bytes(&d, RN50_OP_BWD_WEIGHT));
-            if (dt != RN50_DTYPE_BF16_ACT_F32IN) wsc = std::max(wsc, conv_bwd_data_pretransposed_ws(&d));
+            for (int v = 0; v < 3; ++v) {  // on the fp32 instruction; split operands, without and with a filter prepared beforehand
+                const Fp32Math math = v ? kFp32Split : kFp32Unit;
+                for (int op : {RN50_OP_FWD, RN50_OP_FWD_BNSTATS, RN50_OP_BWD_WEIGHT, RN50_OP_BWD_DATA_FLIPPED})
+                    if (op != RN50_OP_BWD_DATA_FLIPPED || dt != RN50_DTYPE_BF16_ACT_F32IN) wsc = std::max(wsc, conv_workspace(&d, op, math, v == 2));
+            }
         }
         wsb = std::max(wsb, rn50_bn_workspace_bytes(batch, l.k, l.hout, l.hout));
     }
+    for (size_t i = 0; i < n.convs.size(); ++i) {
+        const ConvL &l = n.convs[i];
+        p.bn_layers.push_back(BnLayerHost{(long)l.g_off, (long)l.b_off, (long)p.mean[i], (long)p.invstd[i], (long)p.scale[i], (long)p.shift[i], l.k, 0});
+    }
+    p.bn_table = take(cur, p.bn_layers.size() * sizeof(BnLayerHost));
     // flipped filters of every convolution whose data gradient is needed (all but the stem)
     size_t wt_floats = 0;
     int blocks = 0;
@@ -179,6 +197,31 @@ static Plan make_plan(int batch, int variant)
     p.flip_blocks = blocks;
     p.flip_jobs = take(cur, p.jobs.size() * sizeof(FlipJobHost));
     p.wt_arena = take(cur, wt_floats * 4);
+    for (int dir = 0; dir < 2; ++dir) {
+        size_t room = 0;
+        for (int act = 0; act < 2; ++act) {
+            Plan::Planes &pp = p.planes[dir][act];
+            pp.has.assign(n.convs.size(), 0);
+            pp.off.assign(n.convs.size(), 0);
+            pp.blocks = 0;
+            size_t bytes = 0;
+            for (size_t i = 1; i < n.convs.size(); ++i) {
+                const ConvL &l = n.convs[i];
+                const rn50_conv_desc d = desc_of(l, batch, act ? RN50_DTYPE_BF16_ACT : RN50_DTYPE_F32);
+                const size_t need = conv_planes_bytes(&d, dir ? RN50_OP_BWD_DATA : RN50_OP_FWD);
+                if (!need || (!dir && !act && !config()->split_products)) continue;
+                const SplitJobHost j = split_job(dir ? l.c : l.k, l.r * l.r * (dir ? l.k : l.c), (long)(dir ? p.wt[i] : l.w_off), (long)bytes, pp.blocks);
+                pp.has[i] = 1;
+                pp.off[i] = bytes;
+                pp.blocks += split_job_blocks(j.rows, j.kdim);
+                pp.jobs.push_back(j);
+                bytes += (need + 255) / 256 * 256;
+            }
+            pp.jobs_off = take(cur, pp.jobs.size() * sizeof(SplitJobHost));
+            room = std::max(room, bytes);
+        }
+        p.planes[dir][0].arena = p.planes[dir][1].arena = take(cur, room);
+    }
     const size_t pool_cnt = (size_t)batch * 56 * 56 * 64;
     p.pool_out = take(cur, pool_cnt * 4);
     p.pool_arg = take(cur, pool_cnt);
@@ -226,6 +269,11 @@ struct rn50_ctx {
     // RN50_DTYPE_BF16_ACT: every activation and activation gradient the step keeps in memory is bfloat16 (parameters, their
     // gradients, BN statistics, pooled features, logits and all sums stay fp32); the buffers are planned at their fp32 size.
     int conv_dtype = RN50_DTYPE_F32;
+    // The training step's fp32 convolutions.  The gradients are formed from split operands.  The forward pass keeps the fp32 instruction
+    // and the order of sums it has always had, unless the option "split_products" is set at rn50_create: which side of a ReLU a near
+    // tie falls on depends on it, and with other decisions an iteration's gradient moves by 2 % and the weights by 3e-3 of their norm
+    // within two iterations, whatever the precision.
+    Fp32Math fwd_math = kFp32Unit, bwd_math = kFp32Split;
     // The BN + ReLU behind the stem and behind the a and b convolutions of a block has ONE consumer each (the max pooling, the
     // next convolution): it is applied by that consumer as it loads (and again by the consumer's filter gradient) instead
     // of by a kernel of its own, and its output is never written.  Option "fuse_bn" = 0 at rn50_create switches this off.
@@ -250,7 +298,7 @@ struct rn50_ctx {
     hipEvent_t pfork = nullptr, pjoin = nullptr;
     // The flipped/transposed filters of the backward pass depend only on the parameters: they are produced on the side
     // stream while the forward pass runs.
-    hipEvent_t entry = nullptr, flipped = nullptr;
+    hipEvent_t entry = nullptr, flipped = nullptr, fsplit = nullptr;
     // Filter gradients in grouped launches (option "wgrad_group" = blocks per group at rn50_create; fp32 contexts): the layers
     // of that many consecutive blocks go into one launch once the last of their BN-input gradients is written.  A group
     // launches after the layers of its last block in backward order.
@@ -385,6 +433,13 @@ extern "C" int rn50_create(rn50_ctx **out, int batch, int variant, int conv_dtyp
     hipError_t e = hipMemcpy(c->arena + c->plan.mask_off, mask.data(), mask.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(c->arena + c->plan.flip_jobs, c->plan.jobs.data(), c->plan.jobs.size() * sizeof(FlipJobHost), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(c->arena + c->plan.bn_table, c->plan.bn_layers.data(), c->plan.bn_layers.size() * sizeof(BnLayerHost), hipMemcpyHostToDevice);
+    for (int i = 0; i < 4; ++i) {
+        const Plan::Planes &pp = c->plan.planes[i >> 1][i & 1];
+        if (e == hipSuccess && !pp.jobs.empty())
+            e = hipMemcpy(c->arena + pp.jobs_off, pp.jobs.data(), pp.jobs.size() * sizeof(SplitJobHost), hipMemcpyHostToDevice);
+    }
     if (e != hipSuccess) {
         delete c;
         return fail(RN50_EHIP, "rn50_create: upload failed: %s", hipGetErrorString(e));
@@ -395,6 +450,7 @@ extern "C" int rn50_create(rn50_ctx **out, int batch, int variant, int conv_dtyp
     c->fuse_bn = cfg->fuse_bn >= 0 ? cfg->fuse_bn : (conv_dtype == RN50_DTYPE_BF16_ACT ? 1 : 3);
     c->relu_mask = cfg->relu_mask;
     c->conv_bn_stats = cfg->conv_bn_stats;
+    if (cfg->split_products) c->fwd_math = kFp32Split;
     c->bn_out_stale.assign(n.convs.size(), 0);
     if (cfg->side_stream) {
         bool ok = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) == hipSuccess &&
@@ -403,6 +459,7 @@ extern "C" int rn50_create(rn50_ctx **out, int batch, int variant, int conv_dtyp
                   hipEventCreateWithFlags(&c->pjoin, hipEventDisableTiming) == hipSuccess &&
                   hipEventCreateWithFlags(&c->entry, hipEventDisableTiming) == hipSuccess &&
                   hipEventCreateWithFlags(&c->flipped, hipEventDisableTiming) == hipSuccess &&
+                  hipEventCreateWithFlags(&c->fsplit, hipEventDisableTiming) == hipSuccess &&
                   hipEventCreateWithFlags(&c->pbn, hipEventDisableTiming) == hipSuccess &&
                   hipEventCreateWithFlags(&c->gdone, hipEventDisableTiming) == hipSuccess;
         for (int i = 0; i < 3 && ok; ++i)
@@ -435,6 +492,7 @@ extern "C" void rn50_destroy(rn50_ctx *ctx)
     if (ctx->pjoin) (void)hipEventDestroy(ctx->pjoin);
     if (ctx->entry) (void)hipEventDestroy(ctx->entry);
     if (ctx->flipped) (void)hipEventDestroy(ctx->flipped);
+    if (ctx->fsplit) (void)hipEventDestroy(ctx->fsplit);
     if (ctx->pbn) (void)hipEventDestroy(ctx->pbn);
     if (ctx->gdone) (void)hipEventDestroy(ctx->gdone);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
@@ -513,6 +571,23 @@ extern "C" const float *rn50_peek(rn50_ctx *ctx, int layer, int what, size_t *co
 #define RN50_TRY(call) \
     do { if (int rc_ = (call)) return rc_; } while (0)
 
+// All filters of one direction prepared for their calls (dir 0: from theta; 1: from the flipped filters in the arena), in one launch;
+// planes_of: a layer's, or null where its call takes none.
+static const Plan::Planes &planes_set(const rn50_ctx *ctx, int dir) { return ctx->plan.planes[dir][ctx->conv_dtype == RN50_DTYPE_BF16_ACT]; }
+static void launch_planes(const rn50_ctx *ctx, int dir, const float *theta, hipStream_t st)
+{
+    const Plan::Planes &pp = planes_set(ctx, dir);
+    if (pp.jobs.empty()) return;
+    char *A = ctx->arena;
+    launch_filter_planes_batched(A + pp.jobs_off, (int)pp.jobs.size(), pp.blocks, ctx->conv_dtype == RN50_DTYPE_BF16_ACT,
+                                 dir ? (const float *)(A + ctx->plan.wt_arena) : theta, A + pp.arena, st);
+}
+static const char *planes_of(const rn50_ctx *ctx, int dir, int li)
+{
+    const Plan::Planes &pp = planes_set(ctx, dir);
+    return pp.has[li] ? ctx->arena + pp.arena + pp.off[li] : nullptr;
+}
+
 // Validation-side forward (Section 2): every BN normalises with the statistics the context holds, i.e. those the last
 // training forward saved (with several workers: after averaging them, which bn_stats_average does on gathered sets and
 // rn50_set_bn_stats stores back).  Overwrites the stored activations of the last training step.
@@ -528,15 +603,18 @@ extern "C" int rn50_forward_eval(rn50_ctx *ctx, const float *images, const float
     const int N = ctx->batch;
     char *A = ctx->arena;
     auto F = [&](size_t off) { return (float *)(A + off); };
-    void *wsc = A + pl.ws_conv, *wsb = A + pl.ws_bn;
+    void *wsc = A + pl.ws_conv;
     const int L = (int)n.convs.size();
+    const bool split = ctx->conv_dtype == RN50_DTYPE_F32 && ctx->fwd_math == kFp32Split;  // the same bits as the training forward
+    if (split) launch_planes(ctx, 0, theta, (hipStream_t)stream);
+    // scale and shift of every BN in one launch (one launch per layer was a quarter of the launches of a single image)
+    launch_bn_scale_shift_batched(A + pl.bn_table, L, 2048, theta, A, (hipStream_t)stream);
     auto conv_bn = [&](int li, const float *x, const float *residual, int relu) -> int {
         const ConvL &l = n.convs[li];
         const rn50_conv_desc d = desc_of(l, N, ctx->conv_dtype);
-        RN50_TRY(conv2d_fwd(&d, x, theta + l.w_off, F(pl.conv_out[li]), wsc, pl.ws_conv_bytes, stream));
         ctx->bn_out_stale[li] = 0;  // every BN output is written here
-        return bn_fwd_inference(N, l.k, l.hout, l.hout, RN50_LAYOUT_NHWC, F(pl.conv_out[li]), theta + l.g_off, theta + l.b_off,
-                                F(pl.mean[li]), F(pl.invstd[li]), residual, relu, F(pl.bn_out[li]), wsb, pl.ws_bn_bytes, stream);
+        return conv_fwd_apply_math(ctx->fwd_math, &d, x, theta + l.w_off, split ? planes_of(ctx, 0, li) : nullptr, F(pl.conv_out[li]), F(pl.scale[li]),
+                                   F(pl.shift[li]), residual, relu, F(pl.bn_out[li]), wsc, pl.ws_conv_bytes, (hipStream_t)stream);
     };
     RN50_TRY(conv_bn(0, images, nullptr, 1));
     RN50_TRY(maxpool3x3s2_fwd(N, 64, 112, 112, F(pl.bn_out[0]), F(pl.pool_out), (uint8_t *)(A + pl.pool_arg), stream));
@@ -611,6 +689,12 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
     auto HW_ = [](float *q) { return reinterpret_cast<uint16_t *>(q); };
     // the first layer reads the fp32 image whatever the activation storage
     auto dtype_of = [&](int li) { return a16 && li == 0 ? RN50_DTYPE_BF16_ACT_F32IN : ctx->conv_dtype; };
+    const Fp32Math fmath = ctx->fwd_math, bmath = ctx->bwd_math;
+    // whether the filters of the forward pass and of the data gradients are prepared beforehand
+    const bool f32 = ctx->conv_dtype == RN50_DTYPE_F32, act16 = ctx->conv_dtype == RN50_DTYPE_BF16_ACT;
+    const bool fsplit = act16 || (f32 && fmath == kFp32Split), bsplit = act16 || (f32 && bmath == kFp32Split);
+    auto fplanes = [&](int li, int prod = -1) { return fsplit && !(act16 && prod >= 0) ? planes_of(ctx, 0, li) : nullptr; };
+    auto bplanes = [&](int li) { return bsplit ? planes_of(ctx, 1, li) : nullptr; };
     auto conv_bn = [&](int li, const float *x, const float *residual, int relu, bool branch = false, int prod = -1) -> int {
         const ConvL &l = n.convs[li];
         const rn50_conv_desc d = desc_of(l, N, dtype_of(li));
@@ -618,10 +702,10 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
         if (ctx->conv_bn_stats) {
             // statistics gathered by the convolution itself; what is left of the BN is the normalising pass, where the
             // consumer does not normalise as it loads
-            RN50_TRY(conv2d_fwd_bnstats(&d, prod >= 0 ? F(pl.conv_out[prod]) : x, prod >= 0 ? F(pl.scale[prod]) : nullptr,
-                                        prod >= 0 ? F(pl.shift[prod]) : nullptr, theta + l.w_off, F(pl.conv_out[li]), theta + l.g_off,
-                                        theta + l.b_off, bn_eps, F(pl.mean[li]), F(pl.invstd[li]), F(pl.scale[li]), F(pl.shift[li]),
-                                        branch ? A + pl.ws_conv3 : wsc, pl.ws_conv_bytes, st));
+            RN50_TRY(conv_fwd_bnstats_math(fmath, &d, prod >= 0 ? F(pl.conv_out[prod]) : x, prod >= 0 ? F(pl.scale[prod]) : nullptr,
+                                           prod >= 0 ? F(pl.shift[prod]) : nullptr, theta + l.w_off, fplanes(li, prod), F(pl.conv_out[li]),
+                                           theta + l.g_off, theta + l.b_off, bn_eps, F(pl.mean[li]), F(pl.invstd[li]), F(pl.scale[li]),
+                                           F(pl.shift[li]), branch ? A + pl.ws_conv3 : wsc, pl.ws_conv_bytes, (hipStream_t)st));
             ctx->bn_out_stale[li] = fused_out(li) ? 1 : 0;
             if (fused_out(li)) return RN50_OK;
             uint8_t *mask = l.block_pos == 3 && ctx->relu_mask ? (uint8_t *)(A + pl.relu_mask[li]) : nullptr;
@@ -632,10 +716,11 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
                                 F(pl.bn_out[li]), mask, st);
         }
         if (prod >= 0)
-            RN50_TRY(conv2d_fwd_bnrelu_input(&d, F(pl.conv_out[prod]), F(pl.scale[prod]), F(pl.shift[prod]), theta + l.w_off,
-                                             F(pl.conv_out[li]), branch ? A + pl.ws_conv3 : wsc, pl.ws_conv_bytes, st));
+            RN50_TRY(conv_fwd_math(fmath, &d, F(pl.conv_out[prod]), F(pl.scale[prod]), F(pl.shift[prod]), theta + l.w_off, fplanes(li, prod),
+                                   F(pl.conv_out[li]), branch ? A + pl.ws_conv3 : wsc, pl.ws_conv_bytes, (hipStream_t)st));
         else
-            RN50_TRY(conv2d_fwd(&d, x, theta + l.w_off, F(pl.conv_out[li]), branch ? A + pl.ws_conv3 : wsc, pl.ws_conv_bytes, st));
+            RN50_TRY(conv_fwd_math(fmath, &d, x, nullptr, nullptr, theta + l.w_off, fplanes(li), F(pl.conv_out[li]),
+                                   branch ? A + pl.ws_conv3 : wsc, pl.ws_conv_bytes, (hipStream_t)st));
         if (fused_out(li)) {
             ctx->bn_out_stale[li] = 1;
             if (a16)
@@ -666,8 +751,15 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
     if (ctx->use_side) {
         RN50_HIP(hipEventRecord(ctx->entry, main_st));
         RN50_HIP(hipStreamWaitEvent(ctx->side, ctx->entry, 0));
+        if (fsplit) {  // the forward filters first: the second layer waits for them
+            launch_planes(ctx, 0, theta, ctx->side);
+            RN50_HIP(hipEventRecord(ctx->fsplit, ctx->side));
+        }
         launch_filter_flip_batched(A + pl.flip_jobs, (int)pl.jobs.size(), pl.flip_blocks, theta, F(pl.wt_arena), ctx->side);
+        if (bsplit) launch_planes(ctx, 1, theta, ctx->side);
         RN50_HIP(hipEventRecord(ctx->flipped, ctx->side));
+    } else if (fsplit) {
+        launch_planes(ctx, 0, theta, main_st);
     }
 
     // ---------------- forward ----------------
@@ -681,6 +773,7 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
                                                (uint8_t *)(A + pl.pool_arg), stream));
     else
         RN50_TRY(maxpool3x3s2_fwd(N, 64, 112, 112, F(pl.bn_out[0]), F(pl.pool_out), (uint8_t *)(A + pl.pool_arg), stream));
+    if (fsplit && ctx->use_side) RN50_HIP(hipStreamWaitEvent(main_st, ctx->fsplit, 0));
     const float *h = F(pl.pool_out);
     std::vector<const float *> block_in;  // input activation of each block
     std::vector<int> block_first;         // index of its 'a' convolution
@@ -714,7 +807,10 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
     // ---------------- backward ----------------
     RN50_TRY(fc_bwd(N, 2048, 1000, F(pl.feat), theta + n.fcw_off, F(pl.dlogits), F(pl.dfeat), grad + n.fcw_off, grad + n.fcb_off, stream));
     if (ctx->use_side) RN50_HIP(hipStreamWaitEvent(main_st, ctx->flipped, 0));
-    else launch_filter_flip_batched(A + pl.flip_jobs, (int)pl.jobs.size(), pl.flip_blocks, theta, F(pl.wt_arena), main_st);
+    else {
+        launch_filter_flip_batched(A + pl.flip_jobs, (int)pl.jobs.size(), pl.flip_blocks, theta, F(pl.wt_arena), main_st);
+        if (bsplit) launch_planes(ctx, 1, theta, main_st);
+    }
     float *T2 = F(pl.gbuf[1]);
     float *setO[2] = {F(pl.gbuf[2]), F(pl.gbuf[4])}, *setR[2] = {F(pl.gbuf[3]), F(pl.gbuf[5])};
     float *ring[3] = {F(pl.dconv[0]), F(pl.dconv[1]), F(pl.dconv[2])};
@@ -761,9 +857,9 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
                                        dres, grad + l.g_off, grad + l.b_off, wsb, pl.ws_bn_bytes, stream));
         auto wgrad = [&](void *ws, void *st) -> int {
             if (x_prod >= 0)
-                return conv2d_bwd_weight_bnrelu_input(&d, F(pl.conv_out[x_prod]), F(pl.scale[x_prod]), F(pl.shift[x_prod]), dconv,
-                                                      grad + l.w_off, ws, pl.ws_conv_bytes, st);
-            return conv2d_bwd_weight(&d, x_in, dconv, grad + l.w_off, ws, pl.ws_conv_bytes, st);
+                return conv_bwd_weight_math(bmath, &d, F(pl.conv_out[x_prod]), F(pl.scale[x_prod]), F(pl.shift[x_prod]), dconv, grad + l.w_off, ws,
+                                            pl.ws_conv_bytes, (hipStream_t)st);
+            return conv_bwd_weight_math(bmath, &d, x_in, nullptr, nullptr, dconv, grad + l.w_off, ws, pl.ws_conv_bytes, (hipStream_t)st);
         };
         if (in_group) {
             // the launch of its group follows the last layer of the group; the event is for a projection branch that starts here
@@ -783,7 +879,8 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
             RN50_TRY(wgrad(wsc, stream));
         }
         if (dx_or_null)
-            RN50_TRY(conv_bwd_data_pretransposed(&d, dconv, F(pl.wt_arena) + pl.wt[li], dx_or_null, wsc, pl.ws_conv_bytes, main_st));
+            RN50_TRY(conv_bwd_data_pretransposed(bmath, &d, dconv, F(pl.wt_arena) + pl.wt[li], dx_or_null, wsc, pl.ws_conv_bytes, main_st,
+                                                 bplanes(li)));
         ++calls;
         return RN50_OK;
     };
@@ -804,15 +901,15 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
         RN50_TRY(bn_bwd_batchstats(N, l.k, l.hout, l.hout, RN50_LAYOUT_NHWC, F(pl.conv_out[lp]), dshortcut, nullptr, nullptr,
                                    theta + l.g_off, F(pl.mean[lp]), F(pl.invstd[lp]), 0, dconv, nullptr, grad + l.g_off,
                                    grad + l.b_off, A + pl.ws_bn2, pl.ws_bn_bytes, ctx->side2));
-        RN50_TRY(conv_bwd_data_pretransposed(&d, dconv, F(pl.wt_arena) + pl.wt[lp], F(pl.gbuf_p), A + pl.ws_conv3, pl.ws_conv_bytes,
-                                             ctx->side2));
+        RN50_TRY(conv_bwd_data_pretransposed(bmath, &d, dconv, F(pl.wt_arena) + pl.wt[lp], F(pl.gbuf_p), A + pl.ws_conv3, pl.ws_conv_bytes,
+                                             ctx->side2, bplanes(lp)));
         RN50_HIP(hipEventRecord(ctx->pjoin, ctx->side2));
         if (grouped) {  // its filter gradient is part of the block's grouped launch, which waits for this BN backward
             RN50_HIP(hipEventRecord(ctx->pbn, ctx->side2));
             return RN50_OK;
         }
         // the filter gradient is needed only at the end of the pass: after the join point
-        return conv2d_bwd_weight(&d, x_in, dconv, grad + l.w_off, A + pl.ws_conv3, pl.ws_conv_bytes, ctx->side2);
+        return conv_bwd_weight_math(bmath, &d, x_in, nullptr, nullptr, dconv, grad + l.w_off, A + pl.ws_conv3, pl.ws_conv_bytes, ctx->side2);
     };
     // The grouped launch that ends with block b, once every BN-input gradient of its layers is enqueued.
     auto launch_group_after = [&](int b) -> int {
