@@ -518,16 +518,32 @@ static BwdDataPlan plan_bwd_data(const rn50_conv_desc *d, Fp32Math math, bool gi
     return b;
 }
 
+// The network's first layer (fp32, or an fp32 image in front of bf16 activations), which has kernels of its own, and whether its output
+// is a whole number of their tiles of 8 x 16 pixels.
+static bool stem_layer(const rn50_conv_desc *d)
+{
+    return d->c == 3 && d->r == 7 && d->s == 7 && d->stride == 2 && d->pad == 3 && d->k == 64 &&
+           (d->in_dtype == RN50_DTYPE_F32 || d->in_dtype == RN50_DTYPE_BF16_ACT_F32IN) && (long)d->n * d->h * d->w * 3 < (1l << 31) &&
+           !config()->no_stem_kernel;
+}
+static bool stem_whole(const Geom &ge) { return ge.P % kStemTH == 0 && ge.Q % kStemTW == 0; }
+// Whether its forward kernel leaves the batch statistics of its tiles (not on the fp32 instruction)
+static bool stem_stats(const rn50_conv_desc *d, const Geom &ge, Fp32Math math)
+{
+    return stem_layer(d) && stem_whole(ge) && (act_of(d) || math != kFp32Unit);
+}
+
 // Forward pass that also gathers the output's batch statistics: workspace = [the forward pass's own][statistics region].
 // The region holds mean and squared deviations per (row tile, output channel), or, for a shape whose forward pass does not
 // run through the tiled kernel, the band partials of the separate statistics pass; it is sized for both.
-struct FwdStatsPlan { IgemmPlan g; int tiles_m; size_t conv_bytes, stat_bytes; };
+struct FwdStatsPlan { IgemmPlan g; int tiles_m, rows; size_t conv_bytes, stat_bytes; };
 static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool given = false)
 {
     const Geom ge = geom(d);
     FwdStatsPlan f;
     f.g = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, given);
-    f.tiles_m = ceil_div(ge.Mout, f.g.bm);
+    f.rows = stem_stats(d, ge, math) ? kStemTH * kStemTW : f.g.bm;
+    f.tiles_m = ceil_div(ge.Mout, f.rows);
     f.conv_bytes = align_up(igemm_part_bytes(f.g) + (given ? 0 : igemm_planes_bytes(f.g, d->k, ge.Kdim)), 256);
     f.stat_bytes = align_up(std::max((size_t)2 * f.tiles_m * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
     return f;
@@ -540,9 +556,8 @@ using namespace rn50;
 // Workgroups of the first layer's own filter-gradient kernel (0: the layer goes through the general kernel).
 static int stem_wgrad_grid(const rn50_conv_desc *d, const Geom &ge)
 {
-    if (!(d->c == 3 && d->r == 7 && d->s == 7 && d->stride == 2 && d->pad == 3 && d->k == 64 && d->in_dtype == RN50_DTYPE_F32 &&
-          (long)d->n * d->h * d->w * 3 < (1l << 31)) || config()->no_stem_kernel)
-        return 0;
+    // with bf16 activations whole tiles only: pixels outside the output multiply image values with zeros, which an infinite value shows
+    if (!stem_layer(d) || (act_of(d) && !stem_whole(ge))) return 0;
     const int ntiles = d->n * ceil_div(ge.P, kStemTH) * ceil_div(ge.Q, kStemTW);
     return std::min(ntiles, 2 * (int)kCUs);
 }
@@ -586,10 +601,10 @@ extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn,
         const IgemmPlan pl = (op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) ? plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, false)
                                                                                     : plan_bwd_data(d, kFp32Split).g;
         v[0] = pl.bm; v[1] = pl.bn; v[2] = pl.tail_tiles ? pl.tail_split : 1; v[3] = pl.grid;
-        if ((op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) && stem_wgrad_grid(d, ge)) {
+        if ((op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) && stem_layer(d) && (op == RN50_OP_FWD || !act_of(d) || stem_whole(ge))) {
             // the first layer's own forward kernel (same shapes as its filter-gradient kernel): tiles of 8 x 16 pixels x 64 filters
             v[0] = kStemTH * kStemTW; v[1] = 64; v[2] = 1;
-            v[3] = std::min(d->n * ceil_div(ge.P, kStemTH) * ceil_div(ge.Q, kStemTW), 3 * (int)kCUs);
+            v[3] = std::min(d->n * ceil_div(ge.P, kStemTH) * ceil_div(ge.Q, kStemTW), (act_of(d) ? 3 : 2) * (int)kCUs);
         }
     } else if (op == RN50_OP_BWD_WEIGHT) {
         const GemmPlan pl = wgrad_is_copy(d) ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, kFp32Split);
@@ -645,15 +660,28 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     }
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(!in_scale || act_of(d) != 2, RN50_EUNSUPPORTED, "%s: the fused input transform needs a bf16 or fp32 input of the variant's own type", who);
-    if (d->c == 3 && d->r == 7 && d->s == 7 && d->stride == 2 && d->pad == 3 && d->k == 64 && d->in_dtype == RN50_DTYPE_F32 && !in_scale &&
-        (long)d->n * d->h * d->w * 3 < (1l << 31) && !config()->no_stem_kernel) {
-        // the network's first layer has a kernel of its own (input tile and filter in LDS)
-        StemP sp{};
-        sp.x = x; sp.w = w; sp.y = y;
-        sp.N = d->n; sp.IH = d->h; sp.IW = d->w; sp.OH = ge.P; sp.OW = ge.Q;
-        sp.tiles_h = ceil_div(ge.P, kStemTH); sp.tiles_w = ceil_div(ge.Q, kStemTW);
-        sp.ntiles = d->n * sp.tiles_h * sp.tiles_w;
-        hipLaunchKernelGGL(stem_fwd_kernel, dim3(std::min(sp.ntiles, 3 * (int)kCUs)), dim3(kConvThreads), 0, (hipStream_t)stream, sp);
+    const bool swhole = stem_stats(d, ge, math);
+    if (stem_layer(d) && !in_scale && !(act_of(d) && stats && !swhole)) {
+        // the network's first layer has kernels of its own (input tile and filter in LDS)
+        const int tiles_h = ceil_div(ge.P, kStemTH), tiles_w = ceil_div(ge.Q, kStemTW), ntiles = d->n * tiles_h * tiles_w;
+        if (act_of(d) || math != kFp32Unit) {
+            StemMP sp{};
+            sp.x = x; sp.w = w; sp.y = y;
+            sp.N = d->n; sp.IH = d->h; sp.IW = d->w; sp.OH = ge.P; sp.OW = ge.Q;
+            sp.tiles_h = tiles_h; sp.tiles_w = tiles_w; sp.ntiles = ntiles;
+            if (stats && swhole) {
+                sp.mean = stats;
+                sp.m2 = stats + (size_t)ntiles * d->k;
+                *gathered = true;
+            }
+            launch_stem_fwd(act_of(d) ? 1 : 2, sp.mean != nullptr, sp, (hipStream_t)stream);
+        } else {
+            StemP sp{};
+            sp.x = x; sp.w = w; sp.y = y;
+            sp.N = d->n; sp.IH = d->h; sp.IW = d->w; sp.OH = ge.P; sp.OW = ge.Q;
+            sp.tiles_h = tiles_h; sp.tiles_w = tiles_w; sp.ntiles = ntiles;
+            hipLaunchKernelGGL(stem_fwd_kernel, dim3(std::min(sp.ntiles, 3 * (int)kCUs)), dim3(kConvThreads), 0, (hipStream_t)stream, sp);
+        }
         if (ap)
             if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
         return launch_status(who);
@@ -728,7 +756,7 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
     bool gathered = false;
     if (int rc = conv_fwd_impl(who, d, x, in_scale_or_null, in_shift_or_null, w, y, ws, f.conv_bytes, stream, stats, &gathered, math, planes)) return rc;
     if (gathered) {
-        bn_finalize_partials(ge.Mout, d->k, f.tiles_m, f.g.bm, stats, stats + (size_t)f.tiles_m * d->k, gamma, beta, eps, save_mean, save_invstd,
+        bn_finalize_partials(ge.Mout, d->k, f.tiles_m, f.rows, stats, stats + (size_t)f.tiles_m * d->k, gamma, beta, eps, save_mean, save_invstd,
                              scale, shift, (hipStream_t)stream);
         return launch_status(who);
     }
@@ -862,7 +890,7 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
         sp.N = d->n; sp.IH = d->h; sp.IW = d->w; sp.OH = ge.P; sp.OW = ge.Q;
         sp.tiles_h = ceil_div(ge.P, kStemTH); sp.tiles_w = ceil_div(ge.Q, kStemTW);
         sp.ntiles = d->n * sp.tiles_h * sp.tiles_w;
-        hipLaunchKernelGGL(stem_wgrad_kernel, dim3(sgrid), dim3(kConvThreads), 0, (hipStream_t)stream, sp);
+        launch_stem_wgrad(act_of(d) ? 1 : 2, sgrid, sp, (hipStream_t)stream);
         const long scount4 = (long)d->k * ge.Kdim / 4;
         hipLaunchKernelGGL(splitk_reduce_kernel, dim3(ceil_div(scount4, 64)), dim3(256), 0, (hipStream_t)stream, scount4, sgrid,
                            (long)d->k * ge.Kdim, (const float *)ws, dw);
