@@ -892,8 +892,7 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
         sp.ntiles = d->n * sp.tiles_h * sp.tiles_w;
         launch_stem_wgrad(act_of(d) ? 1 : 2, sgrid, sp, (hipStream_t)stream);
         const long scount4 = (long)d->k * ge.Kdim / 4;
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3(ceil_div(scount4, 64)), dim3(256), 0, (hipStream_t)stream, scount4, sgrid,
-                           (long)d->k * ge.Kdim, (const float *)ws, dw);
+        launch_splitk_reduce(scount4, sgrid, (long)d->k * ge.Kdim, (const float *)ws, dw, (hipStream_t)stream);
         return launch_status(who);
     }
     const size_t partial = (size_t)d->k * ge.Kdim * sizeof(float);
@@ -935,8 +934,7 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
 #undef RN50_WG
     }
     const long count4 = p.split_stride / 4;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(ceil_div(count4, 64)), dim3(256), 0, st, count4, pl.split, p.split_stride,
-                       (const float *)ws, dw);
+    launch_splitk_reduce(count4, pl.split, p.split_stride, (const float *)ws, dw, st);
     return launch_status(who);
 }
 

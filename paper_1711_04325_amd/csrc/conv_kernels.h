@@ -1772,22 +1772,35 @@ static __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(Wgrad
 // out[i] = sum_s part[s][i].  Workgroup = 64 float4 columns x 4 lanes over the splits; lane q adds splits q, q+4, ...
 // in increasing order (several loads in flight), then the four lane sums are added in lane order through LDS.
 // The order is fixed by (split count, position), so the result is bit-identical from call to call.
-static __global__ __launch_bounds__(256) void splitk_reduce_kernel(long count4, int split, long stride, const float *__restrict__ part,
-                                                            float *__restrict__ out)
+// COLS: float4 columns of a workgroup (16: one wavefront, see launch_splitk_reduce).  Bound by the latency of the loads: eight of a thread
+// are in flight (512 partials of 2352 columns, the first layer at N = 32: 14.2 us with four in workgroups of 64 columns, now 8.6).
+template <int COLS>
+__global__ __launch_bounds__(4 * COLS) void splitk_reduce_kernel(long count4, int split, long stride, const float *__restrict__ part,
+                                                                float *__restrict__ out)
 {
-    __shared__ float4 red[4][64];
-    const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const long i = (long)blockIdx.x * 64 + c;
+    __shared__ float4 red[4][COLS];
+    const int c = threadIdx.x % COLS, q = threadIdx.x / COLS;
+    const long i = (long)blockIdx.x * COLS + c;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](const float4 &v) {
+        acc.x += v.x;
+        acc.y += v.y;
+        acc.z += v.z;
+        acc.w += v.w;
+    };
     if (i < count4) {
-#pragma unroll 4
-        for (int s = q; s < split; s += 4) {
-            const float4 v = reinterpret_cast<const float4 *>(part + (long)s * stride)[i];
-            acc.x += v.x;
-            acc.y += v.y;
-            acc.z += v.z;
-            acc.w += v.w;
+        const float4 *src = reinterpret_cast<const float4 *>(part) + i;
+        const long step = stride;  // four partials on, in float4
+        int s = q;
+        src += (long)q * (stride / 4);
+        for (; s + 28 < split; s += 32, src += 8 * step) {
+            float4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[u * step];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) add(v[u]);
         }
+        for (; s < split; s += 4, src += step) add(*src);
     }
     red[q][c] = acc;
     __syncthreads();
@@ -1802,6 +1815,13 @@ static __global__ __launch_bounds__(256) void splitk_reduce_kernel(long count4, 
         }
         reinterpret_cast<float4 *>(out)[i] = r;
     }
+}
+// Few columns leave most CUs idle in workgroups of 64: with 16 of them to a workgroup 2352 (the first layer's) are 147 workgroups instead of 37.
+// From 256 workgroups of 64 on the wider ones are as fast.
+inline void launch_splitk_reduce(long count4, int split, long stride, const float *part, float *out, hipStream_t st)
+{
+    if (count4 < 64 * 256) hipLaunchKernelGGL(splitk_reduce_kernel<16>, dim3((unsigned)((count4 + 15) / 16)), dim3(64), 0, st, count4, split, stride, part, out);
+    else hipLaunchKernelGGL(splitk_reduce_kernel<64>, dim3((unsigned)((count4 + 63) / 64)), dim3(256), 0, st, count4, split, stride, part, out);
 }
 
 // Filter of the data gradient: wt[c][R-1-r][S-1-s][k] = w[k][r][s][c].  One workgroup transposes a 64 (k) x 64 (c) tile
