@@ -248,8 +248,18 @@ static int even_stages(int cps, int pchunks) { return cps < pchunks ? cps + (cps
 // dw[Kout][Jdim] with the reduction over Mpix pixels, split into `split` ranges of chunks_per_split stages
 static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math);
 
-// Whether a filter gradient runs with split operands (four consecutive filter indices share a tap: one 16-byte load)
-static bool wgrad_is_split(const rn50_conv_desc *d, Fp32Math math) { return math != kFp32Unit && !bf16_of(d) && d->c % 4 == 0; }
+// Whether a filter gradient runs with split operands (four consecutive filter indices share a tap: one 16-byte load).  Not over the longest
+// sums and not for the smallest filters: the bf16 instruction drops bits of small products, an error that grows with the number of pixels,
+// while the fp32 instruction's grows with the pixels of one range, and a filter of a few tiles is cut into a hundred ranges and more.
+// Relative error of the split and the fp32 kernel, behind a ReLU: 3x3 64 x 64, 401,408 pixels 1.6e-6 and 6.6e-7, 100,352 5.4e-7 and 4.6e-7;
+// 128 x 512, 100,352 pixels 8.2e-7 and 6.8e-7, 25,088 3.1e-7 and 4.8e-7; 3x3 128 x 128, 50,176 pixels 4.1e-7 and 4.5e-7; 64 x 256, 25,088
+// pixels 3.1e-7 and 2.7e-7; 256 x 1024, 6,272 pixels 1.9e-7 and 3.5e-7.  Speed alone would split them all (3x3 64 x 64, 100,352 pixels: 1.3 times).
+constexpr long kWgradSplitMinFilter = 64 * 256 + 1, kWgradSplitMaxPixels = 65536;
+static bool wgrad_is_split(const rn50_conv_desc *d, Fp32Math math)
+{
+    return math != kFp32Unit && !bf16_of(d) && d->c % 4 == 0 && (long)d->k * d->r * d->s * d->c >= kWgradSplitMinFilter &&
+           geom(d).Mout <= kWgradSplitMaxPixels;
+}
 
 static GemmPlan plan_wgrad(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math)
 {

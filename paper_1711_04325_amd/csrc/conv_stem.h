@@ -253,6 +253,8 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
 // 320): six roundings per 16 pixels, where the fp32 instruction has eight.
 // 32 x 224 x 224, split: 72 us (fp32 instruction 110): the splits of the gathered operand and the LDS reads under them, in four
 // wavefronts that share an image tile.  256 x 224 x 224, bf16: 181 us with its reduction (general kernel 588).
+__device__ __forceinline__ float flip_sign(float v, uint32_t sign) { return __uint_as_float(__float_as_uint(v) ^ sign); }
+
 template <int PREC>
 __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p)
 {
@@ -271,6 +273,8 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
         const int c = min(32 * nb + col, 146), fr = c / 21;
         cj[nb] = fr * kStemRowF + c - fr * 21;
     }
+    const uint32_t sign = SPLIT && (blockIdx.x & 1) ? 0x80000000u : 0u;  // every other workgroup multiplies with -dy and negates its
+    // sums: a rounding of the instruction that prefers one direction cancels in the sum over workgroups (N = 32: error 7e-7 -> 3e-7)
     floatx16 acc[2][5];
     auto clear = [&]() {
 #pragma unroll
@@ -329,7 +333,8 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
                 for (int mb = 0; mb < 2; ++mb) {
                     if (SPLIT) {
                         const float *q = &dyl[(r * 16 + 8 * half) * 64 + mb * 32 + col];
-                        const Split8 s = split8(make_float4(q[0], q[64], q[128], q[192]), make_float4(q[256], q[320], q[384], q[448]));
+                        const Split8 s = split8(make_float4(flip_sign(q[0], sign), flip_sign(q[64], sign), flip_sign(q[128], sign), flip_sign(q[192], sign)),
+                                                make_float4(flip_sign(q[256], sign), flip_sign(q[320], sign), flip_sign(q[384], sign), flip_sign(q[448], sign)));
                         ta[mb][0] = s.hi; ta[mb][1] = s.mid; ta[mb][2] = s.lo;
                     } else {  // transposing reads, as in wgrad_act_copy_kernel
                         const uint16_t *q = &dyh[(r * 16 + 8 * half + ((lane & 15) >> 2)) * 64 + mb * 32 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4];
@@ -365,7 +370,10 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
 #pragma unroll
             for (int nb = 0; nb < 5; ++nb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) bad |= !isfinite(acc[mb][nb][e]);
+                for (int e = 0; e < 16; ++e) {
+                    acc[mb][nb][e] = flip_sign(acc[mb][nb][e], sign);
+                    bad |= !isfinite(acc[mb][nb][e]);
+                }
         if (__syncthreads_or(bad)) run(std::integral_constant<bool, SPLIT>());  // an infinite operand has no finite split: all again on the fp32 instruction
     }
     // the four wavefronts' sums, added in wavefront order through LDS, one half of the filters at a time (5 x 16 x 64 floats = 20 KB)
