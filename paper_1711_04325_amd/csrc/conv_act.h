@@ -1,4 +1,4 @@
-// Implicit-GEMM kernel for activations kept as bfloat16 in memory (device code; included by conv_act.hip).
+// Implicit-GEMM kernel for activations kept as bfloat16 in memory (device code; included by conv_split.hip).
 //
 // What bounded the general kernel here (igemm_kernel with ACT = 1): every operand element passed through registers on its way
 // to LDS (the filter in fp32, rounded there, once per row tile), two barriers a stage, and never more than one stage in

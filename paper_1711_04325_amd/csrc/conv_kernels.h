@@ -1,4 +1,4 @@
-// fp32-MFMA implicit-GEMM kernels for the ResNet-50 convolutions (device code; included by conv.hip).
+// Implicit-GEMM kernels for the ResNet-50 convolutions (device code).
 //
 // Two kernels cover the three directions:
 //   igemm_kernel : out[m][j] = sum_kk A[m][kk] * B[j][kk], both operands contiguous along the
@@ -9,7 +9,8 @@
 //                  along the OUTPUT index; the reduction runs over pixels and is split over workgroups
 //                  into partial sums that a second kernel adds in a fixed order.
 // Tiles are staged through LDS and multiplied with v_mfma_f32_32x32x2_f32 (the paper computes in
-// single precision).  256 threads = 4 wavefronts in a 2x2 arrangement; each wavefront owns
+// single precision) or, split into exact bf16 terms (split8), with v_mfma_f32_32x32x16_bf16; conv_split.h and conv_act.h hold the
+// kernels whose operands are copied to LDS without registers, conv_stem.h the first layer's.  256 threads = 4 wavefronts in a 2x2 arrangement; each wavefront owns
 // (BM/2) x (BN/2) outputs as 32x32 MFMA blocks.
 #pragma once
 #include "common.h"
