@@ -68,10 +68,20 @@ typedef uint16_t bf16_t;
 
 // fp32 -> bfloat16 bits, round to nearest, ties to even (NaN stays NaN): gfx950 converts in hardware, two values per
 // instruction (v_cvt_pk_bf16_f32); in integer arithmetic the same rounding costs about five instructions per value, in
-// kernels that round every operand on its way into LDS.  Written as the instruction itself: the compiler emits it for a
-// conversion of a two-element vector too, but building that vector from elements of two register arrays made it keep the
-// arrays in scratch memory in the filter-gradient kernels.
+// kernels that round every operand on its way into LDS.  A conversion that the compiler knows: it keeps the wait states
+// that the hardware wants between it and a matrix instruction, whose operand it makes (2) or whose result it reads (up to
+// 20).  Around inline assembly it counts none.
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t bf16_pack2(float lo, float hi)
+{
+    const floatx2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// The same as the bare instruction, for values in registers that neither come from a matrix instruction nor go to one: the
+// filter-gradient kernels pair elements of two register arrays, and building a vector of those makes the compiler keep the
+// arrays in scratch memory.
+__device__ inline uint32_t bf16_pack2_bare(float lo, float hi)
 {
     uint32_t r;
     asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));

@@ -274,25 +274,12 @@ __device__ __forceinline__ void igemm_join_split(const IgemmP &p, int mw, int nw
     }
 }
 
-// Between a matrix instruction and a read of its result the hardware wants up to 19 other cycles (16 passes).  The compiler sees to that,
-// but not ahead of inline assembly, which the rounding to bf16 is (bf16_pack2): accumulators pass through here first.
-template <int N>
-__device__ __forceinline__ void mfma_settle(floatx16 (&acc)[N])
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[i]));
-}
-
 // What follows a tile's (or, part set, a piece's) reduction: the batch statistics (STATS; s_mean, s_m2: BN floats of LDS each) ...
 template <int BM, int BN, bool O16, bool STATS, int MI, int NI>
 __device__ __forceinline__ void igemm_stats(const IgemmP &p, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
 {
     constexpr int WTM = BM / 2, WTN = BN / 2;
     const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
-    if (O16) {
-#pragma unroll
-        for (int i = 0; i < MI; ++i) mfma_settle(acc[i]);
-    }
     // Column statistics of the tile (whole tiles only: the pieces of a split tile are added up by another kernel, which
     // gathers them there), before the tile is written out: the wavefronts have just left the loop's last barrier together, so
     // the barrier below costs little here, and the write-out that follows stays unsynchronised (behind the stores it would
@@ -1324,18 +1311,18 @@ __device__ __forceinline__ void wgrad_tile(const WgradP &p, const int item, floa
 #pragma unroll
             for (int i = 0; i < RA / 2; ++i) {
                 uint32_t *d = Aw + (ca * 4) * LDW + pa + PA * i;
-                d[0] = bf16_pack2(ra[2 * i].x, ra[2 * i + 1].x);
-                d[LDW] = bf16_pack2(ra[2 * i].y, ra[2 * i + 1].y);
-                d[2 * LDW] = bf16_pack2(ra[2 * i].z, ra[2 * i + 1].z);
-                d[3 * LDW] = bf16_pack2(ra[2 * i].w, ra[2 * i + 1].w);
+                d[0] = bf16_pack2_bare(ra[2 * i].x, ra[2 * i + 1].x);
+                d[LDW] = bf16_pack2_bare(ra[2 * i].y, ra[2 * i + 1].y);
+                d[2 * LDW] = bf16_pack2_bare(ra[2 * i].z, ra[2 * i + 1].z);
+                d[3 * LDW] = bf16_pack2_bare(ra[2 * i].w, ra[2 * i + 1].w);
             }
 #pragma unroll
             for (int i = 0; i < RB / 2; ++i) {
                 uint32_t *d = Bw + (cb * 4) * LDW + pb + PB * i;
-                d[0] = bf16_pack2(rb[2 * i].x, rb[2 * i + 1].x);
-                d[LDW] = bf16_pack2(rb[2 * i].y, rb[2 * i + 1].y);
-                d[2 * LDW] = bf16_pack2(rb[2 * i].z, rb[2 * i + 1].z);
-                d[3 * LDW] = bf16_pack2(rb[2 * i].w, rb[2 * i + 1].w);
+                d[0] = bf16_pack2_bare(rb[2 * i].x, rb[2 * i + 1].x);
+                d[LDW] = bf16_pack2_bare(rb[2 * i].y, rb[2 * i + 1].y);
+                d[2 * LDW] = bf16_pack2_bare(rb[2 * i].z, rb[2 * i + 1].z);
+                d[3 * LDW] = bf16_pack2_bare(rb[2 * i].w, rb[2 * i + 1].w);
             }
             return;
         }
@@ -1704,7 +1691,7 @@ static __global__ __launch_bounds__(kConvThreads, 4) void wgrad_act_kernel(Wgrad
         uint32_t *dst = (is_dy ? Aw : Bw) + (c8 * 8) * LDW + pp;
         if (!is_dy) {
 #pragma unroll
-            for (int e = 0; e < NE; ++e) dst[e * LDW] = bf16_pack2(sg.xf[0][e], sg.xf[1][e]);
+            for (int e = 0; e < NE; ++e) dst[e * LDW] = bf16_pack2_bare(sg.xf[0][e], sg.xf[1][e]);
             return;
         }
         // word e = (index e of the first pixel, index e of the second): low and high halves of the two loads' words

@@ -165,7 +165,6 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
                 }
             }
         }
-        if (!SPLIT) mfma_settle(acc);
         if (STATS) {  // of the tensor as stored; a wavefront's 32 pixels in two passes, the four wavefronts merged after Chan et al.
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
