@@ -94,6 +94,9 @@ int rn50_set_option(const char *name, const char *value_or_null);
  * Cross-correlation, zero padding, square stride, no bias:
  *   y[n,p,q,k] = sum_{r,s,c} x[n, p*stride+r-pad, q*stride+s-pad, c] * w[k,r,s,c]
  * with P = (H + 2*pad - R)/stride + 1 (floor), Q likewise.
+ * RN50_DTYPE_F32: operands of any magnitude keep their 24 bits, infinities and NaNs reach the outputs they would reach in fp32
+ * arithmetic.  Where a result is not finite, or an operand is 2^111 or a result 2^95 and more, its part of the output (32 x 32
+ * to 64 x 64 elements) is formed a second time, by a slower instruction.
  * ------------------------------------------------------------------------------------------ */
 typedef struct {
     int n, c, h, w;      /* input  N x H x W x C */

@@ -30,7 +30,7 @@ __device__ inline void split_rows(const SplitJob &job, const float *__restrict__
         a = ldg4(p);
         b = ldg4(p + 16);
     }
-    const Split8 v = split8(a, b);
+    const Split8 v = split8(a, b, split_up());
     uint4 *o = reinterpret_cast<uint4 *>(dst + ((long)kc * job.plane_rows + j) * kPlaneRow) + (c ^ ((j >> 2) & 3));
     o[0] = v.hi;
     o[4] = v.mid;
@@ -234,13 +234,14 @@ __global__ __launch_bounds__(kConvThreads, igemm_pre_occupancy(BM, BN)) void ige
         }
     };
     auto store_a = [&]() {
+        const float up = split_up();
 #pragma unroll
         for (int i = 0; i < RA; ++i) {
             if (INAFF && (in_ok & (1u << i))) {
                 ra[i][0] = bn_relu4(ra[i][0], in_sc[0], in_sh[0]);
                 ra[i][1] = bn_relu4(ra[i][1], in_sc[1], in_sh[1]);
             }
-            const Split8 v = split8(ra[i][0], ra[i][1]);
+            const Split8 v = split8(ra[i][0], ra[i][1], up);
             const int at = split_chunk(arow + 64 * i, 0, q);
             As[at] = v.hi;
             As[at + 4] = v.mid;
@@ -392,7 +393,8 @@ __global__ __launch_bounds__(kConvThreads, wgrad_split_occupancy(BM, BN)) void w
         bpix += kBK;
         aoff += p.adv_dy;
     };
-    auto put = [&](uint16_t *d, int plane, float4 v) {  // four indices of one pixel; d: the hi plane's place
+    auto put = [&](uint16_t *d, int plane, float4 v, float up) {  // four indices of one pixel; d: the hi plane's place
+        v = scaled4(v, up);
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const uint32_t w0 = t < 2 ? split_pair(v.x, v.y) : bf16_pack2(v.x, v.y), w1 = t < 2 ? split_pair(v.z, v.w) : bf16_pack2(v.z, v.w);
@@ -400,12 +402,13 @@ __global__ __launch_bounds__(kConvThreads, wgrad_split_occupancy(BM, BN)) void w
         }
     };
     auto store = [&]() {
+        const float up = split_up();
 #pragma unroll
-        for (int i = 0; i < RA; ++i) put(&As[(pa + PA * i) * LA + ca * 4], kBK * LA, ra[i]);
+        for (int i = 0; i < RA; ++i) put(&As[(pa + PA * i) * LA + ca * 4], kBK * LA, ra[i], up);
 #pragma unroll
         for (int i = 0; i < RB; ++i) {
             if (INAFF && (in_ok & (1u << i))) rb[i] = bn_relu4(rb[i], in_sc, in_sh);  // padding stays zero
-            put(&Bs[(pb + PB * i) * LB + cb * 4], kBK * LB, rb[i]);
+            put(&Bs[(pb + PB * i) * LB + cb * 4], kBK * LB, rb[i], up);
         }
     };
 
@@ -465,7 +468,7 @@ __global__ __launch_bounds__(kConvThreads, wgrad_split_occupancy(BM, BN)) void w
         for (int n = 0; n < NI; ++n)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                acc[i][n][e] += accl[i][n][e];
+                acc[i][n][e] = (acc[i][n][e] + accl[i][n][e]) * kSplitDown;
                 probe = fmaf(acc[i][n][e], 0.f, probe);
             }
     if (__any(probe != probe)) {  // see igemm_join_split

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
         for (int e = 0; e < 8; ++e) v[e] = g < 21 && j0 + e < 21 ? p.w[n * 147 + fr * 21 + j0 + e] : 0.f;
         const float4 a = make_float4(v[0], v[1], v[2], v[3]), b = make_float4(v[4], v[5], v[6], v[7]);
         if (SPLIT) {
-            const Split8 s = split8(a, b);
+            const Split8 s = split8(a, b, split_up());
             wl[0][i] = s.hi;
             wl[NPL > 1 ? 1 : 0][i] = NPL > 1 ? s.mid : s.hi;
             wl[NPL > 2 ? 2 : 0][i] = NPL > 2 ? s.lo : s.hi;
@@ -84,12 +84,13 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
     if ((int)blockIdx.x < p.ntiles) stem_load_patch(p, blockIdx.x, v);
     for (int tile = blockIdx.x; tile < p.ntiles; tile += gridDim.x) {
         const StemTile t = stem_tile(p, tile);
+        const float up = split_up();
 #pragma unroll
         for (int u = 0; u < kStemLoads; ++u) {
             const int i = tid + u * kConvThreads;
             const int pr = i / kStemCols, pc = i - pr * kStemCols;
             if (i < kStemRows * kStemCols) {
-                if (SPLIT) patch[pr * kStemRowF + pc] = v[u];
+                if (SPLIT) patch[pr * kStemRowF + pc] = v[u] * up;
                 else patch16[pr * kStemRowF + pc] = (uint16_t)bf16_rne(v[u]);
             }
         }
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
                 float4 lo = make_float4(q0.x, q0.y, q1.x, q1.y), hi = make_float4(q2.x, q2.y, q3.x, q3.y);
                 if (tail) hi.y = hi.z = hi.w = 0.f;
                 if (none) lo = hi = z4;
-                const Split8 sp = split8(lo, hi);
+                const Split8 sp = split8_scaled(lo, hi);
                 ta[0] = sp.hi; ta[1] = sp.mid; ta[2] = sp.lo;
             } else {
                 const uint32_t *q = reinterpret_cast<const uint32_t *>(patch16) + ((abase + off) >> 1);
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    acc[j][e] += accl[j][e];
+                    acc[j][e] = (acc[j][e] + accl[j][e]) * kSplitDown;
                     bad |= !isfinite(acc[j][e]);
                 }
             if (__any(bad)) {  // an infinite operand has no finite split: this block on the fp32 instruction
@@ -155,10 +156,11 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 #pragma clang loop unroll(disable)
-                for (int k = 0; k < 7 * 11; ++k) {
+                for (int k = 0; k < 7 * 11; ++k) {  // from memory: the patch holds scaled values
                     const int fr = k / 11, j = 2 * (k - fr * 11) + half;
                     const bool ok = j < 21;
-                    const float a = ok ? patch[abase + fr * kStemRowF + j] : 0.f;
+                    const int ih = 2 * (t.oh0 + tr) - 3 + fr, f = (2 * (t.ow0 + tc) - 3) * 3 + j;
+                    const float a = ok && ih >= 0 && ih < p.IH && f >= 0 && f < p.IW * 3 ? p.x[((long)t.n * p.IH + ih) * (p.IW * 3) + f] : 0.f;
                     const int wo = pix * 147 + fr * 21 + min(j, 20);
                     acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, ok ? p.w[wo] : 0.f, acc[0], 0, 0, 0);
                     acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, ok ? p.w[wo + 32 * 147] : 0.f, acc[1], 0, 0, 0);
@@ -252,8 +254,6 @@ __global__ __launch_bounds__(kConvThreads, PREC == 2 ? 2 : 3) void stem_mm_fwd_k
 // 320): six roundings per 16 pixels, where the fp32 instruction has eight.
 // 32 x 224 x 224, split: 72 us (fp32 instruction 110): the splits of the gathered operand and the LDS reads under them, in four
 // wavefronts that share an image tile.  256 x 224 x 224, bf16: 181 us with its reduction (general kernel 588).
-__device__ __forceinline__ float flip_sign(float v, uint32_t sign) { return __uint_as_float(__float_as_uint(v) ^ sign); }
-
 template <int PREC>
 __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p)
 {
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
         const int c = min(32 * nb + col, 146), fr = c / 21;
         cj[nb] = fr * kStemRowF + c - fr * 21;
     }
-    const uint32_t sign = SPLIT && (blockIdx.x & 1) ? 0x80000000u : 0u;  // every other workgroup multiplies with -dy and negates its
+    const float sign = blockIdx.x & 1 ? -1.f : 1.f;  // SPLIT: every other workgroup multiplies with -dy and negates its
     // sums: a rounding of the instruction that prefers one direction cancels in the sum over workgroups (N = 32: error 7e-7 -> 3e-7)
     floatx16 acc[2][5];
     auto clear = [&]() {
@@ -300,14 +300,19 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
                 g[u] = (oh < p.OH && ow < p.OW) ? *reinterpret_cast<const uint4 *>(src) : make_uint4(0u, 0u, 0u, 0u);
             }
             __syncthreads();  // every wavefront is done with the previous tile
+            constexpr bool SCALED = SPLIT && !UNIT;
+            const float up = split_up(), upg = sign * up;
 #pragma unroll
             for (int u = 0; u < kStemLoads; ++u) {
                 const int i = tid + u * kConvThreads;
                 const int pr = i / kStemCols, pc = i - pr * kStemCols;
-                if (i < kStemRows * kStemCols) patch[pr * kStemRowF + pc] = v[u];
+                if (i < kStemRows * kStemCols) patch[pr * kStemRowF + pc] = SCALED ? v[u] * up : v[u];
             }
 #pragma unroll
-            for (int u = 0; u < DYL; ++u) reinterpret_cast<uint4 *>(dyl)[tid + u * kConvThreads] = g[u];
+            for (int u = 0; u < DYL; ++u) {
+                if (SCALED) g[u] = __builtin_bit_cast(uint4, scaled4(__builtin_bit_cast(float4, g[u]), upg));
+                reinterpret_cast<uint4 *>(dyl)[tid + u * kConvThreads] = g[u];
+            }
             __syncthreads();
             if (UNIT) {
 #pragma clang loop unroll(disable)
@@ -332,8 +337,7 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
                 for (int mb = 0; mb < 2; ++mb) {
                     if (SPLIT) {
                         const float *q = &dyl[(r * 16 + 8 * half) * 64 + mb * 32 + col];
-                        const Split8 s = split8(make_float4(flip_sign(q[0], sign), flip_sign(q[64], sign), flip_sign(q[128], sign), flip_sign(q[192], sign)),
-                                                make_float4(flip_sign(q[256], sign), flip_sign(q[320], sign), flip_sign(q[384], sign), flip_sign(q[448], sign)));
+                        const Split8 s = split8_scaled(make_float4(q[0], q[64], q[128], q[192]), make_float4(q[256], q[320], q[384], q[448]));
                         ta[mb][0] = s.hi; ta[mb][1] = s.mid; ta[mb][2] = s.lo;
                     } else {  // transposing reads, as in wgrad_act_copy_kernel
                         const uint16_t *q = &dyh[(r * 16 + 8 * half + ((lane & 15) >> 2)) * 64 + mb * 32 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4];
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
                     const float *q = &patch[2 * r * kStemRowF + 48 * half + cj[nb]];
                     const float4 lo = make_float4(q[0], q[6], q[12], q[18]), hi = make_float4(q[24], q[30], q[36], q[42]);
                     if (SPLIT) {
-                        const Split8 s = split8(lo, hi);
+                        const Split8 s = split8_scaled(lo, hi);
                         const uint4 tb[3] = {s.hi, s.mid, s.lo};
                         constexpr int ia[6] = {0, 2, 1, 0, 1, 0}, ib[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(kConvThreads, 2) void stem_mm_wgrad_kernel(StemWP p
             for (int nb = 0; nb < 5; ++nb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    acc[mb][nb][e] = flip_sign(acc[mb][nb][e], sign);
+                    acc[mb][nb][e] *= sign * kSplitDown;
                     bad |= !isfinite(acc[mb][nb][e]);
                 }
         if (__syncthreads_or(bad)) run(std::integral_constant<bool, SPLIT>());  // an infinite operand has no finite split: all again on the fp32 instruction

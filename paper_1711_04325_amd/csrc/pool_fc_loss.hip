@@ -175,7 +175,7 @@ __device__ inline float fc_join(const floatx4 &acc, const floatx4 &accl, float (
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[wave][(4 * (lane >> 4) + e) * kFcTile + (lane & 15)] = acc[e] + accl[e];
+    for (int e = 0; e < 4; ++e) red[wave][(4 * (lane >> 4) + e) * kFcTile + (lane & 15)] = (acc[e] + accl[e]) * kSplitDown;
     __syncthreads();
     float s = 0.f;
     if (threadIdx.x < kFcTile * kFcTile) {
@@ -199,9 +199,10 @@ __device__ __forceinline__ void fc_products(int steps, LoadA load_a, LoadB load_
             a[u] = load_a(s0 + u * kFcWaves);
             b[u] = load_b(s0 + u * kFcWaves);
         }
+        const float up = split_up();
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const Split8 sa = split8(a[u].lo, a[u].hi), sb = split8(b[u].lo, b[u].hi);
+            const Split8 sa = split8(a[u].lo, a[u].hi, up), sb = split8(b[u].lo, b[u].hi, up);
             const uint4 ta[3] = {sa.hi, sa.mid, sa.lo}, tb[3] = {sb.hi, sb.mid, sb.lo};
             constexpr int ia[6] = {0, 0, 1, 1, 0, 2}, ib[6] = {0, 1, 0, 1, 2, 0};
 #pragma unroll

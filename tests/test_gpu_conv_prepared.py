@@ -83,6 +83,20 @@ def test_prepared_filter(case, act):
         assert _err(dx, dx_ref) <= BAR[act], (plan, "bwd_data", _err(dx, dx_ref))
 
 
+def test_prepared_filter_at_the_bottom_of_the_range():
+    """Operands of 1e-36, whose low bits lie below the smallest bf16 number: the input, then the filter."""
+    case = FWD_BWD[0]
+    x, w, dy, y_ref, dx_ref = _reference(case, False)
+    d = _desc(case, False)
+    s = 2.0 ** -120   # a power of two: the references scale exactly
+    for sx, sw in ((s, 1.0), (1.0, s)):
+        y, dx = torch.full_like(dy, 7.0).cuda(), torch.full_like(x, 7.0).cuda()
+        rn.conv2d_fwd(d, (x * sx).cuda(), (w * sw).cuda(), y, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD)))
+        rn.conv2d_bwd_data(d, (dy * sx).cuda(), (w * sw).cuda(), dx, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA)))
+        torch.cuda.synchronize()
+        assert _err(y, y_ref * s) <= BAR[False] and _err(dx, dx_ref * s) <= BAR[False], (sx, sw, _err(y, y_ref * s), _err(dx, dx_ref * s))
+
+
 def test_prepared_filter_and_values_without_a_finite_split():
     """An infinity, a NaN and a number that rounds to infinity in bf16 reach the outputs that fp32 arithmetic would let them reach."""
     case = FWD_BWD[0]

@@ -1,4 +1,4 @@
-"""fp32 convolutions on the bf16 matrix instruction: every operand is the exact sum of three bf16 terms.  What that could break
+"""fp32 convolutions on the bf16 matrix instruction: every operand, times 2^16, is the exact sum of three bf16 terms.  What that could break
 and a plain comparison at the usual bar would not show: precision below the bar, operands that have no finite split, magnitudes
 whose small terms leave the bf16 range.  References: float64 on the CPU from the same fp32 operands."""
 import numpy as np
@@ -50,7 +50,7 @@ def _device(case, x, w, dy):
     return y.cpu(), dx.cpu(), dw.cpu()
 
 
-# 1e-30: the smallest terms of a split are 2^-24 of it, 6e-38, still normal; sums of products stay above 1e-38 as w is of order 0.1
+# 1e-30: every term of a split is a normal number; smaller operands: test_precision_at_the_bottom_of_the_range
 @pytest.mark.parametrize("scale", [1.0, 1e-30, 1e25])
 @pytest.mark.parametrize("case", CASES)
 def test_precision_is_that_of_fp32_sums(case, scale):
@@ -66,6 +66,26 @@ def test_precision_is_that_of_fp32_sums(case, scale):
     for what, a, b in zip(("fwd", "bwd_data", "bwd_weight"), got, refs):
         err = ((a.double() - b).norm() / b.norm()).item()
         assert err <= 8e-7, "%s %s scale %g: %.2e" % (what, case, scale, err)
+
+
+@pytest.mark.parametrize("small", ["x and dy", "w"])
+@pytest.mark.parametrize("scale", [2.0 ** -112, 1e-36, 2.0 ** -125])
+@pytest.mark.parametrize("case", CASES)
+def test_precision_at_the_bottom_of_the_range(case, scale, small):
+    """Operands whose low bits lie below the smallest bf16 number (2^-112: a few of them, 1e-36: all, 2^-125: subnormal operands too).
+    The bar is that of the test above; results are rounded to 2^-149, at 2^-126 to an rms of 4e-8 of them."""
+    n, c, h, k, r, stride, pad = case
+    x, w, dy = _operands(case, 31 + sum(case), scale if small != "w" else 1.0)
+    if small == "w":
+        w = w * scale
+    y, dx, _ = _device(case, x, w, dy)
+    dw = _device(case, x, w, dy / scale)[2] if small != "w" else None   # one small factor only
+    refs = {"fwd": (y, _conv64(x, w, stride, pad)), "bwd_data": (dx, _dx64(dy, w, stride, pad, h))}
+    if dw is not None:
+        refs["bwd_weight"] = (dw, _dw64(x, dy / scale, r, stride, pad))
+    for what, (a, b) in refs.items():
+        err = ((a.double() - b).norm() / b.norm()).item()
+        assert err <= 8e-7, "%s %s %s %g: %.2e" % (what, case, small, scale, err)
 
 
 @pytest.mark.parametrize("plan", [None, "128,128,1", "64,64,3"])

@@ -48,6 +48,16 @@ def test_first_layer(n, h, act):
     assert err <= 1e-6, err
 
 
+@pytest.mark.parametrize("sx,sw", [(2.0 ** -120, 1.0), (1.0, 2.0 ** -120)])
+def test_first_layer_at_the_bottom_of_the_range(sx, sw):
+    """Images, or filters and output gradients, of 1e-36: their low bits lie below the smallest bf16 number."""
+    x, w, dy, d = _problem(3, 64, False)
+    x, w, dy = x * sx, w * sw, dy * sw
+    (y, dw), (y_ref, dw_ref) = _run(x, w, dy, d), _refs(x, w, dy, False)
+    assert ((y.double() - y_ref).norm() / y_ref.norm()).item() <= 8e-7
+    assert ((dw.double() - dw_ref).norm() / dw_ref.norm()).item() <= 1e-6
+
+
 @pytest.mark.parametrize("act", [False, True])
 @pytest.mark.parametrize("n,h", SIZES)
 def test_first_layer_statistics(n, h, act):

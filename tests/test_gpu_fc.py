@@ -16,11 +16,19 @@ def _run(n, j, k, f, w, b, dy):
     return [t.double().cpu() for t in (y, df, dw, db)]
 
 
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -120])
 @pytest.mark.parametrize("n,j,k", [(1, 4, 1), (3, 36, 17), (16, 2048, 1000), (17, 516, 15), (33, 100, 33), (40, 2052, 21), (65, 64, 1000)])
-def test_fully_connected(n, j, k):
-    """Sums of exact products rounded 32 at a time (fwd, df) or sample by sample (dw, db: up to 65 of them, 2^-25 * sqrt(65) * 2): below 8e-7."""
+def test_fully_connected(n, j, k, scale):
+    """Sums of exact products rounded 32 at a time (fwd, df) or sample by sample (dw, db: up to 65 of them, 2^-25 * sqrt(65) * 2): below 8e-7.
+    With weights and output gradients of 1e-36 as well, whose low bits lie below the smallest bf16 number."""
     g = torch.Generator().manual_seed(n + j + k)
     f, w, b, dy = torch.randn(n, j, generator=g), torch.randn(k, j, generator=g), torch.randn(k, generator=g), torch.randn(n, k, generator=g)
+    if scale != 1.0:   # df multiplies two of these: only one of them is small
+        ws, bs = w * scale, b * scale
+        got = _run(n, j, k, f, ws, bs, dy)
+        for what, a, ref in (("y", got[0], f.double() @ ws.double().t() + bs.double()), ("df", got[1], dy.double() @ ws.double())):
+            assert ((a - ref).norm() / ref.norm()).item() <= 8e-7, what
+        dy = dy * scale
     f64, w64, dy64 = f.double(), w.double(), dy.double()
     refs = (f64 @ w64.t() + b.double(), dy64 @ w64, dy64.t() @ f64, dy64.sum(0))
     for what, got, ref in zip(("y", "df", "dw", "db"), _run(n, j, k, f, w, b, dy), refs):
