@@ -53,7 +53,7 @@ constexpr double kCUs = 256.0;
 constexpr double kBytesPerClk = 8e12 / 2.4e9;  // HBM bytes per core clock, whole chip
 constexpr double kLaunchClks = 6000.0;         // one extra kernel launch, in core clocks
 
-struct GemmPlan { int bm, bn, split, chunks_per_split; };
+struct GemmPlan { int bm, bn, split, chunks_per_split; bool products = false; };  // products: of split operands (wgrad_split_kernel)
 
 // Kernel of a forward or data-gradient call: the general implicit GEMM, or one that takes the filter prepared beforehand: split into bf16
 // terms (igemm_pre_kernel, fp32 operands) or rounded to bf16 (igemm_act_kernel, bf16 activations).
@@ -248,17 +248,19 @@ static int even_stages(int cps, int pchunks) { return cps < pchunks ? cps + (cps
 // dw[Kout][Jdim] with the reduction over Mpix pixels, split into `split` ranges of chunks_per_split stages
 static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math);
 
-// Whether a filter gradient runs with split operands (four consecutive filter indices share a tap: one 16-byte load).  Not over the longest
-// sums and not for the smallest filters: the bf16 instruction drops bits of small products, an error that grows with the number of pixels,
-// while the fp32 instruction's grows with the pixels of one range, and a filter of a few tiles is cut into a hundred ranges and more.
-// Relative error of the split and the fp32 kernel, behind a ReLU: 3x3 64 x 64, 401,408 pixels 1.6e-6 and 6.6e-7, 100,352 5.4e-7 and 4.6e-7;
-// 128 x 512, 100,352 pixels 8.2e-7 and 6.8e-7, 25,088 3.1e-7 and 4.8e-7; 3x3 128 x 128, 50,176 pixels 4.1e-7 and 4.5e-7; 64 x 256, 25,088
-// pixels 3.1e-7 and 2.7e-7; 256 x 1024, 6,272 pixels 1.9e-7 and 3.5e-7.  Speed alone would split them all (3x3 64 x 64, 100,352 pixels: 1.3 times).
-constexpr long kWgradSplitMinFilter = 64 * 256 + 1, kWgradSplitMaxPixels = 65536;
-static bool wgrad_is_split(const rn50_conv_desc *d, Fp32Math math)
+// Whether a filter gradient over `pixels` is as precise with split operands in `ranges` ranges as on the fp32 instruction in `unit` ranges.
+// The fp32 instruction rounds the sum of a range every two pixels, the bf16 instruction every 16, but that one drops low bits of products
+// that are small beside others of the 16, towards zero.  Behind a BN's backward pass and a ReLU half of the products are small and of
+// one sign, and what is dropped of them does not fall with the length of a range.  Relative error E against 64 bits for such operands,
+// measured for 26 shapes of 6,272 to 65,536 pixels: E^2 / pixels is 2.1 - 3.0e-16 / unit on the fp32 instruction and 4.5e-17 / ranges +
+// 2.6e-18 + 3.2e-23 pixels with split operands.  (Over 401,408 pixels, 3x3 64 x 64: 6.6e-7 in 224 ranges, split 1.6e-6 however cut.)
+// Where all products have one sign both fall with 1 / ranges, and the split's is that of 2.3 times as many.
+// The sides of the line: 128 -> 512, 50,176 pixels 4.9e-7 in 61 ranges, split in 61 5.0e-7 (not split); 3x3 128 x 128, 50,176 pixels 4.5e-7 in
+// 56, split in 112 4.1e-7 (split); 3x3 256 x 256, 25,088 pixels 4.3e-7 in 28, split in 7 4.7e-7 and in 16 3.5e-7 (split in 13 or more).
+// Speed alone would split them all (3x3 64 x 64, 100,352 pixels: 1.3 times).
+static bool wgrad_split_as_precise(long pixels, int unit, int ranges)
 {
-    return math != kFp32Unit && !bf16_of(d) && d->c % 4 == 0 && (long)d->k * d->r * d->s * d->c >= kWgradSplitMinFilter &&
-           geom(d).Mout <= kWgradSplitMaxPixels;
+    return 4.5e-17 / ranges + 2.6e-18 + 3.2e-23 * pixels <= 2.6e-16 / unit && ranges * 2.3 >= unit;
 }
 
 static GemmPlan plan_wgrad(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math)
@@ -330,40 +332,48 @@ static GemmPlan plan_wgrad_copy(const rn50_conv_desc *d, int Kout, int Jdim, lon
 static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix, Fp32Math math)
 {
     const int pchunks = ceil_div(Mpix, kBK);
-    GemmPlan best{64, 64, 1, pchunks};
-    GemmPlan forced;
     const std::shared_ptr<const Config> cfg = config();
-    const bool split = wgrad_is_split(d, math);
-    if (forced_plan(cfg->has_wgrad_plan, cfg->wgrad_plan, &forced) ||
-        (split ? override_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &forced) : tuned_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &forced))) {
-        if (forced.split > pchunks) forced.split = pchunks;
-        forced.chunks_per_split = even_stages(ceil_div(pchunks, forced.split), pchunks);
-        forced.split = ceil_div(pchunks, forced.chunks_per_split);
-        return forced;
-    }
-    double best_cost = 1e300;
-    for (int bm = 128; bm >= 64; bm -= 64)
-        for (int bn = 128; bn >= 64; bn -= 64) {
-            if (bm == 128 && Kout <= 64) continue;
-            if (bn == 128 && Jdim <= 64) continue;
-            const double tiles = (double)ceil_div(Kout, bm) * ceil_div(Jdim, bn);
+    const bool may_split = math != kFp32Unit && !bf16_of(d) && d->c % 4 == 0;  // c % 4: four filter indices share a tap, one 16-byte load
+    GemmPlan unit{64, 64, 1, pchunks}, best = unit;
+    double unit_cost = 1e300, best_cost = 1e300;
+    auto every_cut = [&](auto try_one) {
+        for (int bm = 128; bm >= 64; bm -= 64)
+            for (int bn = 128; bn >= 64; bn -= 64) {
+                if ((bm == 128 && Kout <= 64) || (bn == 128 && Jdim <= 64)) continue;
+                for (int s = 1; s <= 2048; s = (s < 8 ? s + 1 : s + s / 4)) {
+                    if (s > 1 && pchunks / s < 2) break;
+                    const int cps = even_stages(ceil_div(pchunks, s), pchunks);
+                    try_one(bm, bn, ceil_div(pchunks, cps), cps);
+                }
+            }
+    };
+    const bool given = forced_plan(cfg->has_wgrad_plan, cfg->wgrad_plan, &unit) || override_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &unit);
+    if (given || tuned_plan(*cfg, d, RN50_OP_BWD_WEIGHT, &unit)) {
+        if (unit.split > pchunks) unit.split = pchunks;
+        unit.chunks_per_split = even_stages(ceil_div(pchunks, unit.split), pchunks);
+        unit.split = ceil_div(pchunks, unit.chunks_per_split);
+        if (given) {
+            unit.products = may_split && wgrad_split_as_precise(Mpix, unit.split, unit.split);
+            return unit;
+        }
+    } else {
+        every_cut([&](int bm, int bn, int sp, int cps) {
             const int occ = wgrad_occupancy(bm, bn);
             const double chunk_clks = 4096.0 * (bm * bn / 16384.0);
-            for (int s = 1; s <= 2048; s = (s < 8 ? s + 1 : s + s / 4)) {
-                if (s > 1 && pchunks / s < 2) break;
-                const int cps = even_stages(ceil_div(pchunks, s), pchunks);
-                const int sp = ceil_div(pchunks, cps);
-                const double wgs = tiles * sp;
-                const double per_cu = ceil(wgs / kCUs);            // workgroups the busiest CU runs
-                const double conc = std::min((double)occ, per_cu);  // of which this many at a time
-                // a stage costs its MFMA time, but no less than what the load latency allows at this concurrency
-                const double stage = std::max(chunk_clks, 3000.0 / conc);
-                const double cost = split ? wgrad_split_cost(bm, bn, Kout, Jdim, sp, cps) :
-                                    per_cu * (cps + 3.0) * stage + kLaunchClks + (sp + 1.0) * Kout * Jdim * 4.0 / kBytesPerClk;
-                if (cost < best_cost) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps}; }
-            }
-        }
-    return best;
+            const double per_cu = ceil((double)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * sp / kCUs);  // workgroups the busiest CU runs
+            const double conc = std::min((double)occ, per_cu);                                        // of which this many at a time
+            // a stage costs its MFMA time, but no less than what the load latency allows at this concurrency
+            const double stage = std::max(chunk_clks, 3000.0 / conc);
+            const double cost = per_cu * (cps + 3.0) * stage + kLaunchClks + (sp + 1.0) * Kout * Jdim * 4.0 / kBytesPerClk;
+            if (cost < unit_cost) { unit_cost = cost; unit = GemmPlan{bm, bn, sp, cps}; }
+        });
+    }
+    if (may_split)
+        every_cut([&](int bm, int bn, int sp, int cps) {
+            const double cost = wgrad_split_cost(bm, bn, Kout, Jdim, sp, cps);
+            if (cost < best_cost && wgrad_split_as_precise(Mpix, unit.split, sp)) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps, true}; }
+        });
+    return best.products ? best : unit;
 }
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -921,7 +931,7 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
     const int grid = p.tiles_k * p.tiles_j * pl.split;
     hipStream_t st = (hipStream_t)stream;
     const bool bf16 = bf16_of(d);
-    if (wgrad_is_split(d, math)) {
+    if (pl.products) {
         launch_wgrad_split(pl.bm, pl.bn, grid, p, st);
     } else if (copy) {
         launch_wgrad_act_copy(pl.bm, pl.bn, grid, p, st);

@@ -88,6 +88,35 @@ def test_precision_at_the_bottom_of_the_range(case, scale, small):
         assert err <= 8e-7, "%s %s %s %g: %.2e" % (what, case, small, scale, err)
 
 
+# (n, c, h, k, r), the errors of the fp32 instruction in the plan it has for that call, behind a BN's backward pass and for operands of
+# one sign, each plus 5 % for other draws: calls on both sides of the rule that sends them to split operands
+LONG = [((128, 256, 14, 256, 3), 4.6e-7, 8.0e-8), ((16, 128, 64, 144, 1), 4.2e-7, 6.1e-8), ((64, 512, 28, 128, 1), 3.7e-7, 6.6e-8),
+        ((64, 128, 28, 128, 3), 4.8e-7, 7.0e-8), ((64, 512, 32, 512, 3), 1.97e-6, 7.0e-7), ((2, 64, 56, 256, 1), 2.1e-7, 6.3e-8)]
+
+
+@pytest.mark.parametrize("case,bar,bar_one_sign", LONG)
+def test_filter_gradients_over_many_pixels_are_as_precise_as_on_the_fp32_instruction(case, bar, bar_one_sign):
+    n, c, h, k, r = case
+    g = torch.Generator(device="cuda").manual_seed(sum(case))
+    x = torch.randn(n, h, h, c, generator=g, device="cuda").relu_()
+    # what a BN + ReLU passes back: half of the gradient is zero before the BN, small and of one sign behind it
+    y = torch.randn(n * h * h, k, generator=g, device="cuda")
+    dz = torch.randn(n * h * h, k, generator=g, device="cuda") * 0.01 * (y > 0)
+    dy = (dz - dz.mean(0) - y * (dz * y).mean(0)).reshape(n, h, h, k)
+    del dz, y
+    ck, cc = min(k, 64), min(c, 64)   # the reference covers 64 x 64 filter channels, in float64 on the GPU
+    xp = torch.nn.functional.pad(x[..., :cc].double(), (0, 0, r // 2, r // 2, r // 2, r // 2))
+    d = rn.conv_desc(n, c, h, h, k, r, r, 1, r // 2)
+    ws = ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_WEIGHT))
+    for what, grad, limit in (("BN", dy, bar), ("one sign", dy.abs(), bar_one_sign)):
+        dw = torch.full((k, r, r, c), 7.0, device="cuda")
+        rn.conv2d_bwd_weight(d, x, grad, dw, ws)
+        flat = grad[..., :ck].double().reshape(-1, ck).t().contiguous()
+        ref = torch.stack([torch.stack([flat @ xp[:, i:i + h, j:j + h, :].reshape(-1, cc) for j in range(r)], 1) for i in range(r)], 1)
+        err = ((dw[:ck, :, :, :cc].double() - ref).norm() / ref.norm()).item()
+        assert err <= limit, "%s %s: %.2e" % (what, case, err)
+
+
 @pytest.mark.parametrize("plan", [None, "128,128,1", "64,64,3"])
 @pytest.mark.parametrize("case", CASES)
 def test_values_without_a_finite_split(case, plan):
