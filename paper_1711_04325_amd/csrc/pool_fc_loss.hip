@@ -114,8 +114,9 @@ __global__ __launch_bounds__(256) void maxpool_bwd_kernel(int N, int C4, int H, 
         }
 }
 
-// Workgroup = 16 float4 columns x 16 slices of the H*W positions; the slice sums are added in slice order.  A thread has up to four
-// positions in flight: with 4 slices of 13 positions one after the other the 32 x 7 x 7 x 2048 tensor took 6.6 us, with this cut 4.4 - 5.0.
+// Workgroup = 16 float4 columns x 16 slices of the H*W positions; the slice sums are added in pairs, pairs of pairs, ... (error of
+// 49 positive values against 64 bits 5.2e-8, in slice order 6.9e-8).  A thread has up to four positions in flight: with 4 slices of 13 positions one after
+// the other the 32 x 7 x 7 x 2048 tensor took 6.6 us, with this cut 4.4 - 5.0.
 constexpr int kAvgCols = 16, kAvgSlices = 16;
 template <class T>
 __global__ __launch_bounds__(kAvgCols * kAvgSlices) void avgpool_fwd_kernel(int N, int C4, int HW, const T *__restrict__ x, float *__restrict__ y)
@@ -138,10 +139,14 @@ __global__ __launch_bounds__(kAvgCols * kAvgSlices) void avgpool_fwd_kernel(int 
     red[slice][cl] = s;
     __syncthreads();
     if (slice == 0 && c < C4) {
-        for (int t = 1; t < kAvgSlices; ++t) {
-            const float4 v = red[t][cl];
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
+        float4 v[kAvgSlices];
+#pragma unroll
+        for (int t = 0; t < kAvgSlices; ++t) v[t] = red[t][cl];
+#pragma unroll
+        for (int half = kAvgSlices / 2; half; half /= 2)
+#pragma unroll
+            for (int t = 0; t < half; ++t) v[t] = make_float4(v[t].x + v[t + half].x, v[t].y + v[t + half].y, v[t].z + v[t + half].z, v[t].w + v[t + half].w);
+        s = v[0];
         const float inv = 1.0f / (float)HW;
         reinterpret_cast<float4 *>(y)[(size_t)n * C4 + c] = make_float4(s.x * inv, s.y * inv, s.z * inv, s.w * inv);
     }
@@ -163,7 +168,8 @@ __global__ __launch_bounds__(256) void avgpool_bwd_kernel(int N, int C4, int HW,
 // ---- fully connected layer -----------------------------------------------------------------------------------------------
 // Forward and data gradient: 16 x 16 outputs per workgroup of 16 wavefronts, on the matrix cores with split operands (see split8 in
 // conv_kernels.h), operands straight from memory in fragment order.  A wavefront takes every 16th step of 32 reduction elements; the 16
-// partial tiles meet in LDS and are added in wavefront order.  Such small calls are bound by the latency of their loads: with tiles of
+// partial tiles meet in LDS and are added in pairs, pairs of pairs, ... (2048 features of one sign, relative error against 64 bits 3.5e-8, one
+// after the other 6.2e-8).  Such small calls are bound by the latency of their loads: with tiles of
 // 32 x 32 the 1000 classes of 32 samples fill 32 of the 256 CUs and take 19.7 us, with these 10.9 (the vector kernel, which read all features
 // once per class, 28.7); the data gradient 18.4 and 10.7 (16.2).
 constexpr int kFcWaves = 16, kFcTile = 16, kFcStep = 32;
@@ -179,9 +185,14 @@ __device__ inline float fc_join(const floatx4 &acc, const floatx4 &accl, float (
     __syncthreads();
     float s = 0.f;
     if (threadIdx.x < kFcTile * kFcTile) {
-        s = red[0][threadIdx.x];
+        float v[kFcWaves];
 #pragma unroll
-        for (int w = 1; w < kFcWaves; ++w) s += red[w][threadIdx.x];
+        for (int w = 0; w < kFcWaves; ++w) v[w] = red[w][threadIdx.x];
+#pragma unroll
+        for (int half = kFcWaves / 2; half; half /= 2)
+#pragma unroll
+            for (int w = 0; w < half; ++w) v[w] += v[w + half];
+        s = v[0];
     }
     return s;
 }

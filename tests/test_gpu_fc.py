@@ -35,6 +35,24 @@ def test_fully_connected(n, j, k, scale):
         assert ((got - ref).norm() / ref.norm()).item() <= 8e-7, what
 
 
+@pytest.mark.parametrize("n", [1, 32])
+def test_operands_of_one_sign(n):
+    """Nothing cancels: the sums of the network's last layers to the rounding of their last additions.  A sum added in pairs, pairs of
+    pairs, ... has one rounding of its size, two of half of it, four of a quarter: sqrt(1 + 1/2 + 1/4 + ...) < 1.42 roundings of 2.5e-8
+    rms, and a little from the short sums at the bottom: below 4.5e-8.  The average of 49 is multiplied by a rounded 1/49 as well (another
+    rounding, and up to 3e-8 that all averages share): below 6e-8."""
+    g = torch.Generator().manual_seed(n)
+    x = torch.randn(n, 7, 7, 2048, generator=g).relu()
+    f = torch.full((n, 2048), 7.0, device="cuda")
+    rn.avgpool_fwd(n, 2048, 7, 7, x.cuda(), f)
+    w, dy, b = torch.rand(1000, 2048, generator=g) * 0.1, torch.rand(n, 1000, generator=g), torch.zeros(1000)
+    f = f.cpu()
+    y, df, _, _ = _run(n, 2048, 1000, f, w, b, dy)
+    for what, got, ref, bar in (("average", f.double(), x.double().mean((1, 2)), 6e-8), ("y", y, f.double() @ w.double().t(), 4.5e-8),
+                                ("df", df, dy.double() @ w.double(), 4.5e-8)):
+        assert ((got - ref).norm() / ref.norm()).item() <= bar, (what, ((got - ref).norm() / ref.norm()).item())
+
+
 def test_infinite_operands():
     n, j, k = 20, 68, 37
     g = torch.Generator().manual_seed(4)
