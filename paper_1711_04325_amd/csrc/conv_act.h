@@ -249,6 +249,15 @@ __global__ __launch_bounds__(kConvThreads, igemm_act_occupancy(BM, BN)) void ige
             load(nx.n0, kc, buf ^ 1);
         }
         compute();
+        if (MODE == 1 && next_chunk(it.kc_begin, it.kc_end, ph, pw) >= it.kc_end) {
+            // no stage reaches this item: it has multiplied one of zeros, of which an infinite weight makes NaNs
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        }
         buf ^= 1;
         drained = true;  // igemm_finish_act waits for the copies before it stores
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // every wavefront has read the last stage: its buffers stage the write-out

@@ -113,6 +113,37 @@ def test_prepared_filter_and_values_without_a_finite_split():
     assert torch.isfinite(y[fine]).all() and ((y.double() - ref)[fine].norm() / ref[fine].norm()).item() <= BAR[False]
 
 
+@pytest.mark.parametrize("plan", PLANS)
+@pytest.mark.parametrize("act", [False, True])
+def test_infinite_weight_of_a_tap_that_a_piece_skips(act, plan):
+    """Data gradient of a strided 3x3 by parity classes, a whole number of tiles each: an infinite weight at one corner of the filter
+    reaches one class only.  In pieces of the reduction none of whose taps reach a class nothing is multiplied, not even zeros."""
+    case = n, c, h, k, r, stride, pad = 8, 256, 32, 512, 3, 2, 1
+    x, w, dy = _operands(case, 77, torch.bfloat16 if act else torch.float32)
+    w[5, 2, 2, 3] = float("inf")
+    d = _desc(case, act)
+    if plan:
+        rn.rn50_set_option("pre_plans", "%d,%d,%d,%d,%d,%d,%d,%d,%s" % (rn.OP_BWD_DATA, n, c, h, k, r, stride, pad, plan))
+    try:
+        dx = torch.full_like(x, 7.0).cuda()
+        rn.conv2d_bwd_data(d, dy.cuda(), w.cuda(), dx, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA)))
+        torch.cuda.synchronize()
+    finally:
+        rn.rn50_set_option("pre_plans", None)
+    wq = w.to(torch.bfloat16).double() if act else w.double()
+    wq[5, 2, 2, 3] = 0.0
+    ref = torch.nn.grad.conv2d_input((n, c, h, h), wq.permute(0, 3, 1, 2), _nchw64(dy), stride, pad).permute(0, 2, 3, 1)
+    dx = dx.cpu().double()
+    for ph in (0, 1):
+        for pw in (0, 1):   # tap (2, 2) reaches the odd rows and columns; the infinity makes channel 3 there infinite
+            got, want = dx[:, ph::2, pw::2], ref[:, ph::2, pw::2]
+            if (ph, pw) == (1, 1):
+                assert not torch.isfinite(got[..., 3]).any()
+                got, want = got[..., 4:], want[..., 4:]
+            assert torch.isfinite(got).all(), (ph, pw)
+            assert ((got - want).norm() / want.norm()).item() <= BAR[act], (ph, pw)
+
+
 @pytest.mark.parametrize("act", [False, True])
 @pytest.mark.parametrize("case", FWD_BWD[:2] + [(2, 64, 14, 64, 3, 1, 1), (128, 256, 14, 1024, 1, 1, 0)])
 def test_workspace_limits(case, act):
