@@ -107,7 +107,9 @@ typedef struct {
 } rn50_conv_desc;
 
 /* Bytes of scratch the given operation needs for this shape (0 is possible).  Returns 0 for an
- * invalid descriptor as well: the operation itself reports the error. */
+ * invalid descriptor as well: the operation itself reports the error.  With that much a call's results are the same bits every
+ * time.  With less it runs kernels that need less, if that is enough for them (for fp32 operands: on the fp32 matrix
+ * instruction, whose sums round differently), and returns RN50_EWORKSPACE if not. */
 size_t rn50_conv_workspace_bytes(const rn50_conv_desc *d, int op);
 
 /* The launch plan the given operation would use for this shape, for reports: tile of bm output rows x bn output columns

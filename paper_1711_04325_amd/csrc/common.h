@@ -126,9 +126,10 @@ namespace rn50 {
 // Internal entry points used by the whole-step schedule (csrc/conv.hip).
 int conv_check(const char *who, const rn50_conv_desc *d);  // argument checks shared by the convolution entry points
 // How products of fp32 operands are formed.  kFp32Split: operands split into bf16 terms (see split8 in conv_kernels.h; every call
-// of the ABI; kFp32SplitNoPlanes: the same without room for a filter split beforehand).  kFp32Unit: the fp32 matrix instruction, with the
+// of the ABI that has the workspace its query names).  kFp32Unit: the fp32 matrix instruction, with the
 // tiles, pieces and order of sums of the measured table (the forward pass of a training context: see rn50_ctx).
-enum Fp32Math { kFp32Unit, kFp32Split, kFp32SplitNoPlanes };
+// kNoPlanes: the fp32 instruction, and with bf16 activations the kernels that take the filter as it is (a call with less workspace).
+enum Fp32Math { kFp32Unit, kFp32Split, kNoPlanes };
 size_t conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool given);  // rn50_conv_workspace_bytes; given: with `planes`
 // `planes`: the call's filter prepared beforehand by launch_filter_planes_batched (null: the call does it where its kernel wants it
 // so); conv_planes_bytes says how much room it takes (0: the kernel of this call takes none), for op RN50_OP_FWD or RN50_OP_BWD_DATA.

@@ -208,6 +208,14 @@ constexpr int kActStage = 64;          // channels of igemm_act_kernel's stage
 constexpr long kPlanesMinRows = 1024;
 constexpr double kPlanesMinFlops = 5e9, kPlanesMinFlopsF32 = 1e10;  // the latter for fp32 reductions shorter than 1024
 
+// The network's first layer (fp32, or an fp32 image in front of bf16 activations), which has kernels of its own (tiles of 8 x 16 pixels)
+static bool stem_layer(const rn50_conv_desc *d)
+{
+    return d->c == 3 && d->r == 7 && d->s == 7 && d->stride == 2 && d->pad == 3 && d->k == 64 &&
+           (d->in_dtype == RN50_DTYPE_F32 || d->in_dtype == RN50_DTYPE_BF16_ACT_F32IN) && (long)d->n * d->h * d->w * 3 < (1l << 31) &&
+           !config()->no_stem_kernel;
+}
+
 // out[M][Nout] with reduction length Kdim (in elements)
 // cin: channels of the gathered tensor (the forward pass gathers x, the data gradient dy)
 // given: the call comes with its filter prepared
@@ -217,13 +225,13 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
     const int kchunks = ceil_div(Kdim, bk);
     GemmPlan pl;
     const std::shared_ptr<const Config> cfg = config();
-    const bool split = math != kFp32Unit && !bf16_of(d);
+    const bool split = math == kFp32Split && !bf16_of(d) && !(op == RN50_OP_FWD && stem_layer(d));  // (the first layer: what its query names)
     if (forced_plan(cfg->has_igemm_plan, cfg->igemm_plan, &pl) || override_plan(*cfg, d, op, &pl))
         return make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
     // the dilated gather of a strided data gradient needs registers that a 128-row tile does not leave (igemm_pre_kernel spills)
     const bool dilated = op == RN50_OP_BWD_DATA && d->stride == 2 && !is_scatter2(d);
     const double flops = 2.0 * M * Nout * Kdim;
-    const bool geometry = M >= kPlanesMinRows && (op == RN50_OP_FWD || d->stride <= 2) && math != kFp32SplitNoPlanes &&
+    const bool geometry = M >= kPlanesMinRows && (op == RN50_OP_FWD || d->stride <= 2) && math != kNoPlanes &&
                           (given || flops >= (split && Kdim < 1024 ? kPlanesMinFlopsF32 : kPlanesMinFlops));
     if (split && geometry && cin % kBK == 0) {
         for (const PlanRow &t : cfg->pre_plans)
@@ -333,7 +341,7 @@ static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim,
 {
     const int pchunks = ceil_div(Mpix, kBK);
     const std::shared_ptr<const Config> cfg = config();
-    const bool may_split = math != kFp32Unit && !bf16_of(d) && d->c % 4 == 0;  // c % 4: four filter indices share a tap, one 16-byte load
+    const bool may_split = math == kFp32Split && !bf16_of(d) && d->c % 4 == 0;  // c % 4: four filter indices share a tap, one 16-byte load
     GemmPlan unit{64, 64, 1, pchunks}, best = unit;
     double unit_cost = 1e300, best_cost = 1e300;
     auto every_cut = [&](auto try_one) {
@@ -538,19 +546,12 @@ static BwdDataPlan plan_bwd_data(const rn50_conv_desc *d, Fp32Math math, bool gi
     return b;
 }
 
-// The network's first layer (fp32, or an fp32 image in front of bf16 activations), which has kernels of its own, and whether its output
-// is a whole number of their tiles of 8 x 16 pixels.
-static bool stem_layer(const rn50_conv_desc *d)
-{
-    return d->c == 3 && d->r == 7 && d->s == 7 && d->stride == 2 && d->pad == 3 && d->k == 64 &&
-           (d->in_dtype == RN50_DTYPE_F32 || d->in_dtype == RN50_DTYPE_BF16_ACT_F32IN) && (long)d->n * d->h * d->w * 3 < (1l << 31) &&
-           !config()->no_stem_kernel;
-}
+// Whether the first layer's output is a whole number of its kernels' tiles
 static bool stem_whole(const Geom &ge) { return ge.P % kStemTH == 0 && ge.Q % kStemTW == 0; }
 // Whether its forward kernel leaves the batch statistics of its tiles (not on the fp32 instruction)
 static bool stem_stats(const rn50_conv_desc *d, const Geom &ge, Fp32Math math)
 {
-    return stem_layer(d) && stem_whole(ge) && (act_of(d) || math != kFp32Unit);
+    return stem_layer(d) && stem_whole(ge) && (act_of(d) || math == kFp32Split);
 }
 
 // Forward pass that also gathers the output's batch statistics: workspace = [the forward pass's own][statistics region].
@@ -671,11 +672,12 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     RN50_REQUIRE(x && w && y, RN50_EINVAL, "%s: null pointer", who);
     RN50_REQUIRE(aligned16(x) && aligned16(w) && aligned16(y) && aligned16(ws), RN50_EINVAL, "%s: pointers must be 16-byte aligned", who);
     const Geom ge = geom(d);
-    if (in_scale && act_of(d)) math = kFp32SplitNoPlanes;  // the copies of igemm_act_kernel apply no transform: the general kernel
+    if (in_scale && act_of(d)) math = kNoPlanes;  // the copies of igemm_act_kernel apply no transform: the general kernel
     IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, planes != nullptr);
     size_t need = igemm_part_bytes(pl) + (planes ? 0 : igemm_planes_bytes(pl, d->k, ge.Kdim));
-    if (pl.kind != kGeneral && (ws_bytes < need || !ws)) {  // no room for the prepared filter: the general kernel splits as it loads
-        pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32SplitNoPlanes, false);
+    if (math != kNoPlanes && need && (ws_bytes < need || !ws)) {  // less room than the query names: see kNoPlanes
+        math = kNoPlanes;
+        pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, false);
         need = igemm_part_bytes(pl);
     }
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
@@ -684,7 +686,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     if (stem_layer(d) && !in_scale && !(act_of(d) && stats && !swhole)) {
         // the network's first layer has kernels of its own (input tile and filter in LDS)
         const int tiles_h = ceil_div(ge.P, kStemTH), tiles_w = ceil_div(ge.Q, kStemTW), ntiles = d->n * tiles_h * tiles_w;
-        if (act_of(d) || math != kFp32Unit) {
+        if (act_of(d) || math == kFp32Split) {
             StemMP sp{};
             sp.x = x; sp.w = w; sp.y = y;
             sp.N = d->n; sp.IH = d->h; sp.IW = d->w; sp.OH = ge.P; sp.OW = ge.Q;
@@ -716,7 +718,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
         if (gathered) *gathered = true;
     }
     set_planes(p, pl, planes, ws, (hipStream_t)stream);
-    if (!run_igemm(p, pl, y, (float *)ws, bf16_of(d), math != kFp32Unit, act_of(d), (hipStream_t)stream, ap) && ap)
+    if (!run_igemm(p, pl, y, (float *)ws, bf16_of(d), math == kFp32Split, act_of(d), (hipStream_t)stream, ap) && ap)
         if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
     return launch_status(who);
 }
@@ -764,10 +766,10 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
     RN50_REQUIRE(d->k % 4 == 0, RN50_EUNSUPPORTED, "%s: K must be a multiple of 4", who);
     RN50_REQUIRE(eps >= 0.f, RN50_EINVAL, "%s: negative eps", who);
     const Geom ge = geom(d);
-    if (in_scale_or_null && act_of(d)) math = kFp32SplitNoPlanes;  // see conv_fwd_impl
+    if (in_scale_or_null && act_of(d)) math = kNoPlanes;  // see conv_fwd_impl
     FwdStatsPlan f = plan_fwd_stats(d, math, planes != nullptr);
-    if (f.g.kind != kGeneral && ws_bytes < f.conv_bytes + f.stat_bytes) {  // no room for the prepared filter
-        math = kFp32SplitNoPlanes;
+    if (ws_bytes < f.conv_bytes + f.stat_bytes) {  // less room than the query names
+        math = kNoPlanes;
         f = plan_fwd_stats(d, math);
     }
     RN50_REQUIRE(ws && aligned16(ws) && ws_bytes >= f.conv_bytes + f.stat_bytes, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who,
@@ -795,7 +797,7 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
 {
     const Geom ge = geom(d);
     BwdDataPlan b = plan_bwd_data(d, math, planes != nullptr);
-    if (b.g.kind != kGeneral && (ws_bytes < b.part_bytes || !ws)) b = plan_bwd_data(d, kFp32SplitNoPlanes);  // no room for the prepared filter
+    if (b.part_bytes && (ws_bytes < b.part_bytes || !ws)) b = plan_bwd_data(d, math = kNoPlanes);  // less room than the query names
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
     RN50_REQUIRE(ws_bytes >= b.part_bytes && (b.part_bytes == 0 || ws), RN50_EWORKSPACE,
                  "conv2d_bwd_data: workspace too small (%zu < %zu)", ws_bytes, b.part_bytes);
@@ -815,7 +817,7 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
         }
     }
     set_planes(p, b.g, planes, ws, st);
-    run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), math != kFp32Unit, act_of(d), st);
+    run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), math == kFp32Split, act_of(d), st);
     return launch_status("conv2d_bwd_data");
 }
 
@@ -839,14 +841,14 @@ extern "C" int conv2d_bwd_data(const rn50_conv_desc *d, const float *dy, const f
                  "conv2d_bwd_data: pointers must be 16-byte aligned");
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
     BwdDataPlan b = plan_bwd_data(d, kFp32Split);
-    if (b.g.kind != kGeneral && ws_bytes < b.wt_bytes + b.part_bytes) b = plan_bwd_data(d, kFp32SplitNoPlanes);  // no room for the prepared filter
+    if (ws_bytes < b.wt_bytes + b.part_bytes) b = plan_bwd_data(d, kNoPlanes);  // less room than the query names
     RN50_REQUIRE(ws && ws_bytes >= b.wt_bytes + b.part_bytes, RN50_EWORKSPACE, "conv2d_bwd_data: workspace too small (%zu < %zu)",
                  ws_bytes, b.wt_bytes + b.part_bytes);
     hipStream_t st = (hipStream_t)stream;
     // workspace = [flipped filter][partial tiles]
     float *wt = (float *)ws;
     launch_filter_flip(d->k, d->c, d->r * d->s, w, wt, st);
-    return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, (char *)ws + b.wt_bytes, b.part_bytes, st);
+    return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, (char *)ws + b.wt_bytes, ws_bytes - b.wt_bytes, st);
 }
 
 extern "C" int conv2d_filter_flip(const rn50_conv_desc *d, const float *w, float *wt, void *stream)
@@ -868,7 +870,7 @@ extern "C" int conv2d_bwd_data_flipped(const rn50_conv_desc *d, const float *dy,
                  "conv2d_bwd_data_flipped: pointers must be 16-byte aligned");
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data_flipped: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
     size_t need = plan_bwd_data(d, kFp32Split).part_bytes;
-    if (ws_bytes < need) need = plan_bwd_data(d, kFp32SplitNoPlanes).part_bytes;  // no room for the prepared filter
+    if (ws_bytes < need) need = plan_bwd_data(d, kNoPlanes).part_bytes;
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "conv2d_bwd_data_flipped: workspace too small (%zu < %zu)",
                  ws_bytes, need);
     return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, ws, ws_bytes, (hipStream_t)stream);
@@ -901,9 +903,11 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
     RN50_REQUIRE(d->k % 4 == 0, RN50_EUNSUPPORTED, "%s: K must be a multiple of 4", who);
     const Geom ge = geom(d);
     const bool vec = d->c % 4 == 0;
-    if (const int sgrid = in_scale ? 0 : stem_wgrad_grid(d, ge)) {
+    const size_t partial = (size_t)d->k * ge.Kdim * sizeof(float);
+    const int sgrid = in_scale ? 0 : stem_wgrad_grid(d, ge);
+    if (sgrid && (!act_of(d) || ws_bytes >= sgrid * partial)) {
         // the network's first layer has a kernel of its own (input tile and dy tile in LDS, one partial per workgroup)
-        const size_t sneed = (size_t)sgrid * d->k * ge.Kdim * sizeof(float);
+        const size_t sneed = sgrid * partial;
         RN50_REQUIRE(ws && ws_bytes >= sneed, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, sneed);
         StemWP sp{};
         sp.x = x; sp.dy = dy; sp.part = (float *)ws;
@@ -915,9 +919,9 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
         launch_splitk_reduce(scount4, sgrid, (long)d->k * ge.Kdim, (const float *)ws, dw, (hipStream_t)stream);
         return launch_status(who);
     }
-    const size_t partial = (size_t)d->k * ge.Kdim * sizeof(float);
     const bool copy = wgrad_is_copy(d);
-    const GemmPlan pl = copy ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, math);
+    GemmPlan pl = copy ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, math);
+    if (ws_bytes < pl.split * partial) pl = plan_wgrad(d, d->k, ge.Kdim, ge.Mout, kNoPlanes);  // less room than the query names: another cut
     const size_t need = pl.split * partial;
     RN50_REQUIRE(ws && ws_bytes >= need, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(((long)d->k * ge.Kdim) % 4 == 0, RN50_EUNSUPPORTED, "%s: filter size must be a multiple of 4", who);
