@@ -119,7 +119,7 @@ static double tile_eff(int bm, int bn) { return bm == 128 && bn == 128 ? 1.0 : (
 
 // Persistent implicit-GEMM launch: G workgroups; the first full_items tiles whole, the last tail_tiles tiles cut
 // into tail_split pieces of tail_chunks reduction chunks each.
-struct IgemmPlan { int kind, bm, bn, grid, full_items, tail_tiles, tail_split, tail_chunks; size_t ws_floats; };
+struct IgemmPlan { int kind, bm, bn, grid, full_items, tail_tiles, tail_split, tail_chunks; size_t ws_floats; bool products = false; };  // products: of split operands (kGeneral)
 
 
 static IgemmPlan make_igemm_plan(int kind, int bm, int bn, long M, int Nout, int kchunks, int want_split, bool allow_split)
@@ -226,8 +226,12 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
     GemmPlan pl;
     const std::shared_ptr<const Config> cfg = config();
     const bool split = math == kFp32Split && !bf16_of(d) && !(op == RN50_OP_FWD && stem_layer(d));  // (the first layer: what its query names)
+    auto as_split = [&](IgemmPlan g) {
+        g.products = split;
+        return g;
+    };
     if (forced_plan(cfg->has_igemm_plan, cfg->igemm_plan, &pl) || override_plan(*cfg, d, op, &pl))
-        return make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
+        return as_split(make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split));
     // the dilated gather of a strided data gradient needs registers that a 128-row tile does not leave (igemm_pre_kernel spills)
     const bool dilated = op == RN50_OP_BWD_DATA && d->stride == 2 && !is_scatter2(d);
     const double flops = 2.0 * M * Nout * Kdim;
@@ -245,8 +249,13 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
         if (tuned_plan(*cfg, d, op, &pl)) return make_igemm_plan(kAct, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
         return model_plan(kAct, M, Nout, kchunks, bk, allow_split);
     }
-    if (!split && tuned_plan(*cfg, d, op, &pl)) return make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
-    return model_plan(kGeneral, M, Nout, kchunks, bk, allow_split);
+    const IgemmPlan general = tuned_plan(*cfg, d, op, &pl) ? make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split)
+                                                            : model_plan(kGeneral, M, Nout, kchunks, bk, allow_split);
+    // fp32 operands split as they are loaded pay where the matrix unit has work: with more than one workgroup on a CU (time on the fp32
+    // instruction / split, 110 shapes of 0.001 - 11 GFLOP: 0.94-0.98 with fewer, 1.02-1.6 with more), and where channels are gathered one by
+    // one, with 128-row tiles (1.00-1.12, with 64-row tiles 0.87-1.01).  Below that the shorter kernel wins.
+    if (split && general.grid > (int)kCUs && (cin % kBK == 0 || general.bm == 128)) return as_split(model_plan(kGeneral, M, Nout, kchunks, bk, allow_split));
+    return general;
 }
 
 // The filter-gradient kernels take two stages per trip of their loop: a range of an odd number of stages ends with a stage of
@@ -457,13 +466,14 @@ static void launch_tail_reduce_stats(const IgemmPlan &pl, const IgemmP &p, hipSt
 }
 
 // Runs out[M][Nout] (+ optional stride-2 scatter) and, when tail tiles are split, the ordered sum of their pieces.
-// act: storage of the gathered operand and of the output (see act_of); split: fp32 operands as split operands.
+// act: storage of the gathered operand and of the output (see act_of).
 // ap (a forward pass, fp32 output): what to make of the output besides; returns whether it was made (where every tile is split the
 // ordered sum makes it, a launch and a pass less), else it is the caller's to do.
-static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials, bool bf16, bool split, int act, hipStream_t st,
+static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials, bool bf16, int act, hipStream_t st,
                       const TailApply *ap = nullptr)
 {
     const bool fast = p.Cin % kBK == 0 && act != 2;  // an fp32 input beside bf16 activations goes through the scalar gather
+    const bool split = pl.products;
     p.kchunks = ceil_div(p.Kdim, fast ? igemm_bk(bf16, act, p.Cin) : kBK);
     p.tiles_m = ceil_div(p.M, pl.bm);
     p.tiles_n = ceil_div(p.Nout, pl.bn);
@@ -718,7 +728,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
         if (gathered) *gathered = true;
     }
     set_planes(p, pl, planes, ws, (hipStream_t)stream);
-    if (!run_igemm(p, pl, y, (float *)ws, bf16_of(d), math == kFp32Split, act_of(d), (hipStream_t)stream, ap) && ap)
+    if (!run_igemm(p, pl, y, (float *)ws, bf16_of(d), act_of(d), (hipStream_t)stream, ap) && ap)
         if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
     return launch_status(who);
 }
@@ -817,7 +827,7 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
         }
     }
     set_planes(p, b.g, planes, ws, st);
-    run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), math == kFp32Split, act_of(d), st);
+    run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), act_of(d), st);
     return launch_status("conv2d_bwd_data");
 }
 
