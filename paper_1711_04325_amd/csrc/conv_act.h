@@ -66,14 +66,14 @@ template <int BM, int BN, bool STATS, int MI, int NI>
 __device__ __forceinline__ void igemm_finish_act(const IgemmP &p, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2,
                                                  uint16_t *stage)
 {
+    const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
     if (part || (p.Nout & 7)) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        igemm_finish<BM, BN, true, STATS>(p, acc, part, m0, n0, tm, s_mean, s_m2);
+        igemm_finish<BM, BN, true, STATS>(p, tid, wave, acc, part, m0, n0, tm, s_mean, s_m2);
         return;
     }
-    igemm_stats<BM, BN, true, STATS>(p, acc, part, m0, n0, tm, s_mean, s_m2);
+    igemm_stats<BM, BN, true, STATS>(p, tid, wave, acc, part, m0, n0, tm, s_mean, s_m2);
     constexpr int WTM = BM / 2, WTN = BN / 2, LPR = WTN / 8, RPI = 64 / LPR;  // lanes per row of 16-byte pieces, rows per instruction
-    const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll

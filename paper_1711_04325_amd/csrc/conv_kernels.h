@@ -289,12 +289,14 @@ __device__ __forceinline__ void igemm_join_split(const IgemmP &p, int mw, int nw
     }
 }
 
-// What follows a tile's (or, part set, a piece's) reduction: the batch statistics (STATS; s_mean, s_m2: BN floats of LDS each) ...
+// What follows a tile's (or, part set, a piece's) reduction.  tid, wave: the thread and wavefront index, opaque and in a scalar
+// register in the kernels that are short of vector registers; in igemm_kernel without split operands those it has already are better
+// (14 x 7 x 7 x 208 -> 192 3x3 19.8 -> 19.4 us, N = 32 step 9.79 -> 9.73 ms).  The batch statistics (STATS; s_mean, s_m2: BN floats of LDS each) ...
 template <int BM, int BN, bool O16, bool STATS, int MI, int NI>
-__device__ __forceinline__ void igemm_stats(const IgemmP &p, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
+__device__ __forceinline__ void igemm_stats(const IgemmP &p, int tid, int wave, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
 {
     constexpr int WTM = BM / 2, WTN = BN / 2;
-    const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+    const int lane = tid & 63, wm = wave >> 1, wn = wave & 1;
     // Column statistics of the tile (whole tiles only: the pieces of a split tile are added up by another kernel, which
     // gathers them there), before the tile is written out: the wavefronts have just left the loop's last barrier together, so
     // the barrier below costs little here, and the write-out that follows stays unsynchronised (behind the stores it would
@@ -384,11 +386,11 @@ __device__ __forceinline__ void igemm_stats(const IgemmP &p, floatx16 (&acc)[MI]
 }
 // ... and the write-out.  Accumulator element e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32 of its block.
 template <int BM, int BN, bool O16, bool STATS, int MI, int NI>
-__device__ __forceinline__ void igemm_finish(const IgemmP &p, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
+__device__ __forceinline__ void igemm_finish(const IgemmP &p, int tid, int wave, floatx16 (&acc)[MI][NI], float *part, int m0, int n0, int tm, float *s_mean, float *s_m2)
 {
-    igemm_stats<BM, BN, O16, STATS>(p, acc, part, m0, n0, tm, s_mean, s_m2);
+    igemm_stats<BM, BN, O16, STATS>(p, tid, wave, acc, part, m0, n0, tm, s_mean, s_m2);
     constexpr int WTM = BM / 2, WTN = BN / 2;
-    const int tid = opaque_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+    const int lane = tid & 63, wm = wave >> 1, wn = wave & 1;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -817,7 +819,8 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
         if constexpr (SPLIT)
             igemm_join_split<BK, INAFF>(p, m0 + wm * WTM, n0 + wn * WTN, next_chunk(kc_begin), kc_end, next_chunk, [&](int kr) { return kr * BK; }, acc,
                                         accl);
-        igemm_finish<BM, BN, O16, STATS>(p, acc, part, m0, n0, tm, s_stat[0], s_stat[1]);
+        const int etid = SPLIT ? opaque_tid() : tid, ewave = SPLIT ? __builtin_amdgcn_readfirstlane(etid >> 6) : wave;
+        igemm_finish<BM, BN, O16, STATS>(p, etid, ewave, acc, part, m0, n0, tm, s_stat[0], s_stat[1]);
     }
 }
 

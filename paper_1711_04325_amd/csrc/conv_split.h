@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kConvThreads, igemm_pre_occupancy(BM, BN)) void ige
         }
         igemm_join_split<kBK, INAFF>(p, it.m0 + wm * WTM, it.n0 + wn * WTN, next_chunk(it.kc_begin, it.kc_end, ph, pw), it.kc_end,
                                      [&](int k) { return next_chunk(k, it.kc_end, ph, pw); }, [&](int k) { return k * kBK; }, acc, accl);
-        igemm_finish<BM, BN, false, STATS>(p, acc, it.part, it.m0, it.n0, it.tm, s_stat[0], s_stat[1]);
+        igemm_finish<BM, BN, false, STATS>(p, opaque_tid(), wave, acc, it.part, it.m0, it.n0, it.tm, s_stat[0], s_stat[1]);
         if (!more) break;
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         it = nx;
