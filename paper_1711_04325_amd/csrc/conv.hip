@@ -304,8 +304,8 @@ static double wgrad_split_cost(int bm, int bn, int Kout, int Jdim, int split, in
     static const double c128x128[3] = {1.383, 2.172, 1.929}, c128x64[3] = {0.793, 0.692, 1.123}, c64x128[3] = {0.822, 0.797, 1.279},
                         c64x64[3] = {0.470, 0.147, 0.729};
     const double *c = bm == 128 ? (bn == 128 ? c128x128 : c128x64) : (bn == 128 ? c64x128 : c64x64);
-    const double per_cu = ceil((double)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split / kCUs);
-    return std::max(per_cu * (cps * c[0] + c[1]), ceil(per_cu / wgrad_split_occupancy(bm, bn)) * (cps * c[2] + 0.71)) +
+    const int per_cu = ceil_div((long)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split, (int)kCUs);
+    return std::max(per_cu * (cps * c[0] + c[1]), ceil_div(per_cu, wgrad_split_occupancy(bm, bn)) * (cps * c[2] + 0.71)) +
            (split + 1.0) * Kout * Jdim * 4.0 / 7.94e6;
 }
 
@@ -317,8 +317,8 @@ static double wgrad_act_cost(int bm, int bn, int Kout, int Jdim, int split, int 
     static const double c128x128[3] = {0.568, 2.462, 1.021}, c128x64[3] = {0.371, 0.852, 0.580}, c64x128[3] = {0.424, 0.987, 0.722},
                         c64x64[3] = {0.258, 0.376, 0.420};
     const double *c = bm == 128 ? (bn == 128 ? c128x128 : c128x64) : (bn == 128 ? c64x128 : c64x64);
-    const double per_cu = ceil((double)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split / kCUs), stages = ceil(cps / 2.0);
-    return std::max(per_cu * (stages * c[0] + c[1]), ceil(per_cu / igemm_act_occupancy(bm, bn)) * stages * c[2]) +
+    const int per_cu = ceil_div((long)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split, (int)kCUs), stages = ceil_div(cps, 2);
+    return std::max(per_cu * (stages * c[0] + c[1]), ceil_div(per_cu, igemm_act_occupancy(bm, bn)) * stages * c[2]) +
            (split + 1.0) * Kout * Jdim * 4.0 / 5.03e6;
 }
 // Whether a filter gradient runs through wgrad_act_copy_kernel: bf16 activations (the fp32 image in front of them: wgrad_act_kernel)
@@ -380,18 +380,19 @@ static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim,
         every_cut([&](int bm, int bn, int sp, int cps) {
             const int occ = wgrad_occupancy(bm, bn);
             const double chunk_clks = 4096.0 * (bm * bn / 16384.0);
-            const double per_cu = ceil((double)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * sp / kCUs);  // workgroups the busiest CU runs
-            const double conc = std::min((double)occ, per_cu);                                        // of which this many at a time
+            const int per_cu = ceil_div((long)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * sp, (int)kCUs);        // workgroups the busiest CU runs
+            const double conc = std::min(occ, per_cu);                                                // of which this many at a time
             // a stage costs its MFMA time, but no less than what the load latency allows at this concurrency
             const double stage = std::max(chunk_clks, 3000.0 / conc);
             const double cost = per_cu * (cps + 3.0) * stage + kLaunchClks + (sp + 1.0) * Kout * Jdim * 4.0 / kBytesPerClk;
             if (cost < unit_cost) { unit_cost = cost; unit = GemmPlan{bm, bn, sp, cps}; }
         });
     }
-    if (may_split)
+    if (may_split && wgrad_split_as_precise(Mpix, unit.split, pchunks))  // in some number of ranges
         every_cut([&](int bm, int bn, int sp, int cps) {
+            if (!wgrad_split_as_precise(Mpix, unit.split, sp)) return;
             const double cost = wgrad_split_cost(bm, bn, Kout, Jdim, sp, cps);
-            if (cost < best_cost && wgrad_split_as_precise(Mpix, unit.split, sp)) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps, true}; }
+            if (cost < best_cost) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps, true}; }
         });
     return best.products ? best : unit;
 }
