@@ -4,7 +4,8 @@
 A "step" is one pass of the whole hot path over one synthetic batch resident in HBM: forward, loss, backward,
 fp32->fp16 gradient pack, unpack*1/1024 and the RMSprop-warm-up update, all through rn50_step of librn50.so.
 Prints ONE JSON line.  Also timed, with events on the stream the kernels run on: every convolution of the
-network in the step's own launch configuration (the `roofline` object: fp32-MFMA bound), the bandwidth-bound
+network as a call of its own (the `roofline` object: against the rate of the matrix instruction of the operands' type;
+fp32 calls may run with operands split into bf16 terms, which the step's forward pass does not), the bandwidth-bound
 kernels (`kernels`), and the fp64 CPU oracle on a bounded sample of the same workload (`cpu_baseline`).
 """
 import argparse
@@ -476,8 +477,10 @@ def main():
                            "peak_measured": ceilings, "frac_of_measured_mfma": round(ach / meas, 4),
                            # every layer at its own ceiling min(MFMA peak, flop/byte x HBM peak) would take ceiling_ms_per_step
                            "ceiling_ms_per_step": round(ceil_ms, 4), "frac_of_shape_ceilings": round(ceil_ms / (conv_ms - flip_ms), 4),
-                           "kernel": "igemm_kernel / wgrad_kernel (%s MFMA implicit-GEMM convolutions): all 158 convolution "
-                                     "launches of one step and its one filter-flip launch, each timed with events on its stream" % a.conv_dtype,
+                           "kernel": "implicit-GEMM and filter-gradient kernels (%s): all 158 convolution calls of one step's shapes and its "
+                                     "one filter-flip launch, each timed with events on its stream%s" %
+                                     (a.conv_dtype, "" if bf16 else "; peak is the fp32 instruction's, most of these calls form their products "
+                                      "from operands split into bf16 terms, the step's own forward pass stays on the fp32 instruction"),
                            "flop_per_step": conv_flop, "ms_per_step": round(conv_ms, 4),
                            "with_grouped_filter_gradients": alt,
                            "filter_gradients": {"launches_per_step": (ngroups + 1) if ngroups else 53,

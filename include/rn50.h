@@ -73,7 +73,8 @@ const char *rn50_last_error(void);
  *   "plan_overrides" "op,n,c,h,k,r,stride,pad,bm,bn,split;...": rows placed before the measured plan table; rows that
  *                         do not parse are skipped
  *   "pre_plans"      the same rows for the forward and data-gradient calls whose kernel takes a filter prepared beforehand (fp32 operands
- *                         split into bf16 terms, or bf16 activations); the three options above force the general kernel instead
+ *                         split into bf16 terms, or bf16 activations).  igemm_plan and plan_overrides send these calls to the general
+ *                         kernel instead; for filter gradients wgrad_plan and plan_overrides set the tile and the cut only
  *   "no_tuned"       0/1  ignore the measured plan table (cost model only)
  *   "no_stem_kernel" 0/1  send the first layer through the implicit GEMM instead of its own kernel
  *   "conv_bn_stats"  0/1  rn50_create: the forward convolutions gather the BN statistics of their output as they write it
