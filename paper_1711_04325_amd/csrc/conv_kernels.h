@@ -160,7 +160,8 @@ __device__ inline void store_out(const IgemmP &p, long row, int col, float v)
 // It is exact and changes no other result's bits (one vector instruction more to 5.5 per element: 3x3 256 channels, 14x14,
 // N = 128, backward 428 -> 445 us, the N = 32 step 9.82 -> 9.91 ms).
 // bf16 products are exact in fp32; hi*hi and the five small products keep accumulators of their own, which rounds the large sum once
-// per 16 products (the fp32 instruction rounds it at every product).  Measured against 64 bits (relative 2-norm, normal
+// per 16 products (the fp32 instruction rounds it at every other).  The instruction also drops low bits of products that are small beside
+// others of the 16, which shows where the small ones have one sign (see wgrad_split_as_precise in conv.hip).  Measured against 64 bits (relative 2-norm, normal
 // operands, reduction of 64 / 576 / 4608): 4.9e-8 / 1.4e-7 / 4.2e-7, with v_mfma_f32_32x32x2_f32 1.4e-7 / 4.3e-7 / 1.2e-6.
 // Rate: six v_mfma_f32_32x32x16_bf16 (32 cycles each) do the work of eight v_mfma_f32_32x32x2_f32 (64 cycles each): 192
 // against 512 cycles, 407 against 149 TFLOP/s at the clocks a loop of nothing else sustains.

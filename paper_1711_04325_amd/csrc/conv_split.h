@@ -2,7 +2,7 @@
 // conv_split.hip).  See split8 in conv_kernels.h for the products and their precision.
 //
 // What bounds the general kernel (igemm_kernel) once its products run on the bf16 matrix instruction is the vector work of
-// splitting: 5.5 instructions per operand element and stage, as many cycles as the matrix work of a 64-wide tile.  The
+// splitting: 6.5 instructions per operand element and stage, as many cycles as the matrix work of a 64-wide tile.  The
 // filter is the same for every row tile, so here it is split once per call (or once per training step), stored in the
 // order and bank swizzle of the LDS image, and copied from memory to LDS without passing through registers.
 #pragma once
