@@ -37,8 +37,18 @@ def _operands(case, seed, scale=1.0):
     return x, torch.randn(k, r, r, c, generator=g) * (2.0 / (c * r * r)) ** 0.5, dy
 
 
-def _device(case, x, w, dy):
-    """Forward output, data gradient, filter gradient."""
+def _device(case, x, w, dy, plan=None):
+    """Forward output, data gradient, filter gradient.  Calls this small run on the fp32 instruction by themselves in the first two; with a
+    given plan every call runs with split operands."""
+    if plan:
+        rn.rn50_set_option("igemm_plan", plan)
+    try:
+        return _run(case, x, w, dy)
+    finally:
+        rn.rn50_set_option("igemm_plan", None)
+
+
+def _run(case, x, w, dy):
     n, c, h, k, r, stride, pad = case
     d = rn.conv_desc(n, c, h, h, k, r, r, stride, pad)
     dx_, dw_, ddy = x.cuda(), w.cuda(), dy.cuda()
@@ -51,15 +61,16 @@ def _device(case, x, w, dy):
 
 
 # 1e-30: every term of a split is a normal number; smaller operands: test_precision_at_the_bottom_of_the_range
+@pytest.mark.parametrize("plan", [None, "64,64,2", "128,64,1"])
 @pytest.mark.parametrize("scale", [1.0, 1e-30, 1e25])
 @pytest.mark.parametrize("case", CASES)
-def test_precision_is_that_of_fp32_sums(case, scale):
+def test_precision_is_that_of_fp32_sums(case, scale, plan):
     """One rounding of a sum of up to 16 products at a time: rms error of L/16 roundings of 2^-25 of the growing sum, below
     2^-25 * sqrt(L/16) * 2; the longest reduction here (2304) gives 7e-7.  The bar is 8e-7 for all (fp32 sums product by product
     would need 2e-6)."""
     n, c, h, k, r, stride, pad = case
     x, w, dy = _operands(case, 11 + sum(case), scale)
-    got = _device(case, x, w, dy)
+    got = _device(case, x, w, dy, plan)
     if scale != 1.0:
         got = got[:2]   # the filter gradient multiplies two scaled tensors: out of range by design
     refs = (_conv64(x, w, stride, pad), _dx64(dy, w, stride, pad, h), _dw64(x, dy, r, stride, pad))
@@ -68,18 +79,19 @@ def test_precision_is_that_of_fp32_sums(case, scale):
         assert err <= 8e-7, "%s %s scale %g: %.2e" % (what, case, scale, err)
 
 
+@pytest.mark.parametrize("plan", [None, "64,64,2", "128,64,1"])
 @pytest.mark.parametrize("small", ["x and dy", "w"])
 @pytest.mark.parametrize("scale", [2.0 ** -112, 1e-36, 2.0 ** -125])
 @pytest.mark.parametrize("case", CASES)
-def test_precision_at_the_bottom_of_the_range(case, scale, small):
+def test_precision_at_the_bottom_of_the_range(case, scale, small, plan):
     """Operands whose low bits lie below the smallest bf16 number (2^-112: a few of them, 1e-36: all, 2^-125: subnormal operands too).
     The bar is that of the test above; results are rounded to 2^-149, at 2^-126 to an rms of 4e-8 of them."""
     n, c, h, k, r, stride, pad = case
     x, w, dy = _operands(case, 31 + sum(case), scale if small != "w" else 1.0)
     if small == "w":
         w = w * scale
-    y, dx, _ = _device(case, x, w, dy)
-    dw = _device(case, x, w, dy / scale)[2] if small != "w" else None   # one small factor only
+    y, dx, _ = _device(case, x, w, dy, plan)
+    dw = _device(case, x, w, dy / scale, plan)[2] if small != "w" else None   # one small factor only
     refs = {"fwd": (y, _conv64(x, w, stride, pad)), "bwd_data": (dx, _dx64(dy, w, stride, pad, h))}
     if dw is not None:
         refs["bwd_weight"] = (dw, _dw64(x, dy / scale, r, stride, pad))
@@ -115,6 +127,18 @@ def test_filter_gradients_over_many_pixels_are_as_precise_as_on_the_fp32_instruc
         ref = torch.stack([torch.stack([flat @ xp[:, i:i + h, j:j + h, :].reshape(-1, cc) for j in range(r)], 1) for i in range(r)], 1)
         err = ((dw[:ck, :, :, :cc].double() - ref).norm() / ref.norm()).item()
         assert err <= limit, "%s %s: %.2e" % (what, case, err)
+
+
+# (n, c, h, k, r, stride, pad): either side of the lines where a call changes its instruction: 256 and 272 workgroups; channels gathered one
+# by one with 64-row tiles and with 128-row tiles
+@pytest.mark.parametrize("case", [(16, 64, 16, 256, 1, 1, 0), (17, 64, 16, 256, 1, 1, 0), (40, 40, 28, 64, 1, 1, 0), (54, 40, 56, 104, 1, 1, 0)])
+def test_both_sides_of_the_choice_of_instruction(case):
+    """The bar of the fp32 instruction: 2^-25 * sqrt(L/2) * 2 for sums of up to 256 products."""
+    n, c, h, k, r, stride, pad = case
+    x, w, dy = _operands(case, 41 + sum(case))
+    y, dx, _ = _run(case, x, w, dy)
+    for what, a, b in (("fwd", y, _conv64(x, w, stride, pad)), ("bwd_data", dx, _dx64(dy, w, stride, pad, h))):
+        assert ((a.double() - b).norm() / b.norm()).item() <= 7e-7, what
 
 
 @pytest.mark.parametrize("plan", [None, "128,128,1", "64,64,3"])
