@@ -41,6 +41,7 @@ struct Config {
     bool has_igemm_plan = false, has_wgrad_plan = false;
     int igemm_plan[3] = {0, 0, 0}, wgrad_plan[3] = {0, 0, 0};  // bm, bn, split forced for every call
     std::vector<PlanRow> pre_plans;                            // plans of the calls whose filter is prepared beforehand
+    std::vector<PlanRow> operand_plans;                        // plans of calls that prepare both operands, which their call then does
     std::vector<PlanRow> overrides;                            // rows that go before the measured table
 };
 std::shared_ptr<const Config> config();  // the current snapshot (immutable; a call keeps the one it started with)
@@ -128,8 +129,9 @@ int conv_check(const char *who, const rn50_conv_desc *d);  // argument checks sh
 // How products of fp32 operands are formed.  kFp32Split: operands split into bf16 terms (see split8 in conv_kernels.h; every call
 // of the ABI that has the workspace its query names).  kFp32Unit: the fp32 matrix instruction, with the
 // tiles, pieces and order of sums of the measured table (the forward pass of a training context: see rn50_ctx).
+// kNoHalf: kFp32Split without the kernels on fp16 halves (conv_half.h).
 // kNoPlanes: the fp32 instruction, and with bf16 activations the kernels that take the filter as it is (a call with less workspace).
-enum Fp32Math { kFp32Unit, kFp32Split, kNoPlanes };
+enum Fp32Math { kFp32Unit, kFp32Split, kNoHalf, kNoPlanes };
 size_t conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool given);  // rn50_conv_workspace_bytes; given: with `planes`
 // `planes`: the call's filter prepared beforehand by launch_filter_planes_batched (null: the call does it where its kernel wants it
 // so); conv_planes_bytes says how much room it takes (0: the kernel of this call takes none), for op RN50_OP_FWD or RN50_OP_BWD_DATA.
@@ -143,7 +145,7 @@ int conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const float *x
                           const float *w, const char *planes, float *y, const float *gamma, const float *beta, float eps, float *save_mean,
                           float *save_invstd, float *scale, float *shift, void *ws, size_t ws_bytes, hipStream_t st);
 int conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws, size_t ws_bytes,
-                                hipStream_t st, const char *planes = nullptr);
+                                hipStream_t st, const char *planes = nullptr, bool flipped = true);
 int conv_bwd_weight_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift, const float *dy,
                          float *dw, void *ws, size_t ws_bytes, hipStream_t st);
 void launch_filter_flip(int K, int C, int RS, const float *w, float *wt, hipStream_t st);

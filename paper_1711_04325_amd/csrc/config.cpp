@@ -65,6 +65,7 @@ static bool apply_option(Config &c, const char *name, const char *value)
         c.has_wgrad_plan = false;
         if (!unset && !(c.has_wgrad_plan = parse_plan(value, c.wgrad_plan))) return false;
     } else if (!strcmp(name, "plan_overrides")) c.overrides = unset ? std::vector<PlanRow>() : parse_rows(value);
+    else if (!strcmp(name, "operand_plans")) c.operand_plans = unset ? std::vector<PlanRow>() : parse_rows(value);
     else if (!strcmp(name, "pre_plans")) c.pre_plans = unset ? std::vector<PlanRow>() : parse_rows(value);
     else return false;
     return true;
@@ -77,7 +78,7 @@ static std::shared_ptr<const Config> from_environment()
 {
     static const char *const names[] = {"side_stream", "fuse_bn", "relu_mask", "no_tuned", "no_stem_kernel", "conv_bn_stats", "split_products", "igemm_plan", "wgrad_plan", "wgrad_group",
                                         "wgrad_group_stages", "wgrad_group_tile", "wgrad_group_wgs_per_cu",
-                                        "plan_overrides", "pre_plans"};
+                                        "plan_overrides", "pre_plans", "operand_plans"};
     auto c = std::make_shared<Config>();
     for (const char *n : names) {
         char var[64] = "RN50_";

@@ -53,14 +53,14 @@ constexpr double kCUs = 256.0;
 constexpr double kBytesPerClk = 8e12 / 2.4e9;  // HBM bytes per core clock, whole chip
 constexpr double kLaunchClks = 6000.0;         // one extra kernel launch, in core clocks
 
-struct GemmPlan { int bm, bn, split, chunks_per_split; bool products = false; };  // products: of split operands (wgrad_split_kernel)
+struct GemmPlan { int bm, bn, split, chunks_per_split; bool products = false, terms = false; };  // products: of split operands (wgrad_split_kernel)
 
 // Kernel of a forward or data-gradient call: the general implicit GEMM, or one that takes the filter prepared beforehand: split into bf16
 // terms (igemm_pre_kernel, fp32 operands) or rounded to bf16 (igemm_act_kernel, bf16 activations).
-enum IgemmKind { kGeneral = 0, kPre = 1, kAct = 2 };
+enum IgemmKind { kGeneral = 0, kPre = 1, kAct = 2, kHalf = 3 };
 static int igemm_kind_occupancy(int kind, int bm, int bn)
 {
-    return kind == kPre ? igemm_pre_occupancy(bm, bn) : kind == kAct ? igemm_act_occupancy(bm, bn) : igemm_occupancy(bm, bn);
+    return kind == kHalf ? half_occupancy(bm, bn) : kind == kPre ? igemm_pre_occupancy(bm, bn) : kind == kAct ? igemm_act_occupancy(bm, bn) : igemm_occupancy(bm, bn);
 }
 
 // Plans measured on the MI355X for the ResNet-50 layer shapes: {op, n, c, h, k, r, stride, pad, bm, bn, split}.
@@ -119,7 +119,7 @@ static double tile_eff(int bm, int bn) { return bm == 128 && bn == 128 ? 1.0 : (
 
 // Persistent implicit-GEMM launch: G workgroups; the first full_items tiles whole, the last tail_tiles tiles cut
 // into tail_split pieces of tail_chunks reduction chunks each.
-struct IgemmPlan { int kind, bm, bn, grid, full_items, tail_tiles, tail_split, tail_chunks; size_t ws_floats; bool products = false; };  // products: of split operands (kGeneral)
+struct IgemmPlan { int kind, bm, bn, grid, full_items, tail_tiles, tail_split, tail_chunks; size_t ws_floats; bool products = false; size_t prep_bytes = 0; double cost = 0; };  // products: of split operands (kGeneral); prep_bytes: workspace of the operands prepared by the call; cost: model_plan's
 
 
 static IgemmPlan make_igemm_plan(int kind, int bm, int bn, long M, int Nout, int kchunks, int want_split, bool allow_split)
@@ -175,23 +175,41 @@ static double igemm_pre_cost(const IgemmPlan &pl, int kchunks)
     return t;
 }
 
+// The same for igemm_half_kernel, without its preparation.  Fitted to 1,554 measured launches (86 calls, every tile, seven splits): the plan it picks
+// takes 1.5 % longer than the best one measured on average, 5 % at the 90th percentile.
+static double igemm_half_cost(const IgemmPlan &pl, int kchunks)
+{
+    static const double c128x64[3] = {0.364, 1.301, 0.642}, c64x128[3] = {0.331, 0.771, 0.566}, c64x64[3] = {0.195, 0.464, 0.473};
+    const double *c = pl.bm == 128 ? c128x64 : pl.bn == 128 ? c64x128 : c64x64;
+    const int occ = half_occupancy(pl.bm, pl.bn);
+    double t = pl.full_items / (kCUs * occ) * occ * (kchunks * c[0] + c[1]);
+    if (pl.tail_tiles) {
+        const double per_cu = ceil((double)pl.tail_tiles * pl.tail_split / kCUs);
+        t += std::max(per_cu * (pl.tail_chunks * c[0] + c[1]), pl.tail_chunks * c[2]);
+        if (pl.tail_split > 1) t += 3.1 + (pl.tail_split + 1.0) * pl.tail_tiles * pl.bm * pl.bn * 4.0 / 5.8e6;
+    }
+    return t;
+}
+
 static IgemmPlan model_plan(int kind, long M, int Nout, int kchunks, int bk, bool allow_split, int max_bm = 128)
 {
     IgemmPlan best{};
-    double best_cost = 1e300;
+    double best_cost = 1e300;  // left in best.cost
     static const int splits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32};
     for (int bm = max_bm; bm >= 64; bm -= 64)
         for (int bn = 128; bn >= 64; bn -= 64) {
             if (bn == 128 && Nout <= 64) continue;
             if (bm == 128 && M <= 64) continue;
+            if (kind == kHalf && bm == 128 && bn == 128) continue;  // no registers for its three sets of sums
             for (int sp : splits) {
                 if (sp > 1 && (!allow_split || kchunks / sp < 2)) break;
                 const IgemmPlan pl = make_igemm_plan(kind, bm, bn, M, Nout, kchunks, sp, allow_split);
-                const double cost = kind == kPre ? igemm_pre_cost(pl, kchunks)
+                const double cost = kind == kHalf ? igemm_half_cost(pl, kchunks) : kind == kPre ? igemm_pre_cost(pl, kchunks)
                                                  : igemm_cost(pl, kchunks, 4096.0 * (bk / (double)kBK) * (bm * bn / 16384.0) / tile_eff(bm, bn));
                 if (cost < best_cost) { best_cost = cost; best = pl; }
             }
         }
+    best.cost = best_cost;
     return best;
 }
 
@@ -217,16 +235,45 @@ static bool stem_layer(const rn50_conv_desc *d)
            !config()->no_stem_kernel;
 }
 
+// What a call with less workspace than its query names runs: without the halves; below that without any preparation.
+static Fp32Math less_room(Fp32Math math) { return math == kFp32Split ? kNoHalf : kNoPlanes; }
+// Operands as fp16 halves (conv_half.h) where that is as precise as the call's other plan, whose sums of `piece` elements are the longest.
+// Relative error against 64 bits, halves / bf16 terms (90 calls): forward behind a ReLU 1.07 - 1.26e-7 whatever the length, with terms 0.9 - 1.2e-7 in
+// pieces of 300 - 650 elements, 1.24e-7 in 768, 1.43e-7 in 1024, 1.5e-7 in 1152; data gradients 1.11 - 1.31e-7, with terms 1.47e-7 in 512,
+// 1.55e-7 in 576, 2.1e-7 in 1152 (1.2 - 1.5e-7 in 384).
+static bool half_as_precise(bool fwd, double piece) { return piece >= (fwd ? 700 : 480); }
+// Preparing both operands (two launches and one more gap than the other plan has; the gathered tensor is read twice and written once), in microseconds;
+// what the other plan takes beyond igemm_pre_cost: the filter's preparation, in a data gradient its flip.
+static double half_prep_cost(double elems) { return 14.75 + 2.28e-6 * elems; }
+static double pre_extra_cost(bool fwd, bool given) { return given ? 3.0 : fwd ? 6.0 : 10.0; }
+constexpr double kHalfMinFlops = 1e9;
+// Workspace of their preparation: [exponents][shares of the largest magnitude][marks][filter][gathered tensor]
+constexpr int kHalfShares = 512;
+struct HalfRoom { size_t part, marks, planes, halves, total; int nmarks; };
+static HalfRoom half_room(long pixels, int cin, int rows, int kdim)
+{
+    HalfRoom r;
+    size_t cur = 256;
+    auto take = [&](size_t b) { const size_t o = cur; cur += (b + 255) / 256 * 256; return o; };
+    r.part = take(2 * kHalfShares * 4);
+    r.nmarks = 1 + (int)((pixels >> kHalfMarkShift) + 1) + rows;
+    r.marks = take((size_t)r.nmarks * 4);
+    r.planes = take((size_t)(kdim / kBK) * plane_rows_of(rows) * 128);
+    r.halves = take((size_t)pixels * cin * 4 + 256);  // zeros ahead of it
+    r.total = cur;
+    return r;
+}
+
 // out[M][Nout] with reduction length Kdim (in elements)
 // cin: channels of the gathered tensor (the forward pass gathers x, the data gradient dy)
 // given: the call comes with its filter prepared
-static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, bool allow_split, int cin, Fp32Math math, bool given)
+static IgemmPlan plan_igemm_kind(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, bool allow_split, int cin, Fp32Math math, bool given)
 {
     const int bk = igemm_bk(bf16_of(d), act_of(d), cin);
     const int kchunks = ceil_div(Kdim, bk);
     GemmPlan pl;
     const std::shared_ptr<const Config> cfg = config();
-    const bool split = math == kFp32Split && !bf16_of(d) && !(op == RN50_OP_FWD && stem_layer(d));  // (the first layer: what its query names)
+    const bool split = (math == kFp32Split || math == kNoHalf) && !bf16_of(d) && !(op == RN50_OP_FWD && stem_layer(d));  // (the first layer: what its query names)
     auto as_split = [&](IgemmPlan g) {
         g.products = split;
         return g;
@@ -238,6 +285,25 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
     const double flops = 2.0 * M * Nout * Kdim;
     const bool geometry = M >= kPlanesMinRows && (op == RN50_OP_FWD || d->stride <= 2) && math != kNoPlanes &&
                           (given || flops >= (split && Kdim < 1024 ? kPlanesMinFlopsF32 : kPlanesMinFlops));
+    const bool fwd = op == RN50_OP_FWD;
+    const long gathered = fwd ? (long)d->n * d->h * d->w : geom(d).Mout;
+    if (split && math != kNoHalf && !dilated && cin % kBK == 0 && Nout % 4 == 0 && (fwd || d->stride <= 2) && d->r * d->s <= 32 && gathered * cin < (1l << 30) - 64) {
+        IgemmPlan half{};
+        for (const PlanRow &t : cfg->operand_plans)
+            if (plan_matches(t, d, op) && (t.bm == 64 || t.bn == 64)) half = make_igemm_plan(kHalf, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
+        if (!half.grid && M >= kPlanesMinRows && flops >= kHalfMinFlops) {
+            const IgemmPlan other = plan_igemm_kind(d, op, M, Nout, Kdim, allow_split, cin, kNoHalf, given);
+            if (!half_as_precise(fwd, other.full_items || other.tail_split < 2 ? Kdim : (double)Kdim / other.tail_split)) return other;
+            half = model_plan(kHalf, M, Nout, kchunks, bk, allow_split);
+            // right in 79 of 83 calls measured both ways, the others within 9 %
+            if (half.cost + half_prep_cost((double)gathered * cin) >= 0.95 * (model_plan(kPre, M, Nout, kchunks, bk, allow_split).cost + pre_extra_cost(fwd, given)))
+                return other;
+        }
+        if (half.grid) {
+            half.prep_bytes = half_room(gathered, cin, Nout, Kdim).total;
+            return half;
+        }
+    }
     if (split && geometry && cin % kBK == 0) {
         for (const PlanRow &t : cfg->pre_plans)
             if (plan_matches(t, d, op) && (!dilated || t.bm == 64))
@@ -257,6 +323,13 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
     // one, with 128-row tiles (1.00-1.12, with 64-row tiles 0.87-1.01).  Below that the shorter kernel wins.
     if (split && general.grid > (int)kCUs && (cin % kBK == 0 || general.bm == 128)) return as_split(model_plan(kGeneral, M, Nout, kchunks, bk, allow_split));
     return general;
+}
+
+static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, bool allow_split, int cin, Fp32Math math, bool given)
+{
+    IgemmPlan pl = plan_igemm_kind(d, op, M, Nout, Kdim, allow_split, cin, math, given);
+    if (pl.kind == kPre || pl.kind == kAct) pl.prep_bytes = given ? 0 : filter_planes_bytes(Nout, Kdim, pl.kind == kAct);
+    return pl;
 }
 
 // The filter-gradient kernels take two stages per trip of their loop: a range of an odd number of stages ends with a stage of
@@ -322,6 +395,33 @@ static double wgrad_act_cost(int bm, int bn, int Kout, int Jdim, int split, int 
     return std::max(per_cu * (stages * c[0] + c[1]), ceil_div(per_cu, igemm_act_occupancy(bm, bn)) * stages * c[2]) +
            (split + 1.0) * Kout * Jdim * 4.0 / 5.03e6;
 }
+static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
+// The same for wgrad_terms_kernel, with its preparation (`elems` numbers in both tensors) and launches.  Fitted to 1,620 measured launches (45 calls, every tile,
+// twelve cuts): the plan it picks takes 1.6 % longer than the best one on average.
+static double wgrad_terms_cost(int bm, int bn, int Kout, int Jdim, int split, int cps, double elems)
+{
+    static const double c128x64[3] = {0.558, 0.684, 0.748}, c64x128[3] = {0.512, 0.882, 0.822}, c64x64[3] = {0.292, 0.371, 0.506};
+    const double *c = bm == 128 ? c128x64 : bn == 128 ? c64x128 : c64x64;
+    const int per_cu = ceil_div((long)ceil_div(Kout, bm) * ceil_div(Jdim, bn) * split, (int)kCUs);
+    return std::max(per_cu * (cps * c[0] + c[1]), ceil_div(per_cu, wgrad_terms_occupancy(bm, bn)) * (cps * c[2] + 0.7)) +
+           (split + 1.0) * Kout * Jdim * 4.0 / 5.26e6 + 11.2 + 2.05e-6 * elems;
+}
+constexpr double kWgradSplitLaunches = 14.7;  // what wgrad_split_cost leaves out of a call
+constexpr double kWgradTermsMinFlops = 1.5e9;
+static bool wgrad_may_split_terms(const rn50_conv_desc *d, long Mpix, Fp32Math math)
+{
+    return math == kFp32Split && !bf16_of(d) && d->c % 32 == 0 && d->k % 32 == 0 && (long)d->n * d->h * d->w * d->c < (1l << 29) && Mpix * d->k < (1l << 29);
+}
+struct WgradTermsRoom { size_t part, terms[2], total; };
+static WgradTermsRoom wgrad_terms_room(const rn50_conv_desc *d, const GemmPlan &pl, int Kout, int Jdim, long Mpix)
+{
+    WgradTermsRoom r;
+    r.terms[0] = align_up((size_t)pl.split * Kout * Jdim * sizeof(float), 256);
+    r.terms[1] = r.terms[0] + align_up((size_t)d->n * d->h * d->w * d->c * 6 + kTermsZeros, 256);
+    r.total = r.terms[1] + align_up((size_t)Mpix * d->k * 6 + kTermsZeros, 256);
+    return r;
+}
+
 // Whether a filter gradient runs through wgrad_act_copy_kernel: bf16 activations (the fp32 image in front of them: wgrad_act_kernel)
 static bool wgrad_is_copy(const rn50_conv_desc *d) { return act_of(d) == 1 && d->k % 8 == 0 && d->c % 8 == 0; }
 static GemmPlan plan_wgrad_copy(const rn50_conv_desc *d, int Kout, int Jdim, long Mpix)
@@ -354,7 +454,7 @@ static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim,
 {
     const int pchunks = ceil_div(Mpix, kBK);
     const std::shared_ptr<const Config> cfg = config();
-    const bool may_split = math == kFp32Split && !bf16_of(d) && d->c % 4 == 0;  // c % 4: four filter indices share a tap, one 16-byte load
+    const bool may_split = (math == kFp32Split || math == kNoHalf) && !bf16_of(d) && d->c % 4 == 0;  // c % 4: four filter indices share a tap, one 16-byte load
     GemmPlan unit{64, 64, 1, pchunks}, best = unit;
     double unit_cost = 1e300, best_cost = 1e300;
     auto every_cut = [&](auto try_one) {
@@ -395,10 +495,26 @@ static GemmPlan plan_wgrad_any_tile(const rn50_conv_desc *d, int Kout, int Jdim,
             const double cost = wgrad_split_cost(bm, bn, Kout, Jdim, sp, cps);
             if (cost < best_cost) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps, true}; }
         });
+    if (wgrad_may_split_terms(d, Mpix, math)) {
+        for (const PlanRow &t : cfg->operand_plans)
+            if (plan_matches(t, d, RN50_OP_BWD_WEIGHT) && (t.bm == 64 || t.bn == 64)) {
+                const int cps = ceil_div(pchunks, std::min(t.split, pchunks));
+                return GemmPlan{t.bm, t.bn, ceil_div(pchunks, cps), cps, true, true};
+            }
+    }
+    if (best.products && 2.0 * Mpix * Kout * Jdim >= kWgradTermsMinFlops && wgrad_may_split_terms(d, Mpix, math)) {
+        // both tensors split beforehand: the same products in no fewer ranges, so no larger an error
+        const double elems = (double)d->n * d->h * d->w * d->c + (double)Mpix * d->k;
+        const int ranges = best.split;
+        best_cost = 0.97 * (best_cost + kWgradSplitLaunches);
+        every_cut([&](int bm, int bn, int sp, int cps) {
+            if ((bm == 128 && bn == 128) || sp < ranges) return;
+            const double cost = wgrad_terms_cost(bm, bn, Kout, Jdim, sp, cps, elems);
+            if (cost < best_cost) { best_cost = cost; best = GemmPlan{bm, bn, sp, cps, true, true}; }
+        });
+    }
     return best.products ? best : unit;
 }
-
-static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 template <int MODE, int PREC, bool INAFF, int ACT, bool STATS, int BK>
 static void launch_igemm_bk(const IgemmPlan &pl, const IgemmP &p, hipStream_t st)
@@ -492,7 +608,10 @@ static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
     p.div_ow = make_fastdiv(p.OW);
     p.div_cin = make_fastdiv(p.Cin);
     p.div_s = make_fastdiv(p.S);
-    if (pl.kind == kPre) {
+    p.div_rs = make_fastdiv(p.R * p.S);
+    if (pl.kind == kHalf) {
+        launch_igemm_half(pl.bm, pl.bn, pl.grid, p, st);
+    } else if (pl.kind == kPre) {
         launch_igemm_pre(pl.bm, pl.bn, pl.grid, p, st);
     } else if (pl.kind == kAct) {
         launch_igemm_act(pl.bm, pl.bn, pl.grid, p, st);
@@ -534,17 +653,56 @@ static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
 
 // Workspace of a forward or data-gradient call: [partial tiles][prepared filter], the latter only where the plan's kernel takes one.
 static size_t igemm_part_bytes(const IgemmPlan &pl) { return pl.kind == kGeneral ? pl.ws_floats * sizeof(float) : align_up(pl.ws_floats * sizeof(float), 256); }
-static size_t igemm_planes_bytes(const IgemmPlan &pl, int rows, int kdim) { return pl.kind == kGeneral ? 0 : filter_planes_bytes(rows, kdim, pl.kind == kAct); }
-// The prepared filter of a call: the one it was given, or prepared now in the workspace behind the partial tiles.
-static void set_planes(IgemmP &p, const IgemmPlan &pl, const char *planes, void *ws, hipStream_t st)
+// The prepared filter of a call: the one it was given, or prepared now in the workspace behind the partial tiles.  Operands as fp16 halves:
+// both prepared there, the gathered tensor of `pixels` pixels among them.
+static void set_planes(IgemmP &p, const IgemmPlan &pl, const char *planes, long pixels, void *ws, hipStream_t st)
 {
     if (pl.kind == kGeneral) return;
     p.plane_rows = plane_rows_of(p.Nout);
     p.planes = planes;
     if (planes) return;
     char *own = (char *)ws + igemm_part_bytes(pl);
-    launch_filter_planes(p.Nout, p.Kdim, pl.kind == kAct, p.b, own, st);
     p.planes = own;
+    if (pl.kind != kHalf) {
+        launch_filter_planes(p.Nout, p.Kdim, pl.kind == kAct, p.b, own, st);
+        return;
+    }
+    const HalfRoom room = half_room(pixels, p.Cin, p.Nout, p.Kdim);
+    unsigned *marks = (unsigned *)(own + room.marks);
+    p.planes = own + room.planes;
+    p.halves = own + room.halves;
+    p.half_up = (const int *)own;
+    p.half_any = marks;
+    p.half_marks[0] = marks + 1;
+    p.half_marks[1] = marks + room.nmarks - p.Nout;
+    HalfPrep q{};
+    q.in_scale = p.in_scale;
+    q.in_shift = p.in_shift;
+    q.div_c4 = make_fastdiv(p.Cin / 4);
+    q.marks = marks;
+    q.nmarks = room.nmarks;
+    for (int i = 0; i < 2; ++i) {
+        HalfOperand &o = q.op[i];
+        o.src = i ? p.b : p.a;
+        o.dst = own + (i ? room.planes : room.halves);
+        const long count = i ? (long)p.Nout * p.Kdim : pixels * p.Cin;
+        o.n4 = (unsigned)(count / 4);
+        o.n8 = (unsigned)(i ? (long)p.plane_rows * p.Kdim / 8 : count / 8);
+        o.kind = i ? (p.flip_taps ? kHalfFlipped : kHalfFilter) : kHalfPixels;
+        o.blocks = std::min(kHalfShares, ceil_div(o.n4, 1024));
+        o.split_blocks = std::min(2048, ceil_div(o.n8, 512));
+        o.rows = p.Nout;
+        o.plane_rows = p.plane_rows;
+        o.kdim = p.Kdim;
+        o.taps = p.R * p.S;
+        o.div8 = make_fastdiv(!i ? p.Cin / 8 : p.flip_taps ? p.plane_rows : p.Kdim / 8);
+        o.div_k = make_fastdiv(p.Cin);
+        o.part = (unsigned *)(own + room.part) + i * kHalfShares;
+        o.marks = const_cast<unsigned *>(p.half_marks[i]);
+        o.any = marks;
+        o.up = (int *)own + i;
+    }
+    launch_half_prep(q, st);
 }
 
 struct BwdDataPlan { IgemmPlan g; bool scatter; size_t wt_bytes, part_bytes; };  // part_bytes: partial tiles and prepared filter
@@ -557,7 +715,7 @@ static BwdDataPlan plan_bwd_data(const rn50_conv_desc *d, Fp32Math math, bool gi
     const int Kd = d->r * d->s * d->k;
     b.g = plan_igemm(d, RN50_OP_BWD_DATA, M, d->c, Kd, true, d->k, math, given);
     b.wt_bytes = align_up((size_t)d->k * d->r * d->s * d->c * sizeof(float), 256);
-    b.part_bytes = igemm_part_bytes(b.g) + (given ? 0 : igemm_planes_bytes(b.g, d->c, Kd));
+    b.part_bytes = igemm_part_bytes(b.g) + b.g.prep_bytes;
     return b;
 }
 
@@ -566,7 +724,7 @@ static bool stem_whole(const Geom &ge) { return ge.P % kStemTH == 0 && ge.Q % kS
 // Whether its forward kernel leaves the batch statistics of its tiles (not on the fp32 instruction)
 static bool stem_stats(const rn50_conv_desc *d, const Geom &ge, Fp32Math math)
 {
-    return stem_layer(d) && stem_whole(ge) && (act_of(d) || math == kFp32Split);
+    return stem_layer(d) && stem_whole(ge) && (act_of(d) || math == kFp32Split || math == kNoHalf);
 }
 
 // Forward pass that also gathers the output's batch statistics: workspace = [the forward pass's own][statistics region].
@@ -580,7 +738,7 @@ static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool 
     f.g = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, given);
     f.rows = stem_stats(d, ge, math) ? kStemTH * kStemTW : f.g.bm;
     f.tiles_m = ceil_div(ge.Mout, f.rows);
-    f.conv_bytes = align_up(igemm_part_bytes(f.g) + (given ? 0 : igemm_planes_bytes(f.g, d->k, ge.Kdim)), 256);
+    f.conv_bytes = align_up(igemm_part_bytes(f.g) + f.g.prep_bytes, 256);
     f.stat_bytes = align_up(std::max((size_t)2 * f.tiles_m * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
     return f;
 }
@@ -604,12 +762,17 @@ extern "C" size_t rn50_conv_workspace_bytes(const rn50_conv_desc *d, int op)
     return conv_workspace(d, op, kFp32Split, false);
 }
 
+static size_t wgrad_bytes(const rn50_conv_desc *d, const GemmPlan &pl, const Geom &ge)
+{
+    return pl.terms ? wgrad_terms_room(d, pl, d->k, ge.Kdim, ge.Mout).total : (size_t)pl.split * d->k * ge.Kdim * sizeof(float);
+}
+
 size_t rn50::conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool given)
 {
     const Geom ge = geom(d);
     if (op == RN50_OP_FWD) {
         const IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, given);
-        return igemm_part_bytes(pl) + (given ? 0 : igemm_planes_bytes(pl, d->k, ge.Kdim));
+        return igemm_part_bytes(pl) + pl.prep_bytes;
     }
     if (op == RN50_OP_BWD_DATA) {
         const BwdDataPlan b = plan_bwd_data(d, math, given);
@@ -618,7 +781,7 @@ size_t rn50::conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool
     if (op == RN50_OP_BWD_WEIGHT) {
         if (stem_wgrad_grid(d, ge)) return (size_t)stem_wgrad_grid(d, ge) * d->k * ge.Kdim * sizeof(float);
         const GemmPlan pl = wgrad_is_copy(d) ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, math);
-        return (size_t)pl.split * d->k * ge.Kdim * sizeof(float);
+        return wgrad_bytes(d, pl, ge);
     }
     if (op == RN50_OP_BWD_DATA_FLIPPED) return plan_bwd_data(d, math, given).part_bytes;
     if (op == RN50_OP_FWD_BNSTATS) {
@@ -689,11 +852,11 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     const Geom ge = geom(d);
     if (in_scale && act_of(d)) math = kNoPlanes;  // the copies of igemm_act_kernel apply no transform: the general kernel
     IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, planes != nullptr);
-    size_t need = igemm_part_bytes(pl) + (planes ? 0 : igemm_planes_bytes(pl, d->k, ge.Kdim));
-    if (math != kNoPlanes && need && (ws_bytes < need || !ws)) {  // less room than the query names: see kNoPlanes
-        math = kNoPlanes;
+    size_t need = igemm_part_bytes(pl) + pl.prep_bytes;
+    while (math != kNoPlanes && need && (ws_bytes < need || !ws)) {  // less room than the query names: see less_room
+        math = less_room(math);
         pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, false);
-        need = igemm_part_bytes(pl);
+        need = igemm_part_bytes(pl) + pl.prep_bytes;
     }
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(!in_scale || act_of(d) != 2, RN50_EUNSUPPORTED, "%s: the fused input transform needs a bf16 or fp32 input of the variant's own type", who);
@@ -701,7 +864,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     if (stem_layer(d) && !in_scale && !(act_of(d) && stats && !swhole)) {
         // the network's first layer has kernels of its own (input tile and filter in LDS)
         const int tiles_h = ceil_div(ge.P, kStemTH), tiles_w = ceil_div(ge.Q, kStemTW), ntiles = d->n * tiles_h * tiles_w;
-        if (act_of(d) || math == kFp32Split) {
+        if (act_of(d) || math == kFp32Split || math == kNoHalf) {
             StemMP sp{};
             sp.x = x; sp.w = w; sp.y = y;
             sp.N = d->n; sp.IH = d->h; sp.IW = d->w; sp.OH = ge.P; sp.OW = ge.Q;
@@ -732,7 +895,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
         p.stat_m2 = stats + (size_t)ceil_div(ge.Mout, pl.bm) * d->k;
         if (gathered) *gathered = true;
     }
-    set_planes(p, pl, planes, ws, (hipStream_t)stream);
+    set_planes(p, pl, planes, ge.Min, ws, (hipStream_t)stream);
     if (!run_igemm(p, pl, y, (float *)ws, bf16_of(d), act_of(d), (hipStream_t)stream, ap) && ap)
         if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
     return launch_status(who);
@@ -762,8 +925,9 @@ int rn50::conv_fwd_apply_math(Fp32Math math, const rn50_conv_desc *d, const floa
 size_t rn50::conv_planes_bytes(const rn50_conv_desc *d, int op)
 {
     const Geom ge = geom(d);
-    if (op == RN50_OP_FWD) return igemm_planes_bytes(plan_igemm(d, op, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, true), d->k, ge.Kdim);
-    return igemm_planes_bytes(plan_bwd_data(d, kFp32Split, true).g, d->c, d->r * d->s * d->k);
+    const bool fwd = op == RN50_OP_FWD;
+    const IgemmPlan pl = fwd ? plan_igemm(d, op, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, true) : plan_bwd_data(d, kFp32Split, true).g;
+    return pl.kind == kPre || pl.kind == kAct ? filter_planes_bytes(fwd ? d->k : d->c, fwd ? ge.Kdim : d->r * d->s * d->k, pl.kind == kAct) : 0;
 }
 
 int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const float *x, const float *in_scale_or_null, const float *in_shift_or_null,
@@ -783,8 +947,8 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
     const Geom ge = geom(d);
     if (in_scale_or_null && act_of(d)) math = kNoPlanes;  // see conv_fwd_impl
     FwdStatsPlan f = plan_fwd_stats(d, math, planes != nullptr);
-    if (ws_bytes < f.conv_bytes + f.stat_bytes) {  // less room than the query names
-        math = kNoPlanes;
+    while (math != kNoPlanes && ws_bytes < f.conv_bytes + f.stat_bytes) {  // less room than the query names
+        math = less_room(math);
         f = plan_fwd_stats(d, math);
     }
     RN50_REQUIRE(ws && aligned16(ws) && ws_bytes >= f.conv_bytes + f.stat_bytes, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who,
@@ -808,11 +972,11 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
 // Data gradient with the filter already flipped and transposed (wt[c][R-1-r][S-1-s][k] = w[k][r][s][c]): a
 // forward-type gather over dy.  ws = the implicit GEMM's partial tiles only.
 int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws,
-                                      size_t ws_bytes, hipStream_t st, const char *planes)
+                                      size_t ws_bytes, hipStream_t st, const char *planes, bool flipped)
 {
     const Geom ge = geom(d);
     BwdDataPlan b = plan_bwd_data(d, math, planes != nullptr);
-    if (b.part_bytes && (ws_bytes < b.part_bytes || !ws)) b = plan_bwd_data(d, math = kNoPlanes);  // less room than the query names
+    while (math != kNoPlanes && b.part_bytes && (ws_bytes < b.part_bytes || !ws)) b = plan_bwd_data(d, math = less_room(math));  // less room than the query names
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
     RN50_REQUIRE(ws_bytes >= b.part_bytes && (b.part_bytes == 0 || ws), RN50_EWORKSPACE,
                  "conv2d_bwd_data: workspace too small (%zu < %zu)", ws_bytes, b.part_bytes);
@@ -831,7 +995,8 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
             p.div_class = make_fastdiv(p.M / 4);
         }
     }
-    set_planes(p, b.g, planes, ws, st);
+    p.flip_taps = b.g.kind == kHalf && !flipped ? d->r * d->s : 0;
+    set_planes(p, b.g, planes, ge.Mout, ws, st);
     run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), act_of(d), st);
     return launch_status("conv2d_bwd_data");
 }
@@ -855,15 +1020,19 @@ extern "C" int conv2d_bwd_data(const rn50_conv_desc *d, const float *dy, const f
     RN50_REQUIRE(aligned16(dy) && aligned16(w) && aligned16(dx) && aligned16(ws), RN50_EINVAL,
                  "conv2d_bwd_data: pointers must be 16-byte aligned");
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
-    BwdDataPlan b = plan_bwd_data(d, kFp32Split);
-    if (ws_bytes < b.wt_bytes + b.part_bytes) b = plan_bwd_data(d, kNoPlanes);  // less room than the query names
+    Fp32Math math = kFp32Split;
+    BwdDataPlan b = plan_bwd_data(d, math);
+    while (math != kNoPlanes && ws_bytes < b.wt_bytes + b.part_bytes) b = plan_bwd_data(d, math = less_room(math));  // less room than the query names
     RN50_REQUIRE(ws && ws_bytes >= b.wt_bytes + b.part_bytes, RN50_EWORKSPACE, "conv2d_bwd_data: workspace too small (%zu < %zu)",
                  ws_bytes, b.wt_bytes + b.part_bytes);
     hipStream_t st = (hipStream_t)stream;
     // workspace = [flipped filter][partial tiles]
+    char *rest = (char *)ws + b.wt_bytes;
+    if (b.g.kind == kHalf)  // its preparation flips as well
+        return conv_bwd_data_pretransposed(math, d, dy, w, dx, rest, ws_bytes - b.wt_bytes, st, nullptr, false);
     float *wt = (float *)ws;
     launch_filter_flip(d->k, d->c, d->r * d->s, w, wt, st);
-    return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, (char *)ws + b.wt_bytes, ws_bytes - b.wt_bytes, st);
+    return conv_bwd_data_pretransposed(math, d, dy, wt, dx, rest, ws_bytes - b.wt_bytes, st);
 }
 
 extern "C" int conv2d_filter_flip(const rn50_conv_desc *d, const float *w, float *wt, void *stream)
@@ -884,11 +1053,12 @@ extern "C" int conv2d_bwd_data_flipped(const rn50_conv_desc *d, const float *dy,
     RN50_REQUIRE(aligned16(dy) && aligned16(wt) && aligned16(dx) && aligned16(ws), RN50_EINVAL,
                  "conv2d_bwd_data_flipped: pointers must be 16-byte aligned");
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data_flipped: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
-    size_t need = plan_bwd_data(d, kFp32Split).part_bytes;
-    if (ws_bytes < need) need = plan_bwd_data(d, kNoPlanes).part_bytes;
+    Fp32Math math = kFp32Split;
+    size_t need = plan_bwd_data(d, math).part_bytes;
+    while (math != kNoPlanes && ws_bytes < need) need = plan_bwd_data(d, math = less_room(math)).part_bytes;
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "conv2d_bwd_data_flipped: workspace too small (%zu < %zu)",
                  ws_bytes, need);
-    return conv_bwd_data_pretransposed(kFp32Split, d, dy, wt, dx, ws, ws_bytes, (hipStream_t)stream);
+    return conv_bwd_data_pretransposed(math, d, dy, wt, dx, ws, ws_bytes, (hipStream_t)stream);
 }
 
 static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
@@ -936,8 +1106,9 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
     }
     const bool copy = wgrad_is_copy(d);
     GemmPlan pl = copy ? plan_wgrad_copy(d, d->k, ge.Kdim, ge.Mout) : plan_wgrad(d, d->k, ge.Kdim, ge.Mout, math);
+    if (pl.terms && ws_bytes < wgrad_bytes(d, pl, ge)) pl = plan_wgrad(d, d->k, ge.Kdim, ge.Mout, kNoHalf);
     if (ws_bytes < pl.split * partial) pl = plan_wgrad(d, d->k, ge.Kdim, ge.Mout, kNoPlanes);  // less room than the query names: another cut
-    const size_t need = pl.split * partial;
+    const size_t need = wgrad_bytes(d, pl, ge);
     RN50_REQUIRE(ws && ws_bytes >= need, RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(((long)d->k * ge.Kdim) % 4 == 0, RN50_EUNSUPPORTED, "%s: filter size must be a multiple of 4", who);
     const int act = act_of(d);
@@ -950,7 +1121,23 @@ static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const 
     const int grid = p.tiles_k * p.tiles_j * pl.split;
     hipStream_t st = (hipStream_t)stream;
     const bool bf16 = bf16_of(d);
-    if (pl.products) {
+    if (pl.terms) {
+        const WgradTermsRoom room = wgrad_terms_room(d, pl, d->k, ge.Kdim, ge.Mout);
+        TermsPrep q{};
+        q.in_scale = in_scale;
+        q.in_shift = in_shift;
+        for (int i = 0; i < 2; ++i) {
+            q.src[i] = i ? dy : x;
+            q.dst[i] = (char *)ws + room.terms[i];
+            q.n8[i] = (unsigned)((i ? ge.Mout * d->k : ge.Min * d->c) / 8);
+            q.blocks[i] = std::min(2048, ceil_div(q.n8[i], 512));
+            q.div8[i] = make_fastdiv((i ? d->k : d->c) / 8);
+        }
+        p.x_terms = q.dst[0];
+        p.dy_terms = q.dst[1];
+        launch_terms_prep(q, st);
+        launch_wgrad_terms(pl.bm, pl.bn, grid, p, st);
+    } else if (pl.products) {
         launch_wgrad_split(pl.bm, pl.bn, grid, p, st);
     } else if (copy) {
         launch_wgrad_act_copy(pl.bm, pl.bn, grid, p, st);

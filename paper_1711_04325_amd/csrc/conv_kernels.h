@@ -95,6 +95,14 @@ struct IgemmP {
     // Kernels of conv_split.h and conv_act.h: the filter operand prepared beforehand, [stage][plane_rows][bytes of a row's stage].
     const char *planes;
     int plane_rows;
+    // Kernels of conv_half.h: the gathered operand as fp16 halves, the exponents of both operands' scales, whether there are marks
+    // of small operands, and those (of groups of pixels, of filter rows); flip_taps: p.b is the filter as it is, [k][taps][row].
+    const char *halves;
+    const int *half_up;
+    const unsigned *half_any;
+    const unsigned *half_marks[2];
+    int flip_taps;
+    FastDiv div_rs;  // by R*S: their stages go through the taps of one group of 32 channels before the next group
 };
 
 __device__ inline float4 ldg4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -1144,6 +1152,7 @@ struct WgradP {
     unsigned carry_row;       // one output row on, OW output columns back
     unsigned carry_img;       // one image on, OH output rows back
     unsigned adv_dy;          // kBK*Kout
+    const char *x_terms, *dy_terms;  // wgrad_terms_kernel: both tensors split beforehand
 };
 
 // Fills everything of a filter gradient's launch parameters but the pointers: tiles of bm x bn, the pixels cut into `split`
@@ -1514,6 +1523,42 @@ inline int plane_rows_of(int rows) { return (rows + 127) / 128 * 128; }  // filt
 constexpr int igemm_pre_occupancy(int bm, int bn) { return (bm == 64 && bn == 64) ? 4 : (bm == 128 && bn == 64) ? 3 : 2; }
 constexpr int igemm_act_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) ? 2 : (bm == 64 && bn == 64) ? 4 : 3; }
 constexpr int wgrad_split_occupancy(int bm, int bn) { return (bm == 128 && bn == 128) ? 2 : (bm == 64 && bn == 64) ? 4 : 3; }
+constexpr int half_occupancy(int bm, int bn) { return (bm == 64 && bn == 64) ? 4 : 3; }  // workgroups on a CU
+// Operands of a call as fp16 halves (conv_half.h): what one preparation of two tensors is given.
+enum { kHalfPixels = 0, kHalfFilter = 1, kHalfFlipped = 2 };
+constexpr int kHalfMarkShift = 5;   // pixels to a mark: 32
+struct HalfOperand {
+    const float *src;
+    char *dst;
+    unsigned n4, n8;                // float4 to look at, groups of eight to write
+    int kind, blocks, split_blocks; // workgroups of the two launches
+    int rows, plane_rows, kdim, taps;
+    FastDiv div8, div_k;
+    unsigned *part, *marks, *any;
+    int *up;
+};
+struct HalfPrep {
+    HalfOperand op[2];
+    const float *in_scale, *in_shift;  // the first operand is max(0, x * in_scale[c] + in_shift[c])
+    FastDiv div_c4;
+    unsigned *marks;                   // cleared by the first launch
+    int nmarks;
+};
+void launch_half_prep(const HalfPrep &p, hipStream_t st);
+// Both tensors of a filter gradient split into bf16 terms beforehand (conv_terms.h)
+constexpr int kTermsZeros = 256;  // zero bytes ahead of each
+constexpr int wgrad_terms_occupancy(int bm, int bn) { return (bm == 64 && bn == 64) ? 3 : 2; }
+struct TermsPrep {
+    const float *src[2];
+    char *dst[2];
+    unsigned n8[2];                    // groups of eight elements
+    int blocks[2];
+    FastDiv div8[2];                   // by C / 8
+    const float *in_scale, *in_shift;  // the first tensor is max(0, x * in_scale[c] + in_shift[c])
+};
+void launch_terms_prep(const TermsPrep &p, hipStream_t st);
+void launch_wgrad_terms(int bm, int bn, int grid, const WgradP &p, hipStream_t st);
+void launch_igemm_half(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
 size_t filter_planes_bytes(int rows, int kdim, bool act);
 void launch_filter_planes(int rows, int kdim, bool act, const float *w, char *planes, hipStream_t st);
 void launch_igemm_pre(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
