@@ -74,6 +74,8 @@ const char *rn50_last_error(void);
  *                         do not parse are skipped
  *   "operand_plans"  the same rows for calls with fp32 operands both of which are prepared beforehand (forward pass and data gradient as
  *                    fp16 halves, filter gradient split into bf16 terms; tiles of 128 x 64, 64 x 128, 64 x 64), whatever the call would choose
+ *   "small_plans"    the same rows for forward and data-gradient calls with fp32 operands that do not fill the chip (tiles of 16 or 32 rows and
+ *                    columns; the split says nothing), whatever the call would choose
  *   "pre_plans"      the same rows for the forward and data-gradient calls whose kernel takes a filter prepared beforehand (fp32 operands
  *                         split into bf16 terms, or bf16 activations).  igemm_plan and plan_overrides send these calls to the general
  *                         kernel instead; for filter gradients wgrad_plan and plan_overrides set the tile and the cut only

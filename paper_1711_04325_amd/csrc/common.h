@@ -42,6 +42,7 @@ struct Config {
     int igemm_plan[3] = {0, 0, 0}, wgrad_plan[3] = {0, 0, 0};  // bm, bn, split forced for every call
     std::vector<PlanRow> pre_plans;                            // plans of the calls whose filter is prepared beforehand
     std::vector<PlanRow> operand_plans;                        // plans of calls that prepare both operands, which their call then does
+    std::vector<PlanRow> small_plans;                          // plans of igemm_small_kernel (tiles of 16 or 32; the cut says nothing)
     std::vector<PlanRow> overrides;                            // rows that go before the measured table
 };
 std::shared_ptr<const Config> config();  // the current snapshot (immutable; a call keeps the one it started with)

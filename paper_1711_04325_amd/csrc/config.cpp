@@ -21,13 +21,14 @@ static bool parse_plan(const char *v, int out[3])
 }
 
 // "op,n,c,h,k,r,stride,pad,bm,bn,split;...": rows that do not parse or do not name a tile shape are skipped
-static std::vector<PlanRow> parse_rows(const char *v)
+static std::vector<PlanRow> parse_rows(const char *v, bool small = false)
 {
     std::vector<PlanRow> rows;
     for (const char *q = v; q && *q;) {
         PlanRow t;
         if (sscanf(q, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &t.op, &t.n, &t.c, &t.h, &t.k, &t.r, &t.stride, &t.pad, &t.bm, &t.bn, &t.split) == 11 &&
-            (t.bm == 64 || t.bm == 128) && (t.bn == 64 || t.bn == 128) && t.split >= 1)
+            (small ? (t.bm == 16 || t.bm == 32) && (t.bn == 16 || t.bn == 32)
+                   : (t.bm == 64 || t.bm == 128) && (t.bn == 64 || t.bn == 128) && t.split >= 1))
             rows.push_back(t);
         q = strchr(q, ';');
         if (q) ++q;
@@ -65,6 +66,7 @@ static bool apply_option(Config &c, const char *name, const char *value)
         c.has_wgrad_plan = false;
         if (!unset && !(c.has_wgrad_plan = parse_plan(value, c.wgrad_plan))) return false;
     } else if (!strcmp(name, "plan_overrides")) c.overrides = unset ? std::vector<PlanRow>() : parse_rows(value);
+    else if (!strcmp(name, "small_plans")) c.small_plans = unset ? std::vector<PlanRow>() : parse_rows(value, true);
     else if (!strcmp(name, "operand_plans")) c.operand_plans = unset ? std::vector<PlanRow>() : parse_rows(value);
     else if (!strcmp(name, "pre_plans")) c.pre_plans = unset ? std::vector<PlanRow>() : parse_rows(value);
     else return false;
@@ -78,7 +80,7 @@ static std::shared_ptr<const Config> from_environment()
 {
     static const char *const names[] = {"side_stream", "fuse_bn", "relu_mask", "no_tuned", "no_stem_kernel", "conv_bn_stats", "split_products", "igemm_plan", "wgrad_plan", "wgrad_group",
                                         "wgrad_group_stages", "wgrad_group_tile", "wgrad_group_wgs_per_cu",
-                                        "plan_overrides", "pre_plans", "operand_plans"};
+                                        "plan_overrides", "pre_plans", "operand_plans", "small_plans"};
     auto c = std::make_shared<Config>();
     for (const char *n : names) {
         char var[64] = "RN50_";

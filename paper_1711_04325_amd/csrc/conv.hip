@@ -57,7 +57,7 @@ struct GemmPlan { int bm, bn, split, chunks_per_split; bool products = false, te
 
 // Kernel of a forward or data-gradient call: the general implicit GEMM, or one that takes the filter prepared beforehand: split into bf16
 // terms (igemm_pre_kernel, fp32 operands) or rounded to bf16 (igemm_act_kernel, bf16 activations).
-enum IgemmKind { kGeneral = 0, kPre = 1, kAct = 2, kHalf = 3 };
+enum IgemmKind { kGeneral = 0, kPre = 1, kAct = 2, kHalf = 3, kSmall = 4 };
 static int igemm_kind_occupancy(int kind, int bm, int bn)
 {
     return kind == kHalf ? half_occupancy(bm, bn) : kind == kPre ? igemm_pre_occupancy(bm, bn) : kind == kAct ? igemm_act_occupancy(bm, bn) : igemm_occupancy(bm, bn);
@@ -330,6 +330,45 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
     IgemmPlan pl = plan_igemm_kind(d, op, M, Nout, Kdim, allow_split, cin, math, given);
     if (pl.kind == kPre || pl.kind == kAct) pl.prep_bytes = given ? 0 : filter_planes_bytes(Nout, Kdim, pl.kind == kAct);
     return pl;
+}
+
+// igemm_small_kernel for a call of fp32 operands whose plan is `other` (grid 0: it stays with that).  It needs no workspace; a call needs what its query
+// names all the same.  beside: microseconds that the other way takes beyond its launches (the normalising pass or the filter's flip).
+// Modelled times of both, in microseconds, from 220 calls of 0.006 - 3 GFLOP, forward and data gradients.
+// Calls with split operands stay (0.2 GFLOP and more; half the error).
+constexpr double kFlipLaunch = 3.5;
+static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, int cin, const IgemmPlan &other, double beside)
+{
+    IgemmPlan s{};
+    const std::shared_ptr<const Config> cfg = config();
+    const double gflop = 2e-9 * M * Nout * Kdim;
+    if (bf16_of(d) || cin % kBK || Nout % 4 || d->r * d->s > 32 || other.kind != kGeneral || other.products || cfg->has_igemm_plan ||
+        (op == RN50_OP_BWD_DATA && d->stride > 1 && !is_scatter2(d)))
+        return s;
+    s.kind = kSmall;
+    s.tail_split = 1;
+    auto set = [&](int bm, int bn) {
+        s.bm = bm; s.bn = bn;
+        s.full_items = s.grid = ceil_div(M, bm) * ceil_div(Nout, bn);
+    };
+    for (const PlanRow &t : cfg->small_plans)
+        if (plan_matches(t, d, op)) {
+            set(t.bm, t.bn);
+            return s;
+        }
+    if (gflop > 1.0 || !cfg->overrides.empty()) return s;
+    // the other way: with an ordered sum, or one launch (its reduction is short then)
+    double best = 0.9 * (beside + (other.tail_split > 1 ? 7.2 + 0.0018 * Kdim + 12.0 * std::max(0.0, gflop - 0.1) : 5.6 + 0.012 * std::min(Kdim, 256) + 8.0 * gflop));
+    for (int bm = 16; bm <= 32; bm += 16)
+        for (int bn = 16; bn <= 32; bn += 16) {
+            const int blocks = bm * bn / 256, per_cu = ceil_div((long)ceil_div(M, bm) * ceil_div(Nout, bn), (int)kCUs);
+            const double t = blocks == 1 ? 2.1 + per_cu * (0.8 + 0.0037 * Kdim) : blocks == 2 ? 2.3 + per_cu * (0.9 + 0.0055 * Kdim) : 2.6 + per_cu * (1.4 + 0.0085 * Kdim);
+            if (t * (d->r > 1 ? 1.15 : 1.0) < best) {
+                best = t * (d->r > 1 ? 1.15 : 1.0);
+                set(bm, bn);
+            }
+        }
+    return s;
 }
 
 // The filter-gradient kernels take two stages per trip of their loop: a range of an odd number of stages ends with a stage of
@@ -609,6 +648,10 @@ static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
     p.div_cin = make_fastdiv(p.Cin);
     p.div_s = make_fastdiv(p.S);
     p.div_rs = make_fastdiv(p.R * p.S);
+    if (pl.kind == kSmall) {
+        launch_igemm_small(pl.bm, pl.bn, pl.grid, p, ap, st);
+        return ap != nullptr;
+    }
     if (pl.kind == kHalf) {
         launch_igemm_half(pl.bm, pl.bn, pl.grid, p, st);
     } else if (pl.kind == kPre) {
@@ -657,7 +700,7 @@ static size_t igemm_part_bytes(const IgemmPlan &pl) { return pl.kind == kGeneral
 // both prepared there, the gathered tensor of `pixels` pixels among them.
 static void set_planes(IgemmP &p, const IgemmPlan &pl, const char *planes, long pixels, void *ws, hipStream_t st)
 {
-    if (pl.kind == kGeneral) return;
+    if (pl.kind == kGeneral || pl.kind == kSmall) return;
     p.plane_rows = plane_rows_of(p.Nout);
     p.planes = planes;
     if (planes) return;
@@ -740,6 +783,14 @@ static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool 
     f.tiles_m = ceil_div(ge.Mout, f.rows);
     f.conv_bytes = align_up(igemm_part_bytes(f.g) + f.g.prep_bytes, 256);
     f.stat_bytes = align_up(std::max((size_t)2 * f.tiles_m * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
+    if (math == kFp32Split || math == kNoHalf) {
+        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, f.g, 0.0);
+        if (sm.grid) {
+            f.rows = sm.bm;
+            f.tiles_m = ceil_div(ge.Mout, f.rows);
+            f.stat_bytes = std::max(f.stat_bytes, align_up((size_t)2 * f.tiles_m * d->k * sizeof(float), 256));
+        }
+    }
     return f;
 }
 
@@ -824,7 +875,7 @@ extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn,
 // stats (may be null): [2][row tiles][K] floats for the output's per-tile statistics; *gathered tells whether they were left
 static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
                          const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats = nullptr, bool *gathered = nullptr,
-                         Fp32Math math = kFp32Split, const char *planes = nullptr, const TailApply *ap = nullptr);
+                         Fp32Math math = kFp32Split, const char *planes = nullptr, const TailApply *ap = nullptr, int stat_rows = 0);
 
 extern "C" int conv2d_fwd(const rn50_conv_desc *d, const float *x, const float *w, float *y, void *ws, size_t ws_bytes,
                           void *stream)
@@ -843,7 +894,7 @@ extern "C" int conv2d_fwd_bnrelu_input(const rn50_conv_desc *d, const float *x, 
 
 static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
                          const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats, bool *gathered, Fp32Math math,
-                         const char *planes, const TailApply *ap)
+                         const char *planes, const TailApply *ap, int stat_rows)
 {
     if (gathered) *gathered = false;
     if (int rc = conv_check(who, d)) return rc;
@@ -860,6 +911,12 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     }
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(!in_scale || act_of(d) != 2, RN50_EUNSUPPORTED, "%s: the fused input transform needs a bf16 or fp32 input of the variant's own type", who);
+    // evaluation (ap): single images.  With more the gain is small, and a larger share of the layers would round otherwise than the training forward
+    // does, whose logits evaluation reproduces to 1e-6
+    if (math == kFp32Split || math == kNoHalf || (ap && (double)ge.Mout * d->k * ge.Kdim < 7.5e7)) {
+        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, ap ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0);
+        if (sm.grid && (!stats || stat_rows == sm.bm)) pl = sm;
+    }
     const bool swhole = stem_stats(d, ge, math);
     if (stem_layer(d) && !in_scale && !(act_of(d) && stats && !swhole)) {
         // the network's first layer has kernels of its own (input tile and filter in LDS)
@@ -955,7 +1012,7 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
                  ws_bytes, f.conv_bytes + f.stat_bytes);
     float *stats = (float *)((char *)ws + f.conv_bytes);
     bool gathered = false;
-    if (int rc = conv_fwd_impl(who, d, x, in_scale_or_null, in_shift_or_null, w, y, ws, f.conv_bytes, stream, stats, &gathered, math, planes)) return rc;
+    if (int rc = conv_fwd_impl(who, d, x, in_scale_or_null, in_shift_or_null, w, y, ws, f.conv_bytes, stream, stats, &gathered, math, planes, nullptr, f.rows)) return rc;
     if (gathered) {
         bn_finalize_partials(ge.Mout, d->k, f.tiles_m, f.rows, stats, stats + (size_t)f.tiles_m * d->k, gamma, beta, eps, save_mean, save_invstd,
                              scale, shift, (hipStream_t)stream);
@@ -995,7 +1052,11 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
             p.div_class = make_fastdiv(p.M / 4);
         }
     }
-    p.flip_taps = b.g.kind == kHalf && !flipped ? d->r * d->s : 0;
+    if (math == kFp32Split || math == kNoHalf) {
+        const IgemmPlan sm = plan_small(d, RN50_OP_BWD_DATA, p.M, d->c, p.Kdim, d->k, b.g, flipped ? 0.0 : kFlipLaunch);
+        if (sm.grid) b.g = sm;
+    }
+    p.flip_taps = (b.g.kind == kHalf || b.g.kind == kSmall) && !flipped ? d->r * d->s : 0;
     set_planes(p, b.g, planes, ge.Mout, ws, st);
     run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), act_of(d), st);
     return launch_status("conv2d_bwd_data");
@@ -1028,7 +1089,8 @@ extern "C" int conv2d_bwd_data(const rn50_conv_desc *d, const float *dy, const f
     hipStream_t st = (hipStream_t)stream;
     // workspace = [flipped filter][partial tiles]
     char *rest = (char *)ws + b.wt_bytes;
-    if (b.g.kind == kHalf)  // its preparation flips as well
+    // the halves' preparation flips as well, and igemm_small_kernel reads the filter as it is
+    if (b.g.kind == kHalf || (math != kNoPlanes && plan_small(d, RN50_OP_BWD_DATA, b.scatter ? geom(d).Mout : geom(d).Min, d->c, d->r * d->s * d->k, d->k, b.g, kFlipLaunch).grid))
         return conv_bwd_data_pretransposed(math, d, dy, w, dx, rest, ws_bytes - b.wt_bytes, st, nullptr, false);
     float *wt = (float *)ws;
     launch_filter_flip(d->k, d->c, d->r * d->s, w, wt, st);

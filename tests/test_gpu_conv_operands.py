@@ -180,6 +180,68 @@ def test_values_without_halves(plan):
         assert fine.any() and torch.isfinite(got[fine]).all() and ((got.double() - ref)[fine].norm() / ref[fine].norm()).item() <= 1.5e-6, o
 
 
+# ---- calls that do not fill the chip (igemm_small_kernel) ----------------------------------------------------------------------------------
+SMALL = ["16,16,1", "32,16,1", "16,32,1", "32,32,1"]
+# sums of a 16th of the reduction or less on the fp32 instruction (1440 / 16 products, rounded at every other: 2e-7), then five additions
+SMALL_BAR = 5e-7
+
+
+@pytest.mark.parametrize("plan", SMALL)
+@pytest.mark.parametrize("case", CASES)
+def test_small_calls(case, plan):
+    """Ragged rows and columns, fewer stages than wavefronts, strides, the scattered data gradient, flipped filters read as they are."""
+    n, c, h, k, r, stride = case
+    x, w, dy = _operands(case, 40 + sum(case))
+    g = torch.Generator().manual_seed(c)
+    scale, shift = torch.rand(c, generator=g) + 0.5, torch.randn(c, generator=g) * 0.3
+    z = (x.double() * scale.double() + shift.double()).float().relu()
+    refs, fused_ref = _refs(case, x, w, dy), _refs(case, z, w, dy)["fwd"]
+    d = rn.conv_desc(n, c, h, h, k, r, r, stride, r // 2)
+    rn.rn50_set_option("small_plans", ";".join("%d,%d,%d,%d,%d,%d,%d,%d,%s" % (o, n, c, h, k, r, stride, r // 2, plan) for o in (rn.OP_FWD, rn.OP_BWD_DATA)))
+    try:
+        fx, fw, fdy = x.cuda(), w.cuda(), dy.cuda()
+        y, yf, dx, dxf, ys = (torch.full_like(t, 7.0) for t in (fdy, fdy, fx, fx, fdy))
+        ws = ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD_BNSTATS) + rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA))
+        rn.conv2d_fwd(d, fx, fw, y, ws)
+        rn.conv2d_fwd_bnrelu_input(d, fx, scale.cuda(), shift.cuda(), fw, yf, ws)
+        rn.conv2d_bwd_data(d, fdy, fw, dx, ws)
+        wt = torch.empty(r * r * c * k, device="cuda")
+        rn.conv2d_filter_flip(d, fw, wt)
+        rn.conv2d_bwd_data_flipped(d, fdy, wt, dxf, ws)
+        vec, ones, zeros = [torch.empty(k).cuda() for _ in range(4)], torch.ones(k).cuda(), torch.zeros(k).cuda()
+        rn.conv2d_fwd_bnstats(d, fx, None, None, fw, ys, ones, zeros, 2e-5, *vec, ws)
+        torch.cuda.synchronize()
+    finally:
+        rn.rn50_set_option("small_plans", None)
+    assert _err(y.cpu(), refs["fwd"]) <= SMALL_BAR and _err(yf.cpu(), fused_ref) <= SMALL_BAR
+    assert torch.equal(ys, y)
+    f = y.double().cpu().reshape(-1, k)
+    mean, invstd = f.mean(0), 1 / torch.sqrt(f.var(0, unbiased=False) + 2e-5)
+    assert (vec[0].double().cpu() - mean).abs().max() <= 1e-6 * f.std() and ((vec[1].double().cpu() - invstd) / invstd).abs().max() <= 1e-6
+    if not (stride == 2 and (r > 1 or h % 2)) or k % 32 == 0:
+        assert _err(dx.cpu(), refs["bwd_data"]) <= TERMS_BAR and _err(dxf.cpu(), refs["bwd_data"]) <= TERMS_BAR
+
+
+def test_small_calls_and_infinities():
+    case = n, c, h, k, r, stride = CASES[6]
+    x, w, dy = _operands(case, 47)
+    x[0, 1, 2, 3], x[2, 3, 0, 5], dy[4, 2, 2, 100] = float("inf"), float("nan"), float("-inf")
+    refs = _refs(case, x, w, dy)
+    d = rn.conv_desc(n, c, h, h, k, r, r, stride, 1)
+    for plan in SMALL:
+        rn.rn50_set_option("small_plans", ";".join("%d,%d,%d,%d,%d,%d,%d,%d,%s" % (o, n, c, h, k, r, stride, 1, plan) for o in (rn.OP_FWD, rn.OP_BWD_DATA)))
+        try:
+            y, dx = torch.full_like(dy, 7.0).cuda(), torch.full_like(x, 7.0).cuda()
+            rn.conv2d_fwd(d, x.cuda(), w.cuda(), y, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD)))
+            rn.conv2d_bwd_data(d, dy.cuda(), w.cuda(), dx, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA)))
+        finally:
+            rn.rn50_set_option("small_plans", None)
+        for got, ref in ((y.cpu(), refs["fwd"]), (dx.cpu(), refs["bwd_data"])):
+            assert torch.isnan(got[torch.isnan(ref)]).all() and torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)].float())
+            fine = torch.isfinite(ref)
+            assert _err(got[fine], ref[fine]) <= SMALL_BAR
+
+
 # calls that go there by themselves, and what the kernels they went to before left of them (relative error of six bf16 products,
 # measured, plus 5 % for other draws)
 @pytest.mark.parametrize("case,bars", [((16, 128, 28, 128, 3, 1), (1.61e-7, 2.25e-7, 2.8e-7)), ((32, 256, 14, 512, 3, 1), (1.62e-7, 2.29e-7, 2.41e-7))])
