@@ -178,7 +178,8 @@ int bn_apply_scale_shift_bf16(int n, int c, int h, int w, const uint16_t *x, con
                               uint16_t *y, hipStream_t st);
 // Merge of per-row-tile statistics gathered by a convolution: `bands` tiles of rows_per_band rows each (the last one
 // ragged) left mean and squared deviations at part_mean / part_m2 [band][C]; writes what the BN forward's merge writes.
-void bn_finalize_partials(long M, int C, int bands, int rows_per_band, const float *part_mean, const float *part_m2,
+// fold: many partials are merged in two launches (another order of the sums).
+void bn_finalize_partials(bool fold, long M, int C, int bands, int rows_per_band, float *part_mean, float *part_m2,
                           const float *gamma, const float *beta, float eps, float *save_mean, float *save_invstd, float *scale,
                           float *shift, hipStream_t st);
 // Filter gradients of several layers in one launch (csrc/conv_group.hip): the extern "C" calls with the tuning values spelled out.

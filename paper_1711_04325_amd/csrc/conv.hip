@@ -1014,8 +1014,9 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
     bool gathered = false;
     if (int rc = conv_fwd_impl(who, d, x, in_scale_or_null, in_shift_or_null, w, y, ws, f.conv_bytes, stream, stats, &gathered, math, planes, nullptr, f.rows)) return rc;
     if (gathered) {
-        bn_finalize_partials(ge.Mout, d->k, f.tiles_m, f.rows, stats, stats + (size_t)f.tiles_m * d->k, gamma, beta, eps, save_mean, save_invstd,
-                             scale, shift, (hipStream_t)stream);
+        // (the forward pass of a training context keeps its order of sums)
+        bn_finalize_partials(act_of(d) || math != kFp32Unit, ge.Mout, d->k, f.tiles_m, f.rows, stats, stats + (size_t)f.tiles_m * d->k, gamma, beta, eps,
+                             save_mean, save_invstd, scale, shift, (hipStream_t)stream);
         return launch_status(who);
     }
     // no tiled kernel ran: the separate pass over y

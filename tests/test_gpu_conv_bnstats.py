@@ -207,3 +207,46 @@ def test_bn_fwd_apply(shape, use_res, relu, mask):
     if relu:
         want = torch.clamp_min(want, 0.0)
     assert torch.equal(yh.view(torch.int16), want.to(torch.bfloat16).view(torch.int16))
+
+
+# (n, c, h, k, in_dtype): row tiles x channels on both sides of where the merge takes a second launch (2^17), with 64-row tiles
+MERGE_CASES = [
+    (32, 32, 64, 64, rn.DTYPE_F32),       # 2048 x 64: as many as the rule asks for
+    (31, 32, 64, 64, rn.DTYPE_F32),       # 1984 x 64: one launch
+    (20, 32, 97, 68, rn.DTYPE_F32),       # 2941 tiles, the last one of 20 rows, in runs of 46 and one of 43; 68 channels are 2 x 32 and 4
+    (20, 32, 97, 68, rn.DTYPE_BF16_ACT),
+    (41, 64, 40, 128, rn.DTYPE_BF16_ACT),  # 1025 tiles: runs of 17, the last one of five, fewer than the slices of a workgroup
+    (64, 64, 32, 160, rn.DTYPE_BF16_ACT),  # 1024 tiles: one launch
+]
+
+
+@pytest.mark.parametrize("case", MERGE_CASES)
+def test_merge_of_many_partials(case):
+    """Statistics of a tensor with many row tiles against those of the tensor as written, in 64 bits.  A value passes through fewer
+    than 100 fp32 roundings on its way (64 rows of a tile in two passes, at most 8 + 16 + 1 + 4 + 4 merges): 100 x 2^-24 of the larger of
+    the mean and the deviation."""
+    n, c, h, k, dtype = case
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5 + n + k)
+    act = torch.bfloat16 if dtype == rn.DTYPE_BF16_ACT else torch.float32
+    x = (torch.randn(n, h, h, c, generator=g, device=DEV) + 0.3).to(act)
+    w = torch.randn(k, 1, 1, c, generator=g, device=DEV) * (2.0 / c) ** 0.5
+    gamma, beta = torch.ones(k, device=DEV), torch.zeros(k, device=DEV)
+    d = rn.conv_desc(n, c, h, h, k, 1, 1, 1, 0, in_dtype=dtype)
+    y, st, again = torch.empty(n, h, h, k, device=DEV, dtype=act), [empty(k) for _ in range(4)], [empty(k) for _ in range(4)]
+    rn.rn50_set_option("igemm_plan", "64,64,1")
+    try:
+        ws = ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD_BNSTATS))
+        rn.conv2d_fwd_bnstats(d, x, None, None, w, y, gamma, beta, EPS, *st, ws)
+        ws.fill_(0xA5)
+        rn.conv2d_fwd_bnstats(d, x, None, None, w, y, gamma, beta, EPS, *again, ws)
+    finally:
+        rn.rn50_set_option("igemm_plan", None)
+    f = y.reshape(-1, k).double()
+    mean, var = f.mean(0), f.var(0, unbiased=False)
+    bound = 100 * 2.0 ** -24
+    assert ((st[0].double() - mean).abs() <= bound * torch.maximum(mean.abs(), var.sqrt())).all()
+    invstd = 1.0 / torch.sqrt(var + EPS)
+    assert ((st[1].double() - invstd).abs() <= bound * invstd).all()
+    for a, b in zip(st, again):
+        assert torch.equal(a, b)
