@@ -141,8 +141,8 @@ static IgemmPlan make_igemm_plan(int kind, int bm, int bn, long M, int Nout, int
     return pl;
 }
 
-// modelled time in core clocks (of the fp32 instruction; the general split kernel and igemm_act_kernel without a measured row are planned
-// with it as well, for want of a model of their own: 5 % off the best plan on average for the former)
+// modelled time in core clocks (of the fp32 instruction; the general split kernel is planned with it as well, for want of a model of its own: 5 % off
+// the best plan on average)
 static double igemm_cost(const IgemmPlan &pl, int kchunks, double chunk_clks)
 {
     const int occ = igemm_kind_occupancy(pl.kind, pl.bm, pl.bn);
@@ -191,7 +191,28 @@ static double igemm_half_cost(const IgemmPlan &pl, int kchunks)
     return t;
 }
 
-static IgemmPlan model_plan(int kind, long M, int Nout, int kchunks, int bk, bool allow_split, int max_bm = 128)
+// The same for igemm_act_kernel (kchunks: stages of 64); a forward pass with its statistics and their merge, which reads a row of partials per row tile.
+// Fitted to 5,100 measured launches (166 calls of 130 shapes, every tile, up to seven splits): the plan it picks takes 1.0 % longer than the best one
+// measured in forward passes, 2.3 % in data gradients, on average.  The rows of the measured table, which igemm_act_kernel took before, are those of the
+// general kernel: 7.7 % longer (64 -> 256 channels at 56x56, N = 256, forward 215 us in tiles of 64 x 128, 180 in 128 x 128; 1024 -> 512 at 14x14, N = 32: 42, 25).
+static double igemm_act_cost(const IgemmPlan &pl, bool fwd, long M, int Nout, int kchunks)
+{
+    static const double f128x128[3] = {0.519, 0.965, 0.625}, f128x64[3] = {0.336, 0.585, 0.393}, f64x128[3] = {0.307, 0.0, 0.347}, f64x64[3] = {0.198, 0.051, 0.230};
+    static const double b128x128[3] = {0.516, 1.405, 0.633}, b128x64[3] = {0.319, 0.800, 0.399}, b64x128[3] = {0.288, 0.788, 0.483}, b64x64[3] = {0.192, 0.401, 0.402};
+    const double *c = pl.bm == 128 ? (pl.bn == 128 ? (fwd ? f128x128 : b128x128) : (fwd ? f128x64 : b128x64))
+                                   : (pl.bn == 128 ? (fwd ? f64x128 : b64x128) : (fwd ? f64x64 : b64x64));
+    const int occ = igemm_act_occupancy(pl.bm, pl.bn);
+    double t = pl.full_items / (kCUs * occ) * occ * (kchunks * c[0] + c[1]);
+    if (pl.tail_tiles) {
+        const double per_cu = ceil((double)pl.tail_tiles * pl.tail_split / kCUs);
+        t += std::max(per_cu * (pl.tail_chunks * c[0] + c[1]), pl.tail_chunks * c[2] + (fwd ? 1.7 : 4.9));
+        if (pl.tail_split > 1) t += (pl.tail_split + 1.0) * pl.tail_tiles * pl.bm * pl.bn * 4.0 / 5.0e6;
+    }
+    const double bands = ceil_div(M, pl.bm);
+    return fwd ? t + 0.0042 * bands + 3.4e-5 * bands * Nout : t;
+}
+
+static IgemmPlan model_plan(int kind, long M, int Nout, int kchunks, int bk, bool allow_split, int max_bm = 128, bool fwd = true)
 {
     IgemmPlan best{};
     double best_cost = 1e300;  // left in best.cost
@@ -205,6 +226,7 @@ static IgemmPlan model_plan(int kind, long M, int Nout, int kchunks, int bk, boo
                 if (sp > 1 && (!allow_split || kchunks / sp < 2)) break;
                 const IgemmPlan pl = make_igemm_plan(kind, bm, bn, M, Nout, kchunks, sp, allow_split);
                 const double cost = kind == kHalf ? igemm_half_cost(pl, kchunks) : kind == kPre ? igemm_pre_cost(pl, kchunks)
+                                                 : kind == kAct ? igemm_act_cost(pl, fwd, M, Nout, kchunks)
                                                  : igemm_cost(pl, kchunks, 4096.0 * (bk / (double)kBK) * (bm * bn / 16384.0) / tile_eff(bm, bn));
                 if (cost < best_cost) { best_cost = cost; best = pl; }
             }
@@ -313,8 +335,7 @@ static IgemmPlan plan_igemm_kind(const rn50_conv_desc *d, int op, long M, int No
     if (act_of(d) == 1 && geometry && cin % kActStage == 0) {
         for (const PlanRow &t : cfg->pre_plans)
             if (plan_matches(t, d, op)) return make_igemm_plan(kAct, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
-        if (tuned_plan(*cfg, d, op, &pl)) return make_igemm_plan(kAct, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
-        return model_plan(kAct, M, Nout, kchunks, bk, allow_split);
+        return model_plan(kAct, M, Nout, kchunks, bk, allow_split, 128, fwd);
     }
     const IgemmPlan general = tuned_plan(*cfg, d, op, &pl) ? make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split)
                                                             : model_plan(kGeneral, M, Nout, kchunks, bk, allow_split);

@@ -187,6 +187,39 @@ def test_bf16_activation_plan_rows_on_sampled_outputs(case, ops):
         assert bool(torch.isfinite(gdx.float()).all()), "bwd_data " + what
 
 
+@pytest.mark.parametrize("case", [(32, 64, 56, 64, 3, 1), (65, 128, 28, 520, 1, 1), (13, 192, 29, 192, 3, 1), (64, 256, 14, 1024, 1, 1),
+                                  (128, 256, 28, 512, 1, 2), (65, 512, 7, 512, 3, 1)])
+def test_bf16_activation_plans_of_the_prepared_filter(case):
+    """Calls whose plan the cost model of the kernel with a prepared filter picks (whole rounds, split tails, ragged rows and columns), against
+    the general kernel.  Both add exact products in fp32, in other orders: the outputs are
+    roundings to 8 bits of sums that differ by some 2^-24 of their size, so few of them differ, by one place."""
+    n, c, h, k, r, stride = case
+    g = torch.Generator(device=DEV)
+    g.manual_seed(sum(case))
+    p = (h + 2 * (r // 2) - r) // stride + 1
+    d = rn.conv_desc(n, c, h, h, k, r, r, stride, r // 2, in_dtype=ACT)
+    x = torch.randn(n, h, h, c, generator=g, device=DEV).relu_().bfloat16()
+    dy = torch.randn(n, p, p, k, generator=g, device=DEV).bfloat16()
+    w = torch.randn(k, r, r, c, generator=g, device=DEV) * (2.0 / (c * r * r)) ** 0.5
+    outs = []
+    for plain in (False, True):
+        y, dx = torch.zeros(n, p, p, k, device=DEV, dtype=torch.bfloat16), torch.zeros_like(x)
+        if plain:
+            rn.rn50_set_option("igemm_plan", "64,64,1")
+        try:
+            rn.conv2d_fwd(d, x, w, y, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD)))
+            if k % 64 == 0:
+                rn.conv2d_bwd_data(d, dy, w, dx, ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA)))
+        finally:
+            rn.rn50_set_option("igemm_plan", None)
+        outs.append((y, dx))
+    for a, b in zip(*outs):
+        a, b = a.float(), b.float()
+        rms = b.square().mean().sqrt()
+        assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * rms).all()
+        assert (a != b).float().mean() <= 5e-3
+
+
 @pytest.mark.parametrize("case", [(2, 3, 64, 64, 64, 7, 2, 3), (1, 3, 50, 38, 64, 7, 2, 3), (2, 32, 12, 12, 64, 3, 1, 1)])
 def test_conv_bf16_activations_with_an_fp32_input(case):
     """The network's first layer: the image is fp32 (rounded on the way into LDS), output and incoming gradient are bf16."""
