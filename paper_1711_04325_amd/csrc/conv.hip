@@ -357,9 +357,12 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
 // names all the same.  beside: microseconds that the other way takes beyond its launches (the normalising pass or the filter's flip).
 // Modelled times of both, in microseconds, from 220 calls of 0.006 - 3 GFLOP, forward and data gradients.
 // Calls with split operands stay (0.2 GFLOP and more; half the error).
+// stat_room: bytes for the statistics of its row tiles (0: the call takes none); a tile whose statistics need more is not taken, so that the workspace
+// that a call asks for, and refuses to go without, is that of its other plan.
 constexpr double kFlipLaunch = 3.5;
-static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, int cin, const IgemmPlan &other, double beside)
+static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, int Kdim, int cin, const IgemmPlan &other, double beside, size_t stat_room = 0)
 {
+    auto fits = [&](int bm) { return !stat_room || (size_t)2 * ceil_div(M, bm) * Nout * sizeof(float) <= stat_room; };
     IgemmPlan s{};
     const std::shared_ptr<const Config> cfg = config();
     const double gflop = 2e-9 * M * Nout * Kdim;
@@ -373,7 +376,7 @@ static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, i
         s.full_items = s.grid = ceil_div(M, bm) * ceil_div(Nout, bn);
     };
     for (const PlanRow &t : cfg->small_plans)
-        if (plan_matches(t, d, op)) {
+        if (plan_matches(t, d, op) && fits(t.bm)) {
             set(t.bm, t.bn);
             return s;
         }
@@ -381,7 +384,7 @@ static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, i
     // the other way: with an ordered sum, or one launch (its reduction is short then)
     double best = 0.9 * (beside + (other.tail_split > 1 ? 7.2 + 0.0018 * Kdim + 12.0 * std::max(0.0, gflop - 0.1) : 5.6 + 0.012 * std::min(Kdim, 256) + 8.0 * gflop));
     for (int bm = 16; bm <= 32; bm += 16)
-        for (int bn = 16; bn <= 32; bn += 16) {
+        for (int bn = 16; fits(bm) && bn <= 32; bn += 16) {
             const int blocks = bm * bn / 256, per_cu = ceil_div((long)ceil_div(M, bm) * ceil_div(Nout, bn), (int)kCUs);
             const double t = blocks == 1 ? 2.1 + per_cu * (0.8 + 0.0037 * Kdim) : blocks == 2 ? 2.3 + per_cu * (0.9 + 0.0055 * Kdim) : 2.6 + per_cu * (1.4 + 0.0085 * Kdim);
             if (t * (d->r > 1 ? 1.15 : 1.0) < best) {
@@ -795,6 +798,10 @@ static bool stem_stats(const rn50_conv_desc *d, const Geom &ge, Fp32Math math)
 // The region holds mean and squared deviations per (row tile, output channel), or, for a shape whose forward pass does not
 // run through the tiled kernel, the band partials of the separate statistics pass; it is sized for both.
 struct FwdStatsPlan { IgemmPlan g; int tiles_m, rows; size_t conv_bytes, stat_bytes; };
+static size_t stat_room(const rn50_conv_desc *d, const Geom &ge, int rows)
+{
+    return align_up(std::max((size_t)2 * ceil_div(ge.Mout, rows) * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
+}
 static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool given = false)
 {
     const Geom ge = geom(d);
@@ -803,13 +810,12 @@ static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool 
     f.rows = stem_stats(d, ge, math) ? kStemTH * kStemTW : f.g.bm;
     f.tiles_m = ceil_div(ge.Mout, f.rows);
     f.conv_bytes = align_up(igemm_part_bytes(f.g) + f.g.prep_bytes, 256);
-    f.stat_bytes = align_up(std::max((size_t)2 * f.tiles_m * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
+    f.stat_bytes = stat_room(d, ge, f.rows);
     if (math == kFp32Split || math == kNoHalf) {
-        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, f.g, 0.0);
+        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, f.g, 0.0, f.stat_bytes);
         if (sm.grid) {
             f.rows = sm.bm;
             f.tiles_m = ceil_div(ge.Mout, f.rows);
-            f.stat_bytes = std::max(f.stat_bytes, align_up((size_t)2 * f.tiles_m * d->k * sizeof(float), 256));
         }
     }
     return f;
@@ -935,7 +941,8 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     // evaluation (ap): single images.  With more the gain is small, and a larger share of the layers would round otherwise than the training forward
     // does, whose logits evaluation reproduces to 1e-6
     if (math == kFp32Split || math == kNoHalf || (ap && (double)ge.Mout * d->k * ge.Kdim < 7.5e7)) {
-        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, ap ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0);
+        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, ap ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0,
+                                        stats ? stat_room(d, ge, pl.bm) : 0);
         if (sm.grid && (!stats || stat_rows == sm.bm)) pl = sm;
     }
     const bool swhole = stem_stats(d, ge, math);
