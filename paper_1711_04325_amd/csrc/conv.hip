@@ -1055,18 +1055,6 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
                                 f.stat_bytes, stream);
 }
 
-// Whether the rows of a stride-2 data gradient are ordered by parity class where the image has an odd size.  Time in image order / by class, us:
-// with a prepared filter 3x3 256 x 256, 29x29, N=64 418 / 231 (bf16 activations 112 / 89), 512 x 512, 7x7, N=128 216 / 142 (73 / 60), 128 x 128, 55x55, N=32
-// 189 / 119 (63 / 43); split operands 96 x 160, 29x29, N=9 39 / 35, 224 x 160, 7x7, N=128 60 / 41.  It loses where stages are short of
-// work for the latency they take: pieces shorter than a tap (64 x 352, 7x7, N=25 21.2 / 22.1), below a GFLOP (64 x 128, 45x45, N=2 20.0 / 20.6), bf16 operands in
-// the general kernel (0.9 - 1.15), and filters of one tap, whose output order costs more than the stages (512 x 256, 29x29, N=64 130 / 170).
-static bool odd_classes(const rn50_conv_desc *d, const IgemmPlan &g)
-{
-    if (d->r == 1) return false;
-    if (g.kind == kPre || g.kind == kAct) return true;
-    return g.kind == kGeneral && g.products && g.tail_split <= d->r * d->s && 2.0 * d->n * d->h * d->w * d->c * d->k * d->r * d->s >= 1e9;
-}
-
 // Data gradient with the filter already flipped and transposed (wt[c][R-1-r][S-1-s][k] = w[k][r][s][c]): a
 // forward-type gather over dy.  ws = the implicit GEMM's partial tiles only.
 int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws,
@@ -1087,14 +1075,10 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
         p.OH = ge.P; p.OW = ge.Q; p.so = 1; p.off = 0; p.sd = 1; p.M = (int)ge.Mout; p.scatter2 = 1;
     } else {
         p.OH = d->h; p.OW = d->w; p.so = 1; p.off = d->pad - (d->r - 1); p.sd = d->stride; p.M = (int)ge.Min; p.scatter2 = 0;
-        if (d->stride == 2 && d->k % kBK == 0 && ((d->h % 2 == 0 && d->w % 2 == 0) || odd_classes(d, b.g))) {
+        if (d->stride == 2 && d->h % 2 == 0 && d->w % 2 == 0 && d->k % kBK == 0) {
             // rows grouped by the parity class of their pixel: a tile inside one class skips the taps that never reach it
-            const int hh[2] = {(d->h + 1) / 2, d->h / 2}, ww[2] = {(d->w + 1) / 2, d->w / 2};
-            p.OH = hh[0]; p.OW = ww[0]; p.scatter2 = 2;
-            p.FH = d->h; p.FW = d->w;
-            for (int c = 0, at = 0; c < 3; ++c) p.cls_begin[c] = at += d->n * hh[c >> 1] * ww[c & 1];
-            for (int c = 0; c < 2; ++c) p.div_oh[c] = make_fastdiv(std::max(hh[c], 1));  // a class of no rows is never divided
-            p.div_ow1 = make_fastdiv(std::max(ww[1], 1));
+            p.OH = d->h / 2; p.OW = d->w / 2; p.scatter2 = 2;
+            p.div_class = make_fastdiv(p.M / 4);
         }
     }
     if (math == kFp32Split || math == kNoHalf) {

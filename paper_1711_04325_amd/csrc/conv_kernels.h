@@ -88,12 +88,10 @@ struct IgemmP {
     // 2: rows are grouped by the parity class (oh%2, ow%2) of their pixel in that tensor: row m = (class, n, oh, ow) is
     // pixel (n, 2*oh + class/2, 2*ow + class%2).  For the data gradient of a stride-2 convolution every row of a class
     // receives the same subset of filter taps, so a tile inside one class skips the other taps instead of multiplying
-    // gathered zeros.  (OH, OW: rows and columns of class 0, the larger halves; where a size is odd, the classes of its odd positions
-    // have one less, so the classes differ in their number of rows.)
+    // gathered zeros (OH, OW are the half sizes here, M = 4*N*OH*OW).
     int scatter2;
     FastDiv div_ohw, div_ow, div_cin, div_s;  // by OH*OW, OW, Cin, S
-    int cls_begin[3], FH, FW;                 // row order 2: first rows of classes 1, 2 and 3, and the sizes of that tensor,
-    FastDiv div_oh[2], div_ow1;               // by the rows of its classes 0 and 1 (2 and 3), by the columns of classes 1 and 3 (0 and 2: div_ow)
+    FastDiv div_class;                        // by M/4 (row order 2)
     // Kernels of conv_split.h and conv_act.h: the filter operand prepared beforehand, [stage][plane_rows][bytes of a row's stage].
     const char *planes;
     int plane_rows;
@@ -118,20 +116,13 @@ __device__ inline float4 ldg4(gcfp p)
 }
 
 // Row m of the GEMM -> first element of its output row (stride-2 scatter of the 1x1/2 data gradient included).
-// row m -> (class, image, row, column), the latter two in halves of row order 2 (class = 0 for the other orders)
-__device__ inline int row_class(const IgemmP &p, int m) { return (m >= p.cls_begin[0]) + (m >= p.cls_begin[1]) + (m >= p.cls_begin[2]); }
+// row m -> (class, image, row, column) with the half sizes of row order 2 (class = 0 for the other orders)
 __device__ inline void decode_row(const IgemmP &p, int m, int &cls, int &n, int &oh, int &ow)
 {
     cls = 0;
     if (p.scatter2 == 2) {
-        cls = row_class(p, m);
-        m -= cls == 0 ? 0 : cls == 1 ? p.cls_begin[0] : cls == 2 ? p.cls_begin[1] : p.cls_begin[2];
-        const FastDiv dw = cls & 1 ? p.div_ow1 : p.div_ow, dh = cls & 2 ? p.div_oh[1] : p.div_oh[0];
-        const int line = (int)fdiv(m, dw);
-        ow = m - line * (int)dw.d;
-        n = (int)fdiv(line, dh);
-        oh = line - n * (int)dh.d;
-        return;
+        cls = (int)fdiv(m, p.div_class);
+        m -= cls * (p.M >> 2);
     }
     n = (int)fdiv(m, p.div_ohw);
     const int rem = m - n * (p.OH * p.OW);
@@ -144,8 +135,7 @@ __device__ inline long out_row_index(const IgemmP &p, int m)
     if (!p.scatter2) return m;
     int cls, n, oh, ow;
     decode_row(p, m, cls, n, oh, ow);
-    if (p.scatter2 == 2) return ((long)n * p.FH + 2 * oh + (cls >> 1)) * p.FW + 2 * ow + (cls & 1);
-    return ((long)n * 2 * p.OH + 2 * oh) * (2 * p.OW) + 2 * ow;
+    return ((long)n * 2 * p.OH + 2 * oh + (cls >> 1)) * (2 * p.OW) + 2 * ow + (cls & 1);
 }
 
 template <bool O16 = false>
@@ -701,7 +691,7 @@ __global__ __launch_bounds__(kConvThreads, igemm_occupancy(BM, BN)) void igemm_k
         // pw + off + s are multiples of the dilation (2): the other chunks are skipped.  Uniform over the workgroup.
         int skip_ph = -1, skip_pw = 0;
         if (MODE == 1 && p.scatter2 == 2) {
-            const int c0 = row_class(p, m0), c1 = row_class(p, min(m0 + BM - 1, p.M - 1));
+            const int mq = p.M >> 2, c0 = m0 / mq, c1 = min(m0 + BM - 1, p.M - 1) / mq;
             if (c0 == c1) {
                 skip_ph = c0 >> 1;
                 skip_pw = c0 & 1;
@@ -883,7 +873,7 @@ __global__ __launch_bounds__(256) void igemm_tail_reduce_kernel(IgemmP p, TailAp
     if (m >= p.M) return;
     const long row = out_row_index(p, m);
     const int col = tn * BN + cl;
-    if (p.scatter2 != 1 && (p.Nout & 3) == 0) {  // rows of whole 16-byte groups
+    if (!p.scatter2 && (p.Nout & 3) == 0) {  // rows of whole 16-byte groups
         if (col < p.Nout) {
             if (O16) st4(reinterpret_cast<bf16_t *>(p.out), (size_t)(row * p.Nout + col) / 4, acc);
             else *reinterpret_cast<float4 *>(&p.out[row * p.Nout + col]) = acc;

@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kConvThreads, igemm_pre_occupancy(BM, BN)) void ige
             }
         }
         if (MODE == 1 && p.scatter2 == 2) {
-            const int c0 = row_class(p, it.m0), c1 = row_class(p, min(it.m0 + BM - 1, p.M - 1));
+            const int mq = p.M >> 2, c0 = it.m0 / mq, c1 = min(it.m0 + BM - 1, p.M - 1) / mq;
             skip_ph = c0 == c1 ? c0 >> 1 : -1;
             skip_pw = c0 & 1;
         }
