@@ -942,7 +942,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     // does, whose logits evaluation reproduces to 1e-6
     if (math == kFp32Split || math == kNoHalf || (ap && (double)ge.Mout * d->k * ge.Kdim < 7.5e7)) {
         const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, ap ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0,
-                                        stats ? stat_room(d, ge, pl.bm) : 0);
+                                        ap || d->k % 4 ? 0 : stat_room(d, ge, pl.bm));  // with and without statistics the same kernel
         if (sm.grid && (!stats || stat_rows == sm.bm)) pl = sm;
     }
     const bool swhole = stem_stats(d, ge, math);
