@@ -45,7 +45,20 @@ struct Config {
     std::vector<PlanRow> small_plans;                          // plans of igemm_small_kernel (tiles of 16 or 32; the cut says nothing)
     std::vector<PlanRow> overrides;                            // rows that go before the measured table
 };
-std::shared_ptr<const Config> config();  // the current snapshot (immutable; a call keeps the one it started with)
+std::shared_ptr<const Config> config();  // the current snapshot (immutable), or the one that this thread's ConfigScope holds
+// A call of the ABI holds the snapshot it started with, whatever other threads set meanwhile: it plans more than once (what to
+// prepare, how much room, what to launch), and the decisions have to be those of one plan.
+class ConfigScope {
+public:
+    ConfigScope();
+    ~ConfigScope();
+    ConfigScope(const ConfigScope &) = delete;
+    ConfigScope &operator=(const ConfigScope &) = delete;
+
+private:
+    std::shared_ptr<const Config> held;
+    bool outermost;
+};
 
 inline int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 

@@ -96,8 +96,20 @@ static std::shared_ptr<const Config> from_environment()
     return c;
 }
 
+static thread_local const std::shared_ptr<const Config> *t_held = nullptr;
+
+ConfigScope::ConfigScope() : held(config()), outermost(!t_held)
+{
+    if (outermost) t_held = &held;
+}
+ConfigScope::~ConfigScope()
+{
+    if (outermost) t_held = nullptr;
+}
+
 std::shared_ptr<const Config> config()
 {
+    if (t_held) return *t_held;
     std::lock_guard<std::mutex> lk(g_mu);
     if (!g_cfg) g_cfg = from_environment();
     return g_cfg;

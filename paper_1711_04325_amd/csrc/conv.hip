@@ -836,6 +836,7 @@ static int stem_wgrad_grid(const rn50_conv_desc *d, const Geom &ge)
 
 extern "C" size_t rn50_conv_workspace_bytes(const rn50_conv_desc *d, int op)
 {
+    const ConfigScope snapshot;
     if (conv_check("rn50_conv_workspace_bytes", d) != RN50_OK) return 0;
     return conv_workspace(d, op, kFp32Split, false);
 }
@@ -847,6 +848,7 @@ static size_t wgrad_bytes(const rn50_conv_desc *d, const GemmPlan &pl, const Geo
 
 size_t rn50::conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool given)
 {
+    const ConfigScope snapshot;
     const Geom ge = geom(d);
     if (op == RN50_OP_FWD) {
         const IgemmPlan pl = plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, math, given);
@@ -871,6 +873,7 @@ size_t rn50::conv_workspace(const rn50_conv_desc *d, int op, Fp32Math math, bool
 
 extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn, int *split, int *workgroups)
 {
+    const ConfigScope snapshot;
     if (int rc = conv_check("rn50_conv_plan", d)) return rc;
     const Geom ge = geom(d);
     int v[4];
@@ -923,6 +926,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
                          const float *w, float *y, void *ws, size_t ws_bytes, void *stream, float *stats, bool *gathered, Fp32Math math,
                          const char *planes, const TailApply *ap, int stat_rows)
 {
+    const ConfigScope snapshot;
     if (gathered) *gathered = false;
     if (int rc = conv_check(who, d)) return rc;
     RN50_REQUIRE(x && w && y, RN50_EINVAL, "%s: null pointer", who);
@@ -1009,6 +1013,7 @@ int rn50::conv_fwd_apply_math(Fp32Math math, const rn50_conv_desc *d, const floa
 
 size_t rn50::conv_planes_bytes(const rn50_conv_desc *d, int op)
 {
+    const ConfigScope snapshot;
     const Geom ge = geom(d);
     const bool fwd = op == RN50_OP_FWD;
     const IgemmPlan pl = fwd ? plan_igemm(d, op, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, true) : plan_bwd_data(d, kFp32Split, true).g;
@@ -1019,6 +1024,7 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
                                   const float *w, const char *planes, float *y, const float *gamma, const float *beta, float eps, float *save_mean,
                                   float *save_invstd, float *scale, float *shift, void *ws, size_t ws_bytes, hipStream_t stream)
 {
+    const ConfigScope snapshot;
     const char *who = "conv2d_fwd_bnstats";
     if (int rc = conv_check(who, d)) return rc;
     RN50_REQUIRE(gamma && beta && save_mean && save_invstd && scale && shift, RN50_EINVAL, "%s: null pointer", who);
@@ -1060,6 +1066,7 @@ int rn50::conv_fwd_bnstats_math(Fp32Math math, const rn50_conv_desc *d, const fl
 int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws,
                                       size_t ws_bytes, hipStream_t st, const char *planes, bool flipped)
 {
+    const ConfigScope snapshot;
     const Geom ge = geom(d);
     BwdDataPlan b = plan_bwd_data(d, math, planes != nullptr);
     while (math != kNoPlanes && b.part_bytes && (ws_bytes < b.part_bytes || !ws)) b = plan_bwd_data(d, math = less_room(math));  // less room than the query names
@@ -1104,6 +1111,7 @@ void rn50::launch_filter_flip(int K, int C, int RS, const float *w, float *wt, h
 extern "C" int conv2d_bwd_data(const rn50_conv_desc *d, const float *dy, const float *w, float *dx, void *ws,
                                size_t ws_bytes, void *stream)
 {
+    const ConfigScope snapshot;
     if (int rc = conv_check("conv2d_bwd_data", d)) return rc;
     RN50_REQUIRE(dy && w && dx, RN50_EINVAL, "conv2d_bwd_data: null pointer");
     RN50_REQUIRE(d->r == d->s, RN50_EUNSUPPORTED, "conv2d_bwd_data: non-square filters are not supported");
@@ -1138,6 +1146,7 @@ extern "C" int conv2d_filter_flip(const rn50_conv_desc *d, const float *w, float
 extern "C" int conv2d_bwd_data_flipped(const rn50_conv_desc *d, const float *dy, const float *wt, float *dx, void *ws,
                                        size_t ws_bytes, void *stream)
 {
+    const ConfigScope snapshot;
     if (int rc = conv_check("conv2d_bwd_data_flipped", d)) return rc;
     RN50_REQUIRE(dy && wt && dx, RN50_EINVAL, "conv2d_bwd_data_flipped: null pointer");
     RN50_REQUIRE(d->r == d->s, RN50_EUNSUPPORTED, "conv2d_bwd_data_flipped: non-square filters are not supported");
@@ -1173,6 +1182,7 @@ extern "C" int conv2d_bwd_weight_bnrelu_input(const rn50_conv_desc *d, const flo
 static int conv_bwd_weight_impl(const char *who, const rn50_conv_desc *d, const float *x, const float *in_scale, const float *in_shift,
                                 const float *dy, float *dw, void *ws, size_t ws_bytes, void *stream, Fp32Math math)
 {
+    const ConfigScope snapshot;
     if (int rc = conv_check(who, d)) return rc;
     RN50_REQUIRE(x && dy && dw, RN50_EINVAL, "%s: null pointer", who);
     RN50_REQUIRE(aligned16(x) && aligned16(dy) && aligned16(dw) && aligned16(ws), RN50_EINVAL, "%s: pointers must be 16-byte aligned", who);

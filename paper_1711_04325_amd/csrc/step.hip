@@ -401,12 +401,14 @@ extern "C" int rn50_param_table(int idx, const char **name, size_t *offset, size
 
 extern "C" size_t rn50_activation_bytes(int batch, int variant)
 {
+    const ConfigScope snapshot;
     if (batch <= 0 || batch > 1024 || (variant != RN50_VARIANT_V1 && variant != RN50_VARIANT_V15)) return 0;
     return make_plan(batch, variant).total;
 }
 
 extern "C" int rn50_create(rn50_ctx **out, int batch, int variant, int conv_dtype, void *act_arena, size_t act_bytes)
 {
+    const ConfigScope snapshot;
     RN50_REQUIRE(out, RN50_EINVAL, "rn50_create: null output pointer");
     *out = nullptr;
     RN50_REQUIRE(batch > 0 && batch <= 1024, RN50_EINVAL, "rn50_create: batch must be in [1, 1024]");
@@ -593,6 +595,7 @@ static const char *planes_of(const rn50_ctx *ctx, int dir, int li)
 // rn50_set_bn_stats stores back).  Overwrites the stored activations of the last training step.
 extern "C" int rn50_forward_eval(rn50_ctx *ctx, const float *images, const float *theta, float *logits_out, void *stream)
 {
+    const ConfigScope snapshot;
     RN50_REQUIRE(ctx && images && theta && logits_out, RN50_EINVAL, "rn50_forward_eval: null pointer");
     RN50_REQUIRE(aligned16(images) && aligned16(theta) && aligned16(logits_out), RN50_EINVAL,
                  "rn50_forward_eval: pointers must be 16-byte aligned");
@@ -993,12 +996,14 @@ static int forward_backward_impl(rn50_ctx *ctx, const float *images, const int32
 extern "C" int rn50_forward_backward(rn50_ctx *ctx, const float *images, const int32_t *labels, const float *theta,
                                      float *grad, float bn_eps, float *loss_out, void *stream)
 {
+    const ConfigScope snapshot;
     return forward_backward_impl(ctx, images, labels, theta, grad, bn_eps, loss_out, stream, nullptr);
 }
 
 extern "C" int rn50_step(rn50_ctx *ctx, const float *images, const int32_t *labels, float *theta, float *grad, float *delta,
                          float *m, uint16_t *grad16, const rn50_opt_hparams *hp, float bn_eps, float *loss_out, void *stream)
 {
+    const ConfigScope snapshot;
     RN50_REQUIRE(ctx && delta && m && grad16 && hp, RN50_EINVAL, "rn50_step: null pointer");
     RN50_REQUIRE(aligned16(delta) && aligned16(m) && aligned16(grad16), RN50_EINVAL, "rn50_step: pointers must be 16-byte aligned");
     hipEvent_t stem_done = nullptr;
