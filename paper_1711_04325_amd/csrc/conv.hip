@@ -727,7 +727,7 @@ static void set_planes(IgemmP &p, const IgemmPlan &pl, const char *planes, long 
     if (pl.kind == kGeneral || pl.kind == kSmall) return;
     p.plane_rows = plane_rows_of(p.Nout);
     p.planes = planes;
-    if (planes) return;
+    if (planes && pl.kind != kHalf) return;  // a filter given as bf16 terms is none of this call's: options set since a context was made can plan halves
     char *own = (char *)ws + igemm_part_bytes(pl);
     p.planes = own;
     if (pl.kind != kHalf) {

@@ -6,6 +6,7 @@ import torch
 
 from paper_1711_04325_amd import binding as rn
 from tests.gpu_util import ws_bytes
+from tests.step_util import gpu_forward_backward, problem
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +44,30 @@ def test_options_set_by_another_thread_during_data_gradients(case, option, value
         other.join()
         rn.rn50_set_option(option, None)
     assert worst <= 8e-7, worst
+
+
+def test_halves_planned_after_a_context_prepared_its_filters():
+    """A context prepares filters as bf16 terms where the options at its creation plan them; a step whose options plan fp16 halves for such a layer
+    prepares its own operands (there is no gathered tensor's halves among what the context prepared)."""
+    batch = 8
+    images, params, labels = problem(31, batch)
+    ctx = rn.Rn50Ctx(batch)
+    loss, before, theta, dimg, dlab = gpu_forward_backward(ctx, images, params, labels, 2e-5)
+    after, again, out = torch.empty_like(before), torch.empty_like(before), torch.empty(1, device="cuda")
+    rows = [(256, 56, 64, 1, 1), (64, 56, 64, 3, 1), (128, 28, 128, 3, 1), (512, 28, 128, 1, 1), (256, 14, 256, 3, 1), (1024, 14, 256, 1, 1)]
+    rn.rn50_set_option("operand_plans", ";".join("%d,%d,%d,%d,%d,%d,%d,%d,64,64,1" % (rn.OP_BWD_DATA, batch, c, h, k, r, s, r // 2) for c, h, k, r, s in rows))
+    try:
+        ctx.forward_backward(dimg, dlab, theta, after, 2e-5, out)
+        torch.cuda.synchronize()
+    finally:
+        rn.rn50_set_option("operand_plans", None)
+    ctx.forward_backward(dimg, dlab, theta, again, 2e-5, out)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert out.item() == loss and torch.equal(again.view(torch.int32), before.view(torch.int32))
+    assert not torch.equal(after.view(torch.int32), before.view(torch.int32))   # the halves ran
+    # the forward pass is the same bits, so every ReLU decides alike and what differs are roundings of 1e-7 in the data gradients: as between two
+    # orders of the sums in test_gpu_step_group
+    for name, off, cnt, dims, kind in rn.rn50_param_table():
+        a, b = after[off:off + cnt].double(), before[off:off + cnt].double()
+        assert ((a - b).norm() / b.norm().clamp_min(1e-30)).item() <= 1e-5, name
