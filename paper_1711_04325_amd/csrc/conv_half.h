@@ -12,10 +12,11 @@
 // 1.6e-7: the sums of hi*hi are moved to accumulators of their own every 128 elements (without that 1.7e-7 .. 4.4e-7).  What stays, 9e-8, are the
 // bits that the halves drop: so reductions of 1024 and more come here (half_precise in conv.hip).
 //
-// The fixed range: numbers below 2^-27 of their tensor's largest one have fewer than 24 bits.  Beside larger ones that is nothing (the
-// fp32 rounding of the sum is larger); where a whole group of 32 channels of a pixel (or of a filter row) is that small and not zero, the split
-// leaves a mark, and the wavefronts whose outputs need it form them again on the fp32 instruction, as do those with results that are
-// not finite.
+// The fixed range: numbers below 2^-27 of their tensor's largest one have fewer than 24 bits, below 2^-52 none.  Beside larger ones that is
+// nothing where those meet weights like the others', but not where theirs are zero or as small as the numbers are large (channels with scales
+// of their own).  So the split counts such numbers by place (32 pixels, or a filter row), and a wavefront forms its outputs again on the fp32
+// instruction where one of them has no sum large enough to hide what the numbers under its block may have lost (kHalfFloor), as it does with
+// results that are not finite.
 #pragma once
 #include "conv_terms.h"
 
@@ -25,7 +26,8 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kHalfTop = 14;                 // exponent that the largest number gets
 constexpr int kHalfLow = 12;                 // lo is kept times 2^12
-constexpr float kHalfSmall = 0x1p-12f;       // a group all below this (and not zero) is marked
+constexpr float kHalfSmall = 0x1p-12f;       // numbers below this (and not zero) lose bits
+constexpr float kHalfFloor = 16.f;           // sums above this for each of them hide what they lose: see igemm_half_kernel
 constexpr int kHalfZeros = 256;               // zero bytes ahead of the gathered tensor's halves
 constexpr int kHalfFlush = 4;                // stages of 32 between two moves of the hi*hi sums
 
@@ -61,8 +63,9 @@ __device__ inline Half8 half8(float4 a, float4 b)  // of scaled numbers
     return r;
 }
 __device__ inline float4 ldexp4(float4 v, int e) { return make_float4(ldexpf(v.x, e), ldexpf(v.y, e), ldexpf(v.z, e), ldexpf(v.w, e)); }
-__device__ inline float abs_max4(float4 v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); }
-__device__ inline bool any4(float4 v) { return v.x != 0.f || v.y != 0.f || v.z != 0.f || v.w != 0.f; }
+// how many of these numbers are not zero and, scaled, too small for the halves to hold their bits
+__device__ inline unsigned tiny1(float v, float scaled) { return v != 0.f && fabsf(scaled) < kHalfSmall; }
+__device__ inline unsigned tiny4(float4 v, float4 scaled) { return tiny1(v.x, scaled.x) + tiny1(v.y, scaled.y) + tiny1(v.z, scaled.z) + tiny1(v.w, scaled.w); }
 
 // ---- preparation: two launches for both operands of a call -----------------------------------------------------------------
 // First: the largest finite magnitude of each workgroup's share; marks cleared.
@@ -178,24 +181,15 @@ static __global__ __launch_bounds__(256) void half_split_kernel(HalfPrep p)
             low_at = (int)((q + 4) ^ sw) - (int)(q ^ sw);
             mark = o.marks + row;
         }
-        const bool some = any4(a) || any4(c);
+        const float4 a0 = a, c0 = c;
         a = ldexp4(a, up);
         c = ldexp4(c, up);
         const Half8 h = half8(a, c);
         hi[0] = h.hi;
         hi[low_at] = h.lo;
-        // a group of 32 channels, all of it tiny: with the lanes of the same group where they are neighbours, else by eights
-        float m = fmaxf(abs_max4(a), abs_max4(c));
-        bool s = some;
-        if (o.kind != kHalfFlipped) {
-#pragma unroll
-            for (int d = 1; d < 4; d <<= 1) {
-                m = fmaxf(m, __shfl_xor(m, d, 64));
-                s = __shfl_xor((int)s, d, 64) || s;
-            }
-        }
-        if (s && m < kHalfSmall) {
-            *mark = 1u;
+        const unsigned tiny = tiny4(a0, a) + tiny4(c0, c);
+        if (tiny) {
+            atomicAdd(mark, tiny);
             *o.any = 1u;
         }
     }
@@ -295,6 +289,7 @@ __device__ __forceinline__ void half_finish(const IgemmP &p, int lane, int wm, i
 
 // A wavefront's block formed on the fp32 instruction straight from memory (see igemm_join_split): results that are not finite, or
 // operands that the halves do not hold.
+constexpr int kAgainLoads = 4;  // groups of four elements (16-byte loads instead took 1.4 - 1.9 times as long where every block came here)
 template <int MI, int NI>
 __device__ __forceinline__ void half_again(const IgemmP &p, int lane, int mw, int nw, int first, int end, floatx4 (&acc)[MI][NI])
 {
@@ -311,35 +306,56 @@ __device__ __forceinline__ void half_again(const IgemmP &p, int lane, int mw, in
 #pragma unroll
         for (int j = 0; j < NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int kc = first; kc < end; ++kc)
-        for (int k2 = 0; k2 < kBK; k2 += 4) {
-            const int chunk = (int)fdiv(kc, p.div_rs), tap = kc - chunk * (p.R * p.S), c = chunk * kBK + k2 + kl;
-            const int r = (int)fdiv(tap, p.div_s), sx = tap - r * p.S;
-            float va[MI], vb[NI];
+    floatx4 run[MI][NI];  // sums of 128 elements, added up in acc
+    for (int kc = first; kc < end; ++kc) {
+        if ((kc - first) % kHalfFlush == 0)
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                const int ih = ih0[i] + r, iw = iw0[i] + sx;
-                const bool ok = (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
-                va[i] = ok ? p.a[(unsigned)(base[i] + (ih * p.IW + iw) * p.Cin + c)] : 0.f;
-                if (p.in_scale && ok) va[i] = fmaxf(fmaf(va[i], p.in_scale[c], p.in_shift[c]), 0.f);
-            }
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                const int col = nw + j * 16 + pl;
-                vb[j] = 0.f;
-                if (col < p.Nout) {
-                    if (p.flip_taps) {  // the filter as it is, [k][tap][row]: see half_split_kernel
-                        vb[j] = p.b[((long)c * p.flip_taps + (p.flip_taps - 1 - tap)) * p.Nout + col];
-                    } else {
-                        vb[j] = p.b[(long)col * p.Kdim + tap * p.Cin + c];
+                for (int j = 0; j < NI; ++j) {
+                    if (kc > first) acc[i][j] += run[i][j];
+                    run[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
+        const int chunk = (int)fdiv(kc, p.div_rs), tap = kc - chunk * (p.R * p.S);
+        const int r = (int)fdiv(tap, p.div_s), sx = tap - r * p.S;
+#pragma unroll 1
+        for (int k2 = 0; k2 < kBK; k2 += 4 * kAgainLoads) {
+            float va[kAgainLoads][MI], vb[kAgainLoads][NI];  // in flight together
+#pragma unroll
+            for (int q = 0; q < kAgainLoads; ++q) {
+                const int c = chunk * kBK + k2 + 4 * q + kl;
+#pragma unroll
+                for (int i = 0; i < MI; ++i) {
+                    const int ih = ih0[i] + r, iw = iw0[i] + sx;
+                    const bool ok = (unsigned)ih < (unsigned)p.IH && (unsigned)iw < (unsigned)p.IW;
+                    va[q][i] = ok ? p.a[(unsigned)(base[i] + (ih * p.IW + iw) * p.Cin + c)] : 0.f;
+                    if (p.in_scale && ok) va[q][i] = fmaxf(fmaf(va[q][i], p.in_scale[c], p.in_shift[c]), 0.f);
+                }
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const int col = nw + j * 16 + pl;
+                    vb[q][j] = 0.f;
+                    if (col < p.Nout) {
+                        if (p.flip_taps) {  // the filter as it is, [k][tap][row]: see half_split_kernel
+                            vb[q][j] = p.b[((long)c * p.flip_taps + (p.flip_taps - 1 - tap)) * p.Nout + col];
+                        } else {
+                            vb[q][j] = p.b[(long)col * p.Kdim + tap * p.Cin + c];
+                        }
                     }
                 }
             }
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+            for (int q = 0; q < kAgainLoads; ++q)
 #pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb[j], va[i], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) run[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb[q][j], va[q][i], run[i][j], 0, 0, 0);
         }
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] += run[i][j];
 }
 
 // The launch parameters read again where they are needed: held in scalar registers through the loop they spill into vector registers, and
@@ -524,26 +540,43 @@ __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_ha
         buf ^= 1;
         const int l2 = opaque_tid() & 63, down = -(p.half_up[0] + p.half_up[1]);
         float probe = 0.f;  // NaN when a sum is not finite
+        // A counted number loses at most 2^-20.4 of its scaled product (2^-37 of quantum and 2^-36 of the dropped lo*lo, times a number below 2^15).
+        // An output one of whose partial sums shows that its products' magnitudes add up to 16 for each of them loses less than 2^-24 of that.
+        // (|lo| is at most twice |hi|: its sums show it from 8 times as much on.)  Three sums that rarely cancel together.
+        float least = 3.4e38f;
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i) {
+            const bool row = it.m0 + wm * WTM + i * 16 + (l2 & 15) < p.M;
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+            for (int j = 0; j < NI; ++j) {
+                float m = 3.4e38f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m = fminf(m, fmaxf(fmaxf(fabsf(acc[i][j][e]), fabsf(top[i][j][e])), 0.125f * fabsf(low[i][j][e])));
+                least = row && it.n0 + wn * WTN + j * 16 + 4 * (l2 >> 4) < p.Nout ? fminf(least, m) : least;
+                asm volatile("" : "+v"(least));  // now: put off to the branch that reads it, it would keep three sets of sums in registers
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float v = fmaf(low[i][j][e], 1.f / (float)(1 << kHalfLow), acc[i][j][e] + top[i][j][e]);
                     acc[i][j][e] = ldexpf(v, down);
                     probe = fmaf(acc[i][j][e], 0.f, probe);
                 }
+            }
+        }
         bool again = probe != probe;
-        if (p.half_any[0]) {  // marks of small operands, rare: of the pixels under this block's rows (whole image rows), of its filter rows
+        const float elements = (float)((it.kc_end - it.kc_begin) * kBK);
+        if (p.half_any[0] && __any(least < kHalfFloor * elements)) {  // their number under this block's rows (whole image rows), and in its filter rows
             const int mw = it.m0 + wm * WTM, nw = it.n0 + wn * WTN;
             int cls, n, oh, ow, n2, oh2, c2;
             decode_row(p, min(mw, p.M - 1), cls, n, oh, ow);
             decode_row(p, min(mw + WTM, p.M) - 1, c2, n2, oh2, ow);
             const int h0 = max(0, oh * p.so + p.off), h1 = min(p.IH - 1, oh2 * p.so + p.off + p.R - 1);
             const int g0 = ((n * p.IH + h0) * p.IW) >> kHalfMarkShift, g1 = ((n2 * p.IH + h1) * p.IW + p.IW - 1) >> kHalfMarkShift;
-            for (int g = g0 + l2; g <= g1; g += 64) again |= p.half_marks[0][g] != 0;
-            for (int g = nw + l2; g < min(nw + WTN, p.Nout); g += 64) again |= p.half_marks[1][g] != 0;
+            float count = 0.f;
+            for (int g = g0 + l2; g <= g1; g += 64) count += (float)p.half_marks[0][g];
+            for (int g = nw + l2; g < min(nw + WTN, p.Nout); g += 64) count += (float)p.half_marks[1][g];
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) count += __shfl_xor(count, d, 64);
+            again |= least < kHalfFloor * fminf(count, elements);  // none: never
         }
         if (__any(again))
             half_again(p, l2, it.m0 + wm * WTM, it.n0 + wn * WTN, it.kc_begin, it.kc_end, acc);

@@ -154,6 +154,54 @@ def test_small_beside_large(what):
         assert _err(got, refs["fwd"]) <= 8e-7 and _err(got[part], refs["fwd"][part]) <= 8e-7, (plan, _err(got[part], refs["fwd"][part]))
 
 
+# A channel of large numbers hides nothing of the others where its weights are zero or as small: 2^-27 of the largest number and below, the halves
+# hold fewer than 24 bits, below 2^-52 none.  Formed again, a sum of 1440 products on the fp32 instruction in parts of 128: the parts' sums round at every
+# other product, 2^-24/sqrt(3) * sqrt(64), a dozen additions of the parts 2^-24/sqrt(3) * sqrt(12/2) more: 2.9e-7, a third more for other draws.
+AGAIN_BAR = 3.9e-7
+
+
+@pytest.mark.parametrize("b", [28, 32, 40, 56, 100])
+@pytest.mark.parametrize("what", ["zero", "inverse", "one row", "filter"])
+def test_channels_of_other_scales(what, b):
+    case = n, c, h, k, r, stride = CASES[6]
+    x, w, dy = _operands(case, 29)
+    g = torch.Generator().manual_seed(b)
+    if what == "zero":          # one channel of each group of 32, without weights
+        x[..., 3::32] *= 2.0 ** b
+        w[..., 3::32] = 0
+        dy[..., 5::32] *= 2.0 ** b
+        w[5::32] = 0
+    elif what == "inverse":     # every channel a scale of its own, its weights the inverse: all products count alike
+        e, f = torch.randint(0, b + 1, (c,), generator=g).float(), torch.randint(0, b + 1, (k,), generator=g).float()
+        x, dy, w = x * 2.0 ** e, dy * 2.0 ** f, w * 2.0 ** -e * 2.0 ** -f.reshape(k, 1, 1, 1)
+    elif what == "one row":     # large beside them in the same block: the outputs of every other filter row and channel
+        x[..., 3] *= 2.0 ** b
+        w[17, :, :, 3] = 0
+        dy[..., 5] *= 2.0 ** b
+        w[5, :, :, 19] = 0
+    else:                       # the filter's numbers are the large ones
+        w[1:, :, :, 3] *= 2.0 ** b
+        x[..., 3] = 0
+        w[5, :, :, 4:] *= 2.0 ** b
+        dy[..., 5] = 0
+    refs = _refs(case, x, w, dy)
+    for plan in PLANS:
+        for o, got in _run(case, plan, x, w, dy, only=("fwd", "bwd_data")).items():
+            ref = refs[o]
+            if what == "inverse":   # outputs have their channels' scales: each channel by itself
+                for ch in range(got.shape[-1]):
+                    assert _err(got[..., ch], ref[..., ch]) <= 2 * AGAIN_BAR, (plan, o, ch, _err(got[..., ch], ref[..., ch]))   # 180 and fewer outputs
+                continue
+            if what == "one row":
+                ch = 17 if o == "fwd" else 19
+                assert _err(got[..., ch], ref[..., ch]) <= 2 * AGAIN_BAR, (plan, o, _err(got[..., ch], ref[..., ch]))
+            elif what == "filter" and o == "bwd_data":   # channel 3's weights are the large ones
+                assert _err(got[..., 3], ref[..., 3]) <= 2 * AGAIN_BAR
+                keep = [i for i in range(c) if i != 3]
+                got, ref = got[..., keep], ref[..., keep]
+            assert _err(got, ref) <= AGAIN_BAR, (plan, o, _err(got, ref))
+
+
 def test_zeros_and_a_single_number():
     case = n, c, h, k, r, stride = CASES[6]
     x, w, dy = _operands(case, 25)
