@@ -313,7 +313,9 @@ static IgemmPlan plan_igemm_kind(const rn50_conv_desc *d, int op, long M, int No
         IgemmPlan half{};
         for (const PlanRow &t : cfg->operand_plans)
             if (plan_matches(t, d, op) && (t.bm == 64 || t.bn == 64)) half = make_igemm_plan(kHalf, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
-        if (!half.grid && M >= kPlanesMinRows && flops >= kHalfMinFlops) {
+        bool pre_row = false;  // a row for igemm_pre_kernel goes before the choice below
+        for (const PlanRow &t : cfg->pre_plans) pre_row |= geometry && plan_matches(t, d, op);
+        if (!half.grid && !pre_row && M >= kPlanesMinRows && flops >= kHalfMinFlops) {
             const IgemmPlan other = plan_igemm_kind(d, op, M, Nout, Kdim, allow_split, cin, kNoHalf, given);
             if (!half_as_precise(fwd, other.full_items || other.tail_split < 2 ? Kdim : (double)Kdim / other.tail_split)) return other;
             half = model_plan(kHalf, M, Nout, kchunks, bk, allow_split);

@@ -235,6 +235,23 @@ def test_options_are_a_snapshot_replaced_as_a_whole():
     assert rn.rn50_conv_workspace_bytes(tuned, rn.OP_BWD_WEIGHT) == with_table
 
 
+@pytest.mark.parametrize("plan", [(128, 128, 1), (128, 64, 2), (64, 128, 1), (64, 64, 3)])
+@pytest.mark.parametrize("case", [(2, 256, 29, 704, 3, 1, 1), (6, 256, 30, 832, 3, 2, 1), (8, 640, 62, 1088, 1, 2, 0)])
+def test_rows_for_prepared_filters_are_taken(case, plan):
+    """A row of "pre_plans" sets the plan of a call that takes a prepared filter, whatever the call would choose by itself."""
+    n, c, h, k, r, stride, pad = case
+    d = rn.conv_desc(n, c, h, h, k, r, r, stride, pad)
+    for op in (rn.OP_FWD, rn.OP_BWD_DATA):
+        if op == rn.OP_BWD_DATA and r > 1 and stride == 2 and plan[0] == 128:
+            continue   # a dilated gather has tiles of 64 rows only
+        rn.rn50_set_option("pre_plans", "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d" % (op, *case, *plan))
+        try:
+            got = rn.rn50_conv_plan(d, op)
+        finally:
+            rn.rn50_set_option("pre_plans", None)
+        assert got[:2] == plan[:2], (op, got)
+
+
 def test_conv_fwd_bnstats_argument_errors():
     L = rn.lib()
     d0 = rn.conv_desc(32, 256, 14, 14, 256, 3, 3, 1, 1)
