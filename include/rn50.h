@@ -86,6 +86,12 @@ const char *rn50_last_error(void);
  *   "split_products" 0/1  rn50_activation_bytes and rn50_create (fp32 contexts): the training step's forward pass forms its products like the conv2d_* calls and
  *                         the backward pass, from operands split into bf16 terms (faster, smaller error), instead of on the fp32
  *                         instruction (default 0: the forward pass keeps its bits, and with them every ReLU decision)
+ *   "half_products"  0..3 forward and data-gradient calls with fp32 operands whose sums are long (700 products and more, 480 in data gradients) form
+ *                         their products from fp16 halves where that is faster: 1 the forward pass, 2 data gradients (default 3; a call of a
+ *                         context plans by the options of that call).  Relative error 1.0e-7 to 1.25e-7 whatever the operands, where bf16 terms
+ *                         leave 1.3e-7 to 2.0e-7 on dense ones, 0.9e-7 to 1.1e-7 with 80 % zeros in one of them, 0.7e-7 to 0.8e-7 with 90 %, and
+ *                         nothing where a filter row has a single weight of 1 (halves: 4.4e-8): 0 for operands of mostly zeros.  And 0 for
+ *                         operands whose magnitudes spread over 2^27 and more: much of the output is formed twice then (up to ten times as long)
  *   "wgrad_group"    0..64 rn50_create (fp32 contexts): 0 = one filter-gradient call per layer (default); k > 0 = the layers
  *                         of k consecutive blocks in one conv2d_bwd_weight_group launch (16 or more: all 52 behind the first)
  *   "wgrad_group_stages"  pixel stages of 32 per work item of a grouped plan (default 48, at least 2; rn50_create: at least 16)
@@ -99,8 +105,9 @@ int rn50_set_option(const char *name, const char *value_or_null);
  * Cross-correlation, zero padding, square stride, no bias:
  *   y[n,p,q,k] = sum_{r,s,c} x[n, p*stride+r-pad, q*stride+s-pad, c] * w[k,r,s,c]
  * with P = (H + 2*pad - R)/stride + 1 (floor), Q likewise.
- * RN50_DTYPE_F32: operands of any magnitude keep their 24 bits, infinities and NaNs reach the outputs they would reach in fp32
- * arithmetic.  Where a result is not finite, or an operand is 2^111 or a result 2^95 and more, its part of the output (32 x 32
+ * RN50_DTYPE_F32: operands of any magnitude keep their 24 bits (as fp16 halves, see the option "half_products", 23), infinities and NaNs reach the
+ * outputs they would reach in fp32 arithmetic.  Where a result is not finite, or an operand is 2^111 or a result 2^95 and more, or,
+ * with halves, where operands below 2^-27 of their tensor's largest number may decide an output, its part of the output (32 x 32
  * to 64 x 64 elements) is formed a second time, by a slower instruction.
  * ------------------------------------------------------------------------------------------ */
 typedef struct {

@@ -33,6 +33,7 @@ struct Config {
     bool no_tuned = false;     // ignore the measured plan table (cost model only)
     bool no_stem_kernel = false;  // first layer through the implicit GEMM
     bool split_products = false;  // rn50_create: the training step's forward pass with split operands as well
+    int half_products = 3;        // calls with fp32 operands that may choose fp16 halves: 1 forward, 2 data gradients
     bool conv_bn_stats = true;    // rn50_create: forward convolutions gather the BN statistics of their output
     int wgrad_group = 0;          // rn50_create: filter gradients launched per layer (0) or grouped, this many blocks to a launch
     int wgrad_group_wgs_per_cu = 0;  // grouped filter gradients: at most this many workgroups of theirs per CU (0: what fits)

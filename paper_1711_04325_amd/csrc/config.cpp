@@ -48,6 +48,7 @@ static bool apply_option(Config &c, const char *name, const char *value)
     else if (!strcmp(name, "no_stem_kernel")) c.no_stem_kernel = unset ? false : atoi(value) != 0;
     else if (!strcmp(name, "conv_bn_stats")) c.conv_bn_stats = unset ? def.conv_bn_stats : atoi(value) != 0;
     else if (!strcmp(name, "split_products")) c.split_products = unset ? false : atoi(value) != 0;
+    else if (!strcmp(name, "half_products")) c.half_products = unset ? def.half_products : (atoi(value) & 3);
     else if (!strcmp(name, "wgrad_group")) c.wgrad_group = unset ? def.wgrad_group : std::max(0, std::min(64, atoi(value)));
     else if (!strcmp(name, "wgrad_group_stages")) c.wgrad_group_stages = unset ? def.wgrad_group_stages : std::max(2, atoi(value));
     else if (!strcmp(name, "wgrad_group_wgs_per_cu")) c.wgrad_group_wgs_per_cu = unset ? def.wgrad_group_wgs_per_cu : std::max(0, std::min(8, atoi(value)));
@@ -78,7 +79,7 @@ static std::shared_ptr<const Config> g_cfg;
 
 static std::shared_ptr<const Config> from_environment()
 {
-    static const char *const names[] = {"side_stream", "fuse_bn", "relu_mask", "no_tuned", "no_stem_kernel", "conv_bn_stats", "split_products", "igemm_plan", "wgrad_plan", "wgrad_group",
+    static const char *const names[] = {"side_stream", "fuse_bn", "relu_mask", "no_tuned", "no_stem_kernel", "conv_bn_stats", "split_products", "half_products", "igemm_plan", "wgrad_plan", "wgrad_group",
                                         "wgrad_group_stages", "wgrad_group_tile", "wgrad_group_wgs_per_cu",
                                         "plan_overrides", "pre_plans", "operand_plans", "small_plans"};
     auto c = std::make_shared<Config>();

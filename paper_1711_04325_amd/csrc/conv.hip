@@ -262,7 +262,10 @@ static Fp32Math less_room(Fp32Math math) { return math == kFp32Split ? kNoHalf :
 // Operands as fp16 halves (conv_half.h) where that is as precise as the call's other plan, whose sums of `piece` elements are the longest.
 // Relative error against 64 bits, halves / bf16 terms (90 calls): forward behind a ReLU 1.07 - 1.26e-7 whatever the length, with terms 0.9 - 1.2e-7 in
 // pieces of 300 - 650 elements, 1.24e-7 in 768, 1.43e-7 in 1024, 1.5e-7 in 1152; data gradients 1.11 - 1.31e-7, with terms 1.47e-7 in 512,
-// 1.55e-7 in 576, 2.1e-7 in 1152 (1.2 - 1.5e-7 in 384).
+// 1.55e-7 in 576, 2.1e-7 in 1152 (1.2 - 1.5e-7 in 384).  What the halves drop stays where most of an operand is zeros, the roundings of a long sum do not:
+// with 80, 90, 97 % zeros in either operand 1.04 - 1.18e-7, 0.97 - 1.12e-7, 0.88 - 1.04e-7, with terms 0.87 - 1.06e-7, 0.69 - 0.82e-7, 0.45 - 0.6e-7 (14 calls);
+// in data gradients in pieces of 512 with 50 % already (1.14e-7, 0.98e-7).  The option half_products is for such operands.  A line at 700 for data
+// gradients as well: the step at N = 32 9.42 -> 9.63 ms.
 static bool half_as_precise(bool fwd, double piece) { return piece >= (fwd ? 700 : 480); }
 // Preparing both operands (two launches and one more gap than the other plan has; the gathered tensor is read twice and written once), in microseconds;
 // what the other plan takes beyond igemm_pre_cost: the filter's preparation, in a data gradient its flip.
@@ -315,7 +318,7 @@ static IgemmPlan plan_igemm_kind(const rn50_conv_desc *d, int op, long M, int No
             if (plan_matches(t, d, op) && (t.bm == 64 || t.bn == 64)) half = make_igemm_plan(kHalf, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
         bool pre_row = false;  // a row for igemm_pre_kernel goes before the choice below
         for (const PlanRow &t : cfg->pre_plans) pre_row |= geometry && plan_matches(t, d, op);
-        if (!half.grid && !pre_row && M >= kPlanesMinRows && flops >= kHalfMinFlops) {
+        if (!half.grid && !pre_row && (cfg->half_products & (fwd ? 1 : 2)) && M >= kPlanesMinRows && flops >= kHalfMinFlops) {
             const IgemmPlan other = plan_igemm_kind(d, op, M, Nout, Kdim, allow_split, cin, kNoHalf, given);
             if (!half_as_precise(fwd, other.full_items || other.tail_split < 2 ? Kdim : (double)Kdim / other.tail_split)) return other;
             half = model_plan(kHalf, M, Nout, kchunks, bk, allow_split);

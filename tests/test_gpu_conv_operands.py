@@ -228,6 +228,34 @@ def test_values_without_halves(plan):
         assert fine.any() and torch.isfinite(got[fine]).all() and ((got.double() - ref)[fine].norm() / ref[fine].norm()).item() <= 1.5e-6, o
 
 
+@pytest.mark.parametrize("op", ["fwd", "bwd_data"])
+def test_option_for_operands_of_mostly_zeros(op):
+    """Halves drop bits whatever the operands, six bf16 products next to none: half_products = 0 keeps a call on the latter.  Bars: the largest of 14 calls
+    measured, a tenth more for other draws; a number that is copied loses up to 2^-23 in halves."""
+    n, c, h, k, r = 16, 128, 28, 128, 3
+    o = rn.OP_FWD if op == "fwd" else rn.OP_BWD_DATA
+    g = torch.Generator().manual_seed(61)
+    x = torch.randn(n, h, h, c, generator=g) * (torch.rand(n, h, h, c, generator=g) < 0.1)
+    w, same = torch.randn(k, r, r, c, generator=g) * (2.0 / (c * r * r)) ** 0.5, torch.zeros(k, r, r, c)
+    same[:, 1, 1] = torch.eye(c)
+    d = rn.conv_desc(n, c, h, h, k, r, r, 1, 1)
+    ref = _refs((n, c, h, k, r, 1), x, w, x)[op]
+    ws = ws_bytes(64 << 20)
+    err, copy = {}, {}
+    for option in ("0", "3"):
+        rn.rn50_set_option("half_products", option)
+        try:
+            assert rn.rn50_conv_workspace_bytes(d, o) <= ws.numel()
+            for f in (w, same):
+                out = torch.full_like(x, 7.0).cuda()
+                (rn.conv2d_fwd if op == "fwd" else rn.conv2d_bwd_data)(d, x.cuda(), f.cuda(), out, ws)
+                (err if f is w else copy)[option] = out.cpu()
+        finally:
+            rn.rn50_set_option("half_products", None)
+    assert torch.equal(copy["0"], x) and not torch.equal(copy["3"], x) and ((copy["3"] - x).abs() <= 2.0 ** -23 * x.abs()).all()
+    assert _err(err["0"], ref) <= 9.0e-8 and _err(err["3"], ref) <= 1.24e-7
+
+
 # ---- calls that do not fill the chip (igemm_small_kernel) ----------------------------------------------------------------------------------
 SMALL = ["16,16,1", "32,16,1", "16,32,1", "32,32,1"]
 # sums of a 16th of the reduction or less on the fp32 instruction (1440 / 16 products, rounded at every other: 2e-7), then five additions
