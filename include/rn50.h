@@ -75,7 +75,9 @@ const char *rn50_last_error(void);
  *   "operand_plans"  the same rows for calls with fp32 operands both of which are prepared beforehand (forward pass and data gradient as
  *                    fp16 halves, filter gradient split into bf16 terms; tiles of 128 x 64, 64 x 128, 64 x 64), whatever the call would choose
  *   "small_plans"    the same rows for forward and data-gradient calls with fp32 operands that do not fill the chip (tiles of 16 or 32 rows and
- *                    columns; the split says nothing), whatever the call would choose
+ *                    columns; the split says nothing), whatever the call would choose of the kernels that take both operands as they are.  Rows
+ *                    for other calls say nothing (channels of the gathered tensor no multiple of 32, columns no multiple of 4, strided data
+ *                    gradients beyond 1x1): see rn50_conv_plan.  conv2d_fwd_bnstats may need more workspace under a row
  *   "pre_plans"      the same rows for the forward and data-gradient calls whose kernel takes a filter prepared beforehand (fp32 operands
  *                         split into bf16 terms, or bf16 activations).  igemm_plan and plan_overrides send these calls to the general
  *                         kernel instead; for filter gradients wgrad_plan and plan_overrides set the tile and the cut only
@@ -127,8 +129,8 @@ size_t rn50_conv_workspace_bytes(const rn50_conv_desc *d, int op);
 /* The launch plan the given operation would use for this shape, for reports: tile of bm output rows x bn output columns
  * (output pixels x channels for the forward pass and the data gradient, output channels x filter elements for the filter
  * gradient), number of pieces the reduction is cut into (forward / data gradient: only the last, partial round of tiles
- * is cut; 1 = no partial sums in memory) and workgroups of the main kernel (RN50_OP_FWD_BNSTATS: the forward plan).  Any output
- * pointer may be NULL.  Host only. */
+ * is cut; 1 = no partial sums in memory) and workgroups of the main kernel (RN50_OP_FWD_BNSTATS: the forward plan), with the workspace that
+ * the query names.  Any output pointer may be NULL.  Host only. */
 int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn, int *split, int *workgroups);
 
 /* y (N x P x Q x K) = conv(x, w).  ws may be NULL when the required size is 0. */

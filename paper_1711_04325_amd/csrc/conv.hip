@@ -371,7 +371,7 @@ static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, i
     IgemmPlan s{};
     const std::shared_ptr<const Config> cfg = config();
     const double gflop = 2e-9 * M * Nout * Kdim;
-    if (bf16_of(d) || cin % kBK || Nout % 4 || d->r * d->s > 32 || other.kind != kGeneral || other.products || cfg->has_igemm_plan ||
+    if (bf16_of(d) || cin % kBK || Nout % 4 || d->r * d->s > 32 || other.kind != kGeneral || cfg->has_igemm_plan ||
         (op == RN50_OP_BWD_DATA && d->stride > 1 && !is_scatter2(d)))
         return s;
     s.kind = kSmall;
@@ -381,11 +381,11 @@ static IgemmPlan plan_small(const rn50_conv_desc *d, int op, long M, int Nout, i
         s.full_items = s.grid = ceil_div(M, bm) * ceil_div(Nout, bn);
     };
     for (const PlanRow &t : cfg->small_plans)
-        if (plan_matches(t, d, op) && fits(t.bm)) {
+        if (plan_matches(t, d, op)) {  // whatever it needs: plan_fwd_stats makes room
             set(t.bm, t.bn);
             return s;
         }
-    if (gflop > 1.0 || !cfg->overrides.empty()) return s;
+    if (gflop > 1.0 || other.products || !cfg->overrides.empty()) return s;
     // the other way: with an ordered sum, or one launch (its reduction is short then)
     double best = 0.9 * (beside + (other.tail_split > 1 ? 7.2 + 0.0018 * Kdim + 12.0 * std::max(0.0, gflop - 0.1) : 5.6 + 0.012 * std::min(Kdim, 256) + 8.0 * gflop));
     for (int bm = 16; bm <= 32; bm += 16)
@@ -807,6 +807,16 @@ static size_t stat_room(const rn50_conv_desc *d, const Geom &ge, int rows)
 {
     return align_up(std::max((size_t)2 * ceil_div(ge.Mout, rows) * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
 }
+// plan_small for a call whose plan is pl.  Forward pass: with and without statistics the same kernel; eval: the normalising pass is its write-out.
+static IgemmPlan small_fwd(const rn50_conv_desc *d, const Geom &ge, const IgemmPlan &pl, bool eval = false)
+{
+    return plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, eval ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0, eval || d->k % 4 ? 0 : stat_room(d, ge, pl.bm));
+}
+static IgemmPlan small_bwd(const rn50_conv_desc *d, const BwdDataPlan &b, bool flipped)
+{
+    const Geom ge = geom(d);
+    return plan_small(d, RN50_OP_BWD_DATA, b.scatter ? ge.Mout : ge.Min, d->c, d->r * d->s * d->k, d->k, b.g, flipped ? 0.0 : kFlipLaunch);
+}
 static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool given = false)
 {
     const Geom ge = geom(d);
@@ -817,10 +827,11 @@ static FwdStatsPlan plan_fwd_stats(const rn50_conv_desc *d, Fp32Math math, bool 
     f.conv_bytes = align_up(igemm_part_bytes(f.g) + f.g.prep_bytes, 256);
     f.stat_bytes = stat_room(d, ge, f.rows);
     if (math == kFp32Split || math == kNoHalf) {
-        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, f.g, 0.0, f.stat_bytes);
+        const IgemmPlan sm = small_fwd(d, ge, f.g);
         if (sm.grid) {
             f.rows = sm.bm;
             f.tiles_m = ceil_div(ge.Mout, f.rows);
+            f.stat_bytes = std::max(f.stat_bytes, stat_room(d, ge, f.rows));
         }
     }
     return f;
@@ -883,10 +894,13 @@ extern "C" int rn50_conv_plan(const rn50_conv_desc *d, int op, int *bm, int *bn,
     const Geom ge = geom(d);
     int v[4];
     if (op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS || op == RN50_OP_BWD_DATA || op == RN50_OP_BWD_DATA_FLIPPED) {
-        const IgemmPlan pl = (op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) ? plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, false)
-                                                                                    : plan_bwd_data(d, kFp32Split).g;
+        const bool fwd = op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS;
+        const BwdDataPlan b = fwd ? BwdDataPlan{} : plan_bwd_data(d, kFp32Split);
+        IgemmPlan pl = fwd ? plan_igemm(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, true, d->c, kFp32Split, false) : b.g;
+        const IgemmPlan sm = fwd ? small_fwd(d, ge, pl) : small_bwd(d, b, op == RN50_OP_BWD_DATA_FLIPPED);
+        if (sm.grid) pl = sm;
         v[0] = pl.bm; v[1] = pl.bn; v[2] = pl.tail_tiles ? pl.tail_split : 1; v[3] = pl.grid;
-        if ((op == RN50_OP_FWD || op == RN50_OP_FWD_BNSTATS) && stem_layer(d) && (op == RN50_OP_FWD || !act_of(d) || stem_whole(ge))) {
+        if (fwd && stem_layer(d) && (op == RN50_OP_FWD || !act_of(d) || stem_whole(ge))) {
             // the first layer's own forward kernel (same shapes as its filter-gradient kernel): tiles of 8 x 16 pixels x 64 filters
             v[0] = kStemTH * kStemTW; v[1] = 64; v[2] = 1;
             v[3] = std::min(d->n * ceil_div(ge.P, kStemTH) * ceil_div(ge.Q, kStemTW), (act_of(d) ? 3 : 2) * (int)kCUs);
@@ -950,8 +964,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     // evaluation (ap): single images.  With more the gain is small, and a larger share of the layers would round otherwise than the training forward
     // does, whose logits evaluation reproduces to 1e-6
     if (math == kFp32Split || math == kNoHalf || (ap && (double)ge.Mout * d->k * ge.Kdim < 7.5e7)) {
-        const IgemmPlan sm = plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, ap ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0,
-                                        ap || d->k % 4 ? 0 : stat_room(d, ge, pl.bm));  // with and without statistics the same kernel
+        const IgemmPlan sm = small_fwd(d, ge, pl, ap != nullptr);
         if (sm.grid && (!stats || stat_rows == sm.bm)) pl = sm;
     }
     const bool swhole = stem_stats(d, ge, math);
@@ -1094,7 +1107,7 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
         }
     }
     if (math == kFp32Split || math == kNoHalf) {
-        const IgemmPlan sm = plan_small(d, RN50_OP_BWD_DATA, p.M, d->c, p.Kdim, d->k, b.g, flipped ? 0.0 : kFlipLaunch);
+        const IgemmPlan sm = small_bwd(d, b, flipped);
         if (sm.grid) b.g = sm;
     }
     p.flip_taps = (b.g.kind == kHalf || b.g.kind == kSmall) && !flipped ? d->r * d->s : 0;
@@ -1132,7 +1145,7 @@ extern "C" int conv2d_bwd_data(const rn50_conv_desc *d, const float *dy, const f
     // workspace = [flipped filter][partial tiles]
     char *rest = (char *)ws + b.wt_bytes;
     // the halves' preparation flips as well, and igemm_small_kernel reads the filter as it is
-    if (b.g.kind == kHalf || (math != kNoPlanes && plan_small(d, RN50_OP_BWD_DATA, b.scatter ? geom(d).Mout : geom(d).Min, d->c, d->r * d->s * d->k, d->k, b.g, kFlipLaunch).grid))
+    if (b.g.kind == kHalf || (math != kNoPlanes && small_bwd(d, b, false).grid))
         return conv_bwd_data_pretransposed(math, d, dy, w, dx, rest, ws_bytes - b.wt_bytes, st, nullptr, false);
     float *wt = (float *)ws;
     launch_filter_flip(d->k, d->c, d->r * d->s, w, wt, st);

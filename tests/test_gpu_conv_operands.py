@@ -275,6 +275,10 @@ def test_small_calls(case, plan):
     d = rn.conv_desc(n, c, h, h, k, r, r, stride, r // 2)
     rn.rn50_set_option("small_plans", ";".join("%d,%d,%d,%d,%d,%d,%d,%d,%s" % (o, n, c, h, k, r, stride, r // 2, plan) for o in (rn.OP_FWD, rn.OP_BWD_DATA)))
     try:
+        assert "%d,%d" % rn.rn50_conv_plan(d, rn.OP_FWD)[:2] == plan[:-2]   # the kernel named here runs
+        small = k % 32 == 0 and (stride == 1 or (r == 1 and h % 2 == 0))
+        for op in (rn.OP_BWD_DATA, rn.OP_BWD_DATA_FLIPPED):
+            assert ("%d,%d" % rn.rn50_conv_plan(d, op)[:2] == plan[:-2]) == small
         fx, fw, fdy = x.cuda(), w.cuda(), dy.cuda()
         y, yf, dx, dxf, ys = (torch.full_like(t, 7.0) for t in (fdy, fdy, fx, fx, fdy))
         ws = ws_bytes(rn.rn50_conv_workspace_bytes(d, rn.OP_FWD_BNSTATS) + rn.rn50_conv_workspace_bytes(d, rn.OP_BWD_DATA))
