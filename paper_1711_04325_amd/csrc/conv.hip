@@ -359,7 +359,7 @@ static IgemmPlan plan_igemm(const rn50_conv_desc *d, int op, long M, int Nout, i
 }
 
 // igemm_small_kernel for a call of fp32 operands whose plan is `other` (grid 0: it stays with that).  It needs no workspace; a call needs what its query
-// names all the same.  beside: microseconds that the other way takes beyond its launches (the normalising pass or the filter's flip).
+// names all the same.  beside: microseconds that the other way takes beyond its launches (the filter's flip).
 // Modelled times of both, in microseconds, from 220 calls of 0.006 - 3 GFLOP, forward and data gradients.
 // Calls with split operands stay (0.2 GFLOP and more; half the error).
 // stat_room: bytes for the statistics of its row tiles (0: the call takes none); a tile whose statistics need more is not taken, so that the workspace
@@ -678,8 +678,8 @@ static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
     p.div_s = make_fastdiv(p.S);
     p.div_rs = make_fastdiv(p.R * p.S);
     if (pl.kind == kSmall) {
-        launch_igemm_small(pl.bm, pl.bn, pl.grid, p, ap, st);
-        return ap != nullptr;
+        launch_igemm_small(pl.bm, pl.bn, pl.grid, p, st);
+        return false;
     }
     if (pl.kind == kHalf) {
         launch_igemm_half(pl.bm, pl.bn, pl.grid, p, st);
@@ -807,10 +807,10 @@ static size_t stat_room(const rn50_conv_desc *d, const Geom &ge, int rows)
 {
     return align_up(std::max((size_t)2 * ceil_div(ge.Mout, rows) * d->k * sizeof(float), rn50_bn_workspace_bytes(d->n, d->k, ge.P, ge.Q)), 256);
 }
-// plan_small for a call whose plan is pl.  Forward pass: with and without statistics the same kernel; eval: the normalising pass is its write-out.
-static IgemmPlan small_fwd(const rn50_conv_desc *d, const Geom &ge, const IgemmPlan &pl, bool eval = false)
+// plan_small for a call whose plan is pl.  Forward pass: with and without statistics the same kernel.
+static IgemmPlan small_fwd(const rn50_conv_desc *d, const Geom &ge, const IgemmPlan &pl)
 {
-    return plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, eval ? (pl.tail_split > 1 ? 0.5 : 3.0) : 0.0, eval || d->k % 4 ? 0 : stat_room(d, ge, pl.bm));
+    return plan_small(d, RN50_OP_FWD, ge.Mout, d->k, ge.Kdim, d->c, pl, 0.0, d->k % 4 ? 0 : stat_room(d, ge, pl.bm));
 }
 static IgemmPlan small_bwd(const rn50_conv_desc *d, const BwdDataPlan &b, bool flipped)
 {
@@ -961,10 +961,10 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
     }
     RN50_REQUIRE(ws_bytes >= need && (need == 0 || ws), RN50_EWORKSPACE, "%s: workspace too small (%zu < %zu)", who, ws_bytes, need);
     RN50_REQUIRE(!in_scale || act_of(d) != 2, RN50_EUNSUPPORTED, "%s: the fused input transform needs a bf16 or fp32 input of the variant's own type", who);
-    // evaluation (ap): single images.  With more the gain is small, and a larger share of the layers would round otherwise than the training forward
-    // does, whose logits evaluation reproduces to 1e-6
-    if (math == kFp32Split || math == kNoHalf || (ap && (double)ge.Mout * d->k * ge.Kdim < 7.5e7)) {
-        const IgemmPlan sm = small_fwd(d, ge, pl, ap != nullptr);
+    // (evaluation, ap, as the training forward of its context: the same sums, and so the same logits from a training batch's own statistics; with other
+    // sums those differ by 1.2e-5 for one to three images, whose 49 to 147 pixels in the last stage leave statistics that magnify roundings)
+    if (math == kFp32Split || math == kNoHalf) {
+        const IgemmPlan sm = small_fwd(d, ge, pl);
         if (sm.grid && (!stats || stat_rows == sm.bm)) pl = sm;
     }
     const bool swhole = stem_stats(d, ge, math);

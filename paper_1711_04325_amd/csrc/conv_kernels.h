@@ -1544,8 +1544,7 @@ struct HalfPrep {
     unsigned *marks;                   // cleared by the first launch
     int nmarks;
 };
-struct TailApply;
-void launch_igemm_small(int bm, int bn, int grid, const IgemmP &p, const TailApply *ap, hipStream_t st);
+void launch_igemm_small(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
 void launch_half_prep(const HalfPrep &p, hipStream_t st);
 // Both tensors of a filter gradient split into bf16 terms beforehand (conv_terms.h)
 constexpr int kTermsZeros = 256;  // zero bytes ahead of each

@@ -3,7 +3,7 @@
 // What bounded the general kernel there is a chain: tiles of 64 x 64 leave most CUs idle unless the reduction is cut over workgroups, whose partial tiles
 // a second launch then adds (2.4 us at the least), and a piece's stages pass one after the other through registers, LDS and two barriers.  Here the
 // reduction is cut over the wavefronts of one workgroup: each loads its fragments straight from memory (the operands are in the caches), all of several
-// stages in flight at once, and the partial tiles meet in LDS, where the sum is also normalised, or its statistics are gathered.
+// stages in flight at once, and the partial tiles meet in LDS, where the sum's statistics are gathered as well.
 #pragma once
 #include "conv_kernels.h"
 
@@ -28,9 +28,9 @@ constexpr int kSmallWaves = 4;  // 8 and 16 were as fast where one workgroup run
 // in eight): the matrix instruction's results follow each other at their full rate, and a sum has a 16th or 32nd of the reduction: errors against 64
 // bits are 0.4 - 1 times those of the pieces and their ordered sum before.
 // Cin % 32 == 0 (a stage stays inside one filter tap), Nout % 4 == 0, R*S <= 32, no dilation.  FLIP: the filter of a data gradient as it is, [k][tap][row].
-// INAFF: see IgemmP.  EPI 0: the output; 1: and what bn_apply_kernel makes of it (ap); 2: and its statistics per TM * 16 rows.
-template <int TM, int TN, bool FLIP, bool INAFF, int EPI>
-__global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmP p, TailApply ap)
+// INAFF: see IgemmP.  STATS: the output's statistics per TM * 16 rows as well.
+template <int TM, int TN, bool FLIP, bool INAFF, bool STATS>
+__global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmP p)
 {
     constexpr int W = kSmallWaves, U = TM + TN == 2 ? 4 : TM + TN == 3 ? 3 : 2;  // stages in flight
     __shared__ floatx4 red[W][TM * TN * 64];
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmP p,
         const floatx4 *r = &red[0][(i * TN + j) * 64 + lane];
         v[i] = (r[0] + r[TM * TN * 64]) + (r[2 * TM * TN * 64] + r[3 * TM * TN * 64]);
     }
-    if (EPI == 2) {
+    if (STATS) {
         const int valid = min(TM * 16, p.M - m0);
         float4 mean, m2;
 #pragma unroll
@@ -192,16 +192,6 @@ __global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmP p,
             *reinterpret_cast<floatx4 *>(&p.out[at + p.Nout]) = z;
             *reinterpret_cast<floatx4 *>(&p.out[at + 2l * p.OW * p.Nout]) = z;
             *reinterpret_cast<floatx4 *>(&p.out[at + (2l * p.OW + 1) * p.Nout]) = z;
-        }
-        if (EPI == 1) {
-            const float4 s = ldg4(ap.scale + col), t = ldg4(ap.shift + col);
-            float4 z = make_float4(fmaf(v[i][0], s.x, t.x), fmaf(v[i][1], s.y, t.y), fmaf(v[i][2], s.z, t.z), fmaf(v[i][3], s.w, t.w));
-            if (ap.residual) {
-                const float4 r = ldg4(ap.residual + at);
-                z = make_float4(z.x + r.x, z.y + r.y, z.z + r.z, z.w + r.w);
-            }
-            if (ap.relu) z = make_float4(fmaxf(z.x, 0.f), fmaxf(z.y, 0.f), fmaxf(z.z, 0.f), fmaxf(z.w, 0.f));
-            *reinterpret_cast<float4 *>(&ap.z[at]) = z;
         }
     }
 }

@@ -4,24 +4,22 @@
 namespace rn50 {
 
 template <int TM, int TN>
-static void launch_small(const IgemmP &p, int grid, const TailApply *ap, hipStream_t st)
+static void launch_small(const IgemmP &p, int grid, hipStream_t st)
 {
     const dim3 g(grid), b(64 * kSmallWaves);
-    const TailApply none{};
-    if (p.flip_taps) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, true, false, 0>), g, b, 0, st, p, none);
-    else if (p.in_scale && p.stat_mean) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, true, 2>), g, b, 0, st, p, none);
-    else if (p.in_scale) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, true, 0>), g, b, 0, st, p, none);
-    else if (p.stat_mean) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, false, 2>), g, b, 0, st, p, none);
-    else if (ap) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, false, 1>), g, b, 0, st, p, *ap);
-    else hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, false, 0>), g, b, 0, st, p, none);
+    if (p.flip_taps) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, true, false, false>), g, b, 0, st, p);
+    else if (p.in_scale && p.stat_mean) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, true, true>), g, b, 0, st, p);
+    else if (p.in_scale) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, true, false>), g, b, 0, st, p);
+    else if (p.stat_mean) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, false, true>), g, b, 0, st, p);
+    else hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, false, false>), g, b, 0, st, p);
 }
 // bm, bn: rows and columns of a workgroup, 16 or 32 each
-void launch_igemm_small(int bm, int bn, int grid, const IgemmP &p, const TailApply *ap, hipStream_t st)
+void launch_igemm_small(int bm, int bn, int grid, const IgemmP &p, hipStream_t st)
 {
-    if (bm == 32 && bn == 32) launch_small<2, 2>(p, grid, ap, st);
-    else if (bm == 32) launch_small<2, 1>(p, grid, ap, st);
-    else if (bn == 32) launch_small<1, 2>(p, grid, ap, st);
-    else launch_small<1, 1>(p, grid, ap, st);
+    if (bm == 32 && bn == 32) launch_small<2, 2>(p, grid, st);
+    else if (bm == 32) launch_small<2, 1>(p, grid, st);
+    else if (bn == 32) launch_small<1, 2>(p, grid, st);
+    else launch_small<1, 1>(p, grid, st);
 }
 
 }  // namespace rn50

@@ -287,6 +287,26 @@ def test_eval_forward_with_saved_statistics():
     ctx.close()
 
 
+@pytest.mark.parametrize("split", [None, "1"])
+@pytest.mark.parametrize("batch", [1, 2, 3])
+def test_eval_of_few_images_reproduces_the_training_forward(batch, split):
+    """The convolutions of an evaluation form the sums of the training forward whatever the batch: from a batch's own statistics, whose 49 pixels an image
+    in the last stage magnify a difference of rounding a hundred times, come that batch's logits."""
+    images, params, labels = problem(41 + batch, batch)
+    rn.rn50_set_option("split_products", split)
+    try:
+        ctx = rn.Rn50Ctx(batch)
+    finally:
+        rn.rn50_set_option("split_products", None)
+    _, _, theta, dimg, _ = gpu_forward_backward(ctx, images, params, labels, BN_EPS)
+    train = ctx.peek(0, 7).view(batch, 1000).cpu().numpy().astype(np.float64)
+    logits = torch.full((batch, 1000), 7.0, device=DEV)
+    ctx.forward_eval(dimg, theta, logits)
+    torch.cuda.synchronize()
+    assert_close(logits.cpu().numpy(), train, 1e-6, "eval forward on the training batch vs training forward")
+    ctx.close()
+
+
 @pytest.mark.parametrize("batch", [1, 3])
 def test_full_step_degenerate_batches(batch):
     """One image (every stage-5 BN sees 49 values per channel, every GEMM has ragged row tiles) and an odd batch:
