@@ -480,7 +480,7 @@ static bool wgrad_may_split_terms(const rn50_conv_desc *d, long Mpix, Fp32Math m
 {
     return math == kFp32Split && !bf16_of(d) && d->c % 32 == 0 && d->k % 32 == 0 && (long)d->n * d->h * d->w * d->c < (1l << 29) && Mpix * d->k < (1l << 29);
 }
-struct WgradTermsRoom { size_t part, terms[2], total; };
+struct WgradTermsRoom { size_t terms[2], total; };
 static WgradTermsRoom wgrad_terms_room(const rn50_conv_desc *d, const GemmPlan &pl, int Kout, int Jdim, long Mpix)
 {
     WgradTermsRoom r;
@@ -1111,6 +1111,7 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
         if (sm.grid) b.g = sm;
     }
     p.flip_taps = (b.g.kind == kHalf || b.g.kind == kSmall) && !flipped ? d->r * d->s : 0;
+    RN50_REQUIRE(flipped || p.flip_taps, RN50_EUNSUPPORTED, "conv2d_bwd_data: the plan's kernel takes a flipped filter");  // see the caller's choice
     set_planes(p, b.g, planes, ge.Mout, ws, st);
     run_igemm(p, b.g, dx, (float *)ws, bf16_of(d), act_of(d), st);
     return launch_status("conv2d_bwd_data");

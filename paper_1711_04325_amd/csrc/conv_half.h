@@ -10,7 +10,7 @@
 // Error against 64 bits (relative 2-norm, normal operands / behind a ReLU, reduction of 512, 1152, 2304, 4608): six bf16 products
 // 1.3e-7, 2.0e-7, 2.9e-7, 4.2e-7 / 1.0e-7, 1.6e-7, 2.3e-7, 3.5e-7; here 1.2e-7, 1.2e-7, 1.4e-7, 1.6e-7 / 1.2e-7, 1.3e-7, 1.4e-7,
 // 1.6e-7: the sums of hi*hi are moved to accumulators of their own every 128 elements (without that 1.7e-7 .. 4.4e-7).  What stays, 9e-8, are the
-// bits that the halves drop: so reductions of 1024 and more come here (half_precise in conv.hip).
+// bits that the halves drop: so sums of 700 products and more come here, of 480 in data gradients (half_as_precise in conv.hip).
 //
 // The fixed range: numbers below 2^-27 of their tensor's largest one have fewer than 24 bits, below 2^-52 none.  Beside larger ones that is
 // nothing where those meet weights like the others', but not where theirs are zero or as small as the numbers are large (channels with scales
@@ -196,15 +196,6 @@ static __global__ __launch_bounds__(256) void half_split_kernel(HalfPrep p)
 }
 
 // ---- implicit GEMM -----------------------------------------------------------------------------------------------------
-__device__ inline float row16_sum(float v)  // sum over the 16 lanes of a row, the same bits in all of them
-{
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // lane ^ 2
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));  // the other four of eight
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true));  // the other eight of 16
-    return v;
-}
-
 // A wavefront's block as the kernels of this file hold it: blocks of 16 pixels x 16 channels, lane l has pixel l % 16 and channels 4 * (l / 16) .. + 3.
 // Statistics (see igemm_stats: whole tiles only) and write-out, 16 bytes per lane.
 template <int BM, int BN, bool STATS, int MI, int NI>

@@ -202,6 +202,14 @@ __device__ inline Split8 split8_scaled(float4 a, float4 b)  // of values scaled 
     return s;
 }
 __device__ inline Split8 split8(float4 a, float4 b, float up) { return split8_scaled(scaled4(a, up), scaled4(b, up)); }
+__device__ inline float row16_sum(float v)  // sum over the 16 lanes of a row, the same bits in all of them
+{
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // lane ^ 2
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));  // the other four of eight
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true));  // the other eight of 16
+    return v;
+}
 __device__ inline float4 bn_relu4(float4 v, const float4 &sc, const float4 &sh)
 {
     return make_float4(fmaxf(fmaf(v.x, sc.x, sh.x), 0.f), fmaxf(fmaf(v.y, sc.y, sh.y), 0.f), fmaxf(fmaf(v.z, sc.z, sh.z), 0.f),

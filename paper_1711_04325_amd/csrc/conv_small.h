@@ -13,15 +13,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ const float4 g_zero4 = {0.f, 0.f, 0.f, 0.f};  // what lanes outside the image load
 
-__device__ inline float small_row_sum(float v)  // sum over the 16 lanes of a row, the same bits in all of them
-{
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xf, 0xf, true));   // lane ^ 1
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));   // lane ^ 2
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xf, 0xf, true));  // the other four of eight
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xf, 0xf, true));  // the other eight of 16
-    return v;
-}
-
 constexpr int kSmallWaves = 4;  // 8 and 16 were as fast where one workgroup runs on a CU, and slower (up to twice) where more do
 
 // A workgroup: TM x TN blocks of 16 rows x 16 columns; wavefront w takes the stages of 32 reduction elements w, w + 4, ..., each in four sums (a single block
@@ -166,14 +157,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmP p)
             float sum = 0.f, dev = 0.f;
 #pragma unroll
             for (int i = 0; i < TM; ++i) sum += i * 16 + pl < valid ? v[i][e] : 0.f;
-            const float mu = small_row_sum(sum) / (float)valid;
+            const float mu = row16_sum(sum) / (float)valid;
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 const float d = v[i][e] - mu;
                 dev = i * 16 + pl < valid ? fmaf(d, d, dev) : dev;
             }
             (&mean.x)[e] = mu;
-            (&m2.x)[e] = small_row_sum(dev);
+            (&m2.x)[e] = row16_sum(dev);
         }
         if (pl == 0 && col < p.Nout) {
             *reinterpret_cast<float4 *>(&p.stat_mean[(long)tm * p.Nout + col]) = mean;
