@@ -280,7 +280,7 @@ __device__ __forceinline__ void half_finish(const IgemmP &p, int lane, int wm, i
 
 // A wavefront's block formed on the fp32 instruction straight from memory (see igemm_join_split): results that are not finite, or
 // operands that the halves do not hold.
-constexpr int kAgainLoads = 4;  // groups of four elements (16-byte loads instead took 1.4 - 1.9 times as long where every block came here)
+constexpr int kAgainLoads = 2;  // groups of four elements: more take no less time, and registers that spill (16-byte loads: 1.4 - 1.9 times the time)
 template <int MI, int NI>
 __device__ __forceinline__ void half_again(const IgemmP &p, int lane, int mw, int nw, int first, int end, floatx4 (&acc)[MI][NI])
 {
@@ -382,10 +382,10 @@ __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_ha
     // This thread copies LDS position tid%8 of rows tid/8 + 32*i, which holds chunk tid%8 ^ (tid/16 % 8) of each of them: of a row three
     // instructions, an addition of the stage's offset, the bit of the filter tap from a mask made once per item, and the choice of the zeros
     // ahead of the tensor.
-    const int arow = tid >> 3;
-    const unsigned ac = (unsigned)(((tid & 7) ^ ((tid >> 4) & 7)) * 16) + kHalfZeros;
     unsigned aoff[RA], amask[RA];
     auto set_rows = [&](const IgemmP &p, const IgemmItem &it) {
+        const int t = opaque_tid(), arow = t >> 3;
+        const unsigned ac = (unsigned)(((t & 7) ^ ((t >> 4) & 7)) * 16) + kHalfZeros;
 #pragma unroll
         for (int i = 0; i < RA; ++i) {
             const int m = it.m0 + arow + STEP * i;
@@ -529,33 +529,45 @@ __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_ha
         }
         multiply();
         buf ^= 1;
-        const int l2 = opaque_tid() & 63, down = -(p.half_up[0] + p.half_up[1]);
+        const int down = -(p.half_up[0] + p.half_up[1]);
+        const bool counted = __builtin_amdgcn_readfirstlane(p.half_any[0]) != 0;
         float probe = 0.f;  // NaN when a sum is not finite
-        // A counted number loses at most 2^-20.4 of its scaled product (2^-37 of quantum and 2^-36 of the dropped lo*lo, times a number below 2^15).
-        // An output one of whose partial sums shows that its products' magnitudes add up to 16 for each of them loses less than 2^-24 of that.
-        // (|lo| is at most twice |hi|: its sums show it from 8 times as much on.)  Three sums that rarely cancel together.
-        float least = 3.4e38f;
+        float sums[MI][NI];  // the least, over four outputs, of the largest magnitude of an output's three sums, which rarely cancel together
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const bool row = it.m0 + wm * WTM + i * 16 + (l2 & 15) < p.M;
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
                 float m = 3.4e38f;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) m = fminf(m, fmaxf(fmaxf(fabsf(acc[i][j][e]), fabsf(top[i][j][e])), 0.125f * fabsf(low[i][j][e])));
-                least = row && it.n0 + wn * WTN + j * 16 + 4 * (l2 >> 4) < p.Nout ? fminf(least, m) : least;
-                asm volatile("" : "+v"(least));  // now: put off to the branch that reads it, it would keep three sets of sums in registers
-#pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float v = fmaf(low[i][j][e], 1.f / (float)(1 << kHalfLow), acc[i][j][e] + top[i][j][e]);
-                    acc[i][j][e] = ldexpf(v, down);
+                    const float s = acc[i][j][e], t = top[i][j][e], l = low[i][j][e];
+                    m = fminf(m, fmaxf(fmaxf(fabsf(s), fabsf(t)), 0.125f * fabsf(l)));
+                    acc[i][j][e] = ldexpf(fmaf(l, 1.f / (float)(1 << kHalfLow), s + t), down);
                     probe = fmaf(acc[i][j][e], 0.f, probe);
+                }
+                // Now: put off to the branch that reads it, it would keep three sets of sums in registers, and those did not fit.  A launch of
+                // 64 x 128 tiles with 36 bytes of scratch took 48.5 us, without 36.2 (3x3 128 -> 128, 28x28, N = 32, with statistics).
+                asm volatile("" : "+v"(m));
+                sums[i][j] = m;
+            }
+        bool again = probe != probe;
+        const int l2 = opaque_tid() & 63;
+        // A counted number loses at most 2^-20.4 of its scaled product (2^-37 of quantum and 2^-36 of the dropped lo*lo, times a number below 2^15).
+        // An output one of whose sums shows that its products' magnitudes add up to 16 for each of them loses less than 2^-24 of that.
+        // (|lo| is at most twice |hi|: its sums show it from 8 times as much on.)
+        float least = 3.4e38f;
+        if (counted) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const bool row = it.m0 + wm * WTM + i * 16 + (l2 & 15) < p.M;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    if (row && it.n0 + wn * WTN + j * 16 + 4 * (l2 >> 4) < p.Nout) least = fminf(least, sums[i][j]);
                 }
             }
         }
-        bool again = probe != probe;
         const float elements = (float)((it.kc_end - it.kc_begin) * kBK);
-        if (p.half_any[0] && __any(least < kHalfFloor * elements)) {  // their number under this block's rows (whole image rows), and in its filter rows
+        if (counted && __any(least < kHalfFloor * elements)) {  // their number under this block's rows (whole image rows), and in its filter rows
             const int mw = it.m0 + wm * WTM, nw = it.n0 + wn * WTN;
             int cls, n, oh, ow, n2, oh2, c2;
             decode_row(p, min(mw, p.M - 1), cls, n, oh, ow);

@@ -105,3 +105,15 @@ def test_wait_states(tmp_path):
             bad += ["%s: %s %s" % (name, op, args) for op, args in violations(code)]
     assert seen.issuperset(PASSES) and "v_cvt_pk_bf16_f32" in seen and "global_load_lds_dwordx4" in seen
     assert not bad, "%d places:\n%s" % (len(bad), "\n".join(bad[:20]))
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler here")
+def test_half_kernels_use_no_scratch(tmp_path):
+    """Three sets of sums leave igemm_half_kernel few registers: where some spill, a launch takes a third longer."""
+    seen = []
+    for i, co in enumerate(code_objects(build.LIB)):
+        path = tmp_path / str(i)
+        path.write_bytes(co)
+        notes = subprocess.run([OBJDUMP.replace("objdump", "readelf"), "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+        seen += [(name, int(scratch)) for name, scratch in re.findall(r"\.name: +(_Z\S*igemm_half_kernel\S*)\n\s+\.private_segment_fixed_size: (\d+)", notes)]
+    assert len(seen) == 6 and all(scratch == 0 for _, scratch in seen), seen
