@@ -658,7 +658,7 @@ static void launch_tail_reduce_stats(const IgemmPlan &pl, const IgemmP &p, hipSt
 // act: storage of the gathered operand and of the output (see act_of).
 // ap (a forward pass, fp32 output): what to make of the output besides; returns whether it was made (where every tile is split the
 // ordered sum makes it, a launch and a pass less), else it is the caller's to do.
-static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials, bool bf16, int act, hipStream_t st,
+static bool run_igemm(IgemmWideP p, const IgemmPlan &pl, float *out, float *partials, bool bf16, int act, hipStream_t st,
                       const TailApply *ap = nullptr)
 {
     const bool fast = p.Cin % kBK == 0 && act != 2;  // an fp32 input beside bf16 activations goes through the scalar gather
@@ -727,7 +727,7 @@ static bool run_igemm(IgemmP p, const IgemmPlan &pl, float *out, float *partials
 static size_t igemm_part_bytes(const IgemmPlan &pl) { return pl.kind == kGeneral ? pl.ws_floats * sizeof(float) : align_up(pl.ws_floats * sizeof(float), 256); }
 // The prepared filter of a call: the one it was given, or prepared now in the workspace behind the partial tiles.  Operands as fp16 halves:
 // both prepared there, the gathered tensor of `pixels` pixels among them.
-static void set_planes(IgemmP &p, const IgemmPlan &pl, const char *planes, long pixels, void *ws, hipStream_t st)
+static void set_planes(IgemmWideP &p, const IgemmPlan &pl, const char *planes, long pixels, void *ws, hipStream_t st)
 {
     if (pl.kind == kGeneral || pl.kind == kSmall) return;
     p.plane_rows = plane_rows_of(p.Nout);
@@ -993,7 +993,7 @@ static int conv_fwd_impl(const char *who, const rn50_conv_desc *d, const float *
             if (int rc = bn_fwd_apply(d->n, d->k, ge.P, ge.Q, RN50_LAYOUT_NHWC, y, ap->scale, ap->shift, ap->residual, ap->relu, ap->z, nullptr, stream)) return rc;
         return launch_status(who);
     }
-    IgemmP p{};
+    IgemmWideP p{};
     p.a = x; p.b = w; p.in_scale = in_scale; p.in_shift = in_shift;
     p.IH = d->h; p.IW = d->w; p.Cin = d->c; p.OH = ge.P; p.OW = ge.Q; p.Nout = d->k; p.R = d->r; p.S = d->s;
     p.so = d->stride; p.off = -d->pad; p.sd = 1; p.M = (int)ge.Mout; p.Kdim = ge.Kdim; p.scatter2 = 0;
@@ -1091,7 +1091,7 @@ int rn50::conv_bwd_data_pretransposed(Fp32Math math, const rn50_conv_desc *d, co
     RN50_REQUIRE(act_of(d) != 2, RN50_EUNSUPPORTED, "conv2d_bwd_data: RN50_DTYPE_BF16_ACT_F32IN is for the forward pass and the filter gradient");
     RN50_REQUIRE(ws_bytes >= b.part_bytes && (b.part_bytes == 0 || ws), RN50_EWORKSPACE,
                  "conv2d_bwd_data: workspace too small (%zu < %zu)", ws_bytes, b.part_bytes);
-    IgemmP p{};
+    IgemmWideP p{};
     p.a = dy; p.b = wt;
     p.IH = ge.P; p.IW = ge.Q; p.Cin = d->k; p.Nout = d->c; p.R = d->r; p.S = d->s;
     p.Kdim = d->r * d->s * d->k;

@@ -282,7 +282,7 @@ __device__ __forceinline__ void half_finish(const IgemmP &p, int lane, int wm, i
 // operands that the halves do not hold.
 constexpr int kAgainLoads = 2;  // groups of four elements: more take no less time, and registers that spill (16-byte loads: 1.4 - 1.9 times the time)
 template <int MI, int NI>
-__device__ __forceinline__ void half_again(const IgemmP &p, int lane, int mw, int nw, int first, int end, floatx4 (&acc)[MI][NI])
+__device__ __forceinline__ void half_again(const IgemmWideP &p, int lane, int mw, int nw, int first, int end, floatx4 (&acc)[MI][NI])
 {
     const int pl = lane & 15, kl = lane >> 4;
     int ih0[MI], iw0[MI], base[MI];
@@ -351,11 +351,11 @@ __device__ __forceinline__ void half_again(const IgemmP &p, int lane, int mw, in
 
 // The launch parameters read again where they are needed: held in scalar registers through the loop they spill into vector registers, and
 // every stage then moves dozens of them.
-__device__ __forceinline__ const IgemmP &again_from_memory()
+__device__ __forceinline__ const IgemmWideP &again_from_memory()
 {
     const char __attribute__((address_space(4))) *q = (const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(q));
-    return *reinterpret_cast<const IgemmP *>((const char *)q);
+    return *reinterpret_cast<const IgemmWideP *>((const char *)q);
 }
 
 // The implicit GEMM of igemm_kernel (its work decomposition; no dilation, Cin % 32 == 0, Nout % 4 == 0, R*S <= 32) on halves: a stage is 32 reduction elements, 64
@@ -365,7 +365,7 @@ __device__ __forceinline__ const IgemmP &again_from_memory()
 // matrix cores and the LDS busy at the same time; one of 128 x 128 with four stages in LDS had its wavefronts read and multiply in step.  3x3 256 -> 256,
 // 14x14, N = 128 (29.6 GFLOP): 137 us that way, 100 with addresses as igemm_act_kernel forms them, 83 now; igemm_pre_kernel 179.
 template <int BM, int BN, bool STATS>
-__global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_half_kernel(IgemmP kernarg)
+__global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_half_kernel(IgemmWideP kernarg)
 {
     constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 16, NI = WTN / 16;
     constexpr int RA = BM / 32, RB = BN / 32, STEP = 32;   // rows per thread: 8 threads copy a row
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_ha
     const size_t b_step = (size_t)kernarg.plane_rows * kActRow;
     int l_kc, l_tap, l_s, buf = 0;
     unsigned l_delta, l_chunk;
-    auto place = [&](const IgemmP &p, int kc, int n0) {
+    auto place = [&](const IgemmWideP &p, int kc, int n0) {
         l_kc = __builtin_amdgcn_readfirstlane(kc);
         const int chunk = __builtin_amdgcn_readfirstlane((int)fdiv(l_kc, p.div_rs));
         l_tap = l_kc - chunk * taps;
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_ha
         l_delta = (unsigned)(r * p.IW + l_s) * px + l_chunk;
         l_b = p.planes + ((size_t)l_kc * p.plane_rows + __builtin_amdgcn_readfirstlane(n0)) * kActRow;
     };
-    auto start = [&](const IgemmP &p, const IgemmItem &x) {
+    auto start = [&](const IgemmWideP &p, const IgemmItem &x) {
         set_rows(p, x);
         place(p, x.kc_begin, x.n0);
     };
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_ha
             }
         }
         // the item's last stage, with the first one of the next item on its way
-        const IgemmP &p = again_from_memory();
+        const IgemmWideP &p = again_from_memory();
         item += G;
         const bool more = item < n_items;
         IgemmItem nx = it;

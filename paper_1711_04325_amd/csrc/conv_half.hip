@@ -16,13 +16,13 @@ void launch_half_prep(const HalfPrep &p, hipStream_t st)
 }
 
 template <int BM, int BN>
-static void launch_half(const IgemmP &p, int grid, hipStream_t st)
+static void launch_half(const IgemmWideP &p, int grid, hipStream_t st)
 {
     const dim3 g(grid), b(kConvThreads);
     if (p.stat_mean) hipLaunchKernelGGL((igemm_half_kernel<BM, BN, true>), g, b, 0, st, p);
     else hipLaunchKernelGGL((igemm_half_kernel<BM, BN, false>), g, b, 0, st, p);
 }
-void launch_igemm_half(int bm, int bn, int grid, const IgemmP &p, hipStream_t st)
+void launch_igemm_half(int bm, int bn, int grid, const IgemmWideP &p, hipStream_t st)
 {
     if (bm == 128) launch_half<128, 64>(p, grid, st);
     else if (bn == 128) launch_half<64, 128>(p, grid, st);

@@ -95,7 +95,13 @@ struct IgemmP {
     // Kernels of conv_split.h and conv_act.h: the filter operand prepared beforehand, [stage][plane_rows][bytes of a row's stage].
     const char *planes;
     int plane_rows;
-    // Kernels of conv_half.h: the gathered operand as fp16 halves, the exponents of both operands' scales, whether there are marks
+};
+// With the 256 bytes that the compiler adds, the launch parameters fill eight cache lines.  With the fields below among them, in a ninth, evaluation of one
+// image (95 launches of kernels that take them) took 649 us instead of 637.
+static_assert(sizeof(IgemmP) <= 256, "launch parameters of the implicit GEMM");
+// What the kernels of conv_half.h and conv_small.h are given beyond that.
+struct IgemmWideP : IgemmP {
+    // conv_half.h: the gathered operand as fp16 halves, the exponents of both operands' scales, whether there are marks
     // of small operands, and those (of groups of pixels, of filter rows); flip_taps: p.b is the filter as it is, [k][taps][row].
     const char *halves;
     const int *half_up;
@@ -1552,7 +1558,7 @@ struct HalfPrep {
     unsigned *marks;                   // cleared by the first launch
     int nmarks;
 };
-void launch_igemm_small(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
+void launch_igemm_small(int bm, int bn, int grid, const IgemmWideP &p, hipStream_t st);
 void launch_half_prep(const HalfPrep &p, hipStream_t st);
 // Both tensors of a filter gradient split into bf16 terms beforehand (conv_terms.h)
 constexpr int kTermsZeros = 256;  // zero bytes ahead of each
@@ -1567,7 +1573,7 @@ struct TermsPrep {
 };
 void launch_terms_prep(const TermsPrep &p, hipStream_t st);
 void launch_wgrad_terms(int bm, int bn, int grid, const WgradP &p, hipStream_t st);
-void launch_igemm_half(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);
+void launch_igemm_half(int bm, int bn, int grid, const IgemmWideP &p, hipStream_t st);
 size_t filter_planes_bytes(int rows, int kdim, bool act);
 void launch_filter_planes(int rows, int kdim, bool act, const float *w, char *planes, hipStream_t st);
 void launch_igemm_pre(int bm, int bn, int grid, const IgemmP &p, hipStream_t st);

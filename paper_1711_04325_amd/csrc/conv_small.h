@@ -21,7 +21,7 @@ constexpr int kSmallWaves = 4;  // 8 and 16 were as fast where one workgroup run
 // Cin % 32 == 0 (a stage stays inside one filter tap), Nout % 4 == 0, R*S <= 32, no dilation.  FLIP: the filter of a data gradient as it is, [k][tap][row].
 // INAFF: see IgemmP.  STATS: the output's statistics per TM * 16 rows as well.
 template <int TM, int TN, bool FLIP, bool INAFF, bool STATS>
-__global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmP p)
+__global__ __launch_bounds__(64 * kSmallWaves) void igemm_small_kernel(IgemmWideP p)
 {
     constexpr int W = kSmallWaves, U = TM + TN == 2 ? 4 : TM + TN == 3 ? 3 : 2;  // stages in flight
     __shared__ floatx4 red[W][TM * TN * 64];

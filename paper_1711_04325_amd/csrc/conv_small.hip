@@ -4,7 +4,7 @@
 namespace rn50 {
 
 template <int TM, int TN>
-static void launch_small(const IgemmP &p, int grid, hipStream_t st)
+static void launch_small(const IgemmWideP &p, int grid, hipStream_t st)
 {
     const dim3 g(grid), b(64 * kSmallWaves);
     if (p.flip_taps) hipLaunchKernelGGL((igemm_small_kernel<TM, TN, true, false, false>), g, b, 0, st, p);
@@ -14,7 +14,7 @@ static void launch_small(const IgemmP &p, int grid, hipStream_t st)
     else hipLaunchKernelGGL((igemm_small_kernel<TM, TN, false, false, false>), g, b, 0, st, p);
 }
 // bm, bn: rows and columns of a workgroup, 16 or 32 each
-void launch_igemm_small(int bm, int bn, int grid, const IgemmP &p, hipStream_t st)
+void launch_igemm_small(int bm, int bn, int grid, const IgemmWideP &p, hipStream_t st)
 {
     if (bm == 32 && bn == 32) launch_small<2, 2>(p, grid, st);
     else if (bm == 32) launch_small<2, 1>(p, grid, st);
