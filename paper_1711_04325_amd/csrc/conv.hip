@@ -195,6 +195,12 @@ static double igemm_half_cost(const IgemmPlan &pl, int kchunks)
 // Fitted to 5,100 measured launches (166 calls of 130 shapes, every tile, up to seven splits): the plan it picks takes 1.0 % longer than the best one
 // measured in forward passes, 2.3 % in data gradients, on average.  The rows of the measured table, which igemm_act_kernel took before, are those of the
 // general kernel: 7.7 % longer (64 -> 256 channels at 56x56, N = 256, forward 215 us in tiles of 64 x 128, 180 in 128 x 128; 1024 -> 512 at 14x14, N = 32: 42, 25).
+// A row stays all the same where the model gains less than this many microseconds: the launches it was fitted to repeat a call on operands that are in the
+// caches, and few large tiles wait longest for those that are not.  3x3 256 -> 256 at 14x14, N = 32, forward: 28.3 us in 200 workgroups of 64 x 128, 30.1 in
+// 496 pieces of 128 x 128; in a step 4 us the other way round.  Step with bf16 activations, rows alone / model alone / margin of 1.5, 2.5, 3.5, 4.5, 6, 8:
+// N = 32 4.62, 4.73 / 4.71, 4.67, 4.64, 4.62, 4.62, 4.63 ms; v1.5 4.90, 4.89 / 4.88, 4.85, 4.82, 4.81, 4.83, 4.84; N = 256 21.71, 21.24 / 21.22, 21.23, 21.17,
+// 21.23, 21.34, 21.43.
+constexpr double kActRowMargin = 4.0;
 static double igemm_act_cost(const IgemmPlan &pl, bool fwd, long M, int Nout, int kchunks)
 {
     static const double f128x128[3] = {0.519, 0.965, 0.625}, f128x64[3] = {0.336, 0.585, 0.393}, f64x128[3] = {0.307, 0.0, 0.347}, f64x64[3] = {0.198, 0.051, 0.230};
@@ -340,7 +346,10 @@ static IgemmPlan plan_igemm_kind(const rn50_conv_desc *d, int op, long M, int No
     if (act_of(d) == 1 && geometry && cin % kActStage == 0) {
         for (const PlanRow &t : cfg->pre_plans)
             if (plan_matches(t, d, op)) return make_igemm_plan(kAct, t.bm, t.bn, M, Nout, kchunks, t.split, allow_split);
-        return model_plan(kAct, M, Nout, kchunks, bk, allow_split, 128, fwd);
+        const IgemmPlan own = model_plan(kAct, M, Nout, kchunks, bk, allow_split, 128, fwd);
+        if (!tuned_plan(*cfg, d, op, &pl)) return own;
+        const IgemmPlan row = make_igemm_plan(kAct, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split);
+        return igemm_act_cost(row, fwd, M, Nout, kchunks) <= own.cost + kActRowMargin ? row : own;
     }
     const IgemmPlan general = tuned_plan(*cfg, d, op, &pl) ? make_igemm_plan(kGeneral, pl.bm, pl.bn, M, Nout, kchunks, pl.split, allow_split)
                                                             : model_plan(kGeneral, M, Nout, kchunks, bk, allow_split);

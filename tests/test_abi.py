@@ -252,6 +252,16 @@ def test_rows_for_prepared_filters_are_taken(case, plan):
         assert got[:2] == plan[:2], (op, got)
 
 
+def test_measured_rows_stay_where_the_model_gains_little():
+    """bf16 activations: a row of the measured table within 4 us of the modelled best is taken, one further off is not, and other shapes follow the model."""
+    def plan(op, n, c, h, k, r, stride):
+        return rn.rn50_conv_plan(rn.conv_desc(n, c, h, h, k, r, r, stride, r // 2, in_dtype=rn.DTYPE_BF16_ACT), op)[:3]
+
+    assert plan(rn.OP_FWD, 32, 256, 14, 256, 3, 1) == (128, 128, 5) and plan(rn.OP_BWD_DATA, 32, 512, 28, 1024, 1, 2) == (64, 128, 1)
+    assert plan(rn.OP_FWD, 256, 64, 56, 256, 1, 1) == (128, 128, 1) and plan(rn.OP_BWD_DATA, 256, 256, 14, 256, 3, 1) == (64, 128, 12)
+    assert plan(rn.OP_FWD, 31, 256, 14, 256, 3, 1) == plan(rn.OP_FWD_BNSTATS, 31, 256, 14, 256, 3, 1) == (64, 128, 1)
+
+
 def test_conv_fwd_bnstats_argument_errors():
     L = rn.lib()
     d0 = rn.conv_desc(32, 256, 14, 14, 256, 3, 3, 1, 1)
