@@ -122,8 +122,10 @@ typedef struct {
 
 /* Bytes of scratch the given operation needs for this shape (0 is possible).  Returns 0 for an
  * invalid descriptor as well: the operation itself reports the error.  With that much a call's results are the same bits every
- * time.  With less it runs kernels that need less, if that is enough for them (for fp32 operands: on the fp32 matrix
- * instruction, whose sums round differently), and returns RN50_EWORKSPACE if not. */
+ * time.  With less it runs kernels that need less, if that is enough for them, and returns RN50_EWORKSPACE if not: for fp32 operands first
+ * those on bf16 terms that prepare the filter at most, then those on the fp32 matrix instruction; sums round differently on each.  Most of what
+ * a query names where it is large are operands prepared by the call: 4 bytes for every element of the gathered tensor and the filter as
+ * fp16 halves, 6 for every element of x and dy in a filter gradient (data gradient of 256 x 56 x 56, 64 -> 64, 3x3: 206 MB, with less 17). */
 size_t rn50_conv_workspace_bytes(const rn50_conv_desc *d, int op);
 
 /* The launch plan the given operation would use for this shape, for reports: tile of bm output rows x bn output columns

@@ -363,7 +363,8 @@ __device__ __forceinline__ const IgemmWideP &again_from_memory()
 // What a stage costs beside its products is instructions (a wavefront issues one in four cycles, a product takes 16) and LDS reads (six fragments of
 // 1 KB to 12 products with 64 x 32 to a wavefront, 128 bytes a cycle).  Three workgroups to a CU, each at another place of its stage, keep the
 // matrix cores and the LDS busy at the same time; one of 128 x 128 with four stages in LDS had its wavefronts read and multiply in step.  3x3 256 -> 256,
-// 14x14, N = 128 (29.6 GFLOP): 137 us that way, 100 with addresses as igemm_act_kernel forms them, 83 now; igemm_pre_kernel 179.
+// 14x14, N = 128 (29.6 GFLOP): 99 us in calls one behind the other, igemm_pre_kernel 179; that way 1.65 times as long, with addresses as igemm_act_kernel
+// forms them 1.2 times.
 template <int BM, int BN, bool STATS>
 __global__ __launch_bounds__(kConvThreads, half_occupancy(BM, BN)) void igemm_half_kernel(IgemmWideP kernarg)
 {
