@@ -274,8 +274,7 @@ def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_1711_04325_amd", "csrc")
-    for f in ("common.h", "conv.hip", "conv_act.h", "conv_kernels.h", "conv_plans.inc", "conv_plans_bf16act.inc", "conv_split.h", "conv_split.hip",
-              "conv_stem.h", "conv_stem.hip"):
+    for f in ["common.h"] + sorted(f for f in os.listdir(csrc) if f.startswith("conv")):
         h.update(f.encode())
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()
